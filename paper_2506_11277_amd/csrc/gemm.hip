@@ -1094,8 +1094,24 @@ static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, b
             const long long limit = g_small_below_tiles.load();
             bool small;
             if (limit < 0) {
-                static constexpr double kSmallSpeed[kSmallMaxS + 1] = {0, 0.7, 0.63, 0.69, 0.74, 0.70, 0.76, 0.87, 0.72, 0.80, 0.93, 0.9, 0.9};
                 const int cus = device_cus();
+                // Fewer tiles than compute units: let the wavefronts of a work-group divide the contraction instead of
+                // leaving most of the chip, or of a compute unit, idle (gemm_small.hip; event times, the launch
+                // included, in us).  32 x 32 tiles while there is about one for every compute unit: 128^3 s = 3 8.6 ->
+                // 6.2, 512^3 s = 3 / 7 14.1 -> 7.5 / 19.7 -> 11.1, 256 x 256 x 4096 s = 7 88.9 -> 28.0; up to 5 slices two
+                // such work-groups fit a compute unit, and from 7 on a second round is still no slower than halves (640^3
+                // s = 4 / 7 / 9 11.0 / 18.6 / 24.0 against 11.6 / 18.7 / 23.8; 640 x 640 x 4000 s = 7 59 against 70; at 700^3, 484
+                // tiles, s = 7 halves win 21.2 to 22.9).  A single slice has little to multiply per byte and keeps to it for
+                // longer (1400^3 22.8 -> 14.7, 1536^3 20.5 -> 17.3).  From 11 slices on the registers do not suffice.
+                const long long tiles32 = (long long)((m + 31) / 32) * ((n + 31) / 32);
+                if (s <= 10 && (tiles32 <= cus || (s != 6 && 4 * tiles32 <= (s <= 5 ? 8LL : 7LL) * cus) || (s == 1 && tiles32 <= 9LL * cus)))
+                    return launch_gemm_eighths(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
+                // 64 x 64 tiles, the contraction in halves, while every tile has a compute unit of its own: 768^3 s = 3 / 7 18.3
+                // -> 11.4 / 24.7 -> 21.3, 1024^3 s = 3 / 5 / 7 / 9 21.6 -> 13.2 / 25.3 -> 19.6 / 32.3 -> 29.8 / 43.3 -> 41.5; 2 and 3 slices: two
+                // work-groups to a compute unit (1400^3: 25.2 -> 17.7 and 28.5 -> 22.7; beyond, 1536^3 s = 3: 31.6 against 30.8)
+                if (s >= 2 && s <= 9 && small_tiles <= (s <= 3 ? 2 : 1) * (long long)cus)
+                    return launch_gemm_halves(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
+                static constexpr double kSmallSpeed[kSmallMaxS + 1] = {0, 0.7, 0.63, 0.69, 0.74, 0.70, 0.76, 0.87, 0.72, 0.80, 0.93, 0.9, 0.9};
                 const double tabulated = fused16_preferred(s, false) ? fused16_launch_cost(s, m, n, cus) : launch_cost(m, n, tm, tn, cus);
                 small = small_tiles > tiles && launch_cost(m, n, 64, 64, cus) / kSmallSpeed[s] < tabulated;
             } else

@@ -154,4 +154,22 @@ struct LevelSum {
     }
 };
 
+// LevelSum over the int32 diagonal sums d[0], ..., d[S - 1] of one entry (diagonals 2, ..., S + 1).  Plain diagonal
+// order (Q = 1) in one conversion and one fused multiply-add per diagonal: the product with a power of two is exact,
+// so the only rounding is that of the addition, as in LevelSum, which takes about nine instructions.
+template <int S>
+__device__ __forceinline__ double diagonal_sum(const int (&d)[S], int Q)
+{
+    if (Q == 1) {
+        double s = 0.0;
+#pragma unroll
+        for (int a = 0; a < S; ++a) s = __builtin_fma((double)d[a], __builtin_ldexp(1.0, -kSliceBits * (a + 2)), s);
+        return s;
+    }
+    LevelSum sum;
+#pragma unroll
+    for (int a = 0; a < S; ++a) sum.add((double)d[a] * __builtin_ldexp(1.0, -kSliceBits * (a + 2)), Q, a == S - 1);
+    return sum.S;
+}
+
 }  // namespace oz

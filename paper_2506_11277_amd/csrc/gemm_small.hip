@@ -1,0 +1,311 @@
+// Fused slice-product kernels for problems whose tiles do not fill the chip: equal slice counts, whole contraction
+// in int32.  Same computation, plane layout and order of the binary64 additions as gemm_fused_kernel (gemm.hip); what
+// differs is that the wavefronts of a work-group also divide the CONTRACTION among each other.
+//
+// A problem of a thousand rows and columns has about one 64 x 64 tile per compute unit.  Four wavefronts of 32 x 32
+// outputs are then all a compute unit gets, one per SIMD, and nobody covers a wavefront that waits for a barrier or
+// an operand.  Here a 64 x 64 tile is worked on by eight wavefronts, two per SIMD: four take the even 32-deep
+// k-blocks, four the odd ones, and the two int32 halves of every diagonal sum are added in LDS at the end (exact, so
+// the result is the same bit for bit).  Smaller problems still use 32 x 32 tiles, each wavefront a k-block in eight.
+#include <type_traits>
+
+#include "gemm_dev.h"
+
+namespace oz {
+
+namespace {
+
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
+    }
+}
+
+// ---- tile 64 x 64, 2 x 2 x 2 wavefronts (m, n, k), operands staged through LDS -----------------------------------
+// A stage is two 32-deep k-blocks of the four fragment rows; ring of three stages where they fit the LDS, else two.
+// The loop is the hand-pipelined one of gemm_fused_kernel: slices of A from the last to the first, operands of slice
+// l - 1 read while the products of slice l run, the end-of-stage barrier before the products of slice 0, copies of a
+// later stage issued one at a time behind single matrix instructions.
+template <int S>
+struct CfgHalves {
+    static constexpr int STAGE = 4 * 2 * S * kFragBytes;
+    static constexpr int NSTG = 3 * STAGE <= kLdsBytes ? 3 : 2;
+    static constexpr int LDS = NSTG * STAGE;                // also holds the exchange of the sums: 16 S KiB
+    static_assert(LDS <= kLdsBytes, "stages do not fit LDS");
+};
+
+template <int S>
+__global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restrict__ pA, const int8_t *__restrict__ pB,
+                                                          const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
+                                                          double *__restrict__ C, int ldc, int m, int n, int KB,
+                                                          int tiles_m, int tiles_n, int Q)
+{
+    using G = CfgHalves<S>;
+    constexpr int NSTG = G::NSTG, STAGE = G::STAGE, CHUNK = 2 * S * kFragBytes, NW = 8, NU = S;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+    int tm, tn;
+    if (!tile_of_block_xcd(blockIdx.x, tiles_m, tiles_n, false, tm, tn)) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave & 1, wn = (wave >> 1) & 1, kg = wave >> 2;
+    const size_t row_bytes = (size_t)KB * (S * kFragBytes);
+    // copy unit u = wave + 8 i of a stage: fragment row u / (2 S) (two of A, two of B), 1 KiB (k-block, slice) u % (2 S)
+    const int8_t *src[NU];
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+        const int u = wave + i * NW, c = u / (2 * S), o = u % (2 * S);
+        src[i] = (c < 2 ? pA + (size_t)(2 * tm + c) * row_bytes : pB + (size_t)(2 * tn + c - 2) * row_bytes) + (size_t)o * kFragBytes;
+    }
+    const unsigned ldsw = lds0 + wave * kFragBytes;
+    auto issue = [&](auto I, unsigned voff, unsigned ldsbuf) {
+        constexpr int i = decltype(I)::value;
+        lds_dma16_at<i * NW * kFragBytes>(src[i], voff, ldsbuf);
+    };
+    const int nst = KB / 2;
+    static_for<0, NSTG - 1>([&](auto P) {
+        constexpr int p = decltype(P)::value;
+        const unsigned v = lane * 16 + (unsigned)(p < nst ? p : nst - 1) * (unsigned)CHUNK;
+        static_for<0, NU>([&](auto I) { issue(I, v, ldsw + p * STAGE); });
+    });
+    wait_vmcnt<(NSTG - 2) * NU>();
+    __syncthreads();
+
+    v16i acc[S];
+#pragma unroll
+    for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][r] = 0;
+    auto readA = [&](int l, const unsigned char *stage) -> v4i {
+        return *(const v4i *)(stage + wm * CHUNK + (kg * S + l) * kFragBytes + lane * 16);
+    };
+    auto readB = [&](int h, const unsigned char *stage) -> v4i {
+        return *(const v4i *)(stage + (2 + wn) * CHUNK + (kg * S + h) * kFragBytes + lane * 16);
+    };
+    v4i bf[S], af = readA(S - 1, lds);
+    bf[0] = readB(0, lds);
+    constexpr int NSLOT = S * (S - 1) / 2;
+    int buf = 0;
+    for (int st = 0; st < nst; ++st) {
+        // (towards the end the copies and the reads ahead go on, of the last stage again: nobody uses them)
+        const int ahead = st + NSTG - 1 < nst ? st + NSTG - 1 : nst - 1;
+        const unsigned vnext = lane * 16 + (unsigned)ahead * (unsigned)CHUNK;
+        const int buf1 = buf + 1 == NSTG ? 0 : buf + 1;
+        const int bufc = NSTG == 2 ? buf1 : (buf1 + 1 == NSTG ? 0 : buf1 + 1);
+        const unsigned ldsnext = ldsw + bufc * STAGE;
+        const unsigned char *cur = lds + buf * STAGE, *nxt = lds + buf1 * STAGE;
+        if constexpr (NU > NSLOT) static_for<0, NU>([&](auto I) { issue(I, vnext, ldsnext); });
+        v4i afn, bfn;
+        static_for<0, S>([&](auto L) {
+            constexpr int l = S - 1 - decltype(L)::value;
+            if constexpr (l > 0) {
+                afn = readA(l - 1, cur);
+                bf[S - l] = readB(S - l, cur);
+                __builtin_amdgcn_sched_barrier(0);          // (the reads stay ahead of the products they hide behind)
+            }
+            static_for<0, S - l>([&](auto HH) {
+                constexpr int hh = decltype(HH)::value, h = l == 0 ? S - 1 - hh : hh;
+                if constexpr (l == 0 && hh == 0) {
+                    // nothing of this stage is left to read, and the next one must have landed
+                    wait_vmcnt<(NSTG - 2) * NU>();
+                    __syncthreads();
+                    afn = readA(S - 1, nxt);
+                    bfn = readB(0, nxt);
+                }
+                acc[l + h] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[h], af, acc[l + h], 0, 0, 0);
+                constexpr int e = (S - 1 - l) * (S - l) / 2 + hh;
+                if constexpr (NU <= NSLOT && e < NU) issue(std::integral_constant<int, (e < NU ? e : 0)>{}, vnext, ldsnext);
+            });
+            __builtin_amdgcn_sched_barrier(0);              // (and no product of the next slice moves up to wait for them)
+            af = afn;
+        });
+        bf[0] = bfn;
+        buf = buf1;
+    }
+
+    // The wavefronts kg = 0 and 1 of an output block hold the sums over the even and the odd k-blocks.  Each hands
+    // over half of its accumulator registers (kg = 0 finishes r < 8, kg = 1 the others): 16 bytes per lane and
+    // group of four registers, in LDS nobody else uses any more.
+    wait_vmcnt<0>();
+    __syncthreads();
+    v4i *xch = (v4i *)lds + (size_t)(wave & 3) * (2 * S * 2 * 64) + lane;
+#pragma unroll
+    for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const int q0 = 8 + 4 * g, q1 = 4 * g;       // registers handed over by kg = 0 / kg = 1
+            v4i v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = kg ? acc[a][q1 + r] : acc[a][q0 + r];
+            xch[((kg * S + a) * 2 + g) * 64] = v;
+        }
+    __syncthreads();
+    int D[S][8];
+#pragma unroll
+    for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const v4i v = xch[(((kg ^ 1) * S + a) * 2 + g) * 64];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) D[a][g * 4 + r] = v[r] + (kg ? acc[a][8 + 4 * g + r] : acc[a][4 * g + r]);
+        }
+    const int mi = (tm * 2 + wm) * 32 + (lane & 31);
+    if (mi >= m) return;
+    const int ea = eA[mi];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const int rr = kg * 8 + r;
+        const int nj = (tn * 2 + wn) * 32 + 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
+        if (nj >= n) continue;
+        int d[S];
+#pragma unroll
+        for (int a = 0; a < S; ++a) d[a] = D[a][r];
+        __builtin_nontemporal_store(ldexp(diagonal_sum<S>(d, Q), ea + eB[nj]), &C[mi + (size_t)nj * ldc]);
+    }
+}
+
+// ---- tile 32 x 32, eight wavefronts along k, operands straight from memory into registers --------------------------
+// Nothing of a tile is shared between wavefronts, so nothing goes through LDS and the loop has no barrier: wavefront w
+// takes the k-blocks w, w + 8, ...; row l of the products frees slice l of A and slice S - 1 - l of B, which are
+// loaded again for its next k-block at once.  The eight sums per output meet in LDS, kRound diagonals at a time;
+// wavefront w finishes accumulator registers 2 w and 2 w + 1.
+template <int S>
+struct CfgEighths {
+    static constexpr int ROUND = S == 1 ? 1 : S <= 5 ? 2 : 4;             // diagonals per round: 32 KiB of LDS each
+    static constexpr int LDS = ROUND * 8 * 8 * 64 * 8;
+};
+
+template <int S>
+__global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restrict__ pA, const int8_t *__restrict__ pB,
+                                                           const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
+                                                           double *__restrict__ C, int ldc, int m, int n, int KB,
+                                                           int tiles_m, int tiles_n, int Q)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    // (four 32 x 32 tiles of a 64 x 64 one after the other; quarters beyond the edge have nothing to do)
+    const int quarter = blockIdx.x & 3, t64 = blockIdx.x >> 2, tiles64_m = (tiles_m + 1) / 2;
+    const int tm = (t64 % tiles64_m) * 2 + (quarter & 1), tn = (t64 / tiles64_m) * 2 + (quarter >> 1);
+    if (tm >= tiles_m || tn >= tiles_n) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t row_bytes = (size_t)KB * (S * kFragBytes);
+    v16i acc[S];
+#pragma unroll
+    for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][r] = 0;
+    if (wave < KB) {
+        const v4i *a = (const v4i *)(pA + (size_t)tm * row_bytes + (size_t)wave * (S * kFragBytes)) + lane;
+        const v4i *b = (const v4i *)(pB + (size_t)tn * row_bytes + (size_t)wave * (S * kFragBytes)) + lane;
+        v4i af[S], bf[S];
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            af[q] = a[q * 64];
+            bf[S - 1 - q] = b[(S - 1 - q) * 64];
+        }
+        for (int kb = wave; kb < KB; kb += 8) {
+            // (the last k-block of a wavefront is loaded once more: nobody uses it)
+            const size_t step = kb + 8 < KB ? (size_t)8 * S * 64 : 0;
+            a += step;
+            b += step;
+            static_for<0, S>([&](auto L) {
+                constexpr int l = decltype(L)::value;
+                static_for<0, S - l>([&](auto HH) {
+                    constexpr int h = S - 1 - l - decltype(HH)::value;
+                    acc[l + h] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[h], af[l], acc[l + h], 0, 0, 0);
+                });
+                af[l] = a[l * 64];
+                bf[S - 1 - l] = b[(S - 1 - l) * 64];
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+    }
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    v2i *x = (v2i *)lds;
+    int D[2][S];
+    constexpr int ROUND = CfgEighths<S>::ROUND;
+    static_for<0, (S + ROUND - 1) / ROUND>([&](auto P) {
+        constexpr int a0 = decltype(P)::value * ROUND, a1 = a0 + ROUND < S ? a0 + ROUND : S;
+        if constexpr (a0 > 0) __syncthreads();
+#pragma unroll
+        for (int a = a0; a < a1; ++a)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) x[(((a - a0) * 8 + r) * 8 + wave) * 64 + lane] = v2i{acc[a][2 * r], acc[a][2 * r + 1]};
+        __syncthreads();
+#pragma unroll
+        for (int a = a0; a < a1; ++a) {
+            v2i s{0, 0};
+#pragma unroll
+            for (int w = 0; w < 8; ++w) s += x[(((a - a0) * 8 + wave) * 8 + w) * 64 + lane];
+            D[0][a] = s[0];
+            D[1][a] = s[1];
+        }
+    });
+    const int mi = tm * 32 + (lane & 31);
+    if (mi >= m) return;
+    const int ea = eA[mi];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int rr = 2 * wave + r;
+        const int nj = tn * 32 + 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
+        if (nj < n) __builtin_nontemporal_store(ldexp(diagonal_sum<S>(D[r], Q), ea + eB[nj]), &C[mi + (size_t)nj * ldc]);
+    }
+}
+
+template <int S>
+hipError_t launch_halves(int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA, const int32_t *eB,
+                         double *C, int ldc, int Q, hipStream_t st)
+{
+    auto kern = gemm_halves_kernel<S>;
+    static std::atomic<unsigned long long> configured{0};
+    if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgHalves<S>::LDS, configured); e != hipSuccess) return e;
+    const int tiles_m = (m + 63) / 64, tiles_n = (n + 63) / 64;
+    note_gemm_kernel("gemm_fused_kernel<%d> equal counts tile 64x64, 8 wavefronts, k in halves", S);
+    kern<<<(unsigned)tile_order_blocks(tiles_m, tiles_n, false), 512, CfgHalves<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag,
+                                                                                           tiles_m, tiles_n, Q);
+    return hipGetLastError();
+}
+
+template <int S>
+hipError_t launch_eighths(int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA, const int32_t *eB,
+                          double *C, int ldc, int Q, hipStream_t st)
+{
+    auto kern = gemm_eighths_kernel<S>;
+    static std::atomic<unsigned long long> configured{0};
+    if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgEighths<S>::LDS, configured); e != hipSuccess) return e;
+    const int tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
+    note_gemm_kernel("gemm_fused_kernel<%d> equal counts tile 64x64 as four of 32x32, 8 wavefronts, k in eighths", S);
+    kern<<<4u * ((tiles_m + 1) / 2) * ((tiles_n + 1) / 2), 512, CfgEighths<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, Q);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_gemm_halves(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
+                              const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
+{
+    if (m <= 0 || n <= 0) return hipSuccess;
+    switch (s) {
+#define OZ_CASE(S_) case S_: return launch_halves<S_>(m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
+        OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9)
+#undef OZ_CASE
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_eighths(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
+                               const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
+{
+    if (m <= 0 || n <= 0) return hipSuccess;
+    switch (s) {
+#define OZ_CASE(S_) case S_: return launch_eighths<S_>(m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
+        OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9) OZ_CASE(10)
+#undef OZ_CASE
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace oz

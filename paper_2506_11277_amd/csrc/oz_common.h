@@ -238,6 +238,12 @@ void fused16_set_tile_choice(int choice);   // test knob: 0 automatic, 1 tabulat
 hipError_t launch_gemm_fused16(int m, int n, int kp, int s, const int8_t *pA, const int8_t *pB,
                                const int32_t *eA, const int32_t *eB, double *C, int ldc,
                                int32_t *dump, long long *totals, int Q, bool kslots, hipStream_t st);
+// equal counts, whole contraction in int32, problems that do not fill the chip (gemm_small.hip): 64 x 64 tiles with the
+// contraction in halves (2 <= s <= 9), 32 x 32 tiles with the contraction in eighths (s <= 10)
+hipError_t launch_gemm_halves(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
+                              const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
+hipError_t launch_gemm_eighths(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
+                               const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
 // product sets beyond the fused kernels (planes with the slices per entry of blocks_plan); totals: blocks_totals_bytes()
 hipError_t launch_gemm_blocks(int m, int n, int kp, int sA, int sB, bool all_products, const int8_t *pA,
                               const int8_t *pB, const int32_t *eA, const int32_t *eB, double *C, int ldc,
