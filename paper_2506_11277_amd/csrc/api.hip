@@ -260,14 +260,20 @@ static int dgemm_impl(int m, int n, int k, const double *A, int lda, const doubl
     prof_mark(prof, 0, st);
     auto *eA = (int32_t *)(ws + w.off_expA), *eB = (int32_t *)(ws + w.off_expB);
     auto *pA = (int8_t *)(ws + w.off_planesA), *pB = (int8_t *)(ws + w.off_planesB);
-    // two launches for the maxima of both operands, one for their exponents and slices
+    // short contractions: one launch for exponents and slices; else two for the maxima of both operands, one for the rest
     auto *maxA = (unsigned long long *)(ws + w.off_maxA), *maxB = (unsigned long long *)(ws + w.off_maxB);
-    OZ_TRY(launch_scales_fused(m, n, k, A, lda, B, ldb, (unsigned long long *)(ws + w.off_header), maxA, maxB, eA, w.mp,
-                               eB, w.np, nearest ? 1 : 0, m == 0 || n == 0, st));
-    if (m == 0 || n == 0) return OZIMMU_OK;
-    prof_mark(prof, 1, st);
+    auto *hdr = (unsigned long long *)(ws + w.off_header);
     // (w.cA, w.cB: the counts the GEMM runs with -- counts that differ little run as equal ones, zero slices appended)
-    OZ_TRY(launch_split_both(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, maxA, maxB, eA, eB, pA, pB, nearest, st));
+    if (scale_split_handles(m, n, k)) {
+        prof_mark(prof, 1, st);
+        OZ_TRY(launch_scale_split(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, eA, eB, pA, pB, nearest, hdr, w.off_minA, st));
+    } else {
+        OZ_TRY(launch_scales_fused(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, eA, w.mp, eB, w.np, nearest ? 1 : 0,
+                                   m == 0 || n == 0, st));
+        if (m == 0 || n == 0) return OZIMMU_OK;
+        prof_mark(prof, 1, st);
+        OZ_TRY(launch_split_both(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, maxA, maxB, eA, eB, pA, pB, nearest, st));
+    }
     prof_mark(prof, 2, st);
     const int cA = w.cA, cB = w.cB;
     if (w.path == kPathBlocks) {
@@ -394,11 +400,24 @@ int ozimmu_profile_stop(int *calls, float *phase_ms)
 int ozimmu_check(void *workspace, void *stream)
 {
     if (!workspace) return OZIMMU_BAD_ARG;
-    unsigned int flag = 0;
+    unsigned long long header[kHeaderBadWords + 3];
     hipStream_t st = (hipStream_t)stream;
-    OZ_TRY(hipMemcpyAsync(&flag, workspace, sizeof(flag), hipMemcpyDeviceToHost, st));
+    OZ_TRY(hipMemcpyAsync(header, workspace, sizeof(header), hipMemcpyDeviceToHost, st));
     OZ_TRY(hipStreamSynchronize(st));
-    return (flag & 1u) ? OZIMMU_NONFINITE : OZIMMU_OK;
+    if (header[0] & 1ULL) return OZIMMU_NONFINITE;
+    // a call that formed scales and slices in one launch has left a word per work-group instead
+    if (header[kHeaderBadWords + 2] != kBadWordsMagic) return OZIMMU_OK;
+    const char *words = (const char *)workspace + header[kHeaderBadWords + 1];
+    for (unsigned long long i = 0; i < header[kHeaderBadWords];) {
+        unsigned int bad[1024];
+        const unsigned long long left = header[kHeaderBadWords] - i, cnt = left < 1024 ? left : 1024;
+        OZ_TRY(hipMemcpyAsync(bad, words + 4 * i, 4 * cnt, hipMemcpyDeviceToHost, st));
+        OZ_TRY(hipStreamSynchronize(st));
+        for (unsigned long long j = 0; j < cnt; ++j)
+            if (bad[j]) return OZIMMU_NONFINITE;
+        i += cnt;
+    }
+    return OZIMMU_OK;
 }
 
 int ozimmu_get_exponents(int m, int n, int k, int s, const void *workspace, int32_t *eA, int32_t *eB, void *stream)

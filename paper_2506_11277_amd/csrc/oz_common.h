@@ -112,8 +112,8 @@ struct Workspace {
     int mp, np, kp;                 // padded extents
     int cA, cB;                     // slices per entry in the planes (gemm_path)
     int path;                       // GemmPath
-    size_t off_header;              // 256 B: [0] u32 non-finite flag, [8] u64 kappa_A bits, [16] u64 kappa_B bits
-    size_t off_maxA, off_minA;      // u64[mp]: integer view of max |a_ij| / min nonzero |a_ij| per row
+    size_t off_header;              // 256 B: [0] u32 non-finite flag, [8] u64 kappa_A bits, [16] u64 kappa_B bits, [64] see kHeaderBadWords
+    size_t off_maxA, off_minA;      // u64[mp]: integer view of max |a_ij| / min nonzero |a_ij| per row (minA onwards: the non-finite words of launch_scale_split)
     size_t off_maxB, off_minB;      // u64[np]
     size_t off_expA, off_expB;      // i32[mp], i32[np]
     size_t off_planesA, off_planesB;
@@ -188,6 +188,17 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
 hipError_t launch_split_both(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int sA, int sB,
                              int cA, int cB, const unsigned long long *maxA, const unsigned long long *maxB,
                              int32_t *eA, int32_t *eB, int8_t *pA, int8_t *pB, bool nearest, hipStream_t st);
+
+// Scales AND slices of both operands in one launch (contractions up to 2048).  Instead of setting the header's
+// non-finite flag it leaves a word per work-group, 0 or 1, at bad_offset bytes from the header (a work-group per 16 rows
+// of A / columns of B), and says so in the header: [kHeaderBadWords] their number, then the offset, then
+// kBadWordsMagic.  ozimmu_check reads them.
+constexpr int kHeaderBadWords = 8;
+constexpr unsigned long long kBadWordsMagic = 0x6f7a696d6d754241ULL;
+bool scale_split_handles(int m, int n, int k);
+hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int sA, int sB, int cA,
+                              int cB, int32_t *eA, int32_t *eB, int8_t *pA, int8_t *pB, bool nearest,
+                              unsigned long long *header, size_t bad_offset, hipStream_t st);
 
 // ---- launchers implemented in gemm.hip ---------------------------------------------------
 // largest s the fused (all diagonals in registers) kernel handles

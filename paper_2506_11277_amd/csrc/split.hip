@@ -14,6 +14,8 @@
 //
 // The MFMA layout written here is the one the GEMM kernel reads (see include/ozimmu.h):
 // fragments of 32 (R) x 32 (K) bytes, 16 contiguous K-bytes per wavefront lane.
+#include <type_traits>
+
 #include "oz_common.h"
 
 namespace oz {
@@ -75,6 +77,111 @@ __device__ __forceinline__ unsigned int slice_of(const Elem &el, int l, unsigned
     return (unsigned int)d & 0xffu;
 }
 
+// Slices of four neighbouring entries (consecutive k) at a time, four bytes to a word.  A 64-bit shift by a variable
+// amount, a compare and a select per slice and entry made the slicing kernels arithmetic-bound at sizes that fit the
+// caches; here the significand is shifted ONCE so that nine slices (eight when rounding to nearest, whose last slice
+// needs the bit below it) lie at fixed bit positions of a 64-bit window -- slice j of the window at bits 63 - 7 j ...
+// 69 - 7 j --, and carry, sign and two's complement are handled for the four bytes of a word together.
+constexpr unsigned kOnes = 0x01010101u, kTops = 0x80808080u, kLows = 0x7f7f7f7fu;
+
+template <bool NEAREST>
+struct Quad {
+    static constexpr int WIN = NEAREST ? 8 : 9;       // slices per window
+    unsigned long long I[4];   // integer significands
+    int base[4];               // as Elem::base
+    unsigned neg;              // byte mask of the negative entries
+    unsigned sticky;           // NEAREST: byte i = last slice (at most 40) below whose guard bit entry i has bits left
+    unsigned carry;            // NEAREST: byte i = c_{l-1} of entry i
+    unsigned lo[4], hi[4];     // the window
+
+    __device__ __forceinline__ void load(const unsigned long long (&bits)[4], int e)
+    {
+        neg = sticky = carry = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const Elem el = decompose(bits[i], e);
+            I[i] = el.I;
+            base[i] = el.base;
+            neg |= el.neg ? 0xffu << (8 * i) : 0u;
+            if (NEAREST) {
+                // bits of I below the guard bit of slice l: ctz(I) < base - 7 l - 1, i.e. l <= (base - ctz - 2) / 7
+                int x = el.I ? base[i] - 2 - __builtin_ctzll(el.I) : 0;
+                x = x < 0 ? 0 : x > 7 * 40 ? 7 * 40 : x;
+                sticky |= (((unsigned)x * 9363u) >> 16) << (8 * i);      // x / 7
+            }
+        }
+    }
+    // window of the slices w + 1, w + 2, ...
+    __device__ __forceinline__ void window(int w)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int sh = base[i] - 63 - kSliceBits * w;
+            unsigned long long F;
+            if (sh >= 0) F = sh < 64 ? I[i] >> sh : 0ULL;
+            else F = sh > -64 ? I[i] << -sh : 0ULL;
+            lo[i] = (unsigned)F;
+            hi[i] = (unsigned)(F >> 32);
+        }
+    }
+    template <int P, int N>
+    __device__ __forceinline__ unsigned field(int i) const      // bits P ... P + N - 1 of the window of entry i
+    {
+        if constexpr (P >= 32) return (hi[i] >> (P - 32)) & ((1u << N) - 1);
+        else if constexpr (P + N <= 32) return (lo[i] >> P) & ((1u << N) - 1);
+        else return __builtin_amdgcn_alignbit(hi[i], lo[i], P) & ((1u << N) - 1);
+    }
+    template <int P, int N>
+    __device__ __forceinline__ unsigned fields() const
+    {
+        return field<P, N>(0) | (field<P, N>(1) << 8) | (field<P, N>(2) << 16) | (field<P, N>(3) << 24);
+    }
+    // the four bytes of slice l = w + J (slices in ascending order: the carry of slice l - 1 is kept)
+    template <int J>
+    __device__ __forceinline__ unsigned word(int l)
+    {
+        unsigned v;
+        if constexpr (!NEAREST) v = fields<63 - kSliceBits * J, 7>();
+        else {
+            const unsigned g = fields<62 - kSliceBits * J, 8>();         // slice and the guard bit below it
+            const unsigned f = (g >> 1) & kLows;
+            const unsigned left = (((sticky | kTops) - (unsigned)l * kOnes) >> 7) & kOnes;   // l <= sticky
+            const unsigned c = g & kOnes & (left | f);
+            v = (f + c) ^ (carry << 7);                                  // + c_l - 128 c_{l-1}, modulo 256
+            carry = c;
+        }
+        const unsigned minus = (kTops - (v & kLows)) ^ (~v & kTops);     // -v, byte by byte
+        return (minus & neg) | (v & ~neg);
+    }
+};
+
+// calls f(l, word of slice l) ... for N quads at once: f(l, words) for l = 1, ..., s
+template <bool NEAREST, int N, class F>
+__device__ __forceinline__ void for_each_slice(Quad<NEAREST> (&q)[N], int s, F &&f)
+{
+    for (int w = 0; w < s; w += Quad<NEAREST>::WIN) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) q[i].window(w);
+        auto one = [&](auto JC) {
+            constexpr int J = decltype(JC)::value;
+            if (w + J > s) return;
+            unsigned wd[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) wd[i] = q[i].template word<J>(w + J);
+            f(w + J, wd);
+        };
+        one(std::integral_constant<int, 1>{});
+        one(std::integral_constant<int, 2>{});
+        one(std::integral_constant<int, 3>{});
+        one(std::integral_constant<int, 4>{});
+        one(std::integral_constant<int, 5>{});
+        one(std::integral_constant<int, 6>{});
+        one(std::integral_constant<int, 7>{});
+        one(std::integral_constant<int, 8>{});
+        if constexpr (!NEAREST) one(std::integral_constant<int, 9>{});
+    }
+}
+
 // ---- side 'A': X is R x K column-major (R contiguous).  lane <-> row, each lane walks 16
 //      consecutive k, so the 16 K-bytes of a lane come out of registers: the transposition to
 //      K-contiguous fragments costs nothing, reads are 512 B per wavefront load, writes are
@@ -93,28 +200,24 @@ __device__ __forceinline__ void split_rows_block(int bx, int by, const unsigned 
     // work-groups of the first k-block store it, zero for the padding rows)
     const int e = r >= R ? 0 : maxbits ? exponent_above(maxbits[r]) + (NEAREST ? 1 : 0) : exps[r];
     if (exps_out && by == 0 && w == 0) exps_out[r] = e;
-    Elem el[16];
+    Quad<NEAREST> el[4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int kk = k0 + i;
-        unsigned long long bits = (r < R && kk < K) ? X[r + (size_t)kk * ldx] : 0ULL;
-        el[i] = decompose(bits, e);
+    for (int q = 0; q < 4; ++q) {
+        unsigned long long bits[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int kk = k0 + 4 * q + i;
+            bits[i] = (r < R && kk < K) ? X[r + (size_t)kk * ldx] : 0ULL;
+        }
+        el[q].load(bits, e);
     }
     const int rb = r >> 5, kb = k0 >> 5, half = (k0 >> 4) & 1;
     // (the planes hold cs >= s slices per entry; those beyond s are zeros)
     uint4 *dst = (uint4 *)(planes + ((size_t)rb * KB + kb) * (size_t)cs * kFragBytes) + ((r & 31) + 32 * half);
     for (int l = s + 1; l <= cs; ++l) dst[(size_t)(l - 1) * (kFragBytes / 16)] = make_uint4(0, 0, 0, 0);
-    unsigned int carry = 0;
-    for (int l = 1; l <= s; ++l) {
-        unsigned int wd[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            wd[q] = slice_of<NEAREST>(el[4 * q], l, carry, 4 * q) |
-                    (slice_of<NEAREST>(el[4 * q + 1], l, carry, 4 * q + 1) << 8) |
-                    (slice_of<NEAREST>(el[4 * q + 2], l, carry, 4 * q + 2) << 16) |
-                    (slice_of<NEAREST>(el[4 * q + 3], l, carry, 4 * q + 3) << 24);
+    for_each_slice<NEAREST, 4>(el, s, [&](int l, const unsigned (&wd)[4]) {
         dst[(size_t)(l - 1) * (kFragBytes / 16)] = make_uint4(wd[0], wd[1], wd[2], wd[3]);
-    }
+    });
 }
 
 // ---- side 'B': X is K x R column-major (K contiguous).  A work-group takes 32 columns x 128 k;
@@ -143,46 +246,42 @@ __device__ __forceinline__ void split_cols_block(int bx, int by, const unsigned 
     const int t = threadIdx.x;
     const int j0 = bx * 32, k0 = by * kColTileK;
     const int kq = (t & 31) * 4;
-    Elem el[4][4];
+    Quad<NEAREST> el[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const int jj = p * 8 + (t >> 5);
         const int j = j0 + jj;
         const int e = j >= R ? 0 : maxbits ? exponent_above(maxbits[j]) + (NEAREST ? 1 : 0) : exps[j];
         if (exps_out && by == 0 && (t & 31) == 0) exps_out[j] = e;
+        unsigned long long bits[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int kk = k0 + kq + i;
-            unsigned long long bits = (j < R && kk < K) ? X[kk + (size_t)j * ldx] : 0ULL;
-            el[p][i] = decompose(bits, e);
+            bits[i] = (j < R && kk < K) ? X[kk + (size_t)j * ldx] : 0ULL;
         }
+        el[p].load(bits, e);
     }
     const int jj2 = t & 31, ch = t >> 5;                    // phase 2: column, 16-byte chunk along k
     const int rb = j0 >> 5;
     const int kb = (k0 + ch * 16) >> 5, half = ch & 1;
     uint4 *dst = (uint4 *)(planes + ((size_t)rb * KB + kb) * (size_t)cs * kFragBytes) + (jj2 + 32 * half);
     for (int l = s + 1; l <= cs; ++l) dst[(size_t)(l - 1) * (kFragBytes / 16)] = make_uint4(0, 0, 0, 0);
-    unsigned int carry = 0;
-    for (int l0 = 1; l0 <= s; l0 += kColGroup) {
-        const int nl = (s - l0 + 1) < kColGroup ? (s - l0 + 1) : kColGroup;
-        for (int dl = 0; dl < nl; ++dl) {
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int jj = p * 8 + (t >> 5);
-                unsigned int wd = slice_of<NEAREST>(el[p][0], l0 + dl, carry, 4 * p) |
-                                  (slice_of<NEAREST>(el[p][1], l0 + dl, carry, 4 * p + 1) << 8) |
-                                  (slice_of<NEAREST>(el[p][2], l0 + dl, carry, 4 * p + 2) << 16) |
-                                  (slice_of<NEAREST>(el[p][3], l0 + dl, carry, 4 * p + 3) << 24);
-                *(unsigned int *)(lds + ((size_t)dl * 32 + jj) * kColLdsRow + kq) = wd;
-            }
-        }
+    // kColGroup slices at a time go through LDS (a window of nine slices is two groups)
+    auto drain = [&](int l) {                               // slices l - (l - 1) % kColGroup ... l are in LDS
+        const int nl = (l - 1) % kColGroup + 1;
         __syncthreads();
         for (int dl = 0; dl < nl; ++dl) {
             uint4 v = *(const uint4 *)(lds + ((size_t)dl * 32 + jj2) * kColLdsRow + ch * 16);
-            dst[(size_t)(l0 + dl - 1) * (kFragBytes / 16)] = v;
+            dst[(size_t)(l - nl + dl) * (kFragBytes / 16)] = v;
         }
         __syncthreads();
-    }
+    };
+    for_each_slice<NEAREST, 4>(el, s, [&](int l, const unsigned (&wd)[4]) {
+        const int dl = (l - 1) % kColGroup;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) *(unsigned int *)(lds + ((size_t)dl * 32 + p * 8 + (t >> 5)) * kColLdsRow + kq) = wd[p];
+        if (dl == kColGroup - 1 || l == s) drain(l);
+    });
 }
 
 template <bool NEAREST>
@@ -207,6 +306,91 @@ __global__ __launch_bounds__(256) void split_both_kernel(const unsigned long lon
     const int b = blockIdx.x;
     if (b < nblkA) split_rows_block<NEAREST>(b % gxA, b / gxA, A, lda, m, K, sA, cA, nullptr, pA, KB, maxA, eA);
     else split_cols_block<NEAREST>((b - nblkA) % gxB, (b - nblkA) / gxB, B, ldb, n, K, sB, cB, nullptr, pB, KB, maxB, eB);
+}
+
+// ---- scales and slices of both operands in one launch, for contractions short enough that a work-group keeps its
+// part of the operand in registers between the two.  A work-group owns 16 rows of A (columns of B) over all of k, so
+// their maxima need no atomics, nothing has to be cleared beforehand, and the operand is read once: at 1024^3, s = 7 one
+// launch takes the place of three (clear, reduce, slice).
+//
+// Lane = 16 rows x 4 quads: a quad is four consecutive k of a row, a wavefront takes 16 rows x 16 k at a time.  Either
+// operand is then read in 128-byte pieces (16 rows of a column of A, 16 k of a column of B), and the four bytes a lane
+// has of a slice make up 256 contiguous bytes of the fragment with those of the other lanes.
+// bad[b] != 0: work-group b has met a NaN or an infinity (the maximum of the bit patterns shows it).
+template <bool NEAREST, int NV>
+__global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long long *__restrict__ A, int lda, int m,
+                                                           const unsigned long long *__restrict__ B, int ldb, int n, int K,
+                                                           int sA, int sB, int cA, int cB, int32_t *__restrict__ eA,
+                                                           int32_t *__restrict__ eB, int8_t *__restrict__ pA,
+                                                           int8_t *__restrict__ pB, int KB, int panelsA,
+                                                           unsigned long long *__restrict__ header, int panels,
+                                                           long long bad_offset, unsigned *__restrict__ bad)
+{
+    __shared__ unsigned long long smx[16][16];
+    const bool isB = (int)blockIdx.x >= panelsA;
+    const int R0 = 16 * ((int)blockIdx.x - (isB ? panelsA : 0));
+    const unsigned long long *X = isB ? B : A;
+    const int ldx = isB ? ldb : lda, R = isB ? n : m, s = isB ? sB : sA, cs = isB ? cB : cA;
+    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    const int row = R0 + r;
+    const size_t rstep = isB ? (size_t)ldx : 1, kstep = isB ? 1 : (size_t)ldx;
+    const unsigned long long *p = X + (size_t)(row < R ? row : R - 1) * rstep;
+    if (blockIdx.x == 0 && threadIdx.x < 4) {
+        // header for ozimmu_check: no flag yet, where the words bad[] are, how many, and a word that makes it valid
+        const unsigned long long v[3] = {(unsigned long long)panels, (unsigned long long)bad_offset, kBadWordsMagic};
+        header[threadIdx.x == 0 ? 0 : kHeaderBadWords + threadIdx.x - 1] = threadIdx.x == 0 ? 0ULL : v[threadIdx.x - 1];
+    }
+
+    unsigned long long x[NV][4], mx = 0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int kq = 16 * (wave + nw * v) + 4 * q;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool in = row < R && kq + i < K;
+            x[v][i] = p[(size_t)(kq + i < K ? kq + i : K - 1) * kstep];
+            x[v][i] = in ? x[v][i] : 0ULL;
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const unsigned long long u = x[v][i] & 0x7fffffffffffffffULL;
+            mx = u > mx ? u : mx;
+        }
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+        const unsigned long long o = __shfl_xor(mx, off);
+        mx = o > mx ? o : mx;
+    }
+    if (q == 0) smx[wave][r] = mx;
+    __syncthreads();
+    mx = 0;
+    for (int i = 0; i < nw; ++i) {
+        const unsigned long long o = smx[i][r];
+        mx = o > mx ? o : mx;
+    }
+    const int e = row < R ? exponent_above(mx) + (NEAREST ? 1 : 0) : 0;
+    if (wave == 0) {
+        if (q == 0) (isB ? eB : eA)[row] = e;
+        const unsigned long long any = __ballot(mx >= 0x7ff0000000000000ULL);
+        if (lane == 0) bad[blockIdx.x] = any ? 1u : 0u;
+    }
+
+    int8_t *base = (isB ? pB : pA) + (size_t)(row >> 5) * KB * ((size_t)cs * kFragBytes) + (row & 31) * 16 + 4 * q;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int c = wave + nw * v;                            // 16 k: half c % 2 of fragment c / 2
+        if (c >= 2 * KB) continue;
+        unsigned *dst = (unsigned *)(base + (size_t)(c >> 1) * ((size_t)cs * kFragBytes) + (c & 1) * (32 * 16));
+        Quad<NEAREST> el[1];
+        el[0].load(x[v], e);
+        for_each_slice<NEAREST, 1>(el, s, [&](int l, const unsigned (&wd)[1]) { dst[(size_t)(l - 1) * (kFragBytes / 4)] = wd[0]; });
+        // (the planes hold cs >= s slices per entry; those beyond s are zeros)
+        for (int l = s + 1; l <= cs; ++l) dst[(size_t)(l - 1) * (kFragBytes / 4)] = 0;
+    }
 }
 
 // ---- plain layout: plane l is a matrix shaped like X (utility / test path) ----
@@ -253,6 +437,32 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
         auto kern = nearest ? split_cols_kernel<true> : split_cols_kernel<false>;
         kern<<<grid, 256, 0, st>>>((const unsigned long long *)X, ldx, R, K, s, exps, planes, KB);
     }
+    return hipGetLastError();
+}
+
+bool scale_split_handles(int m, int n, int k)
+{
+    return m > 0 && n > 0 && k > 0 && round_up(k, kPad) <= 2048;
+}
+
+hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int sA, int sB, int cA,
+                              int cB, int32_t *eA, int32_t *eB, int8_t *pA, int8_t *pB, bool nearest,
+                              unsigned long long *header, size_t bad_offset, hipStream_t st)
+{
+    if (!scale_split_handles(m, n, k) || cA < sA || cB < sB) return hipErrorInvalidValue;
+    const int kp = round_up(k, kPad), panelsA = (m + 15) / 16, panels = panelsA + (n + 15) / 16;
+    auto *bad = (unsigned *)((char *)header + bad_offset);
+    auto launch = [&](auto NVC) {
+        constexpr int NV = decltype(NVC)::value;
+        auto kern = nearest ? scale_split_kernel<true, NV> : scale_split_kernel<false, NV>;
+        kern<<<panels, kp <= 128 ? 512 : 1024, 0, st>>>((const unsigned long long *)A, lda, m, (const unsigned long long *)B, ldb, n, k,
+                                                        sA, sB, cA, cB, eA, eB, pA, pB, kp / kFrag, panelsA, header, panels,
+                                                        (long long)bad_offset, bad);
+    };
+    if (kp <= 256) launch(std::integral_constant<int, 1>{});
+    else if (kp <= 512) launch(std::integral_constant<int, 2>{});
+    else if (kp <= 1024) launch(std::integral_constant<int, 4>{});
+    else launch(std::integral_constant<int, 8>{});
     return hipGetLastError();
 }
 
