@@ -189,9 +189,9 @@ hipError_t launch_split_both(int m, int n, int k, const double *A, int lda, cons
                              int cA, int cB, const unsigned long long *maxA, const unsigned long long *maxB,
                              int32_t *eA, int32_t *eB, int8_t *pA, int8_t *pB, bool nearest, hipStream_t st);
 
-// Scales AND slices of both operands in one launch (contractions up to 2048).  Instead of setting the header's
-// non-finite flag it leaves a word per work-group, 0 or 1, at bad_offset bytes from the header (a work-group per 16 rows
-// of A / columns of B), and says so in the header: [kHeaderBadWords] their number, then the offset, then
+// Scales AND slices of both operands in one launch (contractions up to 2048, for fewer rows 4096).  Instead of setting the header's
+// non-finite flag it leaves a word per work-group, 0 or 1, at bad_offset bytes from the header (a work-group per four or
+// eight rows of A / columns of B), and says so in the header: [kHeaderBadWords] their number, then the offset, then
 // kBadWordsMagic.  ozimmu_check reads them.
 constexpr int kHeaderBadWords = 8;
 constexpr unsigned long long kBadWordsMagic = 0x6f7a696d6d754241ULL;

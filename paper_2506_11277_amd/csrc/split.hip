@@ -309,15 +309,16 @@ __global__ __launch_bounds__(256) void split_both_kernel(const unsigned long lon
 }
 
 // ---- scales and slices of both operands in one launch, for contractions short enough that a work-group keeps its
-// part of the operand in registers between the two.  A work-group owns 16 rows of A (columns of B) over all of k, so
-// their maxima need no atomics, nothing has to be cleared beforehand, and the operand is read once: at 1024^3, s = 7 one
-// launch takes the place of three (clear, reduce, slice).
+// part of the operand in registers between the two.  A work-group owns PR rows of A (columns of B) over all of k, so
+// their maxima need no atomics, nothing has to be cleared beforehand, and the operand is read once: one launch takes the
+// place of three (clear, reduce, slice), with their event overhead 30.8 -> 21.5 us at 1024^3, s = 7, 19.7 -> 11.8 us at 128^3.
 //
-// Lane = 16 rows x 4 quads: a quad is four consecutive k of a row, a wavefront takes 16 rows x 16 k at a time.  Either
-// operand is then read in 128-byte pieces (16 rows of a column of A, 16 k of a column of B), and the four bytes a lane
-// has of a slice make up 256 contiguous bytes of the fragment with those of the other lanes.
+// A lane holds quads, four consecutive k of a row; a wavefront takes PR rows x 16 (16 / PR) k at a time, up to 16
+// wavefronts share k.  The work-group's PR rows are a part of the 16 rows of a cache line of A: the work-groups of one
+// line run on the same XCD, one after the other in launch order.  The four bytes a lane has of a slice make up PR * 16
+// contiguous bytes of the fragment with those of its neighbours.
 // bad[b] != 0: work-group b has met a NaN or an infinity (the maximum of the bit patterns shows it).
-template <bool NEAREST, int NV>
+template <bool NEAREST, int PR, int NV>
 __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long long *__restrict__ A, int lda, int m,
                                                            const unsigned long long *__restrict__ B, int ldb, int n, int K,
                                                            int sA, int sB, int cA, int cB, int32_t *__restrict__ eA,
@@ -326,17 +327,21 @@ __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long l
                                                            unsigned long long *__restrict__ header, int panels,
                                                            long long bad_offset, unsigned *__restrict__ bad)
 {
-    __shared__ unsigned long long smx[16][16];
-    const bool isB = (int)blockIdx.x >= panelsA;
-    const int R0 = 16 * ((int)blockIdx.x - (isB ? panelsA : 0));
+    constexpr int CW = 16 / PR;                             // groups of 16 k a wavefront takes at a time
+    __shared__ unsigned long long smx[16][PR];
+    // (work-groups are dealt round-robin to the 8 XCDs: each XCD takes neighbouring panels, which share cache lines)
+    const int panel = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    if (panel >= panels) return;
+    const bool isB = panel >= panelsA;
+    const int R0 = PR * (panel - (isB ? panelsA : 0));
     const unsigned long long *X = isB ? B : A;
     const int ldx = isB ? ldb : lda, R = isB ? n : m, s = isB ? sB : sA, cs = isB ? cB : cA;
-    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int lane = threadIdx.x & 63, r = lane % PR, q = lane / PR % 4, cl = lane / PR / 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
     const int row = R0 + r;
     const size_t rstep = isB ? (size_t)ldx : 1, kstep = isB ? 1 : (size_t)ldx;
     const unsigned long long *p = X + (size_t)(row < R ? row : R - 1) * rstep;
-    if (blockIdx.x == 0 && threadIdx.x < 4) {
+    if (panel == 0 && threadIdx.x < 4) {
         // header for ozimmu_check: no flag yet, where the words bad[] are, how many, and a word that makes it valid
         const unsigned long long v[3] = {(unsigned long long)panels, (unsigned long long)bad_offset, kBadWordsMagic};
         header[threadIdx.x == 0 ? 0 : kHeaderBadWords + threadIdx.x - 1] = threadIdx.x == 0 ? 0ULL : v[threadIdx.x - 1];
@@ -345,7 +350,7 @@ __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long l
     unsigned long long x[NV][4], mx = 0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int kq = 16 * (wave + nw * v) + 4 * q;
+        const int kq = 16 * ((wave + nw * v) * CW + cl) + 4 * q;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bool in = row < R && kq + i < K;
@@ -361,11 +366,11 @@ __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long l
             mx = u > mx ? u : mx;
         }
 #pragma unroll
-    for (int off = 16; off <= 32; off <<= 1) {
+    for (int off = PR; off <= 32; off <<= 1) {
         const unsigned long long o = __shfl_xor(mx, off);
         mx = o > mx ? o : mx;
     }
-    if (q == 0) smx[wave][r] = mx;
+    if (lane < PR) smx[wave][r] = mx;
     __syncthreads();
     mx = 0;
     for (int i = 0; i < nw; ++i) {
@@ -374,15 +379,15 @@ __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long l
     }
     const int e = row < R ? exponent_above(mx) + (NEAREST ? 1 : 0) : 0;
     if (wave == 0) {
-        if (q == 0) (isB ? eB : eA)[row] = e;
+        if (lane < PR) (isB ? eB : eA)[row] = e;
         const unsigned long long any = __ballot(mx >= 0x7ff0000000000000ULL);
-        if (lane == 0) bad[blockIdx.x] = any ? 1u : 0u;
+        if (lane == 0) bad[panel] = any ? 1u : 0u;
     }
 
     int8_t *base = (isB ? pB : pA) + (size_t)(row >> 5) * KB * ((size_t)cs * kFragBytes) + (row & 31) * 16 + 4 * q;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-        const int c = wave + nw * v;                            // 16 k: half c % 2 of fragment c / 2
+        const int c = (wave + nw * v) * CW + cl;                // 16 k: half c % 2 of fragment c / 2
         if (c >= 2 * KB) continue;
         unsigned *dst = (unsigned *)(base + (size_t)(c >> 1) * ((size_t)cs * kFragBytes) + (c & 1) * (32 * 16));
         Quad<NEAREST> el[1];
@@ -440,9 +445,14 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
     return hipGetLastError();
 }
 
+// Contractions up to 2048 always; up to 4096 while the operands have a few thousand rows and columns (both phases of two
+// launches against one, us: 2048 x 2048 x 4096 s = 7 81.7 -> 67.4, 1024 x 1024 x 4096 52.5 -> 40.5, but 4096^3 147.7 -> 157.5: there a
+// work-group's loads wait for a chip that is busy anyway, and the register-resident form has fewer wavefronts)
 bool scale_split_handles(int m, int n, int k)
 {
-    return m > 0 && n > 0 && k > 0 && round_up(k, kPad) <= 2048;
+    if (m <= 0 || n <= 0 || k <= 0) return false;
+    const int kp = round_up(k, kPad);
+    return kp <= 2048 || (kp <= 4096 && (long long)m + n <= 6000);
 }
 
 hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int sA, int sB, int cA,
@@ -450,19 +460,28 @@ hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, con
                               unsigned long long *header, size_t bad_offset, hipStream_t st)
 {
     if (!scale_split_handles(m, n, k) || cA < sA || cB < sB) return hipErrorInvalidValue;
-    const int kp = round_up(k, kPad), panelsA = (m + 15) / 16, panels = panelsA + (n + 15) / 16;
+    const int kp = round_up(k, kPad);
     auto *bad = (unsigned *)((char *)header + bad_offset);
-    auto launch = [&](auto NVC) {
-        constexpr int NV = decltype(NVC)::value;
-        auto kern = nearest ? scale_split_kernel<true, NV> : scale_split_kernel<false, NV>;
-        kern<<<panels, kp <= 128 ? 512 : 1024, 0, st>>>((const unsigned long long *)A, lda, m, (const unsigned long long *)B, ldb, n, k,
-                                                        sA, sB, cA, cB, eA, eB, pA, pB, kp / kFrag, panelsA, header, panels,
-                                                        (long long)bad_offset, bad);
+    auto launch = [&](auto PRC, auto NVC) {
+        constexpr int PR = decltype(PRC)::value, NV = decltype(NVC)::value;
+        const int panelsA = (m + PR - 1) / PR, panels = panelsA + (n + PR - 1) / PR, waves = kp / 16 * PR / 16;
+        auto kern = nearest ? scale_split_kernel<true, PR, NV> : scale_split_kernel<false, PR, NV>;
+        kern<<<(panels + 7) / 8 * 8, 64 * (waves < 1 ? 1 : waves < 16 ? waves : 16), 0, st>>>(
+            (const unsigned long long *)A, lda, m, (const unsigned long long *)B, ldb, n, k, sA, sB, cA, cB, eA, eB, pA, pB, kp / kFrag,
+            panelsA, header, panels, (long long)bad_offset, bad);
     };
-    if (kp <= 256) launch(std::integral_constant<int, 1>{});
-    else if (kp <= 512) launch(std::integral_constant<int, 2>{});
-    else if (kp <= 1024) launch(std::integral_constant<int, 4>{});
-    else launch(std::integral_constant<int, 8>{});
+    auto by_k = [&](auto PRC) {
+        constexpr int PR = decltype(PRC)::value, SWEEP = 16 * 16 * (16 / PR);       // k of 16 wavefronts
+        if (kp <= SWEEP) launch(PRC, std::integral_constant<int, 1>{});
+        else if (kp <= 2 * SWEEP) launch(PRC, std::integral_constant<int, 2>{});
+        else launch(PRC, std::integral_constant<int, 4>{});
+    };
+    // Four rows to a work-group put the most compute units to work (a compute unit takes in some 10-25 GB/s whatever
+    // it asks for: 1024^3 s = 7 27.1 / 21.3 / 21.5 us for 16 / 8 / 4 rows, 256 x 256 x 1024 25.4 / 18.3 / 15.4, 1024 x 1024 x 2048 41.0 /
+    // 25.9 / 24.4, 2048^3 40.9 / 42.7 / 37.5; two rows: 29.7 in the last but one); eight where there are plenty of rows
+    // and the pieces of cache lines begin to count (8192 x 8192 x 1024: 69.6 / 59.4 / 63.9)
+    if (kp <= 2048 && (long long)m + n >= 12288) by_k(std::integral_constant<int, 8>{});
+    else by_k(std::integral_constant<int, 4>{});
     return hipGetLastError();
 }
 

@@ -58,3 +58,42 @@ def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
         assert kernel in ozimmu.last_gemm_kernel(), ozimmu.last_gemm_kernel()
     check(C, A, B, s, s)
     check(ozimmu.dgemm3(dA, dB, s, s, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2), A, B, s, s, nearest=True, Q=2)
+
+
+@pytest.mark.parametrize("m,n,k", [(5, 3, 1), (4, 9, 127), (64, 6, 128), (17, 33, 129), (70, 50, 1023), (70, 50, 1024), (31, 8, 1025),
+                                   (9, 130, 2048), (33, 20, 2049), (65, 40, 4096), (7, 5, 4097), (9000, 3288, 40), (8200, 4100, 513),
+                                   (12000, 300, 1100)])
+@pytest.mark.parametrize("sA,sB,nearest", [(1, 1, False), (7, 7, True), (9, 9, False), (9, 10, True), (19, 18, False), (24, 32, True)])
+def test_scales_and_slices_in_one_launch(m, n, k, sA, sB, nearest):
+    # every number of sweeps over k, both panel heights, the limits of the rule, windows of slices that end on and off
+    # a whole window, zero slices appended to the short operand, leading dimensions that are odd
+    if m > 4000 and sA + sB > 19:
+        pytest.skip("large shapes with one pair of windows only")
+    A, B = workloads.pow2_scaled(m, n, k, 30, 11 + k)
+    if m > 4 and k > 2:
+        special(A, B)
+    dA, dB = ozimmu.colmajor_empty(m + 1, k)[1:, :], ozimmu.colmajor_empty(k + 3, n)[:k, :]
+    dA.copy_(torch.as_tensor(A))
+    dB.copy_(torch.as_tensor(B))
+    splitting = ozimmu.SPLIT_NEAREST if nearest else ozimmu.SPLIT_TRUNCATE
+    check(ozimmu.dgemm3(dA, dB, sA, sB, splitting=splitting), A, B, sA, sB, nearest=nearest)
+
+
+@pytest.mark.parametrize("k", [100, 3000, 5000])
+def test_non_finite_is_reported_and_forgotten(k):
+    # the report of a call replaces that of the call before it in the same workspace, whichever way either slices
+    m, n, s = 70, 6000 if k == 3000 else 50, 3
+    A, B = workloads.uniform(m, n, k, 3)
+    ws = torch.empty(max(ozimmu.workspace_bytes(m, n, kk, s) for kk in (k, 100)), dtype=torch.uint8, device="cuda")
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    small = ozimmu.to_colmajor(A[:, :100]), ozimmu.to_colmajor(B[:100])
+    for X, at, value in [(dA, (0, 0), np.nan), (dA, (m - 1, k - 1), -np.inf), (dB, (k - 1, n - 1), np.inf), (dB, (k // 2, 17), np.nan)]:
+        old = X[at].item()
+        X[at] = value
+        with pytest.raises(ozimmu.OzimmuError):
+            ozimmu.dgemm(dA, dB, s, workspace=ws, check_finite=True)
+        ozimmu.dgemm(*small, s, workspace=ws, check_finite=True)
+        X[at] = old
+        ozimmu.dgemm(dA, dB, s, workspace=ws, check_finite=True)
+        assert ozimmu.estimate_slices(dA, dB, 1e-6, workspace=ws)[1] in (ozimmu.OK, ozimmu.UNREACHABLE)
+        ozimmu.check(ws)
