@@ -14,9 +14,7 @@
 //
 // The MFMA layout written here is the one the GEMM kernel reads (see include/ozimmu.h):
 // fragments of 32 (R) x 32 (K) bytes, 16 contiguous K-bytes per wavefront lane.
-#include <type_traits>
-
-#include "oz_common.h"
+#include "slice_dev.h"
 
 namespace oz {
 
@@ -75,111 +73,6 @@ __device__ __forceinline__ unsigned int slice_of(const Elem &el, int l, unsigned
     carry = (carry & ~(1u << bit)) | ((unsigned int)c << bit);
     d = el.neg ? -d : d;
     return (unsigned int)d & 0xffu;
-}
-
-// Slices of four neighbouring entries (consecutive k) at a time, four bytes to a word.  A 64-bit shift by a variable
-// amount, a compare and a select per slice and entry made the slicing kernels arithmetic-bound at sizes that fit the
-// caches; here the significand is shifted ONCE so that nine slices (eight when rounding to nearest, whose last slice
-// needs the bit below it) lie at fixed bit positions of a 64-bit window -- slice j of the window at bits 63 - 7 j ...
-// 69 - 7 j --, and carry, sign and two's complement are handled for the four bytes of a word together.
-constexpr unsigned kOnes = 0x01010101u, kTops = 0x80808080u, kLows = 0x7f7f7f7fu;
-
-template <bool NEAREST>
-struct Quad {
-    static constexpr int WIN = NEAREST ? 8 : 9;       // slices per window
-    unsigned long long I[4];   // integer significands
-    int base[4];               // as Elem::base
-    unsigned neg;              // byte mask of the negative entries
-    unsigned sticky;           // NEAREST: byte i = last slice (at most 40) below whose guard bit entry i has bits left
-    unsigned carry;            // NEAREST: byte i = c_{l-1} of entry i
-    unsigned lo[4], hi[4];     // the window
-
-    __device__ __forceinline__ void load(const unsigned long long (&bits)[4], int e)
-    {
-        neg = sticky = carry = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const Elem el = decompose(bits[i], e);
-            I[i] = el.I;
-            base[i] = el.base;
-            neg |= el.neg ? 0xffu << (8 * i) : 0u;
-            if (NEAREST) {
-                // bits of I below the guard bit of slice l: ctz(I) < base - 7 l - 1, i.e. l <= (base - ctz - 2) / 7
-                int x = el.I ? base[i] - 2 - __builtin_ctzll(el.I) : 0;
-                x = x < 0 ? 0 : x > 7 * 40 ? 7 * 40 : x;
-                sticky |= (((unsigned)x * 9363u) >> 16) << (8 * i);      // x / 7
-            }
-        }
-    }
-    // window of the slices w + 1, w + 2, ...
-    __device__ __forceinline__ void window(int w)
-    {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int sh = base[i] - 63 - kSliceBits * w;
-            unsigned long long F;
-            if (sh >= 0) F = sh < 64 ? I[i] >> sh : 0ULL;
-            else F = sh > -64 ? I[i] << -sh : 0ULL;
-            lo[i] = (unsigned)F;
-            hi[i] = (unsigned)(F >> 32);
-        }
-    }
-    template <int P, int N>
-    __device__ __forceinline__ unsigned field(int i) const      // bits P ... P + N - 1 of the window of entry i
-    {
-        if constexpr (P >= 32) return (hi[i] >> (P - 32)) & ((1u << N) - 1);
-        else if constexpr (P + N <= 32) return (lo[i] >> P) & ((1u << N) - 1);
-        else return __builtin_amdgcn_alignbit(hi[i], lo[i], P) & ((1u << N) - 1);
-    }
-    template <int P, int N>
-    __device__ __forceinline__ unsigned fields() const
-    {
-        return field<P, N>(0) | (field<P, N>(1) << 8) | (field<P, N>(2) << 16) | (field<P, N>(3) << 24);
-    }
-    // the four bytes of slice l = w + J (slices in ascending order: the carry of slice l - 1 is kept)
-    template <int J>
-    __device__ __forceinline__ unsigned word(int l)
-    {
-        unsigned v;
-        if constexpr (!NEAREST) v = fields<63 - kSliceBits * J, 7>();
-        else {
-            const unsigned g = fields<62 - kSliceBits * J, 8>();         // slice and the guard bit below it
-            const unsigned f = (g >> 1) & kLows;
-            const unsigned left = (((sticky | kTops) - (unsigned)l * kOnes) >> 7) & kOnes;   // l <= sticky
-            const unsigned c = g & kOnes & (left | f);
-            v = (f + c) ^ (carry << 7);                                  // + c_l - 128 c_{l-1}, modulo 256
-            carry = c;
-        }
-        const unsigned minus = (kTops - (v & kLows)) ^ (~v & kTops);     // -v, byte by byte
-        return (minus & neg) | (v & ~neg);
-    }
-};
-
-// calls f(l, word of slice l) ... for N quads at once: f(l, words) for l = 1, ..., s
-template <bool NEAREST, int N, class F>
-__device__ __forceinline__ void for_each_slice(Quad<NEAREST> (&q)[N], int s, F &&f)
-{
-    for (int w = 0; w < s; w += Quad<NEAREST>::WIN) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) q[i].window(w);
-        auto one = [&](auto JC) {
-            constexpr int J = decltype(JC)::value;
-            if (w + J > s) return;
-            unsigned wd[N];
-#pragma unroll
-            for (int i = 0; i < N; ++i) wd[i] = q[i].template word<J>(w + J);
-            f(w + J, wd);
-        };
-        one(std::integral_constant<int, 1>{});
-        one(std::integral_constant<int, 2>{});
-        one(std::integral_constant<int, 3>{});
-        one(std::integral_constant<int, 4>{});
-        one(std::integral_constant<int, 5>{});
-        one(std::integral_constant<int, 6>{});
-        one(std::integral_constant<int, 7>{});
-        one(std::integral_constant<int, 8>{});
-        if constexpr (!NEAREST) one(std::integral_constant<int, 9>{});
-    }
 }
 
 // ---- side 'A': X is R x K column-major (R contiguous).  lane <-> row, each lane walks 16
@@ -492,7 +385,7 @@ hipError_t launch_split_both(int m, int n, int k, const double *A, int lda, cons
     if (cA < sA || cB < sB) return hipErrorInvalidValue;
     const int mp = round_up(m > 0 ? m : 1, kPad), np = round_up(n > 0 ? n : 1, kPad), kp = round_up(k > 0 ? k : 1, kPad);
     const int gxA = mp / 64, gxB = np / 32;
-    const long long nblkA = (long long)gxA * (kp / 64), nblkB = (long long)gxB * (kp / kColTileK);
+    const long long nblkA = pA ? (long long)gxA * (kp / 64) : 0, nblkB = pB ? (long long)gxB * (kp / kColTileK) : 0;
     if (nblkA + nblkB > 0x7fffffffLL) return hipErrorInvalidValue;
     auto kern = nearest ? split_both_kernel<true> : split_both_kernel<false>;
     kern<<<(unsigned)(nblkA + nblkB), 256, 0, st>>>((const unsigned long long *)A, lda, m,
