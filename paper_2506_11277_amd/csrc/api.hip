@@ -264,6 +264,16 @@ static int dgemm_impl(int m, int n, int k, const double *A, int lda, const doubl
     auto *maxA = (unsigned long long *)(ws + w.off_maxA), *maxB = (unsigned long long *)(ws + w.off_maxB);
     auto *hdr = (unsigned long long *)(ws + w.off_header);
     // (w.cA, w.cB: the counts the GEMM runs with -- counts that differ little run as equal ones, zero slices appended)
+    if (w.path == kPathFused && !all_products && fused_automatic() && gemm_vectors_handles(m, n, k, sA, sB, w.cA, w.cB, nearest, lda, ldb)) {
+        OZ_TRY(launch_scales_fused(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, eA, w.mp, eB, w.np, nearest ? 1 : 0, false, st));
+        prof_mark(prof, 1, st);
+        OZ_TRY(launch_split_both(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, maxA, maxB, eA, eB, m < n ? pA : nullptr,
+                                 m < n ? nullptr : pB, nearest, st));
+        prof_mark(prof, 2, st);
+        OZ_TRY(launch_gemm_vectors(m, n, k, A, lda, B, ldb, sA, nearest, maxA, maxB, eA, eB, pA, pB, C, ldc, Q, st));
+        prof_mark(prof, 3, st);
+        return OZIMMU_OK;
+    }
     if (scale_split_handles(m, n, k)) {
         prof_mark(prof, 1, st);
         OZ_TRY(launch_scale_split(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, eA, eB, pA, pB, nearest, hdr, w.off_minA, st));

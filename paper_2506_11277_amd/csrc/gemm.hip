@@ -854,6 +854,8 @@ int fused_max_slices() { return kFusedMaxS; }
 
 void fused_set_small_tile_limit(long long tiles) { g_small_below_tiles = tiles; }
 
+bool fused_automatic() { return g_small_below_tiles.load() < 0 && fused16_tile_choice() == 0; }
+
 // what the fused kernels CAN compute ...
 static bool fused_capable(int sA, int sB, bool all_products)
 {

@@ -796,6 +796,8 @@ int fused16_split_k_slots(int s, int kp)
 
 void fused16_set_tile_choice(int choice) { g_tile_choice.store(choice < 0 || choice > 2 ? 0 : choice); }
 
+int fused16_tile_choice() { return g_tile_choice.load(); }
+
 void fused16_tile(int s, int &tm, int &tn)
 {
     tm = s <= 3 ? 256 : 128;

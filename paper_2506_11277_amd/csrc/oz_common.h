@@ -183,6 +183,7 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
 
 // slices of both operands (MFMA layout) in one launch; the planes have room for cA >= sA and cB >= sB slices per
 // entry, the slices beyond sA (sB) are written as zeros
+// (an operand whose planes are null is left out)
 // (the exponents are formed here from the maxima of launch_scales_fused -- bit patterns of max |x| per row of A /
 // column of B -- and stored to eA, eB, their padding as zeros)
 hipError_t launch_split_both(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int sA, int sB,
@@ -244,6 +245,7 @@ inline int device_cus()
         return 256;
     return cus;
 }
+int fused16_tile_choice();
 void fused16_set_tile_choice(int choice);   // test knob: 0 automatic, 1 tabulated tile, 2 alternative tile (4 slices)
 // (kslots: split-k with an int32 slot per k-block -- fused16_split_k_slots() of them -- instead of int64 totals)
 hipError_t launch_gemm_fused16(int m, int n, int kp, int s, const int8_t *pA, const int8_t *pB,
@@ -255,6 +257,15 @@ hipError_t launch_gemm_halves(int s, int m, int n, int kp, const int8_t *pA, con
                               const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
 hipError_t launch_gemm_eighths(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                                const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
+// equal counts 2 ... 9, one operand of at most 64 rows / columns, the other large (gemm_vectors.hip): the planes of the
+// short operand must hold its slices, the long one is sliced by the kernel (exponents from its maxima, stored as
+// launch_split_both stores them); its planes are only room
+bool gemm_vectors_handles(int m, int n, int k, int sA, int sB, int cA, int cB, bool nearest, int lda, int ldb);
+hipError_t launch_gemm_vectors(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int s, bool nearest,
+                               const unsigned long long *maxA, const unsigned long long *maxB, int32_t *eA, int32_t *eB,
+                               int8_t *pA, int8_t *pB, double *C, int ldc, int Q, hipStream_t st);
+// false while a test knob steers the choice of kernel (the parity tests then look at the planes of both operands)
+bool fused_automatic();
 // product sets beyond the fused kernels (planes with the slices per entry of blocks_plan); totals: blocks_totals_bytes()
 hipError_t launch_gemm_blocks(int m, int n, int kp, int sA, int sB, bool all_products, const int8_t *pA,
                               const int8_t *pB, const int32_t *eA, const int32_t *eB, double *C, int ldc,

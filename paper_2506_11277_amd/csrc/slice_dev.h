@@ -1,4 +1,4 @@
-// Slicing four entries at a time (device code).
+// Slicing four entries at a time (device code of split.hip and gemm_vectors.hip).
 #pragma once
 #include <type_traits>
 

@@ -97,3 +97,29 @@ def test_non_finite_is_reported_and_forgotten(k):
         ozimmu.dgemm(dA, dB, s, workspace=ws, check_finite=True)
         assert ozimmu.estimate_slices(dA, dB, 1e-6, workspace=ws)[1] in (ozimmu.OK, ozimmu.UNREACHABLE)
         ozimmu.check(ws)
+
+
+@pytest.mark.parametrize("m,n,k", [(8192, 64, 2100), (2100, 33, 5000), (300, 1, 30001), (64, 5000, 4500), (31, 260, 9000), (257, 40, 140000),
+                                   (2, 700, 20000), (33000, 7, 4200)])
+@pytest.mark.parametrize("s,nearest,Q", [(2, False, 1), (3, True, 2), (7, False, 1), (8, True, 1), (9, False, 3)])
+def test_long_operand_sliced_on_the_way(m, n, k, s, nearest, Q):
+    # either operand short, one part of k and several, ragged ends of every dimension, leading dimensions that are odd
+    rng = np.random.default_rng(5)
+    A = np.asfortranarray(rng.standard_normal((m, k)) * np.exp2(rng.integers(-20, 20, (m, 1))))
+    B = np.asfortranarray(rng.standard_normal((k, n)) * np.exp2(rng.integers(-20, 20, (1, n))))
+    special(A, B)
+    dA, dB = ozimmu.colmajor_empty(m + 1, k)[1:, :], ozimmu.colmajor_empty(k + 3, n)[:k, :]
+    dA.copy_(torch.as_tensor(A))
+    dB.copy_(torch.as_tensor(B))
+    ws = ozimmu.alloc_workspace(m, n, k, s)
+    C = ozimmu.dgemm3(dA, dB, s, s, splitting=ozimmu.SPLIT_NEAREST if nearest else ozimmu.SPLIT_TRUNCATE,
+                      level_diagonals=min(Q, ozimmu.max_level_diagonals(k, s, s)), workspace=ws, check_finite=True)
+    if k * s <= 133144:
+        assert ozimmu.last_gemm_kernel().startswith("gemm_vectors_kernel"), ozimmu.last_gemm_kernel()
+    check(C, A, B, s, s, nearest=nearest, Q=min(Q, ozimmu.max_level_diagonals(k, s, s)))
+    eA, eB = ozimmu.get_exponents(m, n, k, s, ws)
+    assert eA.shape == (m,) and eB.shape == (n,)
+    mx = np.abs(A).max(axis=1)
+    assert np.array_equal(eA.cpu().numpy(), np.where(mx > 0, np.frexp(mx)[1], 0) + nearest)
+    mx = np.abs(B).max(axis=0)
+    assert np.array_equal(eB.cpu().numpy(), np.where(mx > 0, np.frexp(mx)[1], 0) + nearest)
