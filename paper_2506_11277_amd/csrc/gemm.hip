@@ -400,6 +400,7 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_fused_kernel(const int8_t
 
     // epilogue: accumulator register r of lane holds  (n_local, m_local) = (8*(r/4) + 4*(lane/32) + r%4, lane%32)
     const int m0 = (tm * FA + wm * WMF) * 32, n0 = (tn * FB + wn * WNF) * 32;
+    const bool stream = stream_c(C, ldc);
 #pragma unroll
     for (int i = 0; i < WMF; ++i) {
         const int mi = m0 + i * 32 + (lane & 31);
@@ -415,11 +416,10 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_fused_kernel(const int8_t
 #pragma unroll
                     for (int a = 0; a < NA; ++a) dump[(size_t)a * m * n + mi + (size_t)nj * m] = acc[a][i][j][r];
                 } else {
-                    LevelSum sum;
+                    int d[NA];
 #pragma unroll
-                    for (int a = 0; a < NA; ++a)
-                        sum.add((double)acc[a][i][j][r] * __builtin_ldexp(1.0, -kSliceBits * (a + 2)), Q, a == NA - 1);
-                    __builtin_nontemporal_store(ldexp(sum.S, ea + eB[nj]), &C[mi + (size_t)nj * ldc]);   // (streaming: as in gemm_fused16_kernel)
+                    for (int a = 0; a < NA; ++a) d[a] = acc[a][i][j][r];
+                    store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<NA>(d, Q), ea + eB[nj]), stream);
                 }
             }
         }

@@ -462,6 +462,7 @@ __global__ __launch_bounds__((64 * Cfg16<S, ALT>::WVM * Cfg16<S, ALT>::WVN)) voi
                                                    __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
+    const bool stream = stream_c(C, ldc);
 #pragma unroll
     for (int i = 0; i < WMF; ++i)
 #pragma unroll
@@ -482,14 +483,10 @@ __global__ __launch_bounds__((64 * Cfg16<S, ALT>::WVM * Cfg16<S, ALT>::WVN)) voi
                             for (int a = 0; a < S; ++a)
                                 dump[(size_t)a * m * n + mi + (size_t)nj * m] = acc[a][i][j][i2 * 2 + j2][r];
                         } else {
-                            LevelSum sum;
+                            int d[S];
 #pragma unroll
-                            for (int a = 0; a < S; ++a)
-                                sum.add((double)acc[a][i][j][i2 * 2 + j2][r] * __builtin_ldexp(1.0, -kSliceBits * (a + 2)),
-                                        Q, a == S - 1);
-                            // (streaming store: C is not read again here, and keeping its 8 m n bytes out of the caches
-                            // leaves the reduction of the next call 8 % faster -- 0.202 -> 0.185 ms at 8192^3)
-                            __builtin_nontemporal_store(ldexp(sum.S, ea + eB[nj]), &C[mi + (size_t)nj * ldc]);
+                            for (int a = 0; a < S; ++a) d[a] = acc[a][i][j][i2 * 2 + j2][r];
+                            store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(d, Q), ea + eB[nj]), stream);
                         }
                     }
         }

@@ -154,6 +154,7 @@ __global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restri
         }
     const int mi = (tm * 2 + wm) * 32 + (lane & 31);
     if (mi >= m) return;
+    const bool stream = stream_c(C, ldc);
     const int ea = eA[mi];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restri
         int d[S];
 #pragma unroll
         for (int a = 0; a < S; ++a) d[a] = D[a][r];
-        __builtin_nontemporal_store(ldexp(diagonal_sum<S>(d, Q), ea + eB[nj]), &C[mi + (size_t)nj * ldc]);
+        store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(d, Q), ea + eB[nj]), stream);
     }
 }
 
@@ -246,12 +247,13 @@ __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restr
     });
     const int mi = tm * 32 + (lane & 31);
     if (mi >= m) return;
+    const bool stream = stream_c(C, ldc);
     const int ea = eA[mi];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         const int rr = 2 * wave + r;
         const int nj = tn * 32 + 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
-        if (nj < n) __builtin_nontemporal_store(ldexp(diagonal_sum<S>(D[r], Q), ea + eB[nj]), &C[mi + (size_t)nj * ldc]);
+        if (nj < n) store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[r], Q), ea + eB[nj]), stream);
     }
 }
 

@@ -123,3 +123,18 @@ def test_long_operand_sliced_on_the_way(m, n, k, s, nearest, Q):
     assert np.array_equal(eA.cpu().numpy(), np.where(mx > 0, np.frexp(mx)[1], 0) + nearest)
     mx = np.abs(B).max(axis=0)
     assert np.array_equal(eB.cpu().numpy(), np.where(mx > 0, np.frexp(mx)[1], 0) + nearest)
+
+
+@pytest.mark.parametrize("s", [1, 3, 5, 7, 9, 10, 14])
+@pytest.mark.parametrize("m,n,offset,extra", [(70, 61, 0, 0), (300, 290, 1, 7), (301, 1025, 0, 0), (1100, 1000, 8, 0), (2048, 130, 3, 5)])
+def test_stores_of_c_by_alignment(m, n, offset, extra, s):
+    # columns of C on 64-byte boundaries (streaming stores) and off them, nothing written outside the m x n entries
+    k = 70
+    A, B = workloads.lognormal(m, n, k, 1.0, 5)
+    buf = torch.full(((m + extra) * n + offset + 8,), -7.0, dtype=torch.float64, device="cuda")
+    C = torch.as_strided(buf, (m, n), (1, m + extra), offset)
+    ozimmu.dgemm(ozimmu.to_colmajor(A), ozimmu.to_colmajor(B), s, C=C)
+    check(C, A, B, s, s)
+    outside = buf.clone()
+    torch.as_strided(outside, (m, n), (1, m + extra), offset).fill_(-7.0)
+    assert bool((outside == -7.0).all())
