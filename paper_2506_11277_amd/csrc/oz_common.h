@@ -238,11 +238,16 @@ inline double launch_cost(int m, int n, int tm, int tn, int cus)
     return (0.8 * whole + 0.2 * exact) * tm * tn;
 }
 double fused16_launch_cost(int s, int m, int n, int cus);
+// compute units of the current device, asked for once per device ordinal
 inline int device_cus()
 {
+    static std::atomic<int> known[64];
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        return 256;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    const bool keep = dev >= 0 && dev < 64;
+    if (keep && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+    if (keep) known[dev].store(cus, std::memory_order_relaxed);
     return cus;
 }
 int fused16_tile_choice();

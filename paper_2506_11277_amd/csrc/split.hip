@@ -338,14 +338,15 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
     return hipGetLastError();
 }
 
-// Contractions up to 2048 always; up to 4096 while the operands have a few thousand rows and columns (both phases of two
-// launches against one, us: 2048 x 2048 x 4096 s = 7 81.7 -> 67.4, 1024 x 1024 x 4096 52.5 -> 40.5, but 4096^3 147.7 -> 157.5: there a
-// work-group's loads wait for a chip that is busy anyway, and the register-resident form has fewer wavefronts)
+// Contractions up to 2048 always; up to 4096 while the operands have up to about 18 million entries (both phases of two
+// launches against one, us, s = 7: 2048 x 2048 x 4096 81.7 -> 67.4, 1000 x 1000 x 3000 40.0 -> 27.0, 2500 x 2400 x 2500 64.1 -> 46.0, but
+// 3000 x 2900 x 4000 106.5 -> 112.1 and 4096^3 147.7 -> 157.5: there a work-group's loads wait for a chip that is busy
+// anyway, and the register-resident form has fewer wavefronts)
 bool scale_split_handles(int m, int n, int k)
 {
     if (m <= 0 || n <= 0 || k <= 0) return false;
     const int kp = round_up(k, kPad);
-    return kp <= 2048 || (kp <= 4096 && (long long)m + n <= 6000);
+    return kp <= 2048 || (kp <= 4096 && ((long long)m + n) * kp <= 18LL << 20);
 }
 
 hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int sA, int sB, int cA,
@@ -367,6 +368,7 @@ hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, con
         constexpr int PR = decltype(PRC)::value, SWEEP = 16 * 16 * (16 / PR);       // k of 16 wavefronts
         if (kp <= SWEEP) launch(PRC, std::integral_constant<int, 1>{});
         else if (kp <= 2 * SWEEP) launch(PRC, std::integral_constant<int, 2>{});
+        else if (kp <= 3 * SWEEP) launch(PRC, std::integral_constant<int, 3>{});
         else launch(PRC, std::integral_constant<int, 4>{});
     };
     // Four rows to a work-group put the most compute units to work (a compute unit takes in some 10-25 GB/s whatever

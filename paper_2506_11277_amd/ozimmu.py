@@ -92,8 +92,14 @@ def lib():
     return _lib
 
 
+# (the raw handle of the current stream without a Stream object around it, which costs 2.7 us of a call that takes 12.6)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _colmajor_ld(X, what):
