@@ -60,22 +60,6 @@ inline void prof_mark(hipEvent_t *slot, int phase, hipStream_t st)
     if (slot) (void)hipEventRecord(slot[phase], st);
 }
 
-// scales of both operands into the workspace (optionally with the minima for kappa)
-int scales_into_workspace(const Workspace &w, char *ws, int m, int n, int k, const double *A, int lda,
-                          const double *B, int ldb, bool with_min, int bias, hipStream_t st)
-{
-    auto *hdr = (unsigned long long *)(ws + w.off_header);
-    auto *flags = (unsigned int *)(ws + w.off_header);
-    auto *maxA = (unsigned long long *)(ws + w.off_maxA), *minA = (unsigned long long *)(ws + w.off_minA);
-    auto *maxB = (unsigned long long *)(ws + w.off_maxB), *minB = (unsigned long long *)(ws + w.off_minB);
-    OZ_TRY(launch_clear_header(hdr, st));
-    OZ_TRY(launch_reduce('A', m, k, A, lda, maxA, with_min ? minA : nullptr, flags, st));
-    OZ_TRY(launch_reduce('B', k, n, B, ldb, maxB, with_min ? minB : nullptr, flags, st));
-    OZ_TRY(launch_finalize(maxA, minA, (int32_t *)(ws + w.off_expA), m, w.mp, with_min ? hdr + 1 : nullptr, bias, st));
-    OZ_TRY(launch_finalize(maxB, minB, (int32_t *)(ws + w.off_expB), n, w.np, with_min ? hdr + 2 : nullptr, bias, st));
-    return OZIMMU_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -129,8 +113,9 @@ static int kappas(int m, int n, int k, const double *A, int lda, const double *B
     if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace & 255)) return OZIMMU_BAD_ARG;
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    int rc = scales_into_workspace(w, ws, m, n, k, A, lda, B, ldb, true, 0, st);
-    if (rc) return rc;
+    auto at = [&](size_t off) { return (unsigned long long *)(ws + off); };
+    OZ_TRY(launch_kappas(m, n, k, A, lda, B, ldb, at(w.off_header), at(w.off_maxA), at(w.off_minA), at(w.off_maxB), at(w.off_minB),
+                         (int32_t *)(ws + w.off_expA), w.mp, (int32_t *)(ws + w.off_expB), w.np, st));
     unsigned long long host[3];
     OZ_TRY(hipMemcpyAsync(host, ws + w.off_header, sizeof(host), hipMemcpyDeviceToHost, st));
     OZ_TRY(hipStreamSynchronize(st));
@@ -209,9 +194,9 @@ int ozimmu_split2(char side, int rows, int cols, const double *X, int ldx, int s
     auto *hdr = (unsigned long long *)scratch;
     auto *maxbits = hdr + 32;
     OZ_TRY(launch_clear_header(hdr, st));
-    OZ_TRY(launch_reduce(side, rows, cols, X, ldx, maxbits, nullptr, (unsigned int *)hdr, st));
+    OZ_TRY(launch_reduce(side, rows, cols, X, ldx, maxbits, (unsigned int *)hdr, st));
     const bool nearest = splitting == OZIMMU_SPLIT_NEAREST;
-    OZ_TRY(launch_finalize(maxbits, nullptr, exps, nblk, nblk, nullptr, nearest ? 1 : 0, st));
+    OZ_TRY(launch_finalize(maxbits, exps, nblk, nearest ? 1 : 0, st));
     OZ_TRY(launch_split(side, rows, cols, X, ldx, s, exps, planes, layout, nearest, st));
     return OZIMMU_OK;
 }

@@ -148,17 +148,16 @@ inline Workspace carve(int m, int n, int k, int sA, int sB, bool all_products = 
 
 // ---- launchers implemented in reduce.hip -------------------------------------------------
 // side 'A': per-row reduction of a rows x cols matrix; side 'B': per-column.
-// maxbits/minbits: u64 per block (bit pattern of max |x| and of the smallest nonzero |x|;
-// minbits may be null).  flags: u32, bit 0 set when a NaN/Inf is met.
-hipError_t launch_reduce(char side, int rows, int cols, const double *X, int ldx,
-                         unsigned long long *maxbits, unsigned long long *minbits,
+// maxbits: u64 per block (bit pattern of max |x|).  flags: u32, bit 0 set when a NaN/Inf is met.
+hipError_t launch_reduce(char side, int rows, int cols, const double *X, int ldx, unsigned long long *maxbits,
                          unsigned int *flags, hipStream_t st);
-// exps[b] from maxbits[b], plus `bias` (1 for round-to-nearest slices, whose scale is twice as large);
-// entries b in [nblk, nblk_padded) get 0.  If kappa_bits is non-null (needs minbits) also folds
-// 2*max/min into *kappa_bits with an integer atomic max.
-hipError_t launch_finalize(const unsigned long long *maxbits, const unsigned long long *minbits,
-                           int32_t *exps, int nblk, int nblk_padded, unsigned long long *kappa_bits,
-                           int bias, hipStream_t st);
+// exps[b] from maxbits[b], plus `bias` (1 for round-to-nearest slices, whose scale is twice as large)
+hipError_t launch_finalize(const unsigned long long *maxbits, int32_t *exps, int nblk, int bias, hipStream_t st);
+// maxima, smallest nonzero magnitudes and exponents of both operands, the largest ratio of the two per operand into
+// hdr[1] and hdr[2] (bit patterns of max / min); the header is cleared first.  Three launches.
+hipError_t launch_kappas(int m, int n, int k, const double *A, int lda, const double *B, int ldb, unsigned long long *hdr,
+                         unsigned long long *maxA, unsigned long long *minA, unsigned long long *maxB,
+                         unsigned long long *minB, int32_t *expA, int mp, int32_t *expB, int np, hipStream_t st);
 hipError_t launch_clear_header(void *header, hipStream_t st);
 // the whole scale extraction of ozimmu_dgemm in three launches: clear, reduce both operands, exponents of both
 hipError_t launch_scales_fused(int m, int n, int k, const double *A, int lda, const double *B, int ldb,

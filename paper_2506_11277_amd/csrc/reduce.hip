@@ -77,10 +77,9 @@ __device__ __forceinline__ void colreduce_block(int j, const unsigned long long 
 
 __global__ __launch_bounds__(256) void colreduce_kernel(const unsigned long long *__restrict__ X, int ldx, int rows,
                                                         unsigned long long *__restrict__ maxbits,
-                                                        unsigned long long *__restrict__ minbits,
                                                         unsigned int *__restrict__ flags)
 {
-    colreduce_block(blockIdx.x, X, ldx, rows, maxbits, minbits, flags);
+    colreduce_block(blockIdx.x, X, ldx, rows, maxbits, nullptr, flags);
 }
 
 // ---- side 'A': lane <-> row (coalesced along the column-major rows), 4 wavefronts split a
@@ -130,31 +129,34 @@ __device__ __forceinline__ void rowreduce_block(int bx, int by, const unsigned l
 
 __global__ __launch_bounds__(256) void rowreduce_kernel(const unsigned long long *__restrict__ X, int ldx, int rows,
                                                         int cols, unsigned long long *__restrict__ maxbits,
-                                                        unsigned long long *__restrict__ minbits,
                                                         unsigned int *__restrict__ flags)
 {
-    rowreduce_block(blockIdx.x, blockIdx.y, X, ldx, rows, cols, maxbits, minbits, flags);
+    rowreduce_block(blockIdx.x, blockIdx.y, X, ldx, rows, cols, maxbits, nullptr, flags);
 }
 
 // Both operands in one launch (ozimmu_dgemm: fewer, larger launches matter for small problems): the first
 // nblkA work-groups reduce A (numbered rows-block fastest), the others one column of B each.
+// (minA, minB: null, or where the smallest nonzero magnitudes go as well)
 __global__ __launch_bounds__(256) void reduce_both_kernel(const unsigned long long *__restrict__ A, int lda, int m, int k,
                                                           const unsigned long long *__restrict__ B, int ldb, int n,
                                                           unsigned long long *__restrict__ maxA,
                                                           unsigned long long *__restrict__ maxB,
+                                                          unsigned long long *__restrict__ minA,
+                                                          unsigned long long *__restrict__ minB,
                                                           unsigned int *__restrict__ flags, int gxA, int nblkA)
 {
     const int b = blockIdx.x;
-    if (b < nblkA) rowreduce_block(b % gxA, b / gxA, A, lda, m, k, maxA, nullptr, flags);
-    else colreduce_block(b - nblkA, B, ldb, k, maxB, nullptr, flags);
+    if (b < nblkA) rowreduce_block(b % gxA, b / gxA, A, lda, m, k, maxA, minA, flags);
+    else colreduce_block(b - nblkA, B, ldb, k, maxB, minB, flags);
 }
 
-// header cleared, row maxima of A set to 0 (they are formed with atomic max)
-__global__ void init_scales_kernel(unsigned long long *hdr, unsigned long long *maxA, int m)
+// header cleared, row maxima of A set to 0 and its minima, where wanted, to none (they are formed with atomics)
+__global__ void init_scales_kernel(unsigned long long *hdr, unsigned long long *maxA, unsigned long long *minA, int m)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < 32) hdr[i] = 0ULL;
     if (i < m) maxA[i] = 0ULL;
+    if (minA && i < m) minA[i] = kNoMin;
 }
 
 __global__ void fill_u64_kernel(unsigned long long *p, unsigned long long v, int n)
@@ -168,19 +170,37 @@ __global__ void clear_header_kernel(unsigned long long *hdr)
     if (threadIdx.x < 32) hdr[threadIdx.x] = 0ULL;
 }
 
-__global__ void finalize_kernel(const unsigned long long *__restrict__ maxbits,
-                                const unsigned long long *__restrict__ minbits, int32_t *__restrict__ exps,
-                                int nblk, int nblk_padded, unsigned long long *kappa_bits, int bias)
+__global__ void finalize_kernel(const unsigned long long *__restrict__ maxbits, int32_t *__restrict__ exps, int nblk, int bias)
 {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nblk_padded) return;
-    if (b >= nblk) { exps[b] = 0; return; }
-    unsigned long long mx = maxbits[b];
-    exps[b] = exponent_above(mx) + bias;
-    if (kappa_bits && mx) {
-        double ratio = __longlong_as_double((long long)mx) / __longlong_as_double((long long)minbits[b]);
-        atomicMax(kappa_bits, (unsigned long long)__double_as_longlong(ratio));
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < nblk) exps[b] = exponent_above(maxbits[b]) + bias;
+}
+
+// Exponents of both operands, and the largest max / min over the rows of A into kappa[0], over the columns of B into
+// kappa[1] (bit patterns; blocks without a nonzero entry left out).  The first groups work-groups take A, the others B;
+// a wavefront's maximum is one atomic (an atomic per row took 5 us at 2500 rows, whatever else the launch did).
+__global__ __launch_bounds__(256) void finalize_kappas_kernel(const unsigned long long *__restrict__ maxA,
+                                                              const unsigned long long *__restrict__ minA,
+                                                              int32_t *__restrict__ expA, int m, int mp,
+                                                              const unsigned long long *__restrict__ maxB,
+                                                              const unsigned long long *__restrict__ minB,
+                                                              int32_t *__restrict__ expB, int n, int np,
+                                                              unsigned long long *__restrict__ kappa, int groups)
+{
+    const bool isB = (int)blockIdx.x >= groups;
+    const int b = ((int)blockIdx.x - (isB ? groups : 0)) * 256 + threadIdx.x, nblk = isB ? n : m;
+    unsigned long long ratio = 0;
+    if (b < nblk) {
+        const unsigned long long mx = (isB ? maxB : maxA)[b];
+        (isB ? expB : expA)[b] = exponent_above(mx);
+        if (mx) ratio = (unsigned long long)__double_as_longlong(__longlong_as_double((long long)mx) /
+                                                                 __longlong_as_double((long long)(isB ? minB : minA)[b]));
+    } else if (b < (isB ? np : mp)) (isB ? expB : expA)[b] = 0;
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(ratio, off);
+        ratio = o > ratio ? o : ratio;
     }
+    if ((threadIdx.x & 63) == 0 && ratio) atomicMax(&kappa[isB ? 1 : 0], ratio);
 }
 
 // exponents of both operands in one launch (no kappa)
@@ -196,22 +216,40 @@ __global__ void finalize_both_kernel(const unsigned long long *__restrict__ maxA
 
 }  // namespace
 
-hipError_t launch_scales_fused(int m, int n, int k, const double *A, int lda, const double *B, int ldb,
-                               unsigned long long *hdr, unsigned long long *maxA, unsigned long long *maxB,
-                               int32_t *expA, int mp, int32_t *expB, int np, int bias, bool finalize, hipStream_t st)
+static hipError_t launch_maxima(int m, int n, int k, const double *A, int lda, const double *B, int ldb,
+                                unsigned long long *hdr, unsigned long long *maxA, unsigned long long *maxB,
+                                unsigned long long *minA, unsigned long long *minB, hipStream_t st)
 {
     const int mm = m > 0 ? m : 0;
-    init_scales_kernel<<<(mm + 32 + 255) / 256, 256, 0, st>>>(hdr, maxA, mm);
+    init_scales_kernel<<<(mm + 32 + 255) / 256, 256, 0, st>>>(hdr, maxA, minA, mm);
     const int gxA = (mm + 63) / 64, gyA = k > 0 ? (k + kRowChunk - 1) / kRowChunk : 0;
     const long long nblkA = (long long)gxA * gyA, nblkB = n > 0 ? n : 0;
     if (nblkA + nblkB > 0x7fffffffLL) return hipErrorInvalidValue;
     if (nblkA + nblkB > 0)
         reduce_both_kernel<<<(unsigned)(nblkA + nblkB), 256, 0, st>>>((const unsigned long long *)A, lda, m, k,
-                                                                      (const unsigned long long *)B, ldb, n, maxA, maxB,
+                                                                      (const unsigned long long *)B, ldb, n, maxA, maxB, minA, minB,
                                                                       (unsigned int *)hdr, gxA > 0 ? gxA : 1, (int)nblkA);
+    return hipGetLastError();
+}
+
+hipError_t launch_scales_fused(int m, int n, int k, const double *A, int lda, const double *B, int ldb,
+                               unsigned long long *hdr, unsigned long long *maxA, unsigned long long *maxB,
+                               int32_t *expA, int mp, int32_t *expB, int np, int bias, bool finalize, hipStream_t st)
+{
+    if (hipError_t e = launch_maxima(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, nullptr, nullptr, st); e != hipSuccess) return e;
     // (the slicing kernel that follows forms the exponents from the maxima itself and stores them; only a call that
     // ends here, an empty product, needs them from this launch)
     if (finalize) finalize_both_kernel<<<(mp + np + 255) / 256, 256, 0, st>>>(maxA, expA, m, mp, maxB, expB, n, np, bias);
+    return hipGetLastError();
+}
+hipError_t launch_kappas(int m, int n, int k, const double *A, int lda, const double *B, int ldb, unsigned long long *hdr,
+                         unsigned long long *maxA, unsigned long long *minA, unsigned long long *maxB,
+                         unsigned long long *minB, int32_t *expA, int mp, int32_t *expB, int np, hipStream_t st)
+{
+    if (k > 65535LL * kRowChunk) return hipErrorInvalidValue;
+    if (hipError_t e = launch_maxima(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, minA, minB, st); e != hipSuccess) return e;
+    const int gA = (mp + 255) / 256, gB = (np + 255) / 256;
+    finalize_kappas_kernel<<<gA + gB, 256, 0, st>>>(maxA, minA, expA, m, mp, maxB, minB, expB, n, np, hdr + 1, gA);
     return hipGetLastError();
 }
 
@@ -222,31 +260,27 @@ hipError_t launch_clear_header(void *header, hipStream_t st)
 }
 
 hipError_t launch_reduce(char side, int rows, int cols, const double *X, int ldx, unsigned long long *maxbits,
-                         unsigned long long *minbits, unsigned int *flags, hipStream_t st)
+                         unsigned int *flags, hipStream_t st)
 {
     const int nblk = side == 'A' ? rows : cols;
     if (nblk <= 0) return hipSuccess;
     if (side == 'A') {
         fill_u64_kernel<<<(nblk + 255) / 256, 256, 0, st>>>(maxbits, 0ULL, nblk);
-        if (minbits) fill_u64_kernel<<<(nblk + 255) / 256, 256, 0, st>>>(minbits, kNoMin, nblk);
         if (cols > 0) {
             dim3 grid((rows + 63) / 64, (cols + kRowChunk - 1) / kRowChunk);
             if (grid.y > 65535) return hipErrorInvalidValue;
-            rowreduce_kernel<<<grid, 256, 0, st>>>((const unsigned long long *)X, ldx, rows, cols, maxbits, minbits,
-                                                   flags);
+            rowreduce_kernel<<<grid, 256, 0, st>>>((const unsigned long long *)X, ldx, rows, cols, maxbits, flags);
         }
     } else {
-        colreduce_kernel<<<cols, 256, 0, st>>>((const unsigned long long *)X, ldx, rows, maxbits, minbits, flags);
+        colreduce_kernel<<<cols, 256, 0, st>>>((const unsigned long long *)X, ldx, rows, maxbits, flags);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const unsigned long long *maxbits, const unsigned long long *minbits, int32_t *exps,
-                           int nblk, int nblk_padded, unsigned long long *kappa_bits, int bias, hipStream_t st)
+hipError_t launch_finalize(const unsigned long long *maxbits, int32_t *exps, int nblk, int bias, hipStream_t st)
 {
-    if (nblk_padded <= 0) return hipSuccess;
-    finalize_kernel<<<(nblk_padded + 255) / 256, 256, 0, st>>>(maxbits, minbits, exps, nblk, nblk_padded, kappa_bits,
-                                                               bias);
+    if (nblk <= 0) return hipSuccess;
+    finalize_kernel<<<(nblk + 255) / 256, 256, 0, st>>>(maxbits, exps, nblk, bias);
     return hipGetLastError();
 }
 

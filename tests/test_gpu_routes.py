@@ -99,7 +99,7 @@ def test_non_finite_is_reported_and_forgotten(k):
         ozimmu.check(ws)
 
 
-@pytest.mark.parametrize("m,n,k", [(8192, 64, 2100), (2100, 33, 5000), (300, 1, 30001), (64, 5000, 4500), (31, 260, 9000), (257, 40, 140000),
+@pytest.mark.parametrize("m,n,k", [(9000, 64, 2100), (2100, 33, 5000), (300, 1, 30001), (64, 5000, 4500), (31, 260, 9000), (257, 40, 140000),
                                    (2, 700, 20000), (33000, 7, 4200)])
 @pytest.mark.parametrize("s,nearest,Q", [(2, False, 1), (3, True, 2), (7, False, 1), (8, True, 1), (9, False, 3)])
 def test_long_operand_sliced_on_the_way(m, n, k, s, nearest, Q):
@@ -138,3 +138,23 @@ def test_stores_of_c_by_alignment(m, n, offset, extra, s):
     outside = buf.clone()
     torch.as_strided(outside, (m, n), (1, m + extra), offset).fill_(-7.0)
     assert bool((outside == -7.0).all())
+
+
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (256, 257, 3), (300, 5, 1000), (130, 1025, 70), (4, 0, 5), (0, 3, 4), (3, 4, 0)])
+def test_kappas_of_both_operands(m, n, k):
+    # blocks without a nonzero entry, zeros among the others, subnormal minima; more rows than a work-group finishes
+    A, B = workloads.lognormal(m, n, k, 1.5, 21)
+    if m > 4 and k > 2:
+        A[1, :] = 0.0
+        A[2, 1] = 0.0
+        A[-1, 0] = 5e-324
+        B[0, -1] = -0.0
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    s, status, kA, kB = ozimmu.estimate_slices(dA, dB, 1e-6)
+    want = []
+    for X, axis in ((np.abs(A), 1), (np.abs(B), 0)):
+        mx, mn = X.max(axis=axis, initial=0.0), np.where(X > 0, X, np.inf).min(axis=axis, initial=np.inf)
+        with np.errstate(over="ignore"):
+            want.append(2.0 * max((a / b for a, b in zip(mx, mn) if a > 0), default=0.0))
+    assert (kA, kB) == tuple(want)
+    assert ozimmu.estimate_slices2(dA, dB, 1e-6)[3:] == (kA, kB)
