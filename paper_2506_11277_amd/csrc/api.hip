@@ -31,6 +31,13 @@ inline bool bad_matrix(int rows, int cols, const void *p, int ld)
 }
 
 
+// whether two column-major matrices share memory (between their first and last entries)
+inline bool overlap(const double *X, int rx, int cx, int ldx, const double *Y, int ry, int cy, int ldy)
+{
+    const auto x0 = (uintptr_t)X, y0 = (uintptr_t)Y;
+    return x0 < y0 + 8 * ((uintptr_t)(cy - 1) * ldy + ry) && y0 < x0 + 8 * ((uintptr_t)(cx - 1) * ldx + rx);
+}
+
 #define OZ_TRY(expr)                                        \
     do {                                                    \
         hipError_t e__ = (expr);                            \
@@ -249,7 +256,10 @@ static int dgemm_impl(int m, int n, int k, const double *A, int lda, const doubl
     auto *maxA = (unsigned long long *)(ws + w.off_maxA), *maxB = (unsigned long long *)(ws + w.off_maxB);
     auto *hdr = (unsigned long long *)(ws + w.off_header);
     // (w.cA, w.cB: the counts the GEMM runs with -- counts that differ little run as equal ones, zero slices appended)
-    if (w.path == kPathFused && !all_products && fused_automatic() && gemm_vectors_handles(m, n, k, sA, sB, w.cA, w.cB, nearest, lda, ldb)) {
+    // (the long operand is read while C is written: a C that lies in it takes the general way, whose kernels that write C
+    // read planes only)
+    if (w.path == kPathFused && !all_products && fused_automatic() && gemm_vectors_handles(m, n, k, sA, sB, w.cA, w.cB, nearest, lda, ldb) &&
+        !(m < n ? overlap(C, m, n, ldc, B, k, n, ldb) : overlap(C, m, n, ldc, A, m, k, lda))) {
         OZ_TRY(launch_scales_fused(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, eA, w.mp, eB, w.np, nearest ? 1 : 0, false, st));
         prof_mark(prof, 1, st);
         OZ_TRY(launch_split_both(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, maxA, maxB, eA, eB, m < n ? pA : nullptr,

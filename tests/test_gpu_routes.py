@@ -158,3 +158,18 @@ def test_kappas_of_both_operands(m, n, k):
             want.append(2.0 * max((a / b for a, b in zip(mx, mn) if a > 0), default=0.0))
     assert (kA, kB) == tuple(want)
     assert ozimmu.estimate_slices2(dA, dB, 1e-6)[3:] == (kA, kB)
+
+
+@pytest.mark.parametrize("short_a", [False, True])
+def test_result_inside_the_long_operand(short_a):
+    # C may lie in the memory of an operand: its entries are written when the operand has been read
+    m, n, k, s = (40, 3000, 6000, 3) if short_a else (3000, 40, 6000, 3)
+    A, B = workloads.lognormal(m, n, k, 1.0, 33)
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    want = ozimmu.dgemm(dA, dB, s).clone()
+    assert ozimmu.last_gemm_kernel().startswith("gemm_vectors_kernel")
+    C = dB[:m, :] if short_a else dA[:, :n]
+    ozimmu.dgemm(dA, dB, s, C=C)
+    assert not ozimmu.last_gemm_kernel().startswith("gemm_vectors_kernel")
+    assert torch.equal(C, want)
+    check(C, A, B, s, s)
