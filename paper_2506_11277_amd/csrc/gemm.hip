@@ -400,30 +400,37 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_fused_kernel(const int8_t
 
     // epilogue: accumulator register r of lane holds  (n_local, m_local) = (8*(r/4) + 4*(lane/32) + r%4, lane%32)
     const int m0 = (tm * FA + wm * WMF) * 32, n0 = (tn * FB + wn * WNF) * 32;
-    const bool stream = stream_c(C, ldc);
+    auto entries = [&](auto &&f) {
 #pragma unroll
-    for (int i = 0; i < WMF; ++i) {
-        const int mi = m0 + i * 32 + (lane & 31);
-        if (mi >= m) continue;
-        const int ea = DUMP ? 0 : eA[mi];
+        for (int i = 0; i < WMF; ++i) {
+            const int mi = m0 + i * 32 + (lane & 31);
+            if (mi >= m) continue;
+            const int ea = DUMP ? 0 : eA[mi];
 #pragma unroll
-        for (int j = 0; j < WNF; ++j) {
+            for (int j = 0; j < WNF; ++j) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int nj = n0 + j * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (nj >= n) continue;
-                if (DUMP) {
-#pragma unroll
-                    for (int a = 0; a < NA; ++a) dump[(size_t)a * m * n + mi + (size_t)nj * m] = acc[a][i][j][r];
-                } else {
+                for (int r = 0; r < 16; ++r) {
+                    const int nj = n0 + j * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                    if (nj >= n) continue;
                     int d[NA];
 #pragma unroll
                     for (int a = 0; a < NA; ++a) d[a] = acc[a][i][j][r];
-                    store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<NA>(d, Q), ea + eB[nj]), stream);
+                    f(d, mi, nj, ea);
                 }
             }
         }
-    }
+    };
+    if constexpr (DUMP) {
+        entries([&](const int (&d)[NA], int mi, int nj, int) {
+#pragma unroll
+            for (int a = 0; a < NA; ++a) dump[(size_t)a * m * n + mi + (size_t)nj * m] = d[a];
+        });
+    } else
+        epilogue_variant<NA>(Q, stream_c(C, ldc), [&](auto PLAIN, auto STREAM) {
+            entries([&](const int (&d)[NA], int mi, int nj, int ea) {
+                store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<NA, PLAIN.value>(d, Q), ea + eB[nj]), STREAM);
+            });
+        });
 }
 
 // Second step of the k-blocked mode: binary64 accumulation from the int64 totals, same element

@@ -1,5 +1,7 @@
 // Device-side helpers shared by the GEMM translation units (HIP only; nothing of the oracle).
 #pragma once
+#include <type_traits>
+
 #include "oz_common.h"
 
 namespace oz {
@@ -154,28 +156,31 @@ struct LevelSum {
     }
 };
 
-// Stores of C.  C is not read again by the call, and 8 m n bytes kept out of the caches leave the reduction of the next
-// one 8 % faster (8192^3: 0.202 -> 0.185 ms), hence streaming stores -- unless the columns of C start off a 64-byte
-// boundary: the pieces of cache lines that a wavefront then leaves at either end go to memory one by one instead of
-// meeting in the L2 (6001 x 5200 x 256, s = 3: GEMM 227 us streaming, 107 us plain; 2500 x 2400 x 2500 92.6 and 81.7;
-// columns on 64 bytes, 6000 and 6008 rows: 88 / 94 and 91 / 92).
+// Stores of C.  C is not read again by the call, and 8 m n bytes that do not go through the caches leave them to the
+// planes and to the next call's operands (30000 x 30000 x 512, s = 1 / 2: GEMM 2300 / 2742 us with plain stores, 1351 / 2251
+// streaming; 6000 x 5200 x 256, s = 3: 97 and 91; 8192 x 8192 x 1024, s = 2: scales and slices of the next call 64 and 46),
+// hence streaming stores -- unless the columns of C start off a 64-byte boundary: the pieces of cache lines that a wavefront
+// then leaves at either end go to memory one by one instead of meeting in the L2 (6001 x 5200 x 256, s = 3: GEMM 222 us
+// streaming, 104 plain).
 __device__ __forceinline__ bool stream_c(const double *C, int ldc)
 {
     return (((uintptr_t)C | (uintptr_t)ldc * 8) & 63) == 0;
 }
 __device__ __forceinline__ void store_c(double *p, double v, bool stream)
 {
-    if (stream) __builtin_nontemporal_store(v, p);
+    // (the streaming store is written out: as a builtin the two stores are one and the same to the optimiser, which folds
+    // the branches into a single plain store)
+    if (stream) asm volatile("global_store_dwordx2 %0, %1, off nt" ::"v"(p), "v"(v) : "memory");
     else *p = v;
 }
 
 // LevelSum over the int32 diagonal sums d[0], ..., d[S - 1] of one entry (diagonals 2, ..., S + 1).  Plain diagonal
 // order (Q = 1) in one conversion and one fused multiply-add per diagonal: the product with a power of two is exact,
-// so the only rounding is that of the addition, as in LevelSum, which takes about nine instructions.
-template <int S>
+// so the only rounding is that of the addition, as in LevelSum, which takes about nine instructions.  (PLAIN: Q is 1.)
+template <int S, bool PLAIN = false>
 __device__ __forceinline__ double diagonal_sum(const int (&d)[S], int Q)
 {
-    if (Q == 1) {
+    if (PLAIN || Q == 1) {
         double s = 0.0;
 #pragma unroll
         for (int a = 0; a < S; ++a) s = __builtin_fma((double)d[a], __builtin_ldexp(1.0, -kSliceBits * (a + 2)), s);
@@ -185,6 +190,20 @@ __device__ __forceinline__ double diagonal_sum(const int (&d)[S], int Q)
 #pragma unroll
     for (int a = 0; a < S; ++a) sum.add((double)d[a] * __builtin_ldexp(1.0, -kSliceBits * (a + 2)), Q, a == S - 1);
     return sum.S;
+}
+
+// Runs f(plain order?, streaming stores?) with what is decided once for the work-group as compile-time constants: the
+// entries of a lane (64 of them in the larger tiles) then decide nothing.  30000 x 30000 x 512, s = 2: GEMM 2358 us with
+// two branches per entry, 2251 us so.  Levels of several diagonals share a copy, whose stores are chosen per entry; so do
+// all entries from 17 diagonals on, where the accumulators leave no registers for it (one to eight spilled ones otherwise)
+// and the epilogue counts least.
+template <int DIAGONALS, class F>
+__device__ __forceinline__ void epilogue_variant(int Q, bool stream, F &&f)
+{
+    if constexpr (DIAGONALS >= 17) f(std::false_type{}, stream);
+    else if (Q != 1) f(std::false_type{}, stream);
+    else if (stream) f(std::true_type{}, std::true_type{});
+    else f(std::true_type{}, std::false_type{});
 }
 
 }  // namespace oz

@@ -462,34 +462,40 @@ __global__ __launch_bounds__((64 * Cfg16<S, ALT>::WVM * Cfg16<S, ALT>::WVN)) voi
                                                    __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
-    const bool stream = stream_c(C, ldc);
+    auto entries = [&](auto &&f) {
 #pragma unroll
-    for (int i = 0; i < WMF; ++i)
+        for (int i = 0; i < WMF; ++i)
 #pragma unroll
-        for (int i2 = 0; i2 < 2; ++i2) {
-            const int mi = m0 + i * 32 + i2 * 16 + (lane & 15);
-            if (mi >= m) continue;
-            const int ea = DUMP ? 0 : eA[mi];
+            for (int i2 = 0; i2 < 2; ++i2) {
+                const int mi = m0 + i * 32 + i2 * 16 + (lane & 15);
+                if (mi >= m) continue;
+                const int ea = DUMP ? 0 : eA[mi];
 #pragma unroll
-            for (int j = 0; j < WNF; ++j)
+                for (int j = 0; j < WNF; ++j)
 #pragma unroll
-                for (int j2 = 0; j2 < 2; ++j2)
+                    for (int j2 = 0; j2 < 2; ++j2)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int nj = n0 + j * 32 + j2 * 16 + 4 * (lane >> 4) + r;
-                        if (nj >= n) continue;
-                        if (DUMP) {
-#pragma unroll
-                            for (int a = 0; a < S; ++a)
-                                dump[(size_t)a * m * n + mi + (size_t)nj * m] = acc[a][i][j][i2 * 2 + j2][r];
-                        } else {
+                        for (int r = 0; r < 4; ++r) {
+                            const int nj = n0 + j * 32 + j2 * 16 + 4 * (lane >> 4) + r;
+                            if (nj >= n) continue;
                             int d[S];
 #pragma unroll
                             for (int a = 0; a < S; ++a) d[a] = acc[a][i][j][i2 * 2 + j2][r];
-                            store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(d, Q), ea + eB[nj]), stream);
+                            f(d, mi, nj, ea);
                         }
-                    }
-        }
+            }
+    };
+    if constexpr (DUMP) {
+        entries([&](const int (&d)[S], int mi, int nj, int) {
+#pragma unroll
+            for (int a = 0; a < S; ++a) dump[(size_t)a * m * n + mi + (size_t)nj * m] = d[a];
+        });
+    } else
+        epilogue_variant<S>(Q, stream_c(C, ldc), [&](auto PLAIN, auto STREAM) {
+            entries([&](const int (&d)[S], int mi, int nj, int ea) {
+                store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S, PLAIN.value>(d, Q), ea + eB[nj]), STREAM);
+            });
+        });
 }
 
 // Second step of the k-blocked mode: binary64 accumulation from the int64 totals, same element
