@@ -173,3 +173,17 @@ def test_result_inside_the_long_operand(short_a):
     assert not ozimmu.last_gemm_kernel().startswith("gemm_vectors_kernel")
     assert torch.equal(C, want)
     check(C, A, B, s, s)
+
+
+@pytest.mark.parametrize("m,n,k,name", [(1440, 1440, 512, "32x32"), (1440, 1440, 40960, "32x32"), (1440, 1440, 40961, "128x128"),
+                                        (1408, 1408, 41000, "32x32"), (400, 5600, 41000, "128x128")])
+def test_one_slice_over_long_contractions(m, n, k, name):
+    # where the 128 x 128 tile would be the alternative, 32 x 32 tiles serve one slice up to k = 40960 only
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the expectations are worked out for 256 compute units")
+    dA, dB = workloads.lognormal_device(m, n, k, 1.0, 17)
+    C = ozimmu.dgemm(dA, dB, 1)
+    assert name in ozimmu.last_gemm_kernel(), ozimmu.last_gemm_kernel()
+    rows, cols = [0, m // 2, m - 1], [0, n // 2, n - 1]
+    A, B = dA[rows].cpu().numpy(), dB[:, cols].cpu().numpy()
+    assert np.array_equal(bits(C.cpu().numpy()[np.ix_(rows, cols)]), bits(oracle.dgemm(np.asfortranarray(A), np.asfortranarray(B), 1)))
