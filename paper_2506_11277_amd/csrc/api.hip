@@ -405,24 +405,14 @@ int ozimmu_profile_stop(int *calls, float *phase_ms)
 int ozimmu_check(void *workspace, void *stream)
 {
     if (!workspace) return OZIMMU_BAD_ARG;
-    unsigned long long header[kHeaderBadWords + 3];
+    unsigned int flags = 0;
     hipStream_t st = (hipStream_t)stream;
-    OZ_TRY(hipMemcpyAsync(header, workspace, sizeof(header), hipMemcpyDeviceToHost, st));
+    // a call that formed scales and slices in one launch has left a word per work-group instead of the flag: they are
+    // brought together on the device, so that one copy and one synchronisation do whatever the size
+    OZ_TRY(launch_collect_bad((unsigned long long *)workspace, st));
+    OZ_TRY(hipMemcpyAsync(&flags, workspace, sizeof(flags), hipMemcpyDeviceToHost, st));
     OZ_TRY(hipStreamSynchronize(st));
-    if (header[0] & 1ULL) return OZIMMU_NONFINITE;
-    // a call that formed scales and slices in one launch has left a word per work-group instead
-    if (header[kHeaderBadWords + 2] != kBadWordsMagic) return OZIMMU_OK;
-    const char *words = (const char *)workspace + header[kHeaderBadWords + 1];
-    for (unsigned long long i = 0; i < header[kHeaderBadWords];) {
-        unsigned int bad[1024];
-        const unsigned long long left = header[kHeaderBadWords] - i, cnt = left < 1024 ? left : 1024;
-        OZ_TRY(hipMemcpyAsync(bad, words + 4 * i, 4 * cnt, hipMemcpyDeviceToHost, st));
-        OZ_TRY(hipStreamSynchronize(st));
-        for (unsigned long long j = 0; j < cnt; ++j)
-            if (bad[j]) return OZIMMU_NONFINITE;
-        i += cnt;
-    }
-    return OZIMMU_OK;
+    return (flags & 1u) ? OZIMMU_NONFINITE : OZIMMU_OK;
 }
 
 int ozimmu_get_exponents(int m, int n, int k, int s, const void *workspace, int32_t *eA, int32_t *eB, void *stream)

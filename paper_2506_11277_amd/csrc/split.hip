@@ -234,10 +234,12 @@ __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long l
     const int row = R0 + r;
     const size_t rstep = isB ? (size_t)ldx : 1, kstep = isB ? 1 : (size_t)ldx;
     const unsigned long long *p = X + (size_t)(row < R ? row : R - 1) * rstep;
-    if (panel == 0 && threadIdx.x < 4) {
-        // header for ozimmu_check: no flag yet, where the words bad[] are, how many, and a word that makes it valid
-        const unsigned long long v[3] = {(unsigned long long)panels, (unsigned long long)bad_offset, kBadWordsMagic};
-        header[threadIdx.x == 0 ? 0 : kHeaderBadWords + threadIdx.x - 1] = threadIdx.x == 0 ? 0ULL : v[threadIdx.x - 1];
+    if (panel == 0 && threadIdx.x < 5) {
+        // header for ozimmu_check: no flag yet, how many words bad[] has, where, and two words that make these valid
+        const int i = threadIdx.x;
+        const unsigned long long v[5] = {0ULL, (unsigned long long)panels, (unsigned long long)bad_offset, kBadWordsMagic,
+                                         (unsigned long long)(uintptr_t)header};
+        header[i == 0 ? 0 : kHeaderBadWords + i - 1] = v[i];
     }
 
     unsigned long long x[NV][4], mx = 0;
@@ -289,6 +291,17 @@ __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long l
         // (the planes hold cs >= s slices per entry; those beyond s are zeros)
         for (int l = s + 1; l <= cs; ++l) dst[(size_t)(l - 1) * (kFragBytes / 4)] = 0;
     }
+}
+
+// Sets the header's flag where a work-group of scale_split_kernel has met a NaN or an infinity.
+__global__ __launch_bounds__(256) void collect_bad_kernel(unsigned long long *header)
+{
+    const unsigned long long *h = header + kHeaderBadWords;
+    if (h[2] != kBadWordsMagic || h[3] != (unsigned long long)(uintptr_t)header) return;
+    const unsigned *words = (const unsigned *)((const char *)header + h[1]);
+    unsigned any = 0;
+    for (unsigned long long i = blockIdx.x * 256 + threadIdx.x; i < h[0]; i += gridDim.x * 256) any |= words[i];
+    if (__ballot(any != 0) && (threadIdx.x & 63) == 0) atomicOr((unsigned *)header, 1u);
 }
 
 // ---- plain layout: plane l is a matrix shaped like X (utility / test path) ----
@@ -377,6 +390,12 @@ hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, con
     // and the pieces of cache lines begin to count (8192 x 8192 x 1024: 69.6 / 59.4 / 63.9)
     if (kp <= 2048 && (long long)m + n >= 12288) by_k(std::integral_constant<int, 8>{});
     else by_k(std::integral_constant<int, 4>{});
+    return hipGetLastError();
+}
+
+hipError_t launch_collect_bad(unsigned long long *header, hipStream_t st)
+{
+    collect_bad_kernel<<<32, 256, 0, st>>>(header);
     return hipGetLastError();
 }
 

@@ -2,6 +2,8 @@
 
 (The other parity tests steer the choice of kernel; nothing is steered here.)  Every row of A and column of B has a
 scale of its own, so a sample of rows and columns of C is the oracle's product of these rows and columns."""
+import time
+
 import numpy as np
 import pytest
 
@@ -97,6 +99,35 @@ def test_non_finite_is_reported_and_forgotten(k):
         ozimmu.dgemm(dA, dB, s, workspace=ws, check_finite=True)
         assert ozimmu.estimate_slices(dA, dB, 1e-6, workspace=ws)[1] in (ozimmu.OK, ozimmu.UNREACHABLE)
         ozimmu.check(ws)
+
+
+def test_check_takes_one_round_trip_whatever_the_size():
+    # a million rows are 250 000 work-groups of the launch that forms scales and slices; the first and the last of them
+    # report, and asking takes about as long as for a few rows
+    def seconds(ws):
+        best = 1.0
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            ozimmu.check(ws)
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    took = {}
+    for m in (300, 1_000_000):
+        n, k, s = 20, 16, 1
+        dA, dB = ozimmu.colmajor_empty(m, k).fill_(0.5), ozimmu.colmajor_empty(k, n).fill_(0.25)
+        ws = ozimmu.alloc_workspace(m, n, k, s)
+        C = ozimmu.colmajor_empty(m, n)
+        for X, at in ((dA, (0, 0)), (dA, (m - 1, k - 1)), (dB, (k - 1, n - 1))):
+            X[at] = float("nan")
+            with pytest.raises(ozimmu.OzimmuError):
+                ozimmu.dgemm(dA, dB, s, C=C, workspace=ws, check_finite=True)
+            X[at] = 0.5
+        ozimmu.dgemm(dA, dB, s, C=C, workspace=ws, check_finite=True)
+        took[m] = seconds(ws)
+    print(took, flush=True)
+    assert took[1_000_000] < 8 * took[300], took
 
 
 @pytest.mark.parametrize("m,n,k", [(9000, 64, 2100), (2100, 33, 5000), (300, 1, 30001), (64, 5000, 4500), (31, 260, 9000), (257, 40, 140000),
