@@ -100,8 +100,11 @@ int ozimmu_calibration_copy(void *dst, const void *src, size_t bytes, void *stre
  * ozimmu_debug_slice_product: P[i + j*m] = sum_{kk = k0}^{k1-1} A_(l)[i,kk] B^(h)[kk,j] as int32
  *   for one pair (l, h), 1-based, over the contraction range [k0, k1) with k0 a multiple of 32
  *   and (k1-k0) * 127^2 < 2^31, produced by the generic (pair-by-pair) GEMM kernel.
+ * ozimmu_debug_setup_threads: threads of the launch that forms the scales and slices of both operands of an m x n x k
+ *   product together, 0 where they are formed in separate launches.  Host only: no HIP call is made.
  */
 int ozimmu_debug_diagonals(int m, int n, int k, int s, const void *workspace, int32_t *D, void *stream);
+long long ozimmu_debug_setup_threads(int m, int n, int k);
 int ozimmu_debug_small_tile_limit(long long tiles);
 int ozimmu_debug_tile_choice(int choice);
 int ozimmu_debug_panel_bytes(long long bytes);

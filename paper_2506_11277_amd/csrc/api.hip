@@ -428,6 +428,8 @@ int ozimmu_get_exponents(int m, int n, int k, int s, const void *workspace, int3
 
 const char *ozimmu_last_gemm_kernel(void) { return last_gemm_kernel(); }
 
+long long ozimmu_debug_setup_threads(int m, int n, int k) { return scale_split_threads(m, n, k); }
+
 int ozimmu_debug_panel_bytes(long long bytes)
 {
     fused_set_panel_bytes(bytes);

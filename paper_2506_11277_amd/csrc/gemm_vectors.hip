@@ -267,7 +267,7 @@ bool gemm_vectors_handles(int m, int n, int k, int sA, int sB, int cA, int cB, b
 {
     const int sh = m < n ? m : n, lg = m < n ? n : m;
     if (sA != sB || cA != sA || cB != sB || sA < 2 || sA > (nearest ? 8 : 9)) return false;
-    if (sh < 1 || sh > 64 || lg < 256 || scale_split_handles(m, n, k)) return false;
+    if (sh < 1 || sh > 64 || lg < 256 || k <= 2048 || scale_split_handles(m, n, k)) return false;
     if ((m < n ? ldb : lda) >= 1 << 24) return false;                // (32-bit lane offsets)
     return (long long)lg * k >= (2LL << 20) && vectors_parts(sA, (lg + 31) / 32, round_up(k, kPad)) > 0;
 }

@@ -189,14 +189,15 @@ hipError_t launch_split_both(int m, int n, int k, const double *A, int lda, cons
                              int cA, int cB, const unsigned long long *maxA, const unsigned long long *maxB,
                              int32_t *eA, int32_t *eB, int8_t *pA, int8_t *pB, bool nearest, hipStream_t st);
 
-// Scales AND slices of both operands in one launch (contractions up to 2048, for fewer rows 4096).  Instead of setting the header's
+// Scales AND slices of both operands in one launch (contractions up to 2048, for fewer rows 4096; fewer than 2^32 threads).  Instead of setting the header's
 // non-finite flag it leaves a word per work-group, 0 or 1, at bad_offset bytes from the header (a work-group per four or
 // eight rows of A / columns of B), and says so in the header: [kHeaderBadWords] their number, then the offset, then
 // kBadWordsMagic, then the header's own address (a header that is not this workspace's names no words).
 // launch_collect_bad(), for ozimmu_check, sets the header's flag where one of the words is set.
 constexpr int kHeaderBadWords = 8;
 constexpr unsigned long long kBadWordsMagic = 0x6f7a696d6d754241ULL;
-bool scale_split_handles(int m, int n, int k);
+long long scale_split_threads(int m, int n, int k);      // threads of that launch, 0 where the problem is not one for it
+inline bool scale_split_handles(int m, int n, int k) { return scale_split_threads(m, n, k) > 0; }
 hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int sA, int sB, int cA,
                               int cB, int32_t *eA, int32_t *eB, int8_t *pA, int8_t *pB, bool nearest,
                               unsigned long long *header, size_t bad_offset, hipStream_t st);

@@ -351,29 +351,51 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
     return hipGetLastError();
 }
 
+// Rows to a work-group.  Four put the most compute units to work (a compute unit takes in some 10-25 GB/s whatever
+// it asks for: 1024^3 s = 7 27.1 / 21.3 / 21.5 us for 16 / 8 / 4 rows, 256 x 256 x 1024 25.4 / 18.3 / 15.4, 1024 x 1024 x 2048 41.0 /
+// 25.9 / 24.4, 2048^3 40.9 / 42.7 / 37.5; two rows: 29.7 in the last but one); eight where there are plenty of rows
+// and the pieces of cache lines begin to count (8192 x 8192 x 1024: 69.6 / 59.4 / 63.9)
+static int scale_split_rows(int m, int n, int kp) { return kp <= 2048 && (long long)m + n >= 12288 ? 8 : 4; }
+
+static int scale_split_waves(int rows, int kp)
+{
+    const int waves = kp / 16 * rows / 16;
+    return waves < 1 ? 1 : waves < 16 ? waves : 16;
+}
+
+static long long scale_split_groups(int m, int n, int rows)
+{
+    return (((long long)m + rows - 1) / rows + ((long long)n + rows - 1) / rows + 7) / 8 * 8;
+}
+
 // Contractions up to 2048 always; up to 4096 while the operands have up to about 18 million entries (both phases of two
 // launches against one, us, s = 7: 2048 x 2048 x 4096 81.7 -> 67.4, 1000 x 1000 x 3000 40.0 -> 27.0, 2500 x 2400 x 2500 64.1 -> 46.0, but
 // 3000 x 2900 x 4000 106.5 -> 112.1 and 4096^3 147.7 -> 157.5: there a work-group's loads wait for a chip that is busy
 // anyway, and the register-resident form has fewer wavefronts)
-bool scale_split_handles(int m, int n, int k)
+// A launch holds fewer than 2^32 threads, 8 to 128 per row here: beyond (134 million rows at k <= 128, 33 million from 512 on)
+// the two launches of the general way, which take more, serve.
+long long scale_split_threads(int m, int n, int k)
 {
-    if (m <= 0 || n <= 0 || k <= 0) return false;
+    if (m <= 0 || n <= 0 || k <= 0) return 0;
     const int kp = round_up(k, kPad);
-    return kp <= 2048 || (kp <= 4096 && ((long long)m + n) * kp <= 18LL << 20);
+    if (kp > 2048 && (kp > 4096 || ((long long)m + n) * kp > 18LL << 20)) return 0;
+    const int rows = scale_split_rows(m, n, kp);
+    const long long threads = scale_split_groups(m, n, rows) * 64 * scale_split_waves(rows, kp);
+    return threads < 1LL << 32 ? threads : 0;
 }
 
 hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int sA, int sB, int cA,
                               int cB, int32_t *eA, int32_t *eB, int8_t *pA, int8_t *pB, bool nearest,
                               unsigned long long *header, size_t bad_offset, hipStream_t st)
 {
-    if (!scale_split_handles(m, n, k) || cA < sA || cB < sB) return hipErrorInvalidValue;
+    if (!scale_split_threads(m, n, k) || cA < sA || cB < sB) return hipErrorInvalidValue;
     const int kp = round_up(k, kPad);
     auto *bad = (unsigned *)((char *)header + bad_offset);
     auto launch = [&](auto PRC, auto NVC) {
         constexpr int PR = decltype(PRC)::value, NV = decltype(NVC)::value;
-        const int panelsA = (m + PR - 1) / PR, panels = panelsA + (n + PR - 1) / PR, waves = kp / 16 * PR / 16;
+        const int panelsA = (m + PR - 1) / PR, panels = panelsA + (n + PR - 1) / PR;
         auto kern = nearest ? scale_split_kernel<true, PR, NV> : scale_split_kernel<false, PR, NV>;
-        kern<<<(panels + 7) / 8 * 8, 64 * (waves < 1 ? 1 : waves < 16 ? waves : 16), 0, st>>>(
+        kern<<<(unsigned)scale_split_groups(m, n, PR), 64 * scale_split_waves(PR, kp), 0, st>>>(
             (const unsigned long long *)A, lda, m, (const unsigned long long *)B, ldb, n, k, sA, sB, cA, cB, eA, eB, pA, pB, kp / kFrag,
             panelsA, header, panels, (long long)bad_offset, bad);
     };
@@ -384,11 +406,7 @@ hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, con
         else if (kp <= 3 * SWEEP) launch(PRC, std::integral_constant<int, 3>{});
         else launch(PRC, std::integral_constant<int, 4>{});
     };
-    // Four rows to a work-group put the most compute units to work (a compute unit takes in some 10-25 GB/s whatever
-    // it asks for: 1024^3 s = 7 27.1 / 21.3 / 21.5 us for 16 / 8 / 4 rows, 256 x 256 x 1024 25.4 / 18.3 / 15.4, 1024 x 1024 x 2048 41.0 /
-    // 25.9 / 24.4, 2048^3 40.9 / 42.7 / 37.5; two rows: 29.7 in the last but one); eight where there are plenty of rows
-    // and the pieces of cache lines begin to count (8192 x 8192 x 1024: 69.6 / 59.4 / 63.9)
-    if (kp <= 2048 && (long long)m + n >= 12288) by_k(std::integral_constant<int, 8>{});
+    if (scale_split_rows(m, n, kp) == 8) by_k(std::integral_constant<int, 8>{});
     else by_k(std::integral_constant<int, 4>{});
     return hipGetLastError();
 }

@@ -130,3 +130,22 @@ def test_level_size_limit_and_variant_argument_validation_without_gpu(handle):
     assert handle.ozimmu_dgemm3(*args, 2, 2, 0, 2, 1, ws, 1 << 30, None) == 1      # unknown splitting
     assert handle.ozimmu_dgemm3(*args, 2, 2, 0, 1, 1, ws, 16, None) == 1           # workspace too small
     assert handle.ozimmu_split2(b"A", 4, 4, fake, 4, 2, 5, fake, fake, 0, ws, None) == 1
+
+
+def test_the_one_launch_set_up_stays_within_the_threads_of_a_launch(handle):
+    # a launch holds fewer than 2^32 threads; taller or wider operands go through the separate launches
+    threads = handle.ozimmu_debug_setup_threads
+    assert threads(128, 128, 128) == 64 * 128          # two wavefronts for every four rows or columns
+    assert threads(8192, 8192, 1024) == 2048 * 1024    # sixteen for every eight
+    assert threads(100, 100, 5000) == threads(0, 5, 5) == threads(5, 5, 0) == 0
+    for k in (1, 128, 129, 256, 384, 512, 513, 1024, 2048):
+        for rest in (1, 100, 5000):
+            m = 1000
+            while m < 2 ** 31:
+                for shape in ((m, rest, k), (rest, m, k), (m - 1, rest, k)):
+                    t = threads(*shape)
+                    assert 0 <= t < 2 ** 32, shape
+                    assert t > 0 or m >= 33_000_000, shape
+                m = m * 9 // 8
+    assert threads(2 ** 27 + 5, 1, 1) == 0 and threads(1, 2 ** 27 + 5, 1) == 0 and threads(2 ** 27 - 128, 1, 1) > 0
+    assert threads(2 ** 25 + 5, 1, 512) == 0 and threads(2 ** 25 - 128, 1, 512) > 0

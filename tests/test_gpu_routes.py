@@ -81,6 +81,21 @@ def test_scales_and_slices_in_one_launch(m, n, k, sA, sB, nearest):
     check(ozimmu.dgemm3(dA, dB, sA, sB, splitting=splitting), A, B, sA, sB, nearest=nearest)
 
 
+def test_more_rows_than_the_one_launch_set_up_has_threads_for():
+    # 2^27 rows: the launch that forms scales and slices together would have 2^32 threads, the separate ones serve
+    m, n, k, s = 2 ** 27 + 5, 1, 1, 1
+    free, _ = torch.cuda.mem_get_info()
+    if free < 40 << 30:
+        pytest.skip("needs 40 GB of device memory")
+    A = torch.arange(m, device="cuda", dtype=torch.float64).remainder_(1009).sub_(500).reshape(m, 1)
+    B = torch.full((1, 1), 1.5, dtype=torch.float64, device="cuda")
+    print(f"{m} rows", flush=True)
+    C = ozimmu.dgemm(A, B, s, check_finite=True)
+    rows = torch.as_tensor([0, 1, 2, 500, 1009, 2 ** 26, 2 ** 27 - 1, 2 ** 27, m - 1], device="cuda")
+    want = oracle.dgemm(np.asfortranarray(A[rows].cpu().numpy()), np.array([[1.5]], order="F"), s)
+    assert np.array_equal(bits(C[rows].cpu().numpy()), bits(want))
+
+
 @pytest.mark.parametrize("k", [100, 3000, 5000])
 def test_non_finite_is_reported_and_forgotten(k):
     # the report of a call replaces that of the call before it in the same workspace, whichever way either slices
