@@ -82,9 +82,9 @@ int ozimmu_calibration_copy(void *dst, const void *src, size_t bytes, void *stre
  * ozimmu_debug_diagonals: D[(d-2) * m * n + i + j*m] = sum_{l+h=d} (A_(l) B^(h))_ij as int32,
  *   d = 2..s+1, produced by the main loop of the fused GEMM kernel (needs
  *   s * k * 127^2 < 2^31 and s <= the fused kernel's limit, else OZIMMU_BAD_ARG).
- *   (Both hooks read the planes a call has left in its workspace.  A call that multiplied a large matrix and at most
- *   64 vectors by itself -- ozimmu_last_gemm_kernel() names gemm_vectors_kernel -- leaves those of the short operand
- *   only; with either knob below set, none does.)
+ *   (ozimmu_debug_diagonals and ozimmu_debug_slice_product wait for the stream.  A call that multiplied a large matrix
+ *   and at most 64 vectors by itself -- ozimmu_last_gemm_kernel() names gemm_vectors_kernel -- leaves the planes of the
+ *   short operand only: after it they return OZIMMU_BAD_ARG.  With either knob below set, no call takes that way.)
  * ozimmu_debug_small_tile_limit: ozimmu_dgemm with equal slice counts up to 12 uses a 64 x 64 tile instead of
  *   the tile tabulated for the slice count where that finishes sooner by (rounds of the compute units) x (tile
  *   area) / (relative speed of the kernel); that rule is the default (-1).  0: never the small tile; n > 0: the

@@ -260,7 +260,7 @@ static int dgemm_impl(int m, int n, int k, const double *A, int lda, const doubl
     // read planes only)
     if (w.path == kPathFused && !all_products && fused_automatic() && gemm_vectors_handles(m, n, k, sA, sB, w.cA, w.cB, nearest, lda, ldb) &&
         !(m < n ? overlap(C, m, n, ldc, B, k, n, ldb) : overlap(C, m, n, ldc, A, m, k, lda))) {
-        OZ_TRY(launch_scales_fused(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, eA, w.mp, eB, w.np, nearest ? 1 : 0, false, st));
+        OZ_TRY(launch_scales_fused(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, eA, w.mp, eB, w.np, nearest ? 1 : 0, false, false, st));
         prof_mark(prof, 1, st);
         OZ_TRY(launch_split_both(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, maxA, maxB, eA, eB, m < n ? pA : nullptr,
                                  m < n ? nullptr : pB, nearest, st));
@@ -274,7 +274,7 @@ static int dgemm_impl(int m, int n, int k, const double *A, int lda, const doubl
         OZ_TRY(launch_scale_split(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, eA, eB, pA, pB, nearest, hdr, w.off_minA, st));
     } else {
         OZ_TRY(launch_scales_fused(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, eA, w.mp, eB, w.np, nearest ? 1 : 0,
-                                   m == 0 || n == 0, st));
+                                   m == 0 || n == 0, true, st));
         if (m == 0 || n == 0) return OZIMMU_OK;
         prof_mark(prof, 1, st);
         OZ_TRY(launch_split_both(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, maxA, maxB, eA, eB, pA, pB, nearest, st));
@@ -450,9 +450,19 @@ int ozimmu_debug_tile_choice(int choice)
     return OZIMMU_OK;
 }
 
+// whether the last product on this workspace left the planes of both operands; waits for the stream
+static int planes_of_both(const void *workspace, hipStream_t st)
+{
+    unsigned long long word = 0;
+    OZ_TRY(hipMemcpyAsync(&word, (const unsigned long long *)workspace + kHeaderPlanes, sizeof(word), hipMemcpyDeviceToHost, st));
+    OZ_TRY(hipStreamSynchronize(st));
+    return word == kNoPlanes ? OZIMMU_BAD_ARG : OZIMMU_OK;
+}
+
 int ozimmu_debug_diagonals(int m, int n, int k, int s, const void *workspace, int32_t *D, void *stream)
 {
     if (m <= 0 || n <= 0 || k < 0 || !workspace || !D || !fused_single_block(s, s, k)) return OZIMMU_BAD_ARG;
+    if (int rc = planes_of_both(workspace, (hipStream_t)stream)) return rc;
     const Workspace w = carve(m, n, k, s, s);
     const char *ws = (const char *)workspace;
     OZ_TRY(launch_gemm_fused(m, n, w.kp, s, s, false, (const int8_t *)(ws + w.off_planesA),
@@ -472,6 +482,7 @@ int ozimmu_debug_slice_product(int m, int n, int k, int s, const void *workspace
     // the planes are zero beyond k, so the last (partial) fragment may be read whole
     const int kb_begin = k0 / kFrag, kb_end = (k1 + kFrag - 1) / kFrag;
     if (k1 != k && (k1 % kFrag) != 0) return OZIMMU_BAD_ARG;
+    if (int rc = planes_of_both(workspace, (hipStream_t)stream)) return rc;
     OZ_TRY(launch_gemm_generic(m, n, w.kp, s, (const int8_t *)(ws + w.off_planesA),
                                (const int8_t *)(ws + w.off_planesB), nullptr, nullptr, nullptr, m, l, h, kb_begin,
                                kb_end, P, (hipStream_t)stream));

@@ -112,7 +112,7 @@ struct Workspace {
     int mp, np, kp;                 // padded extents
     int cA, cB;                     // slices per entry in the planes (gemm_path)
     int path;                       // GemmPath
-    size_t off_header;              // 256 B: [0] u32 non-finite flag, [8] u64 kappa_A bits, [16] u64 kappa_B bits, [64] see kHeaderBadWords
+    size_t off_header;              // 256 B: [0] u32 non-finite flag, [8] u64 kappa_A bits, [16] u64 kappa_B bits, [64] see kHeaderBadWords, [96] see kHeaderPlanes
     size_t off_maxA, off_minA;      // u64[mp]: integer view of max |a_ij| / min nonzero |a_ij| per row (minA onwards: the non-finite words of launch_scale_split)
     size_t off_maxB, off_minB;      // u64[np]
     size_t off_expA, off_expB;      // i32[mp], i32[np]
@@ -160,9 +160,11 @@ hipError_t launch_kappas(int m, int n, int k, const double *A, int lda, const do
                          unsigned long long *minB, int32_t *expA, int mp, int32_t *expB, int np, hipStream_t st);
 hipError_t launch_clear_header(void *header, hipStream_t st);
 // the whole scale extraction of ozimmu_dgemm in three launches: clear, reduce both operands, exponents of both
+// (both_planes: whether the call will leave the planes of both operands, for kHeaderPlanes)
 hipError_t launch_scales_fused(int m, int n, int k, const double *A, int lda, const double *B, int ldb,
                                unsigned long long *hdr, unsigned long long *maxA, unsigned long long *maxB,
-                               int32_t *expA, int mp, int32_t *expB, int np, int bias, bool finalize, hipStream_t st);
+                               int32_t *expA, int mp, int32_t *expB, int np, int bias, bool finalize, bool both_planes,
+                               hipStream_t st);
 
 // e = floor(log2 M) + 1 from the bit pattern of M >= 0 (eq. (alpha-def)); the exponent-field
 // shortcut described after eq. (beta-def) for normal numbers, leading-zero count for
@@ -195,6 +197,9 @@ hipError_t launch_split_both(int m, int n, int k, const double *A, int lda, cons
 // kBadWordsMagic, then the header's own address (a header that is not this workspace's names no words).
 // launch_collect_bad(), for ozimmu_check, sets the header's flag where one of the words is set.
 constexpr int kHeaderBadWords = 8;
+// header word that is kNoPlanes while the last product left the slices of one operand only (launch_gemm_vectors), else 0
+constexpr int kHeaderPlanes = 12;
+constexpr unsigned long long kNoPlanes = 0x6f7a6e6f706c616eULL;
 constexpr unsigned long long kBadWordsMagic = 0x6f7a696d6d754241ULL;
 long long scale_split_threads(int m, int n, int k);      // threads of that launch, 0 where the problem is not one for it
 inline bool scale_split_handles(int m, int n, int k) { return scale_split_threads(m, n, k) > 0; }

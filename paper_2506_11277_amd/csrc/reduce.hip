@@ -151,10 +151,12 @@ __global__ __launch_bounds__(256) void reduce_both_kernel(const unsigned long lo
 }
 
 // header cleared, row maxima of A set to 0 and its minima, where wanted, to none (they are formed with atomics)
-__global__ void init_scales_kernel(unsigned long long *hdr, unsigned long long *maxA, unsigned long long *minA, int m)
+// (the header's word on the planes: 0, kNoPlanes, or with keep_planes what it was -- the estimator leaves the planes alone)
+__global__ void init_scales_kernel(unsigned long long *hdr, unsigned long long *maxA, unsigned long long *minA, int m,
+                                   unsigned long long planes, bool keep_planes)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 32) hdr[i] = 0ULL;
+    if (i < 32 && !(i == kHeaderPlanes && keep_planes)) hdr[i] = i == kHeaderPlanes ? planes : 0ULL;
     if (i < m) maxA[i] = 0ULL;
     if (minA && i < m) minA[i] = kNoMin;
 }
@@ -218,10 +220,11 @@ __global__ void finalize_both_kernel(const unsigned long long *__restrict__ maxA
 
 static hipError_t launch_maxima(int m, int n, int k, const double *A, int lda, const double *B, int ldb,
                                 unsigned long long *hdr, unsigned long long *maxA, unsigned long long *maxB,
-                                unsigned long long *minA, unsigned long long *minB, hipStream_t st)
+                                unsigned long long *minA, unsigned long long *minB, unsigned long long planes,
+                                bool keep_planes, hipStream_t st)
 {
     const int mm = m > 0 ? m : 0;
-    init_scales_kernel<<<(mm + 32 + 255) / 256, 256, 0, st>>>(hdr, maxA, minA, mm);
+    init_scales_kernel<<<(mm + 32 + 255) / 256, 256, 0, st>>>(hdr, maxA, minA, mm, planes, keep_planes);
     const int gxA = (mm + 63) / 64, gyA = k > 0 ? (k + kRowChunk - 1) / kRowChunk : 0;
     const long long nblkA = (long long)gxA * gyA, nblkB = n > 0 ? n : 0;
     if (nblkA + nblkB > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -234,9 +237,12 @@ static hipError_t launch_maxima(int m, int n, int k, const double *A, int lda, c
 
 hipError_t launch_scales_fused(int m, int n, int k, const double *A, int lda, const double *B, int ldb,
                                unsigned long long *hdr, unsigned long long *maxA, unsigned long long *maxB,
-                               int32_t *expA, int mp, int32_t *expB, int np, int bias, bool finalize, hipStream_t st)
+                               int32_t *expA, int mp, int32_t *expB, int np, int bias, bool finalize, bool both_planes,
+                               hipStream_t st)
 {
-    if (hipError_t e = launch_maxima(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, nullptr, nullptr, st); e != hipSuccess) return e;
+    if (hipError_t e = launch_maxima(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, nullptr, nullptr, both_planes ? 0ULL : kNoPlanes, false, st);
+        e != hipSuccess)
+        return e;
     // (the slicing kernel that follows forms the exponents from the maxima itself and stores them; only a call that
     // ends here, an empty product, needs them from this launch)
     if (finalize) finalize_both_kernel<<<(mp + np + 255) / 256, 256, 0, st>>>(maxA, expA, m, mp, maxB, expB, n, np, bias);
@@ -247,7 +253,7 @@ hipError_t launch_kappas(int m, int n, int k, const double *A, int lda, const do
                          unsigned long long *minB, int32_t *expA, int mp, int32_t *expB, int np, hipStream_t st)
 {
     if (k > 65535LL * kRowChunk) return hipErrorInvalidValue;
-    if (hipError_t e = launch_maxima(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, minA, minB, st); e != hipSuccess) return e;
+    if (hipError_t e = launch_maxima(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, minA, minB, 0ULL, true, st); e != hipSuccess) return e;
     const int gA = (mp + 255) / 256, gB = (np + 255) / 256;
     finalize_kappas_kernel<<<gA + gB, 256, 0, st>>>(maxA, minA, expA, m, mp, maxB, minB, expB, n, np, hdr + 1, gA);
     return hipGetLastError();

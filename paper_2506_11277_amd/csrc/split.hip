@@ -234,11 +234,13 @@ __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long l
     const int row = R0 + r;
     const size_t rstep = isB ? (size_t)ldx : 1, kstep = isB ? 1 : (size_t)ldx;
     const unsigned long long *p = X + (size_t)(row < R ? row : R - 1) * rstep;
-    if (panel == 0 && threadIdx.x < 5) {
-        // header for ozimmu_check: no flag yet, how many words bad[] has, where, and two words that make these valid
+    if (panel == 0 && threadIdx.x < 6) {
+        // header for ozimmu_check: no flag yet, how many words bad[] has, where, and two words that make these valid;
+        // the planes of both operands will be there
+        static_assert(kHeaderPlanes == kHeaderBadWords + 4, "written together");
         const int i = threadIdx.x;
-        const unsigned long long v[5] = {0ULL, (unsigned long long)panels, (unsigned long long)bad_offset, kBadWordsMagic,
-                                         (unsigned long long)(uintptr_t)header};
+        const unsigned long long v[6] = {0ULL, (unsigned long long)panels, (unsigned long long)bad_offset, kBadWordsMagic,
+                                         (unsigned long long)(uintptr_t)header, 0ULL};
         header[i == 0 ? 0 : kHeaderBadWords + i - 1] = v[i];
     }
 

@@ -233,3 +233,40 @@ def test_one_slice_over_long_contractions(m, n, k, name):
     rows, cols = [0, m // 2, m - 1], [0, n // 2, n - 1]
     A, B = dA[rows].cpu().numpy(), dB[:, cols].cpu().numpy()
     assert np.array_equal(bits(C.cpu().numpy()[np.ix_(rows, cols)]), bits(oracle.dgemm(np.asfortranarray(A), np.asfortranarray(B), 1)))
+
+
+@pytest.mark.parametrize("m,n", [(700, 40), (40, 700)])
+def test_hooks_refuse_planes_that_a_call_has_not_left(m, n):
+    # the few-vectors way writes no slices of the long operand: the hooks that read both operands' say so, also when the
+    # estimator has used the workspace since, until a call leaves them
+    k, s = 5000, 3
+    A, B = workloads.lognormal(m, n, k, 1.0, 55)
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    ws = torch.empty(max(ozimmu.workspace_bytes(m, n, kk, s) for kk in (k, 100)), dtype=torch.uint8, device="cuda")
+
+    def refused():
+        for hook in (lambda: ozimmu.debug_diagonals(m, n, k, s, ws), lambda: ozimmu.debug_slice_product(m, n, k, s, ws, 1, 2)):
+            with pytest.raises(ozimmu.OzimmuError) as info:
+                hook()
+            assert info.value.code == ozimmu.BAD_ARG
+
+    C = ozimmu.dgemm(dA, dB, s, workspace=ws)
+    assert ozimmu.last_gemm_kernel().startswith("gemm_vectors_kernel")
+    refused()
+    ozimmu.estimate_slices(dA, dB, 1e-6, workspace=ws)
+    refused()
+    try:
+        ozimmu.debug_small_tile_limit(0)
+        assert torch.equal(ozimmu.dgemm(dA, dB, s, workspace=ws), C)
+    finally:
+        ozimmu.debug_small_tile_limit(-1)
+    D = ozimmu.debug_diagonals(m, n, k, s, ws)
+    assert torch.equal(D[1], ozimmu.debug_slice_product(m, n, k, s, ws, 1, 2) + ozimmu.debug_slice_product(m, n, k, s, ws, 2, 1))
+    eA, eB = ozimmu.get_exponents(m, n, k, s, ws)
+    S = sum(D[d].cpu().numpy().T * 2.0 ** (-7 * (d + 2)) for d in range(s))
+    assert np.array_equal(np.ldexp(S, eA.cpu().numpy()[:, None] + eB.cpu().numpy()[None, :]), C.cpu().numpy())
+    # and a call with scales and slices in one launch leaves both again after the few-vectors way
+    ozimmu.dgemm(dA, dB, s, workspace=ws)
+    small = ozimmu.to_colmajor(A[:, :100]), ozimmu.to_colmajor(B[:100])
+    ozimmu.dgemm(*small, s, workspace=ws)
+    ozimmu.debug_diagonals(m, n, 100, s, ws)
