@@ -430,6 +430,12 @@ const char *ozimmu_last_gemm_kernel(void) { return last_gemm_kernel(); }
 
 long long ozimmu_debug_setup_threads(int m, int n, int k) { return scale_split_threads(m, n, k); }
 
+int ozimmu_debug_vectors_parts(int m, int n, int k, int s)
+{
+    if (m <= 0 || n <= 0 || k <= 0 || s < 1 || s > OZIMMU_MAX_SLICES || !fused_automatic()) return 0;
+    return gemm_vectors_handles(m, n, k, s, s, s, s, false, m, k) ? gemm_vectors_parts(m, n, k, s) : 0;
+}
+
 int ozimmu_debug_panel_bytes(long long bytes)
 {
     fused_set_panel_bytes(bytes);

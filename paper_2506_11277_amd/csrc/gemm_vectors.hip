@@ -238,21 +238,19 @@ __global__ __launch_bounds__(512) void finish_vectors_kernel(const int32_t *__re
 }
 
 // Parts of k: enough work-groups for the compute units in whole rounds.  A step of 128 k takes about 1 us; a slot is
-// written and read once; no part shorter than 512 k, none longer than int32 sums allow.
+// written and read once; no part shorter than 512 k, none of more (whole) steps than int32 sums allow.
 int vectors_parts(int s, int tiles, int kp)
 {
     const int cus = device_cus();
-    const long long need = ((long long)s * kp + kMaxInt32K - 1) / kMaxInt32K;
+    const int all = kp / 128, longest = (int)(kMaxInt32K / (128LL * s)), need = (all + longest - 1) / longest;
     int best = 0;
     double best_cost = 0.0;
-    for (int parts = (int)need; parts <= kp / 512 && (parts <= 16 || parts == need); ++parts) {
-        // (whole 128-deep steps per part)
-        const int steps = (kp / 128 + parts - 1) / parts;
-        if ((long long)s * steps * 128 > kMaxInt32K) continue;
+    for (int parts = need; parts <= kp / 512 && (parts <= 16 || parts == need); ++parts) {
+        const int steps = (all + parts - 1) / parts;
         const double rounds = (double)(((long long)tiles * parts + cus - 1) / cus);
         const double cost = rounds * (steps + 3.0) + (parts > 1 ? 4.0 + (double)parts * tiles * s * 8192 * 2 / 4.5e6 : 0.0);
         if (!best || cost < best_cost) {
-            best = parts;
+            best = (all + steps - 1) / steps;       // (as many as get a step)
             best_cost = cost;
         }
     }
@@ -263,13 +261,15 @@ int vectors_parts(int s, int tiles, int kp)
 
 // Where it pays: the contraction is too long for the launch that reads the operands once (then 16 bytes per long entry
 // are moved here against 16 + 2 s), and the long operand is a few million entries.
+int gemm_vectors_parts(int m, int n, int k, int s) { return vectors_parts(s, ((m < n ? n : m) + 31) / 32, round_up(k, kPad)); }
+
 bool gemm_vectors_handles(int m, int n, int k, int sA, int sB, int cA, int cB, bool nearest, int lda, int ldb)
 {
     const int sh = m < n ? m : n, lg = m < n ? n : m;
     if (sA != sB || cA != sA || cB != sB || sA < 2 || sA > (nearest ? 8 : 9)) return false;
     if (sh < 1 || sh > 64 || lg < 256 || k <= 2048 || scale_split_handles(m, n, k)) return false;
     if ((m < n ? ldb : lda) >= 1 << 24) return false;                // (32-bit lane offsets)
-    return (long long)lg * k >= (2LL << 20) && vectors_parts(sA, (lg + 31) / 32, round_up(k, kPad)) > 0;
+    return (long long)lg * k >= (2LL << 20) && gemm_vectors_parts(m, n, k, sA) > 0;
 }
 
 hipError_t launch_gemm_vectors(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int s, bool nearest,
@@ -278,9 +278,9 @@ hipError_t launch_gemm_vectors(int m, int n, int k, const double *A, int lda, co
 {
     const bool short_a = m < n;
     const int L = short_a ? n : m, tiles = (L + 31) / 32, kp = round_up(k, kPad);
-    const int want = vectors_parts(s, tiles, kp);
-    if (want < 1) return hipErrorInvalidValue;
-    const int steps = (kp / 128 + want - 1) / want, parts = (kp / 128 + steps - 1) / steps;
+    const int parts = vectors_parts(s, tiles, kp);
+    if (parts < 1) return hipErrorInvalidValue;
+    const int steps = (kp / 128 + parts - 1) / parts;
     // the slots, parts * tiles * s * 8192 bytes, lie in the room for the long operand's planes, tiles * 32 * s * kp bytes or
     // more (parts <= kp / 512)
     int32_t *slots = parts > 1 ? (int32_t *)(short_a ? pB : pA) : nullptr;

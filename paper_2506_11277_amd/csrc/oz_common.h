@@ -273,6 +273,7 @@ hipError_t launch_gemm_eighths(int s, int m, int n, int kp, const int8_t *pA, co
 // short operand must hold its slices, the long one is sliced by the kernel (exponents from its maxima, stored as
 // launch_split_both stores them); its planes are only room
 bool gemm_vectors_handles(int m, int n, int k, int sA, int sB, int cA, int cB, bool nearest, int lda, int ldb);
+int gemm_vectors_parts(int m, int n, int k, int s);      // parts of k of that kernel, 0: none that the int32 sums allow
 hipError_t launch_gemm_vectors(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int s, bool nearest,
                                const unsigned long long *maxA, const unsigned long long *maxB, int32_t *eA, int32_t *eB,
                                int8_t *pA, int8_t *pB, double *C, int ldc, int Q, hipStream_t st);

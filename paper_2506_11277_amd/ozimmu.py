@@ -61,6 +61,7 @@ _SIGNATURES = {
     "ozimmu_debug_tile_choice": (_c.c_int, [_c.c_int]),
     "ozimmu_debug_panel_bytes": (_c.c_int, [_c.c_longlong]),
     "ozimmu_debug_setup_threads": (_c.c_longlong, [_c.c_int] * 3),
+    "ozimmu_debug_vectors_parts": (_c.c_int, [_c.c_int] * 4),
     "ozimmu_debug_diagonals": (_c.c_int, [_c.c_int, _c.c_int, _c.c_int, _c.c_int, _c.c_void_p, _c.c_void_p,
                                           _c.c_void_p]),
     "ozimmu_debug_slice_product": (_c.c_int, [_c.c_int, _c.c_int, _c.c_int, _c.c_int, _c.c_void_p, _c.c_int,

@@ -149,3 +149,18 @@ def test_the_one_launch_set_up_stays_within_the_threads_of_a_launch(handle):
                 m = m * 9 // 8
     assert threads(2 ** 27 + 5, 1, 1) == 0 and threads(1, 2 ** 27 + 5, 1) == 0 and threads(2 ** 27 - 128, 1, 1) > 0
     assert threads(2 ** 25 + 5, 1, 512) == 0 and threads(2 ** 25 - 128, 1, 512) > 0
+
+
+def test_few_vectors_have_parts_of_k_at_every_length(handle):
+    # every contraction within the rule is divided so that no part's int32 sums overflow (s k 127^2 < 2^31, in whole steps
+    # of 128), no part is empty, and their slots fit the room of the long operand's planes
+    parts_of = handle.ozimmu_debug_vectors_parts
+    assert parts_of(8192, 65, 8192, 7) == parts_of(8192, 64, 2000, 7) == parts_of(8192, 64, 8192, 10) == parts_of(200, 8, 50000, 3) == 0
+    for m, n in ((8192, 64), (300, 40), (64, 8192), (1, 100000)):
+        for s in range(2, 10):
+            for k in list(range(7000, 60000, 997)) + list(range(60000, 1_500_000, 128 * 7 + 1)):
+                steps, parts = -(-k // 128), parts_of(m, n, k, s)
+                assert 1 <= parts, (m, n, k, s)
+                longest = -(-steps // parts)
+                assert s * longest * 128 * 127 * 127 < 2 ** 31, (m, n, k, s, parts)
+                assert (parts - 1) * longest < steps and (parts == 1 or 4 * parts <= steps), (m, n, k, s, parts)

@@ -146,7 +146,7 @@ def test_check_takes_one_round_trip_whatever_the_size():
 
 
 @pytest.mark.parametrize("m,n,k", [(9000, 64, 2100), (2100, 33, 5000), (300, 1, 30001), (64, 5000, 4500), (31, 260, 9000), (257, 40, 140000),
-                                   (2, 700, 20000), (33000, 7, 4200)])
+                                   (2, 700, 20000), (33000, 7, 4200), (260, 9, 304256)])
 @pytest.mark.parametrize("s,nearest,Q", [(2, False, 1), (3, True, 2), (7, False, 1), (8, True, 1), (9, False, 3)])
 def test_long_operand_sliced_on_the_way(m, n, k, s, nearest, Q):
     # either operand short, one part of k and several, ragged ends of every dimension, leading dimensions that are odd
@@ -160,8 +160,7 @@ def test_long_operand_sliced_on_the_way(m, n, k, s, nearest, Q):
     ws = ozimmu.alloc_workspace(m, n, k, s)
     C = ozimmu.dgemm3(dA, dB, s, s, splitting=ozimmu.SPLIT_NEAREST if nearest else ozimmu.SPLIT_TRUNCATE,
                       level_diagonals=min(Q, ozimmu.max_level_diagonals(k, s, s)), workspace=ws, check_finite=True)
-    if k * s <= 133144:
-        assert ozimmu.last_gemm_kernel().startswith("gemm_vectors_kernel"), ozimmu.last_gemm_kernel()
+    assert ozimmu.last_gemm_kernel().startswith("gemm_vectors_kernel"), ozimmu.last_gemm_kernel()
     check(C, A, B, s, s, nearest=nearest, Q=min(Q, ozimmu.max_level_diagonals(k, s, s)))
     eA, eB = ozimmu.get_exponents(m, n, k, s, ws)
     assert eA.shape == (m,) and eB.shape == (n,)
