@@ -9,7 +9,7 @@
 // Work-group: 32 rows (columns) of the long operand x 64 of the short one x a part of k; eight wavefronts, two halves of
 // the short side x four groups that take every fourth 32-deep k-block.  The two wavefronts of a group slice a 32 x 32
 // block of the long operand together (8 consecutive k per lane), multiply the block of the step before meanwhile, and
-// keep the raw entries of the step after in flight: 32 KiB per compute unit, which is what full bandwidth takes.
+// keep the raw entries of the one to three steps after in flight, as many as the registers hold: 32 KiB per compute unit each.
 // At 8192 x 64 x 8192, s = 7 the kernel takes 170 us and the maxima before it 80, where reading, slicing, writing and
 // multiplying took 567 us.  What bounds it: the slices of the short operand, read from the L2s once per 32 long rows, 56 KiB
 // per compute unit and step (multiplying alone, with nothing sliced and no long operand read, takes 104 us, 9.6 TB/s out
@@ -35,6 +35,8 @@ __device__ __forceinline__ void static_for(F &&f)
     }
 }
 
+constexpr int kZeroScale = 4096;        // exponent at which every finite number has zero slices only
+
 template <int S, bool NEAREST>
 struct CfgVectors {
     static constexpr int ROUND = S < 4 ? S : 4;             // diagonals that are exchanged at a time
@@ -59,15 +61,15 @@ __global__ __launch_bounds__(512) void gemm_vectors_kernel(const unsigned long l
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), j = wave & 1, kg = wave >> 1;
     const int tile = blockIdx.x, part = blockIdx.y;
     const int row = tile * 32 + r;
-    const int e = row < L ? exponent_above(maxbits[row]) + (NEAREST ? 1 : 0) : 0;
-    if (part == 0 && wave == 0 && hh == 0) exps_out[row] = e;
+    const int e = row < L ? exponent_above(maxbits[row]) + (NEAREST ? 1 : 0) : kZeroScale;
+    if (part == 0 && wave == 0 && hh == 0) exps_out[row] = row < L ? e : 0;
 
     // k-blocks of this part: whole ones [kb0, kb1), and perhaps the ragged one behind them, which is taken first (step -1)
     const int kbF = K / 32, kb0 = part * kb_per_part, kb1 = kb0 + kb_per_part < kbF ? kb0 + kb_per_part : kbF;
     const int steps = kb1 > kb0 ? (kb1 - kb0 + 3) / 4 : 0;
     const int first = (K & 31) && kb0 <= kbF && kbF < kb0 + kb_per_part ? -1 : 0;
     const size_t kstep = 8 * (SHORT_A ? 1 : (size_t)ldx), rstep = 8 * (SHORT_A ? (size_t)ldx : 1);      // bytes
-    // (rows beyond the operand repeat its last one: their products end in entries of C that do not exist)
+    // (rows beyond the operand repeat its last one, at a scale that makes every slice zero)
     const char *base = (const char *)X + (size_t)tile * 32 * rstep;
     const unsigned voff = (unsigned)(row < L ? r : L - 1 - tile * 32) * (unsigned)rstep + (unsigned)(16 * j + 8 * hh) * (unsigned)kstep;
     const char *const sp = (const char *)P + (size_t)j * KB * (S * kFragBytes);
@@ -81,7 +83,7 @@ __global__ __launch_bounds__(512) void gemm_vectors_kernel(const unsigned long l
 #pragma unroll
         for (int t = 0; t < 8; ++t) x[t >> 2][t & 3] = *(const unsigned long long *)(q + (size_t)t * kstep + voff);
     };
-    auto scale = [&](int i) { return kb0 + kg + 4 * i < kb1 ? e : 4096; };
+    auto scale = [&](int i) { return kb0 + kg + 4 * i < kb1 ? e : kZeroScale; };
     auto short_slice = [&](int i, int h) -> v4i {
         const int kb = i < 0 ? kbF : kb0 + kg + 4 * i;
         return *(const v4i *)(sp + ((size_t)(kb < KB ? kb : KB - 1) * S + h) * kFragBytes + (unsigned)lane * 16);
