@@ -265,7 +265,7 @@ hipError_t launch_halves(int m, int n, int kp, const int8_t *pA, const int8_t *p
     static std::atomic<unsigned long long> configured{0};
     if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgHalves<S>::LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + 63) / 64, tiles_n = (n + 63) / 64;
-    note_gemm_kernel("gemm_fused_kernel<%d> equal counts tile 64x64, 8 wavefronts, k in halves", S);
+    note_gemm_kernel("gemm_halves_kernel<%d> tile 64x64, 8 wavefronts, k in halves", S);
     kern<<<(unsigned)tile_order_blocks(tiles_m, tiles_n, false), 512, CfgHalves<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag,
                                                                                            tiles_m, tiles_n, Q);
     return hipGetLastError();
@@ -279,7 +279,7 @@ hipError_t launch_eighths(int m, int n, int kp, const int8_t *pA, const int8_t *
     static std::atomic<unsigned long long> configured{0};
     if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgEighths<S>::LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
-    note_gemm_kernel("gemm_fused_kernel<%d> equal counts tile 64x64 as four of 32x32, 8 wavefronts, k in eighths", S);
+    note_gemm_kernel("gemm_eighths_kernel<%d> tile 32x32, 8 wavefronts, k in eighths", S);
     kern<<<4u * ((tiles_m + 1) / 2) * ((tiles_n + 1) / 2), 512, CfgEighths<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, Q);
     return hipGetLastError();
 }

@@ -720,11 +720,14 @@ def test_small_tile_is_taken_where_it_finishes_sooner():
     # same bits
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the expectations are worked out for 256 compute units")
-    for n, s, want in [(1024, 3, "gemm_fused_kernel<3> equal counts tile 64x64"), (2048, 2, "gemm_fused16_kernel<2> tile 128x128 ring of 3"),
+    for n, s, want in [(1024, 3, "gemm_halves_kernel<3> tile 64x64"), (2048, 2, "gemm_fused16_kernel<2> tile 128x128 ring of 3"),
                        (2560, 2, "gemm_fused16_kernel<2> tile 256x128"), (3000, 3, "gemm_fused16_kernel<3> tile 128x128 ring of 3"),
                        (2304, 4, "gemm_fused16_kernel<4> tile 192x128"), (2560, 4, "gemm_fused16_kernel<4> tile 128x128"),
                        (2304, 6, "gemm_fused16_kernel<6> tile 128x64"), (2560, 6, "gemm_fused16_kernel<6> tile 128x128"),
-                       (3000, 7, "gemm_fused16_kernel<7> tile 128x64"), (100, 7, "gemm_fused_kernel<7> equal counts tile 64x64")]:
+                       (3000, 7, "gemm_fused16_kernel<7> tile 128x64"), (100, 7, "gemm_eighths_kernel<7> tile 32x32"),
+                       (1536, 7, "gemm_fused_kernel<7> equal counts tile 64x64, 4 wavefronts"),
+                       (2240, 7, "gemm_fused_kernel<7> equal counts tile 64x64, 4 wavefronts"),
+                       (1536, 10, "gemm_fused_kernel<10> equal counts tile 64x64, 4 wavefronts")]:
         dA, dB = workloads.lognormal_device(n, n, 96, 1.0, 91)
         ozimmu.debug_small_tile_limit(-1)
         ozimmu.debug_tile_choice(0)

@@ -44,8 +44,8 @@ def special(A, B):
 
 @pytest.mark.parametrize("s", range(1, 11))
 @pytest.mark.parametrize("m,n,k,kernel", [
-    (1, 1, 1, "32x32"), (33, 31, 130, "32x32"), (512, 512, 64, "32x32"), (97, 70, 1000, "32x32"), (40, 300, 2100, "32x32"),
-    (705, 961, 65, "64x64, 8"), (1024, 1000, 129, "64x64, 8"), (65, 8000, 700, "64x64, 8"),
+    (1, 1, 1, "eighths"), (33, 31, 130, "eighths"), (512, 512, 64, "eighths"), (97, 70, 1000, "eighths"), (40, 300, 2100, "eighths"),
+    (705, 961, 65, "halves"), (1024, 1000, 129, "halves"), (65, 8000, 700, "halves"),
 ])
 def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
     # tiles of 32 x 32 (k in eighths) and of 64 x 64 (k in halves): every slice count, k-blocks that do not divide
@@ -57,7 +57,7 @@ def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
     dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
     C = ozimmu.dgemm(dA, dB, s)
     if torch.cuda.get_device_properties(0).multi_processor_count == 256 and 2 <= s <= 9:
-        assert kernel in ozimmu.last_gemm_kernel(), ozimmu.last_gemm_kernel()
+        assert ozimmu.last_gemm_kernel().startswith(f"gemm_{kernel}_kernel<{s}>"), ozimmu.last_gemm_kernel()
     check(C, A, B, s, s)
     check(ozimmu.dgemm3(dA, dB, s, s, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2), A, B, s, s, nearest=True, Q=2)
 
@@ -220,15 +220,17 @@ def test_result_inside_the_long_operand(short_a):
     check(C, A, B, s, s)
 
 
-@pytest.mark.parametrize("m,n,k,name", [(1440, 1440, 512, "32x32"), (1440, 1440, 40960, "32x32"), (1440, 1440, 40961, "128x128"),
-                                        (1408, 1408, 41000, "32x32"), (400, 5600, 41000, "128x128")])
+@pytest.mark.parametrize("m,n,k,name", [(1440, 1440, 512, "gemm_eighths_kernel<1>"), (1440, 1440, 40960, "gemm_eighths_kernel<1>"),
+                                        (1440, 1440, 40961, "gemm_fused_kernel<1> equal counts tile 128x128"),
+                                        (1408, 1408, 41000, "gemm_eighths_kernel<1>"),
+                                        (400, 5600, 41000, "gemm_fused_kernel<1> equal counts tile 128x128")])
 def test_one_slice_over_long_contractions(m, n, k, name):
     # where the 128 x 128 tile would be the alternative, 32 x 32 tiles serve one slice up to k = 40960 only
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the expectations are worked out for 256 compute units")
     dA, dB = workloads.lognormal_device(m, n, k, 1.0, 17)
     C = ozimmu.dgemm(dA, dB, 1)
-    assert name in ozimmu.last_gemm_kernel(), ozimmu.last_gemm_kernel()
+    assert ozimmu.last_gemm_kernel().startswith(name), ozimmu.last_gemm_kernel()
     rows, cols = [0, m // 2, m - 1], [0, n // 2, n - 1]
     A, B = dA[rows].cpu().numpy(), dB[:, cols].cpu().numpy()
     assert np.array_equal(bits(C.cpu().numpy()[np.ix_(rows, cols)]), bits(oracle.dgemm(np.asfortranarray(A), np.asfortranarray(B), 1)))
