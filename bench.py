@@ -77,6 +77,19 @@ class PowerSampler:
                 "source": "hwmon power1_input sampled during the timed steps"}
 
 
+def setup_rates(m, n, k, s, phases, one_launch):
+    """Rates of the HBM-bound set-up kernels, from the bytes each has to move and its phase.  Where one launch forms the
+    scales and the slices (short contractions), each operand is read once and the phase before is only the distance of two
+    events: one rate for both."""
+    entries = m * k + k * n
+    rate = lambda nbytes, ms: nbytes / (ms * 1e-3) / 1e9 if ms > 0 else None
+    if one_launch:
+        return {"scales_and_split_GBs": rate((8.0 + s) * entries, phases["split"]), "scales_GBs": None, "split_GBs": None,
+                "peak_GBs": HBM_PEAK_GBS}
+    return {"scales_GBs": rate(8.0 * entries, phases["scales"]), "split_GBs": rate((8.0 + s) * entries, phases["split"]),
+            "peak_GBs": HBM_PEAK_GBS}
+
+
 def error_measures(C, A, B, Cref):
     """Normwise measure eq. (err_higham) with alpha=1, beta=0, and max componentwise relative
     error eq. (fwd-err-def-mat), both against a binary64 reference product."""
@@ -152,8 +165,6 @@ def main():
     pairs = s * (s + 1) // 2
     gemm_s = phases["gemm"] * 1e-3
     int8_tops = flops * pairs / gemm_s / 1e12
-    split_bytes = (8.0 + s) * (m * k + k * n)
-    scales_bytes = 8.0 * (m * k + k * n)
 
     # bytes beyond the L2s per GEMM launch, per slice count, from the rocprofv3 --pmc runs summarised under
     # profiles/ (null for a slice count or workload that has not been measured)
@@ -191,11 +202,7 @@ def main():
         },
         "phases_ms": phases,
         "board_power": watts,
-        "hbm_kernels": {
-            "scales_GBs": scales_bytes / (phases["scales"] * 1e-3) / 1e9 if phases["scales"] > 0 else None,
-            "split_GBs": split_bytes / (phases["split"] * 1e-3) / 1e9 if phases["split"] > 0 else None,
-            "peak_GBs": HBM_PEAK_GBS,
-        },
+        "hbm_kernels": setup_rates(m, n, k, s, phases, ozimmu.setup_threads(m, n, k) > 0),
     }
 
     if args.calibration_copy:

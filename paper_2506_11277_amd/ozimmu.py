@@ -350,6 +350,11 @@ def last_gemm_kernel():
     return lib().ozimmu_last_gemm_kernel().decode()
 
 
+def setup_threads(m, n, k):
+    """Threads of the launch that forms scales and slices together, 0 where they are formed in separate launches."""
+    return lib().ozimmu_debug_setup_threads(m, n, k)
+
+
 def calibration_copy(dst, src):
     """Plain copy kernel of known traffic (src.nbytes read, the same written) for scaling memory counters."""
     nbytes = src.numel() * src.element_size()

@@ -164,3 +164,17 @@ def test_few_vectors_have_parts_of_k_at_every_length(handle):
                 longest = -(-steps // parts)
                 assert s * longest * 128 * 127 * 127 < 2 ** 31, (m, n, k, s, parts)
                 assert (parts - 1) * longest < steps and (parts == 1 or 4 * parts <= steps), (m, n, k, s, parts)
+
+
+def test_bench_rates_where_one_launch_forms_scales_and_slices(handle):
+    # at k = 1024 the phase before the slices is the distance of two events, not a reduction of 16 MiB: no rate is made
+    # of it; at k = 8192 both phases have one each
+    import bench
+    from paper_2506_11277_amd import ozimmu
+    assert ozimmu.setup_threads(1024, 1024, 1024) > 0 and ozimmu.setup_threads(8192, 8192, 8192) == 0
+    short = bench.setup_rates(1024, 1024, 1024, 7, {"scales": 0.004, "split": 0.013, "gemm": 0.03}, True)
+    assert short["scales_GBs"] is None and short["split_GBs"] is None
+    assert abs(short["scales_and_split_GBs"] - 15 * 2 * 1024 ** 2 / 13e-6 / 1e9) < 1e-6
+    long = bench.setup_rates(8192, 8192, 8192, 7, {"scales": 0.16, "split": 0.37, "gemm": 9.5}, False)
+    assert abs(long["scales_GBs"] - 8 * 2 * 8192 ** 2 / 160e-6 / 1e9) < 1e-6
+    assert abs(long["split_GBs"] - 15 * 2 * 8192 ** 2 / 370e-6 / 1e9) < 1e-6
