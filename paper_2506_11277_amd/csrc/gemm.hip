@@ -1108,14 +1108,17 @@ static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, b
                 // leaving most of the chip, or of a compute unit, idle (gemm_small.hip; event times, the launch
                 // included, in us).  32 x 32 tiles while there is about one for every compute unit: 128^3 s = 3 8.6 ->
                 // 6.2, 512^3 s = 3 / 7 14.1 -> 7.5 / 19.7 -> 11.1, 256 x 256 x 4096 s = 7 88.9 -> 28.0; up to 5 slices two
-                // such work-groups fit a compute unit, and from 7 on a second round is still no slower than halves (640^3
-                // s = 4 / 7 / 9 11.0 / 18.6 / 24.0 against 11.6 / 18.7 / 23.8; 640 x 640 x 4000 s = 7 59 against 70; at 700^3, 484
-                // tiles, s = 7 halves win 21.2 to 22.9).  A single slice has little to multiply per byte and keeps to it for
-                // longer (1400^3 22.8 -> 14.7, 1536 x 1536 x 20000 173 -> 130, 1408 x 1408 x 130000 1905 -> 966), beyond two rounds of 64 x 64
-                // tiles, where the 128 x 128 tile takes their place, up to k = 40960 (1440 x 1440 x 40000 / 61440 / 130000 346 / 577 /
-                // 1396 in 32 x 32 tiles, 360 / 554 / 1136 in 128 x 128).  From 11 slices on the registers do not suffice.
+                // such work-groups fit a compute unit, and from 6 on a second round, up to three quarters full, is no
+                // slower than halves and ahead at long k (halves against 32 x 32 tiles: 640^3 s = 4 / 6 / 7 / 9 11.6 / 15.9 /
+                // 18.7 / 23.8 and 11.0 / 16.3 / 18.6 / 24.0; 672^3 s = 6 17.6 and 17.7; 640 x 640 x 4000 s = 7 70 and 59, 670 x 670 x
+                // 14000 s = 6 167 and 148; at 700^3, 484 tiles, s = 7 halves win 21.2 to 22.9).  A single slice has little to multiply per
+                // byte and keeps to it for longer (1400^3 22.8 -> 14.7, 1536 x 1536 x 20000 173 -> 130, 1408 x 1408 x 130000 1905 ->
+                // 966), beyond two rounds of 64 x 64 tiles, where the 128 x 128 tile takes their place, up to k = 40960 (1440 x
+                // 1440 x 40000 / 61440 / 130000 346 / 577 / 1396 in 32 x 32 tiles, 360 / 554 / 1136 in 128 x 128).  From 11 slices on
+                // the registers do not suffice.
                 const long long tiles32 = (long long)((m + 31) / 32) * ((n + 31) / 32);
-                if (s <= 10 && (tiles32 <= cus || (s != 6 && 4 * tiles32 <= (s <= 5 ? 8LL : 7LL) * cus) || (s == 1 && tiles32 <= 9LL * cus && (kp <= 40960 || small_tiles <= 2LL * cus))))
+                const bool one_slice = s == 1 && tiles32 <= 9LL * cus && (kp <= 40960 || small_tiles <= 2LL * cus);
+                if (s <= 10 && (4 * tiles32 <= (s <= 5 ? 8LL : 7LL) * cus || one_slice))
                     return launch_gemm_eighths(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
                 // 64 x 64 tiles, the contraction in halves, while every tile has a compute unit of its own: 768^3 s = 3 / 7 18.3
                 // -> 11.4 / 24.7 -> 21.3, 1024^3 s = 3 / 5 / 7 / 9 21.6 -> 13.2 / 25.3 -> 19.6 / 32.3 -> 29.8 / 43.3 -> 41.5; 2 and 3 slices: two

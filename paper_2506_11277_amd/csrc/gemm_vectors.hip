@@ -262,7 +262,13 @@ int vectors_parts(int s, int tiles, int kp)
 }  // namespace
 
 // Where it pays: the contraction is too long for the launch that reads the operands once (then 16 bytes per long entry
-// are moved here against 16 + 2 s), and the long operand is a few million entries.
+// are moved here against 16 + 2 s), the short side fits the 64 of a work-group, and the long operand has some million
+// entries.  Against the 32 x 32 and 64 x 64 tiles with their operands sliced beforehand (whole calls, us, tiles and this):
+// below two million entries it loses (400 x 64 x 4200, s = 2 / 7: 27.9 and 34.1 / 48.8 and 59.0), between two and eight it
+// depends on k and s (512 x 64 x 4200, s = 7 47.7 and 59.2; 512 x 64 x 8200, s = 2 / 9 38.0 and 42.0 / 95.0 and 81.7; 256 x 64 x 16000,
+// s = 2 / 7 52.8 and 52.0 / 114 and 92), beyond it wins (2048 x 64 x 8200, s = 2 / 7 75.0 and 67.1 / 121 and 97.5; 8192 x 64 x 4200,
+// s = 7 247 and 140), and where s k passes the int32 range it replaces the split over k-blocks (300 x 10 x 100000, s = 7 845
+// and 280).
 int gemm_vectors_parts(int m, int n, int k, int s) { return vectors_parts(s, ((m < n ? n : m) + 31) / 32, round_up(k, kPad)); }
 
 bool gemm_vectors_handles(int m, int n, int k, int sA, int sB, int cA, int cB, bool nearest, int lda, int ldb)

@@ -355,8 +355,11 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
 
 // Rows to a work-group.  Four put the most compute units to work (a compute unit takes in some 10-25 GB/s whatever
 // it asks for: 1024^3 s = 7 27.1 / 21.3 / 21.5 us for 16 / 8 / 4 rows, 256 x 256 x 1024 25.4 / 18.3 / 15.4, 1024 x 1024 x 2048 41.0 /
-// 25.9 / 24.4, 2048^3 40.9 / 42.7 / 37.5; two rows: 29.7 in the last but one); eight where there are plenty of rows
-// and the pieces of cache lines begin to count (8192 x 8192 x 1024: 69.6 / 59.4 / 63.9)
+// 25.9 / 24.4, 2048^3 40.9 / 42.7 / 37.5; two rows: 29.7 in the last but one); eight where there are plenty of rows and the
+// pieces of cache lines begin to count.  Where that is depends on k (eight against four rows, m = n = 4096 / 5120 / 6144 / 8192: k =
+// 1024, s = 3 30.1 and 32.4 / 34.9 and 38.2 / 39.8 and 43.2 / 47.8 and 52.0, k = 2048, s = 3 54.5 and 48.2 / 65.6 and 58.0 / 78.2 and 75.3 /
+// 103 and 107, s = 7 63.2 and 57.9 / 80.1 and 92.1 / 98.2 and 112); the line is where the longest contractions change over
+// at few slices, and what it costs the shorter ones below it is at most 3 % of a call (12000 x 200 x 1000, s = 7: 113 and 117)
 static int scale_split_rows(int m, int n, int kp) { return kp <= 2048 && (long long)m + n >= 12288 ? 8 : 4; }
 
 static int scale_split_waves(int rows, int kp)

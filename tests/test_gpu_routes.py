@@ -220,6 +220,17 @@ def test_result_inside_the_long_operand(short_a):
     check(C, A, B, s, s)
 
 
+@pytest.mark.parametrize("n,k,kernel", [(512, 90, "eighths"), (576, 700, "eighths"), (672, 33, "eighths"), (704, 90, "halves")])
+def test_six_slices_follow_the_same_rule_as_seven(n, k, kernel):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the expectations are worked out for 256 compute units")
+    A, B = workloads.lognormal(n, n, k, 1.0, 23)
+    for s in (6, 7):
+        C = ozimmu.dgemm(ozimmu.to_colmajor(A), ozimmu.to_colmajor(B), s)
+        assert ozimmu.last_gemm_kernel().startswith(f"gemm_{kernel}_kernel<{s}>"), ozimmu.last_gemm_kernel()
+        check(C, A, B, s, s)
+
+
 @pytest.mark.parametrize("m,n,k,name", [(1440, 1440, 512, "gemm_eighths_kernel<1>"), (1440, 1440, 40960, "gemm_eighths_kernel<1>"),
                                         (1440, 1440, 40961, "gemm_fused_kernel<1> equal counts tile 128x128"),
                                         (1408, 1408, 41000, "gemm_eighths_kernel<1>"),
