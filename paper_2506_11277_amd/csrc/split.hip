@@ -2,15 +2,16 @@
 // (bit-splitting-alg) in its bit-level reading: slice l holds bits (l-1)t+1 .. lt of
 // |x| / 2^e after the binary point, and carries the sign of x).
 //
+// The kernels of the MFMA layout take four entries at a time through windows of nine (eight) slices formed with exact
+// binary64 operations (slice_dev.h).  The plain layout, a utility, is cut entry by entry in integers:
 // |x| = I * 2^q with I the integer significand, so  floor(|x| 2^{lt - e}) mod 2^t  is a
-// shift of I by (e - q - lt) places and a mask: integer work only, exact.
+// shift of I by (e - q - lt) places and a mask.
 //
 // Round-to-nearest variant (second tweak of the "Enhanced algorithm" paragraph of Sect. 3): the block
 // scale is 2^{e+1}, and with R_l = the integer nearest to |x| 2^{7l - e - 1} (ties to even) slice l is
 // sign(x) (R_l - 128 R_{l-1}), a value in [-64, 64].  R_l = floor(.) + c_l with the round-up decision
 //     c_l = guard & (sticky | lsb)
-// read off the bits of I below the cut, so  slice l = field_l + c_l - 128 c_{l-1}:  still shifts and
-// masks only; c_l is carried from one slice to the next.
+// on the bits below the cut, so  slice l = field_l + c_l - 128 c_{l-1};  c_l is carried from one slice to the next.
 //
 // The MFMA layout written here is the one the GEMM kernel reads (see include/ozimmu.h):
 // fragments of 32 (R) x 32 (K) bytes, 16 contiguous K-bytes per wavefront lane.
