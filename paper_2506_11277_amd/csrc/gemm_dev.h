@@ -9,6 +9,16 @@ namespace oz {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
+// f(integral_constant<int, I>) for I = B, ..., E - 1
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
+    }
+}
+
 // kPlain: whole contraction in int32.  kDump: as kPlain but write the int32 diagonal sums (test hook).
 // kBlocked: one work-group per (tile, k-block), diagonal sums added into int64 totals with atomics.
 enum FusedMode { kPlain = 0, kDump = 1, kBlocked = 2 };

@@ -31,22 +31,11 @@
 // more slices per entry (Window16 in gemm_dev.h; blockIdx.z picks one of up to 16 windows) and adds its int32
 // diagonal sums to shared int64 totals at a diagonal offset (launch_fused16_windows; the plan is in gemm.hip,
 // launch_gemm_blocks).
-#include <type_traits>
-
 #include "gemm_dev.h"
 
 namespace oz {
 
 namespace {
-
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 
 // Compile-time schedule of a stage of the 16x16x64 kernel: the matrix instructions are numbered in execution order
 // (slices of A from the last to the first, within a slice the slices of B upwards -- downwards for slice 0 --, MPP

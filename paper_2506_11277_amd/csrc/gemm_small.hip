@@ -7,22 +7,11 @@
 // an operand.  Here a 64 x 64 tile is worked on by eight wavefronts, two per SIMD: four take the even 32-deep
 // k-blocks, four the odd ones, and the two int32 halves of every diagonal sum are added in LDS at the end (exact, so
 // the result is the same bit for bit).  Smaller problems still use 32 x 32 tiles, each wavefront a k-block in eight.
-#include <type_traits>
-
 #include "gemm_dev.h"
 
 namespace oz {
 
 namespace {
-
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 
 // ---- tile 64 x 64, 2 x 2 x 2 wavefronts (m, n, k), operands staged through LDS -----------------------------------
 // A stage is two 32-deep k-blocks of the four fragment rows; ring of three stages where they fit the LDS, else two.

@@ -17,23 +17,12 @@
 // every second step, and the window formed with integer shifts, changed nothing.
 // Few tiles are compensated by several parts of k; each part leaves its int32 sums in a slot of its own (in the room
 // the general path keeps the long operand's planes in) and a second kernel adds them.
-#include <type_traits>
-
 #include "gemm_dev.h"
 #include "slice_dev.h"
 
 namespace oz {
 
 namespace {
-
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 
 constexpr int kZeroScale = 4096;        // exponent at which every finite number has zero slices only
 
