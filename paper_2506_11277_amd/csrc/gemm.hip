@@ -426,9 +426,9 @@ __global__ __launch_bounds__(64 * WVM * WVN) void gemm_fused_kernel(const int8_t
             for (int a = 0; a < NA; ++a) dump[(size_t)a * m * n + mi + (size_t)nj * m] = d[a];
         });
     } else
-        epilogue_variant<NA>(Q, stream_c(C, ldc), [&](auto PLAIN, auto STREAM) {
+        epilogue_variant<NA>(Q, stream_c(C, ldc), [&](auto ORDER, auto STREAM) {
             entries([&](const int (&d)[NA], int mi, int nj, int ea) {
-                store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<NA, PLAIN.value>(d, Q), ea + eB[nj]), STREAM);
+                store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<NA, ORDER.value>(d, Q), ea + eB[nj]), STREAM);
             });
         });
 }

@@ -186,11 +186,12 @@ __device__ __forceinline__ void store_c(double *p, double v, bool stream)
 
 // LevelSum over the int32 diagonal sums d[0], ..., d[S - 1] of one entry (diagonals 2, ..., S + 1).  Plain diagonal
 // order (Q = 1) in one conversion and one fused multiply-add per diagonal: the product with a power of two is exact,
-// so the only rounding is that of the addition, as in LevelSum, which takes about nine instructions.  (PLAIN: Q is 1.)
-template <int S, bool PLAIN = false>
+// so the only rounding is that of the addition, as in LevelSum, which takes about nine instructions.
+enum Order { kAnyOrder, kPlainOrder, kLevels };            // Q not known, 1, more than 1
+template <int S, int ORDER = kAnyOrder>
 __device__ __forceinline__ double diagonal_sum(const int (&d)[S], int Q)
 {
-    if (PLAIN || Q == 1) {
+    if (ORDER == kPlainOrder || (ORDER == kAnyOrder && Q == 1)) {
         double s = 0.0;
 #pragma unroll
         for (int a = 0; a < S; ++a) s = __builtin_fma((double)d[a], __builtin_ldexp(1.0, -kSliceBits * (a + 2)), s);
@@ -202,18 +203,24 @@ __device__ __forceinline__ double diagonal_sum(const int (&d)[S], int Q)
     return sum.S;
 }
 
-// Runs f(plain order?, streaming stores?) with what is decided once for the work-group as compile-time constants: the
-// entries of a lane (64 of them in the larger tiles) then decide nothing.  30000 x 30000 x 512, s = 2: GEMM 2358 us with
-// two branches per entry, 2251 us so.  Levels of several diagonals share a copy, whose stores are chosen per entry; so do
-// all entries from 17 diagonals on, where the accumulators leave no registers for it (one to eight spilled ones otherwise)
-// and the epilogue counts least.
+// Runs f(order, streaming stores?) with both as compile-time constants, decided once for the work-group: the entries of a
+// lane (64 of them in the larger tiles) then decide nothing (30000 x 30000 x 512, s = 2: GEMM 2358 us with two branches per
+// entry, 2251 us so; levels of two or three, 4096 x 4096 x 512, s = 5 and 9: calls 152 -> 145 and 347 -> 343).  From 17 diagonals on
+// every entry decides for itself: the accumulators leave no registers for several copies (one to nine spilled ones,
+// 4096 x 4096 x 512, s = 19: 1219 us against 1176), and the epilogue counts least there.
 template <int DIAGONALS, class F>
 __device__ __forceinline__ void epilogue_variant(int Q, bool stream, F &&f)
 {
-    if constexpr (DIAGONALS >= 17) f(std::false_type{}, stream);
-    else if (Q != 1) f(std::false_type{}, stream);
-    else if (stream) f(std::true_type{}, std::true_type{});
-    else f(std::true_type{}, std::false_type{});
+    using plain = std::integral_constant<int, kPlainOrder>;
+    using levels = std::integral_constant<int, kLevels>;
+    if constexpr (DIAGONALS >= 17) f(std::integral_constant<int, kAnyOrder>{}, stream);
+    else if (Q == 1) {
+        if (stream) f(plain{}, std::true_type{});
+        else f(plain{}, std::false_type{});
+    } else {
+        if (stream) f(levels{}, std::true_type{});
+        else f(levels{}, std::false_type{});
+    }
 }
 
 }  // namespace oz

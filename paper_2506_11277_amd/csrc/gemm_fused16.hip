@@ -480,9 +480,9 @@ __global__ __launch_bounds__((64 * Cfg16<S, ALT>::WVM * Cfg16<S, ALT>::WVN)) voi
             for (int a = 0; a < S; ++a) dump[(size_t)a * m * n + mi + (size_t)nj * m] = d[a];
         });
     } else
-        epilogue_variant<S>(Q, stream_c(C, ldc), [&](auto PLAIN, auto STREAM) {
+        epilogue_variant<S>(Q, stream_c(C, ldc), [&](auto ORDER, auto STREAM) {
             entries([&](const int (&d)[S], int mi, int nj, int ea) {
-                store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S, PLAIN.value>(d, Q), ea + eB[nj]), STREAM);
+                store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S, ORDER.value>(d, Q), ea + eB[nj]), STREAM);
             });
         });
 }
