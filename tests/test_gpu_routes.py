@@ -256,11 +256,16 @@ def test_hooks_refuse_planes_that_a_call_has_not_left(m, n):
     dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
     ws = torch.empty(max(ozimmu.workspace_bytes(m, n, kk, s) for kk in (k, 100)), dtype=torch.uint8, device="cuda")
 
+    def code(hook):              # (no exception is kept: its frames would keep the tensors)
+        try:
+            hook()
+        except ozimmu.OzimmuError as error:
+            return error.code
+        return ozimmu.OK
+
     def refused():
-        for hook in (lambda: ozimmu.debug_diagonals(m, n, k, s, ws), lambda: ozimmu.debug_slice_product(m, n, k, s, ws, 1, 2)):
-            with pytest.raises(ozimmu.OzimmuError) as info:
-                hook()
-            assert info.value.code == ozimmu.BAD_ARG
+        assert code(lambda: ozimmu.debug_diagonals(m, n, k, s, ws)) == ozimmu.BAD_ARG
+        assert code(lambda: ozimmu.debug_slice_product(m, n, k, s, ws, 1, 2)) == ozimmu.BAD_ARG
 
     C = ozimmu.dgemm(dA, dB, s, workspace=ws)
     assert ozimmu.last_gemm_kernel().startswith("gemm_vectors_kernel")
