@@ -281,7 +281,14 @@ static int dgemm_impl(int m, int n, int k, const double *A, int lda, const doubl
     }
     prof_mark(prof, 2, st);
     const int cA = w.cA, cB = w.cB;
-    if (w.path == kPathBlocks) {
+    // 10 ... 20 slices whose contraction is one int32 block: diagonals in passes, where that is the faster way (blocks, whose
+    // planes may hold more slices per entry: equal counts only, different ones have fewer products)
+    const bool triangle = cA == cB && !all_products && (w.path == kPathFused || (w.path == kPathBlocks && sA == sB));
+    const int S = w.path == kPathBlocks ? sA : cA;
+    const PassShape shape = triangle && fused_automatic() && fused_single_block(S, S, k) ? gemm_passes_shape(S, m, n, w.kp, Q) : kNoPasses;
+    if (shape != kNoPasses) {
+        OZ_TRY(launch_gemm_passes(shape, S, m, n, w.kp, cA, pA, pB, eA, eB, C, ldc, Q, st));
+    } else if (w.path == kPathBlocks) {
         OZ_TRY(launch_gemm_blocks(m, n, w.kp, sA, sB, all_products, pA, pB, eA, eB, C, ldc,
                                   (long long *)(ws + w.off_totals), Q, st));
     } else if (w.path == kPathFused) {

@@ -147,6 +147,15 @@ __device__ __forceinline__ void wait_vmcnt()
 
 constexpr int kLdsBytes = 160 * 1024;
 
+// diagonals of the passes before pass p
+template <int NP>
+constexpr int diagonals_before(const int (&w)[NP], int p)
+{
+    int s = 0;
+    for (int q = 0; q < p; ++q) s += w[q];
+    return s;
+}
+
 // Binary64 accumulation of the scaled diagonal sums 2^{-7d} D_d, d ascending, in levels of Q
 // consecutive diagonals (subsection "Accumulation in floating-point arithmetic" of Sect. 4): the
 // terms of a level are added to each other first, then the level to S.  The host admits only Q for

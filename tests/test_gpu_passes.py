@@ -1,0 +1,63 @@
+"""10 ... 20 slices with the diagonals in passes (unsteered), bit for bit: a sample of rows and columns against the oracle,
+every entry against the one-pass kernels that the test knob puts in their place."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2506_11277_amd import ozimmu, workloads
+from tests.test_gpu_routes import check, special
+
+
+def steered(f):
+    try:
+        ozimmu.debug_small_tile_limit(256)
+        return f()
+    finally:
+        ozimmu.debug_small_tile_limit(-1)
+
+
+def both_ways(A, B, sA, sB, name, **kw):
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    run = lambda: ozimmu.dgemm3(dA, dB, sA, sB, **kw)
+    C = run()
+    if name and torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert ozimmu.last_gemm_kernel().startswith(name), ozimmu.last_gemm_kernel()
+    want = steered(run)
+    assert "passes" not in ozimmu.last_gemm_kernel()
+    assert torch.equal(C.view(torch.int64), want.view(torch.int64))
+    check(C, A, B, sA, sB, nearest=kw.get("splitting") == ozimmu.SPLIT_NEAREST, Q=kw.get("level_diagonals", 1))
+
+
+# 128 x 64 tiles: one partly filled round, ragged edges; 64 x 64 tiles: a second work-group on some compute units, edges; two
+# k-steps, an odd number of k-steps of 64, many
+@pytest.mark.parametrize("s", range(10, 21))
+@pytest.mark.parametrize("m,n,k,tile", [(1025, 1153, 1030, "128x64"), (2050, 2020, 1100, "64x64"), (1030, 1400, 65, "64x64"),
+                                        (2300, 4600, 40, "64x64"), (80, 20000, 400, "64x64")])
+def test_passes_through_lds(m, n, k, tile, s):
+    A, B = workloads.lognormal(m, n, k, 1.0, 70 + s)
+    special(A, B)
+    name = f"gemm_passes_kernel<{s}> tile {tile}" if s > 12 or k > 384 else ""
+    both_ways(A, B, s, s, name)
+    both_ways(A, B, s, s, name, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=3)
+
+
+# levels that would straddle two passes take the one-pass kernels; counts that differ little run as equal ones
+@pytest.mark.parametrize("sA,sB,Q", [(13, 13, 2), (13, 13, 4), (16, 16, 2), (12, 13, 1), (18, 17, 3), (20, 19, 1), (10, 14, 1)])
+def test_levels_and_different_counts(sA, sB, Q):
+    A, B = workloads.lognormal(1100, 1090, 300, 1.0, 5)
+    both_ways(A, B, sA, sB, "", level_diagonals=Q)
+
+
+def test_leading_dimensions_and_odd_alignment():
+    m, n, k, s = 1101, 1091, 1100, 14
+    A, B = workloads.lognormal(m, n, k, 1.0, 9)
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    big = ozimmu.colmajor_empty(m + 5, n + 2).fill_(7.0)
+    C = big[3:m + 3, 1:n + 1]
+    ozimmu.dgemm(dA, dB, s, C=C)
+    assert "passes" in ozimmu.last_gemm_kernel()
+    assert torch.equal(C, steered(lambda: ozimmu.dgemm(dA, dB, s)))
+    assert (big[:3] == 7).all() and (big[m + 3:] == 7).all() and (big[:, 0] == 7).all() and (big[:, -1] == 7).all()
