@@ -175,10 +175,11 @@ __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restr
                                                            int tiles_m, int tiles_n, int Q)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    // (four 32 x 32 tiles of a 64 x 64 one after the other; quarters beyond the edge have nothing to do)
-    const int quarter = blockIdx.x & 3, t64 = blockIdx.x >> 2, tiles64_m = (tiles_m + 1) / 2;
-    const int tm = (t64 % tiles64_m) * 2 + (quarter & 1), tn = (t64 / tiles64_m) * 2 + (quarter >> 1);
-    if (tm >= tiles_m || tn >= tiles_n) return;
+    // (equal runs of tiles to the XCDs.  Four tiles of a 64 x 64 one after the other, with nothing to do for those beyond the
+    // edge, gave some XCDs half as many tiles again where a side has an odd number of them: 130 x 1500 x 3000, s = 3 / 7 20.2 / 44.1 us,
+    // now 12.9 / 25.1; 32 x 6000 x 200, s = 7 14.2, now 9.0)
+    int tm, tn;
+    tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t row_bytes = (size_t)KB * (S * kFragBytes);
@@ -269,7 +270,7 @@ hipError_t launch_eighths(int m, int n, int kp, const int8_t *pA, const int8_t *
     if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgEighths<S>::LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
     note_gemm_kernel("gemm_eighths_kernel<%d> tile 32x32, 8 wavefronts, k in eighths", S);
-    kern<<<4u * ((tiles_m + 1) / 2) * ((tiles_n + 1) / 2), 512, CfgEighths<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, Q);
+    kern<<<(unsigned)(tiles_m * tiles_n), 512, CfgEighths<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, Q);
     return hipGetLastError();
 }
 
