@@ -1,5 +1,5 @@
 // Slice products in passes over groups of diagonals: which shape runs, and the launch (kernels: gemm_passes_dev.h, instantiated
-// in gemm_passes_10.hip ... gemm_passes_19.hip).
+// in gemm_passes_10.hip ... gemm_passes_19.hip; 32 x 32 tiles: gemm_small.hip).
 #include "oz_common.h"
 
 namespace oz {
@@ -12,8 +12,12 @@ OZ_DECLARE(18) OZ_DECLARE(19) OZ_DECLARE(20)
 #undef OZ_DECLARE
 
 // Which shape, if any (GEMM phases in us, s = 11 / 13 / 16 / 18).
-// Up to one 64 x 64 tile per compute unit the one-pass kernels on that tile with 512 registers to a wavefront, up to 16
-// slices (800^3: 40.6 / 54.8 / 75.1 / 102, in passes 49.8 / 65.2 / 83.2 / 95.0).
+// Up to one tile of 32 x 32 per compute unit, and up to 1.75 where the products repay a second round: these, k in eighths
+// (402^3 before 25.7 / 33.9 / 44.7 / 62.8, now 16.1 / 18.8 / 23.0 / 26.0; 1.64 tiles: 600 x 700 x 384 21.8 / 28.0 / 36.1 / 49.1, 23.6 / 28.1 / 34.6 / 40.4,
+// 600 x 700 x 188 17.6 / 21.8 / 27.1 / 36.5, 20.8 / 23.9 / 28.5 / 33.0; 800^3, 2.4 tiles, 40.6 / 54.8 / 75.1 / 102, 53.1 / 66.2 / 84.7 / 100;
+// 10 slices have a kernel of one pass there).
+// Then, up to one 64 x 64 tile per compute unit, the one-pass kernels on that tile with 512 registers to a wavefront up to 16
+// slices (800^3: against 49.8 / 65.2 / 83.2 in passes; 18: 95.0).
 // Up to 12 slices the fixed costs of two passes are only repaid by several rounds or a longer k (s = 11, one-pass kernel against
 // passes: 1000 x 1100 x 500 39.7 / 46.3, 1038 x 2512 x 66 33.5 / 36.3, but 1300^3 119 / 114, 3000 x 3000 x 500 234 / 219).
 // 128 x 64 or 64 x 64 by rounds of the chip: two 64 x 64 tiles at a time cost a compute unit 1.04 of a 128 x 64 one, a single one 0.7;
@@ -24,7 +28,9 @@ PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
     if (s < 10 || s > 20 || m <= 0 || n <= 0) return kNoPasses;
     const int cus = device_cus();
     auto tiles = [&](int tm, int tn) { return (long long)((m + tm - 1) / tm) * ((n + tn - 1) / tn); };
-    if (4 * tiles(32, 32) <= 7LL * cus) return kNoPasses;
+    const long long tiny = tiles(32, 32);
+    if (4 * tiny <= 7LL * cus && s == 10) return kNoPasses;
+    if (tiny <= cus || (4 * tiny <= 7LL * cus && (s >= 17 ? kp >= 256 : s * kp >= 6144))) return kPassEighths;
     const PassPlan P = pass_plan(s);
     for (int p = 0, d = 0; p + 1 < P.n; ++p)
         if ((d += P.w[p]) % Q != 0) return kNoPasses;                // a level of Q diagonals straddles two passes
@@ -43,6 +49,7 @@ hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int 
 {
     if (m <= 0 || n <= 0) return hipSuccess;
     if (shape == kNoPasses || stride < s) return hipErrorInvalidValue;
+    if (shape == kPassEighths) return launch_gemm_eighths_passes(s, m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
     const bool small = shape == kPassSmall;
     switch (s) {
 #define OZ_CASE(S_) case S_: return launch_gemm_passes_##S_(small, m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);

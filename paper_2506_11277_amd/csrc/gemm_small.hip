@@ -247,6 +247,112 @@ __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restr
     }
 }
 
+// ---- the same tile for 11 ... 20 slices, whose diagonal sums do not fit the registers together: passes over groups of Ws
+// diagonals, in ascending order, as in gemm_passes_dev.h --------------------------------------------------------------------
+// A pass over the diagonals up to SN + 1 takes the slices 1 ... SN; step i of a k-block brings slice SN - i of A and slice
+// i + 1 of B, and meets the last W slices of B: product j of it belongs to the pass's j-th diagonal from the end.  Operands
+// are loaded AHEAD steps before their use.  The sums of a pass meet in LDS as above, and every wavefront adds them to
+// its two entries, in registers, before the next pass.  What bounds it: operands out of the L2s, 36 to 50 bytes per clock and compute
+// unit where all are busy.  GEMM, us, s = 11 / 13 / 18, one-pass 64 x 64 tiles before -> now: 500 x 384 x 512 25.3 / 34.0 / 62.0 -> 15.9 /
+// 19.0 / 26.9, 300 x 500 x 1000 41.9 / 58.4 / 114 -> 22.4 / 27.2 / 40.4, 130 x 1500 x 3000 109 / 159 / 320 -> 50.7 / 63.6 / 103.
+template <int... Ws>
+__global__ __launch_bounds__(512) void gemm_eighths_passes_kernel(
+    const int8_t *__restrict__ pA, const int8_t *__restrict__ pB, const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
+    double *__restrict__ C, int ldc, int m, int n, int KB, int stride, int tiles_m, int tiles_n, int Q)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    // (equal runs of tiles to the XCDs)
+    int tm, tn;
+    tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    const unsigned lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t kb_bytes = (size_t)stride * kFragBytes, row_bytes = (size_t)KB * kb_bytes;
+    constexpr int NP = sizeof...(Ws), ROUND = 4, AHEAD = 4;
+    constexpr int WS[NP] = {Ws...};
+    LevelSum sum[2];
+    static_for<0, NP>([&](auto PP) {
+        constexpr int p = decltype(PP)::value, W = WS[p], BEFORE = diagonals_before<NP>(WS, p), SN = BEFORE + W;
+        constexpr int AH = AHEAD < SN ? AHEAD : SN;
+        v16i acc[W];
+#pragma unroll
+        for (int a = 0; a < W; ++a)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][r] = 0;
+        if (wave < KB) {
+            const v4i *a = (const v4i *)(pA + (size_t)tm * row_bytes + (size_t)wave * kb_bytes);
+            const v4i *b = (const v4i *)(pB + (size_t)tn * row_bytes + (size_t)wave * kb_bytes);
+            v4i af[SN], bf[SN];
+            static_for<0, AH>([&](auto I) {
+                constexpr int i = decltype(I)::value;
+                af[i] = (a + (SN - 1 - i) * 64)[lane];
+                bf[i] = (b + i * 64)[lane];
+            });
+            for (int kb = wave; kb < KB; kb += 8) {
+                // (the first steps of the last k-block of a wavefront are loaded once more: nobody uses them)
+                const size_t step = kb + 8 < KB ? (size_t)8 * stride * 64 : 0;
+                const v4i *an = a + step, *bn = b + step;
+                v4i an_[AH], bn_[AH];
+                static_for<0, SN>([&](auto I) {
+                    constexpr int i = decltype(I)::value, used = i + 1 < W ? i + 1 : W;
+                    if constexpr (i + AH < SN) {
+                        af[i + AH] = (a + (SN - 1 - i - AH) * 64)[lane];
+                        bf[i + AH] = (b + (i + AH) * 64)[lane];
+                    } else {
+                        an_[i + AH - SN] = (an + (SN - 1 - (i + AH - SN)) * 64)[lane];
+                        bn_[i + AH - SN] = (bn + (i + AH - SN) * 64)[lane];
+                    }
+                    static_for<0, used>([&](auto J) {
+                        constexpr int j = used - 1 - decltype(J)::value;
+                        acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[i - j], af[i], acc[j], 0, 0, 0);
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                a = an;
+                b = bn;
+#pragma unroll
+                for (int i = 0; i < AH; ++i) {
+                    af[i] = an_[i];
+                    bf[i] = bn_[i];
+                }
+            }
+        }
+        typedef int v2i __attribute__((ext_vector_type(2)));
+        v2i *x = (v2i *)lds;
+        static_for<0, (W + ROUND - 1) / ROUND>([&](auto P) {
+            constexpr int a0 = decltype(P)::value * ROUND, a1 = a0 + ROUND < W ? a0 + ROUND : W;
+            if constexpr (a0 > 0 || p > 0) __syncthreads();
+#pragma unroll
+            for (int a = a0; a < a1; ++a)
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+                    x[(((a - a0) * 8 + r) * 8 + wave) * 64 + lane] = v2i{acc[W - 1 - a][2 * r], acc[W - 1 - a][2 * r + 1]};
+            __syncthreads();
+#pragma unroll
+            for (int a = a0; a < a1; ++a) {
+                v2i s{0, 0};
+#pragma unroll
+                for (int w = 0; w < 8; ++w) s += x[(((a - a0) * 8 + wave) * 8 + w) * 64 + lane];
+                const double unit = __builtin_ldexp(1.0, -kSliceBits * (BEFORE + a + 2));
+#pragma unroll
+                for (int r = 0; r < 2; ++r) sum[r].add((double)s[r] * unit, Q, p + 1 == NP && a == W - 1);
+            }
+        });
+        // (the sums are formed before the next pass: left to itself the compiler keeps their terms until after it)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) asm volatile("" : "+v"(sum[r].S), "+v"(sum[r].L));
+    });
+    const int mi = tm * 32 + (lane & 31);
+    if (mi >= m) return;
+    const bool stream = stream_c(C, ldc);
+    const int ea = eA[mi];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int rr = 2 * wave + r;
+        const int nj = tn * 32 + 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
+        if (nj < n) store_c(&C[mi + (size_t)nj * ldc], ldexp(sum[r].S, ea + eB[nj]), stream);
+    }
+}
+
 template <int S>
 hipError_t launch_halves(int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA, const int32_t *eB,
                          double *C, int ldc, int Q, hipStream_t st)
@@ -274,7 +380,42 @@ hipError_t launch_eighths(int m, int n, int kp, const int8_t *pA, const int8_t *
     return hipGetLastError();
 }
 
+template <int... Ws>
+hipError_t launch_eighths_passes(int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, const int32_t *eA, const int32_t *eB,
+                                 double *C, int ldc, int Q, hipStream_t st)
+{
+    auto kern = gemm_eighths_passes_kernel<Ws...>;
+    static std::atomic<unsigned long long> configured{0};
+    constexpr int LDS = 4 * 8 * 8 * 64 * 8;
+    if (hipError_t e = allow_dynamic_lds((const void *)kern, LDS, configured); e != hipSuccess) return e;
+    const int tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
+    note_gemm_kernel("gemm_eighths_passes_kernel<%d> tile 32x32, 8 wavefronts, k in eighths", (Ws + ...));
+    kern<<<(unsigned)(tiles_m * tiles_n), 512, LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride, tiles_m, tiles_n, Q);
+    return hipGetLastError();
+}
+
+template <int S>
+hipError_t launch_eighths_plan(int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, const int32_t *eA,
+                               const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
+{
+    constexpr PassPlan P = pass_plan(S);
+    if constexpr (P.n == 2) return launch_eighths_passes<P.w[0], P.w[1]>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
+    else return launch_eighths_passes<P.w[0], P.w[1], P.w[2]>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
+}
+
 }  // namespace
+
+hipError_t launch_gemm_eighths_passes(int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, const int32_t *eA,
+                                      const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
+{
+    if (m <= 0 || n <= 0) return hipSuccess;
+    switch (s) {
+#define OZ_CASE(S_) case S_: return launch_eighths_plan<S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
+        OZ_CASE(11) OZ_CASE(12) OZ_CASE(13) OZ_CASE(14) OZ_CASE(15) OZ_CASE(16) OZ_CASE(17) OZ_CASE(18) OZ_CASE(19) OZ_CASE(20)
+#undef OZ_CASE
+    }
+    return hipErrorInvalidValue;
+}
 
 hipError_t launch_gemm_halves(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                               const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)

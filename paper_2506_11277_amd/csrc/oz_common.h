@@ -283,7 +283,7 @@ bool fused_automatic();
 hipError_t launch_gemm_blocks(int m, int n, int kp, int sA, int sB, bool all_products, const int8_t *pA,
                               const int8_t *pB, const int32_t *eA, const int32_t *eB, double *C, int ldc,
                               long long *totals, int Q, hipStream_t st);
-// Equal counts 10 ... 20, whole contraction in int32, diagonals in passes (gemm_passes_dev.h).
+// Equal counts 10 ... 20, whole contraction in int32, diagonals in passes (gemm_passes_dev.h; 32 x 32 tiles: gemm_small.hip).
 // Widths of the passes: at most nine diagonals (accumulator registers), the first one small (what is moved goes with the
 // sum of the pass ends) and a multiple of three (levels of three diagonals).  128 x 64 tile at 2500 x 2400 x 2500, us: 10 as (3, 7) / (2, 8) /
 // (5, 5) 531 / 528 / 548, 12 as (3, 9) / (4, 8) / (6, 6) 695 / 708 / 723, 13 as (6, 7) / (4, 9) 806 / 800, 14 as (6, 8) / (5, 9)
@@ -300,11 +300,13 @@ constexpr PassPlan pass_plan(int s)
            : s <= 18 ? PassPlan{2, {9, s - 9, 0}}
                      : PassPlan{3, {3, 9, s - 12}};
 }
-enum PassShape { kNoPasses, kPassSmall, kPassWide };
+enum PassShape { kNoPasses, kPassEighths, kPassSmall, kPassWide };
 PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q);
 // (stride: slices per entry in the planes, at least s; shape from gemm_passes_shape)
 hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,
                               const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
+hipError_t launch_gemm_eighths_passes(int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, const int32_t *eA,
+                                      const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
 // general product band (any sA, sB, any k); totals: scratch of banded_totals_bytes() or null when that is 0
 hipError_t launch_gemm_banded(int m, int n, int kp, int sA, int sB, int dmax, const int8_t *pA, const int8_t *pB,
                               const int32_t *eA, const int32_t *eB, double *C, int ldc, long long *totals,

@@ -44,6 +44,20 @@ def test_passes_through_lds(m, n, k, tile, s):
     both_ways(A, B, s, s, name, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=3)
 
 
+# 32 x 32 tiles, k in eighths: fewer k-blocks than wavefronts, one more than a round of them, edges of tiles, the ends of the rule; any
+# level size
+@pytest.mark.parametrize("s", range(11, 21))
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (33, 31, 130), (97, 70, 289), (512, 512, 64), (512, 896, 560), (40, 1000, 1100), (31, 65, 6657)])
+def test_passes_of_a_divided_contraction(m, n, k, s):
+    A, B = workloads.lognormal(m, n, k, 1.0, 90 + s)
+    if m > 4:
+        special(A, B)
+    name = f"gemm_eighths_passes_kernel<{s}>"
+    both_ways(A, B, s, s, name)
+    for Q in (2, 3):
+        both_ways(A, B, s, s, name, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=Q)
+
+
 # levels that would straddle two passes take the one-pass kernels; counts that differ little run as equal ones
 @pytest.mark.parametrize("sA,sB,Q", [(13, 13, 2), (13, 13, 4), (16, 16, 2), (12, 13, 1), (18, 17, 3), (20, 19, 1), (10, 14, 1)])
 def test_levels_and_different_counts(sA, sB, Q):
