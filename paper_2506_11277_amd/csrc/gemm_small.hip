@@ -162,6 +162,23 @@ __global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restri
 // takes the k-blocks w, w + 8, ...; row l of the products frees slice l of A and slice S - 1 - l of B, which are
 // loaded again for its next k-block at once.  The eight sums per output meet in LDS, kRound diagonals at a time;
 // wavefront w finishes accumulator registers 2 w and 2 w + 1.
+// Tile of a work-group: equal runs of tiles to the XCDs, in strips of four tile rows.  (Four tiles of a 64 x 64 one after the
+// other, with nothing to do for those beyond the edge, gave some XCDs half as many tiles again where a side has an odd number of
+// them: 130 x 1500 x 3000, s = 3 / 7 20.2 / 44.1 us, now 12.9 / 25.1; 32 x 6000 x 200, s = 7 14.2, now 9.0.)  The tile's place is on the way to the
+// first load: one multiplication with magic = ceil(2^32 / (4 tiles_n)) in place of the three divisions of tile_of_block(), which
+// take 0.2 us of 12 (exact while the number of tiles times 4 tiles_n is below 2^32: some thousand tiles at most come here).
+__device__ __forceinline__ void tile_in_strips(unsigned b, int tiles_m, int tiles_n, unsigned magic, int &tm, int &tn)
+{
+    const unsigned nb = (unsigned)(tiles_m * tiles_n), xcd = b & 7, rem = nb & 7;
+    const unsigned lin = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (b >> 3);
+    const unsigned strip = __umulhi(lin, magic), in = lin - strip * (4u * tiles_n);
+    const unsigned left = tiles_m - 4 * strip;                // rows of this strip, if fewer than four
+    const unsigned c = left >= 4 ? in >> 2 : left == 3 ? in / 3u : left == 2 ? in >> 1 : in;
+    tn = (int)c;
+    tm = (int)(4 * strip + in - c * (left >= 4 ? 4u : left));
+}
+inline unsigned strip_magic(int tiles_n) { return (unsigned)(((1ULL << 32) + 4ULL * tiles_n - 1) / (4ULL * tiles_n)); }
+
 template <int S>
 struct CfgEighths {
     static constexpr int ROUND = S == 1 ? 1 : S <= 5 ? 2 : 4;             // diagonals per round: 32 KiB of LDS each
@@ -172,14 +189,11 @@ template <int S>
 __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restrict__ pA, const int8_t *__restrict__ pB,
                                                            const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
                                                            double *__restrict__ C, int ldc, int m, int n, int KB,
-                                                           int tiles_m, int tiles_n, int Q)
+                                                           int tiles_m, int tiles_n, unsigned magic, int Q)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    // (equal runs of tiles to the XCDs.  Four tiles of a 64 x 64 one after the other, with nothing to do for those beyond the
-    // edge, gave some XCDs half as many tiles again where a side has an odd number of them: 130 x 1500 x 3000, s = 3 / 7 20.2 / 44.1 us,
-    // now 12.9 / 25.1; 32 x 6000 x 200, s = 7 14.2, now 9.0)
     int tm, tn;
-    tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    tile_in_strips(blockIdx.x, tiles_m, tiles_n, magic, tm, tn);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t row_bytes = (size_t)KB * (S * kFragBytes);
@@ -258,12 +272,12 @@ __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restr
 template <int... Ws>
 __global__ __launch_bounds__(512) void gemm_eighths_passes_kernel(
     const int8_t *__restrict__ pA, const int8_t *__restrict__ pB, const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
-    double *__restrict__ C, int ldc, int m, int n, int KB, int stride, int tiles_m, int tiles_n, int Q)
+    double *__restrict__ C, int ldc, int m, int n, int KB, int stride, int tiles_m, int tiles_n, unsigned magic,
+    int Q)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    // (equal runs of tiles to the XCDs)
     int tm, tn;
-    tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tm, tn);
+    tile_in_strips(blockIdx.x, tiles_m, tiles_n, magic, tm, tn);
     const unsigned lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t kb_bytes = (size_t)stride * kFragBytes, row_bytes = (size_t)KB * kb_bytes;
@@ -376,7 +390,7 @@ hipError_t launch_eighths(int m, int n, int kp, const int8_t *pA, const int8_t *
     if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgEighths<S>::LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
     note_gemm_kernel("gemm_eighths_kernel<%d> tile 32x32, 8 wavefronts, k in eighths", S);
-    kern<<<(unsigned)(tiles_m * tiles_n), 512, CfgEighths<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, Q);
+    kern<<<(unsigned)(tiles_m * tiles_n), 512, CfgEighths<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, strip_magic(tiles_n), Q);
     return hipGetLastError();
 }
 
@@ -390,7 +404,8 @@ hipError_t launch_eighths_passes(int m, int n, int kp, int stride, const int8_t 
     if (hipError_t e = allow_dynamic_lds((const void *)kern, LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
     note_gemm_kernel("gemm_eighths_passes_kernel<%d> tile 32x32, 8 wavefronts, k in eighths", (Ws + ...));
-    kern<<<(unsigned)(tiles_m * tiles_n), 512, LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride, tiles_m, tiles_n, Q);
+    kern<<<(unsigned)(tiles_m * tiles_n), 512, LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride, tiles_m, tiles_n,
+                                                    strip_magic(tiles_n), Q);
     return hipGetLastError();
 }
 
