@@ -1,5 +1,5 @@
 // Slice products in passes over groups of diagonals: which shape runs, and the launch (kernels: gemm_passes_dev.h, instantiated
-// in gemm_passes_10.hip ... gemm_passes_19.hip; 32 x 32 tiles: gemm_small.hip).
+// in gemm_passes_4.hip ... gemm_passes_19.hip; 32 x 32 tiles: gemm_small.hip).
 #include "oz_common.h"
 
 namespace oz {
@@ -7,6 +7,7 @@ namespace oz {
 #define OZ_DECLARE(S_)                                                                                                      \
     hipError_t launch_gemm_passes_##S_(bool small, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,    \
                                        const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
+OZ_DECLARE(4) OZ_DECLARE(5) OZ_DECLARE(6) OZ_DECLARE(7) OZ_DECLARE(8) OZ_DECLARE(9)     // (64 x 64 tiles only)
 OZ_DECLARE(10) OZ_DECLARE(11) OZ_DECLARE(12) OZ_DECLARE(13) OZ_DECLARE(14) OZ_DECLARE(15) OZ_DECLARE(16) OZ_DECLARE(17)
 OZ_DECLARE(18) OZ_DECLARE(19) OZ_DECLARE(20)
 #undef OZ_DECLARE
@@ -20,7 +21,7 @@ OZ_DECLARE(18) OZ_DECLARE(19) OZ_DECLARE(20)
 // slices (800^3: against 49.8 / 65.2 / 83.2 in passes; 18: 95.0).
 // Up to 12 slices the fixed costs of two passes are only repaid by several rounds or a longer k (s = 11, one-pass kernel against
 // passes: 1000 x 1100 x 500 39.7 / 46.3, 1038 x 2512 x 66 33.5 / 36.3, but 1300^3 119 / 114, 3000 x 3000 x 500 234 / 219).
-// 128 x 64 or 64 x 64 by rounds of the chip: two 64 x 64 tiles at a time cost a compute unit 1.04 of a 128 x 64 one, a single one 0.7;
+// 128 x 64 or 64 x 64 by rounds of the chip: two 64 x 64 tiles at a time cost a compute unit 1.04 of a 128 x 64 one (pair_rounds);
 // at short k the 128 x 64 tile also pays for copies and epilogues that nothing hides (2085 x 4740 x 1000, 4.98 against 4.83
 // rounds, s = 13 580 / 584, 18 953 / 940; 3000 x 3000 x 500, 4.41 against 4.31, s = 13 306 / 280; 2207^3, 2.46 against 2.39, 693 / 627).
 PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
@@ -37,11 +38,8 @@ PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
     const long long small = tiles(64, 64), wide = tiles(128, 64);
     if (small <= cus) return s <= 16 ? kNoPasses : kPassSmall;
     if (s <= 12 && !(kp >= 1024 || (kp >= 384 && wide > cus))) return kNoPasses;
-    const long long pairs = small / (2 * cus), rest = small % (2 * cus);
-    const double cost_small = 1.04 * pairs + (rest == 0 ? 0.0 : rest <= cus ? 0.7 : 1.04);
     const double rounds = (double)wide / cus, whole = (double)((wide + cus - 1) / cus);
-    const double cost_wide = (0.8 * whole + 0.2 * rounds) * (1.0 + 64.0 / kp);
-    return cost_small < cost_wide ? kPassSmall : kPassWide;
+    return 1.04 * pair_rounds(small, cus) < (0.8 * whole + 0.2 * rounds) * short_k_cost(kp) ? kPassSmall : kPassWide;
 }
 
 hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,
@@ -53,6 +51,7 @@ hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int 
     const bool small = shape == kPassSmall;
     switch (s) {
 #define OZ_CASE(S_) case S_: return launch_gemm_passes_##S_(small, m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
+        OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9)
         OZ_CASE(10) OZ_CASE(11) OZ_CASE(12) OZ_CASE(13) OZ_CASE(14) OZ_CASE(15) OZ_CASE(16) OZ_CASE(17) OZ_CASE(18) OZ_CASE(19)
         OZ_CASE(20)
 #undef OZ_CASE

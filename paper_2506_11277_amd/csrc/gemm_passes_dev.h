@@ -25,6 +25,8 @@
 //   4096^3                s = 10 3158 -> 3137 / 3072, 13 2932 -> 3479 / 3423, 16 3183 -> 3637 / 3598, 18 3320 -> 4013 / 3648, 20 2979 -> 4114
 //   2500 x 2400 x 2500    s = 10 2988 -> 3147 / 3001, 13 2996 -> 3508 / 3332, 16 3229 -> 3681 / 3653, 18 2943 -> 3842 / 3776
 //   2207^3                s = 10 2565 -> 2562 / 2787, 13 2745 -> 2823 / 3119, 16 2938 -> 3025 / 3390, 18 2527 -> 3174 / 3577
+// 4 ... 9 slices fit one pass; the 64 x 64 tile serves them too where whole rounds of the larger tiles of gemm_fused16_kernel fit
+// badly or k is short (s = 7: 2304 x 2000 x 2560 264 -> 228 us, 3000 x 3000 x 500 107 -> 94; s = 9: 6001 x 5200 x 256 299 -> 251).
 // What bounds it: the board's power cap, as the other large products (register-only loop of the same instruction: 4200 TOP/s).
 #pragma once
 #include "gemm_dev.h"
@@ -170,18 +172,20 @@ struct PassSched : PassBase<SN, W, V, N, D, DB, TARGET, PAIR> {
     static_assert(ordered(), "a read on the wrong side of a synchronisation");
 };
 
-// WVM x WVN wavefronts of 32 x 32 outputs, a ring of at most SLOTS slots
-template <int WVM_, int WVN_, int SLOTS_>
+// KG groups of WVM x WVN wavefronts of 32 x 32 outputs, a ring of at most SLOTS slots to each group; the groups take every
+// KG-th 64-deep k-step of the same tile
+template <int WVM_, int WVN_, int SLOTS_, int KG_ = 1>
 struct PassTile {
-    static constexpr int WVM = WVM_, WVN = WVN_, NW = WVM * WVN, SLOTS = SLOTS_;
-    static constexpr int SLOT = (WVM + WVN) * 2 * kFragBytes, LDS = SLOTS * SLOT;
-    static_assert(LDS <= kLdsBytes, "ring does not fit LDS");
+    static constexpr int WVM = WVM_, WVN = WVN_, NW = WVM * WVN, SLOTS = SLOTS_, KG = KG_, THREADS = 64 * NW * KG;
+    static constexpr int SLOT = (WVM + WVN) * 2 * kFragBytes, GROUP = SLOTS * SLOT, LDS = KG * GROUP;
+    static_assert(LDS <= kLdsBytes, "rings do not fit LDS");
 };
 using PassTileWide = PassTile<4, 2, 13>;       // 128 x 64, 156 KiB
 using PassTileSmall = PassTile<2, 2, 10>;      // 64 x 64, 80 KiB: two work-groups to a compute unit
 // operands are read from LDS this many matrix instructions ahead; products between synchronisations (16 ... 40 products and
-// 6 ... 16 instructions are within 1 % of each other at 13 and 18 slices)
-constexpr int kPassAhead = 8, kPassProducts = 24;
+// 6 ... 16 instructions are within 1 % of each other at 13 and 18 slices,
+// one pass of 8 slices, 64 x 64 tile, 1024 x 1024 x 4096: 104 us with 16, 111 with 24)
+constexpr int kPassAhead = 8, kPassProducts = 24, kPassProductsOne = 16;
 
 // positions of a stage and slots of the ring: whole stages in the ring or two rings in a stage
 template <int SN, int SLOTS>
@@ -200,22 +204,24 @@ constexpr int widest(const int (&w)[NP])
 }
 
 template <class T, int... Ws>
-__global__ __launch_bounds__(64 * T::NW, 2) void gemm_passes_kernel(
-    const int8_t *__restrict__ pA, const int8_t *__restrict__ pB, const int32_t *__restrict__ eA,
-    const int32_t *__restrict__ eB, double *__restrict__ C, int ldc, int m, int n, int KB, int stride, int tiles_m,
-    int tiles_n, int Q)
+__device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, const int8_t *__restrict__ pB,
+                                                 const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
+                                                 double *__restrict__ C, int ldc, int m, int n, int KB, int stride,
+                                                 int tiles_m, int tiles_n, int Q)
 {
-    constexpr int WVM = T::WVM, WVN = T::WVN, NW = T::NW, SLOT = T::SLOT;
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
+    constexpr int WVM = T::WVM, WVN = T::WVN, NW = T::NW, SLOT = T::SLOT, KG = T::KG;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
     int tm, tn;
     if (!tile_of_block_xcd(blockIdx.x, tiles_m, tiles_n, false, tm, tn)) return;
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kg = KG == 1 ? 0 : wave_all / NW, wave = wave_all - kg * NW;
+    unsigned char *const lds = lds_all + kg * T::GROUP;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
     const int wm = wave % WVM, wn = wave / WVM;
     const size_t row_bytes = (size_t)KB * ((size_t)stride * kFragBytes);
     const unsigned STG = 2u * stride * kFragBytes;       // bytes of a stage in a fragment row of the planes
-    const int nst = KB / 2;
+    const int nst = KB / 2 / KG;                         // stages of a group (KB is a multiple of four)
     // Copies of a step: its slice of the WVM fragment rows of A, two k-halves each, one 1 KiB unit to a wavefront; of the
     // two fragment rows of B likewise, four units, so eight wavefronts (PAIR) copy two steps at a time, wavefronts of
     // class 0 the even step's and of class 1 the odd one's (the last step of an odd number: both the same).
@@ -227,7 +233,7 @@ __global__ __launch_bounds__(64 * T::NW, 2) void gemm_passes_kernel(
     const unsigned dstA = lds0 + wave * kFragBytes, dstB = lds0 + (2 * WVM + ub) * kFragBytes;
     const unsigned dstB2 = dstB + cls * SLOT;            // (from the even step's slot to this class's)
     const unsigned lane16 = lane * 16;
-    auto stage_off = [&](int st) { return lane16 + (unsigned)(st < nst ? st : nst - 1) * STG; };
+    auto stage_off = [&](int st) { return lane16 + (unsigned)((st < nst ? st : nst - 1) * KG + kg) * STG; };
     // this lane's part of a 16 x 64 operand in a pair of 32 x 32 fragments, as in gemm_fused16_kernel
     const int lofs = ((lane >> 4) >> 1) * kFragBytes + ((lane & 15) + 32 * ((lane >> 4) & 1)) * 16;
     const unsigned char *ldsA = lds + wm * 2 * kFragBytes + lofs, *ldsB = lds + (WVM + wn) * 2 * kFragBytes + lofs;
@@ -236,6 +242,22 @@ __global__ __launch_bounds__(64 * T::NW, 2) void gemm_passes_kernel(
     constexpr int WS[NP] = {Ws...};
     v4i acc[widest<NP>(WS)][4];                          // [diagonal of the pass, the last one first][16 x 16 block (i2, j2)]
 
+    static_assert(KG == 1 || (KG == 2 && NP == 1), "k in halves: one pass");
+    // k in halves: a group finishes the blocks of i2 = kg and hands the others over, through LDS nobody else uses any more
+    auto exchange = [&]() {
+        constexpr int W = WS[0];
+        static_assert(KG == 1 || W * NW * 2 * 2 * 1024 <= T::LDS, "exchange does not fit LDS");
+        v4i *x = (v4i *)lds_all + wave * (W * 2 * 2 * 64) + lane;          // [diagonal][i2][j2]
+#pragma unroll
+        for (int a = 0; a < W; ++a)
+#pragma unroll
+            for (int j2 = 0; j2 < 2; ++j2) x[((a * 2 + (kg ^ 1)) * 2 + j2) * 64] = kg ? acc[a][j2] : acc[a][2 + j2];
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < W; ++a)
+#pragma unroll
+            for (int j2 = 0; j2 < 2; ++j2) acc[a][j2] = (kg ? acc[a][2 + j2] : acc[a][j2]) + x[((a * 2 + kg) * 2 + j2) * 64];
+    };
     // Adds the sums of pass p to the entries, in C as they are so far (not yet scaled) between passes.
     const int m0 = (tm * WVM + wm) * 32, n0 = (tn * WVN + wn) * 32;
     const bool stream = stream_c(C, ldc);
@@ -243,8 +265,8 @@ __global__ __launch_bounds__(64 * T::NW, 2) void gemm_passes_kernel(
         constexpr int p = decltype(PP)::value, W = WS[p], BEFORE = diagonals_before<NP>(WS, p);
         auto entries = [&](auto ORDER, auto STREAM) {
 #pragma unroll
-            for (int i2 = 0; i2 < 2; ++i2) {
-                const int mi = m0 + i2 * 16 + (lane & 15);
+            for (int i2 = 0; i2 < 2 / KG; ++i2) {
+                const int mi = m0 + (KG == 1 ? i2 : kg) * 16 + (lane & 15);
                 if (mi >= m) continue;
                 const int ea = p + 1 < NP ? 0 : eA[mi];
 #pragma unroll
@@ -277,7 +299,7 @@ __global__ __launch_bounds__(64 * T::NW, 2) void gemm_passes_kernel(
         constexpr int p = decltype(PP)::value, W = WS[p], SN = diagonals_before<NP>(WS, p) + W;
         using G = PassRing<SN, T::SLOTS>;
         constexpr int V = G::V, N = G::N, R = N > V ? N / V : 1;         // (R: stages in the ring)
-        using S = PassSched<SN, W, V, N, kPassAhead, kPassAhead, kPassProducts, PAIR>;
+        using S = PassSched<SN, W, V, N, kPassAhead, kPassAhead, NP == 1 ? kPassProductsOne : kPassProducts, PAIR>;
         constexpr int NM = S::NM;
         const int8_t *sA[SN], *sB[SN], *sBlast = srcB + (SN - 1 - cls) * kFragBytes;
 #pragma unroll
@@ -376,9 +398,19 @@ __global__ __launch_bounds__(64 * T::NW, 2) void gemm_passes_kernel(
         }
         // no copy is in flight and nobody reads when the next pass begins to fill the ring
         wait_vmcnt<0>();
-        if constexpr (p + 1 < NP) __syncthreads();
+        if constexpr (p + 1 < NP || KG > 1) __syncthreads();
     });
+    if constexpr (KG > 1) exchange();
     finish(std::integral_constant<int, NP - 1>{});
+}
+
+template <class T, int... Ws>
+__global__ __launch_bounds__(T::THREADS, 2) void gemm_passes_kernel(
+    const int8_t *__restrict__ pA, const int8_t *__restrict__ pB, const int32_t *__restrict__ eA,
+    const int32_t *__restrict__ eB, double *__restrict__ C, int ldc, int m, int n, int KB, int stride, int tiles_m,
+    int tiles_n, int Q)
+{
+    passes_of_a_tile<T, Ws...>(pA, pB, eA, eB, C, ldc, m, n, KB, stride, tiles_m, tiles_n, Q);
 }
 
 // hipErrorInvalidValue: a level of Q diagonals would straddle two passes
@@ -393,8 +425,8 @@ hipError_t launch_passes(int m, int n, int kp, int stride, const int8_t *pA, con
     static std::atomic<unsigned long long> configured{0};
     if (hipError_t e = allow_dynamic_lds((const void *)kern, T::LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + TM - 1) / TM, tiles_n = (n + TN - 1) / TN;
-    note_gemm_kernel("gemm_passes_kernel<%d> tile %dx%d, diagonals in %d passes", (Ws + ...), TM, TN, NP);
-    kern<<<(unsigned)tile_order_blocks(tiles_m, tiles_n, false), 64 * T::NW, T::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride,
+    note_gemm_kernel("gemm_passes_kernel<%d> tile %dx%d, %d pass%s", (Ws + ...), TM, TN, NP, NP == 1 ? "" : "es");
+    kern<<<(unsigned)tile_order_blocks(tiles_m, tiles_n, false), T::THREADS, T::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride,
                                                                                     tiles_m, tiles_n, Q);
     return hipGetLastError();
 }
@@ -407,15 +439,17 @@ hipError_t launch_pass_plan(int m, int n, int kp, int stride, const int8_t *pA, 
                             const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
 {
     constexpr PassPlan P = pass_plan(S);
-    if constexpr (P.n == 2) return launch_passes<T, P.w[0], P.w[1]>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
+    if constexpr (P.n == 1) return launch_passes<T, S>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
+    else if constexpr (P.n == 2) return launch_passes<T, P.w[0], P.w[1]>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
     else return launch_passes<T, P.w[0], P.w[1], P.w[2]>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
 }
 #define OZ_DEFINE_GEMM_PASSES(S_)                                                                                           \
     hipError_t launch_gemm_passes_##S_(bool small, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,    \
                                        const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)     \
     {                                                                                                                       \
-        return small ? launch_pass_plan<PassTileSmall, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st)                 \
-                     : launch_pass_plan<PassTileWide, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);                 \
+        if (small) return launch_pass_plan<PassTileSmall, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);             \
+        if constexpr (S_ >= 10) return launch_pass_plan<PassTileWide, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st); \
+        return hipErrorInvalidValue;                                                                                        \
     }
 
 }  // namespace oz

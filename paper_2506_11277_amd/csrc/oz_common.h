@@ -283,7 +283,8 @@ bool fused_automatic();
 hipError_t launch_gemm_blocks(int m, int n, int kp, int sA, int sB, bool all_products, const int8_t *pA,
                               const int8_t *pB, const int32_t *eA, const int32_t *eB, double *C, int ldc,
                               long long *totals, int Q, hipStream_t st);
-// Equal counts 10 ... 20, whole contraction in int32, diagonals in passes (gemm_passes_dev.h; 32 x 32 tiles: gemm_small.hip).
+// Equal counts, whole contraction in int32, slices streamed through a ring of LDS slots (gemm_passes_dev.h): 4 ... 9 slices in one pass,
+// 10 ... 20 with the diagonals in passes (32 x 32 tiles: gemm_small.hip).
 // Widths of the passes: at most nine diagonals (accumulator registers), the first one small (what is moved goes with the
 // sum of the pass ends) and a multiple of three (levels of three diagonals).  128 x 64 tile at 2500 x 2400 x 2500, us: 10 as (3, 7) / (2, 8) /
 // (5, 5) 531 / 528 / 548, 12 as (3, 9) / (4, 8) / (6, 6) 695 / 708 / 723, 13 as (6, 7) / (4, 9) 806 / 800, 14 as (6, 8) / (5, 9)
@@ -294,7 +295,8 @@ struct PassPlan {
 };
 constexpr PassPlan pass_plan(int s)
 {
-    return s <= 10   ? PassPlan{2, {3, 7, 0}}
+    return s <= 9    ? PassPlan{1, {s, 0, 0}}
+           : s <= 10 ? PassPlan{2, {3, 7, 0}}
            : s <= 12 ? PassPlan{2, {3, s - 3, 0}}
            : s <= 15 ? PassPlan{2, {6, s - 6, 0}}
            : s <= 18 ? PassPlan{2, {9, s - 9, 0}}
@@ -302,6 +304,19 @@ constexpr PassPlan pass_plan(int s)
 }
 enum PassShape { kNoPasses, kPassEighths, kPassSmall, kPassWide };
 PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q);
+// Duration of 64 x 64 tiles, two work-groups to a compute unit, in units of the time two of them take together: one alone takes
+// 0.65 of it; behind whole rounds work-groups start as others end, and the last ones count half a unit, or nearly one where some
+// compute units get two of them (s = 7: 1500^3, 576 tiles, 1.53; 2304 x 2000 x 2560, 1152 tiles, 2.48; 3328 x 1562 x 817,
+// 1300 tiles, 2.95; s = 9: 4455 x 700 x 2660, 770 tiles, 1.99).
+inline double pair_rounds(long long tiles, int cus)
+{
+    const long long whole = tiles / (2 * cus), rest = tiles % (2 * cus);
+    const double part = (double)rest / (2 * cus);
+    if (whole == 0) return rest <= cus ? 0.65 : 1.0;
+    return whole + (rest == 0 ? 0.0 : rest <= cus ? 0.5 : part < 0.95 ? 0.95 : part);
+}
+// what launches with fewer, larger tiles lose at short k to copies and epilogues that nothing hides
+inline double short_k_cost(int kp) { return 1.0 + 40.0 / kp; }
 // (stride: slices per entry in the planes, at least s; shape from gemm_passes_shape)
 hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,
                               const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);

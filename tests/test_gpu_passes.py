@@ -1,4 +1,5 @@
-"""10 ... 20 slices with the diagonals in passes (unsteered), bit for bit: a sample of rows and columns against the oracle,
+"""Slices streamed through a ring of LDS slots (unsteered), bit for bit: 4 ... 9 slices in one pass, 10 ... 20 with the diagonals in
+passes; a sample of rows and columns against the oracle,
 every entry against the one-pass kernels that the test knob puts in their place."""
 import numpy as np
 import pytest
@@ -29,6 +30,17 @@ def both_ways(A, B, sA, sB, name, **kw):
     assert "passes" not in ozimmu.last_gemm_kernel()
     assert torch.equal(C.view(torch.int64), want.view(torch.int64))
     check(C, A, B, sA, sB, nearest=kw.get("splitting") == ozimmu.SPLIT_NEAREST, Q=kw.get("level_diagonals", 1))
+
+
+# 64 x 64 tiles, two work-groups to a compute unit: two, three and many k-steps of the ring, edges of tiles, a last round of few
+@pytest.mark.parametrize("s", range(4, 10))
+@pytest.mark.parametrize("m,n,k", [(1500, 1530, 130), (3000, 2900, 195), (2311, 2003, 1281), (61, 37000, 300)])
+def test_one_pass(m, n, k, s):
+    A, B = workloads.lognormal(m, n, k, 1.0, 50 + s)
+    special(A, B)
+    name = f"gemm_passes_kernel<{s}> tile 64x64" if s > 6 else ""
+    both_ways(A, B, s, s, name)
+    both_ways(A, B, s, s - 1, name if s > 7 else "", splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2)
 
 
 # 128 x 64 tiles: one partly filled round, ragged edges; 64 x 64 tiles: a second work-group on some compute units, edges; two
