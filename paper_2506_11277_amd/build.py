@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libozimmu.so")
 SOURCES = ["api.hip", "reduce.hip", "split.hip", "gemm.hip", "gemm_fused16.hip", "gemm_banded.hip", "gemm_small.hip", "gemm_vectors.hip",
-           "gemm_passes.hip", "gemm_passes_4.hip", "gemm_passes_10.hip", "gemm_passes_13.hip", "gemm_passes_15.hip", "gemm_passes_17.hip", "gemm_passes_19.hip", "ceiling.hip"]
+           "gemm_halves16.hip", "gemm_passes.hip", "gemm_passes_4.hip", "gemm_passes_10.hip", "gemm_passes_13.hip", "gemm_passes_15.hip", "gemm_passes_17.hip", "gemm_passes_19.hip", "ceiling.hip"]
 HEADERS = [os.path.join(CSRC, "oz_common.h"), os.path.join(CSRC, "gemm_dev.h"), os.path.join(CSRC, "gemm_passes_dev.h"), os.path.join(CSRC, "slice_dev.h"), os.path.join(HERE, "..", "include", "ozimmu.h"),
            os.path.join(HERE, "..", "include", "ozimmu_bench.h")]
 

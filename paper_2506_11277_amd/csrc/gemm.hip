@@ -1123,8 +1123,11 @@ static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, b
                 // 64 x 64 tiles, the contraction in halves, while every tile has a compute unit of its own: 768^3 s = 3 / 7 18.3
                 // -> 11.4 / 24.7 -> 21.3, 1024^3 s = 3 / 5 / 7 / 9 21.6 -> 13.2 / 25.3 -> 19.6 / 32.3 -> 29.8 / 43.3 -> 41.5; 2 and 3 slices: two
                 // work-groups to a compute unit (1400^3: 25.2 -> 17.7 and 28.5 -> 22.7; beyond, 1536^3 s = 3: 31.6 against 30.8)
+                // (on the 16x16x64 instruction for 7 ... 9 slices, and for 2 and 3 where a compute unit has one tile and k is long)
                 if (s >= 2 && s <= 9 && small_tiles <= (s <= 3 ? 2 : 1) * (long long)cus)
-                    return launch_gemm_halves(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
+                    return s >= 7 || (s <= 3 && kp >= 1024 && small_tiles <= cus)
+                               ? launch_gemm_halves16(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st)
+                               : launch_gemm_halves(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
                 static constexpr double kSmallSpeed[kSmallMaxS + 1] = {0, 0.7, 0.63, 0.69, 0.74, 0.70, 0.76, 0.87, 0.72, 0.80, 0.93, 0.9, 0.9};
                 const double tabulated = fused16_preferred(s, false) ? fused16_launch_cost(s, m, n, cus) : launch_cost(m, n, tm, tn, cus);
                 const double four_waves = launch_cost(m, n, 64, 64, cus) / kSmallSpeed[s];

@@ -258,8 +258,13 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
 #pragma unroll
             for (int j2 = 0; j2 < 2; ++j2) acc[a][j2] = (kg ? acc[a][2 + j2] : acc[a][j2]) + x[((a * 2 + kg) * 2 + j2) * 64];
     };
-    // Adds the sums of pass p to the entries, in C as they are so far (not yet scaled) between passes.
     const int m0 = (tm * WVM + wm) * 32, n0 = (tn * WVN + wn) * 32;
+    // (one pass: the exponents of the 32 rows and columns are asked for here, a value per lane, and not where a lone tile
+    // would wait for them)
+    constexpr bool EARLY = NP == 1;
+    int early = 0;
+    if constexpr (EARLY) early = lane < 32 ? eA[m0 + lane] : eB[n0 + lane - 32];          // (padded like the planes)
+    // Adds the sums of pass p to the entries, in C as they are so far (not yet scaled) between passes.
     const bool stream = stream_c(C, ldc);
     auto finish = [&](auto PP) {
         constexpr int p = decltype(PP)::value, W = WS[p], BEFORE = diagonals_before<NP>(WS, p);
@@ -267,8 +272,14 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
 #pragma unroll
             for (int i2 = 0; i2 < 2 / KG; ++i2) {
                 const int mi = m0 + (KG == 1 ? i2 : kg) * 16 + (lane & 15);
+                int ea = 0, eb[2][4];
+                if constexpr (EARLY) {                   // (before lanes beyond the edge leave)
+                    ea = __shfl(early, (KG == 1 ? i2 : kg) * 16 + (lane & 15));
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) eb[q >> 2][q & 3] = __shfl(early, 32 + (q >> 2) * 16 + 4 * (lane >> 4) + (q & 3));
+                }
                 if (mi >= m) continue;
-                const int ea = p + 1 < NP ? 0 : eA[mi];
+                if constexpr (!EARLY && p + 1 == NP) ea = eA[mi];
 #pragma unroll
                 for (int j2 = 0; j2 < 2; ++j2)
 #pragma unroll
@@ -286,7 +297,7 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
                             else sum.add((double)d * unit, Q, a == W - 1);
                         }
                         if constexpr (p + 1 < NP) *c = sum.S;
-                        else store_c(c, ldexp(sum.S, ea + eB[nj]), STREAM);
+                        else store_c(c, ldexp(sum.S, ea + (EARLY ? eb[j2][r] : eB[nj])), STREAM);
                     }
             }
         };

@@ -13,7 +13,7 @@ namespace oz {
 
 namespace {
 
-// ---- tile 64 x 64, 2 x 2 x 2 wavefronts (m, n, k), operands staged through LDS -----------------------------------
+// ---- tile 64 x 64, 2 x 2 x 2 wavefronts (m, n, k), operands staged through LDS (2 ... 6 slices) -----------------------------------
 // A stage is two 32-deep k-blocks of the four fragment rows; ring of three stages where they fit the LDS, else two.
 // The loop is the hand-pipelined one of gemm_fused_kernel: slices of A from the last to the first, operands of slice
 // l - 1 read while the products of slice l run, the end-of-stage barrier before the products of slice 0, copies of a
@@ -438,7 +438,7 @@ hipError_t launch_gemm_halves(int s, int m, int n, int kp, const int8_t *pA, con
     if (m <= 0 || n <= 0) return hipSuccess;
     switch (s) {
 #define OZ_CASE(S_) case S_: return launch_halves<S_>(m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
-        OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9)
+        OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6)
 #undef OZ_CASE
     }
     return hipErrorInvalidValue;

@@ -264,9 +264,12 @@ hipError_t launch_gemm_fused16(int m, int n, int kp, int s, const int8_t *pA, co
                                const int32_t *eA, const int32_t *eB, double *C, int ldc,
                                int32_t *dump, long long *totals, int Q, bool kslots, hipStream_t st);
 // equal counts, whole contraction in int32, problems that do not fill the chip (gemm_small.hip): 64 x 64 tiles with the
-// contraction in halves (2 <= s <= 9), 32 x 32 tiles with the contraction in eighths (s <= 10)
+// contraction in halves (2 <= s <= 6), 32 x 32 tiles with the contraction in eighths (s <= 10)
 hipError_t launch_gemm_halves(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                               const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
+// (the same on the 16x16x64 instruction, gemm_halves16.hip: 2, 3, 7 ... 9)
+hipError_t launch_gemm_halves16(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
+                                const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
 hipError_t launch_gemm_eighths(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                                const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
 // equal counts 2 ... 9, one operand of at most 64 rows / columns, the other large (gemm_vectors.hip): the planes of the
