@@ -7,7 +7,7 @@ namespace oz {
 #define OZ_DECLARE(S_)                                                                                                      \
     hipError_t launch_gemm_passes_##S_(bool small, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,    \
                                        const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
-OZ_DECLARE(4) OZ_DECLARE(5) OZ_DECLARE(6) OZ_DECLARE(7) OZ_DECLARE(8) OZ_DECLARE(9)     // (64 x 64 tiles only)
+OZ_DECLARE(4) OZ_DECLARE(5) OZ_DECLARE(6) OZ_DECLARE(7) OZ_DECLARE(8) OZ_DECLARE(9)
 OZ_DECLARE(10) OZ_DECLARE(11) OZ_DECLARE(12) OZ_DECLARE(13) OZ_DECLARE(14) OZ_DECLARE(15) OZ_DECLARE(16) OZ_DECLARE(17)
 OZ_DECLARE(18) OZ_DECLARE(19) OZ_DECLARE(20)
 #undef OZ_DECLARE
@@ -39,7 +39,7 @@ PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
     if (small <= cus) return s <= 16 ? kNoPasses : kPassSmall;
     if (s <= 12 && !(kp >= 1024 || (kp >= 384 && wide > cus))) return kNoPasses;
     const double rounds = (double)wide / cus, whole = (double)((wide + cus - 1) / cus);
-    return 1.04 * pair_rounds(small, cus) < (0.8 * whole + 0.2 * rounds) * short_k_cost(kp) ? kPassSmall : kPassWide;
+    return 1.04 * pair_rounds(small, cus) < (0.8 * whole + 0.2 * rounds) * (1.0 + 40.0 / kp) ? kPassSmall : kPassWide;
 }
 
 hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,

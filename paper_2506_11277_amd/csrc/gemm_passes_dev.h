@@ -26,7 +26,10 @@
 //   2500 x 2400 x 2500    s = 10 2988 -> 3147 / 3001, 13 2996 -> 3508 / 3332, 16 3229 -> 3681 / 3653, 18 2943 -> 3842 / 3776
 //   2207^3                s = 10 2565 -> 2562 / 2787, 13 2745 -> 2823 / 3119, 16 2938 -> 3025 / 3390, 18 2527 -> 3174 / 3577
 // 4 ... 9 slices fit one pass; the 64 x 64 tile serves them too where whole rounds of the larger tiles of gemm_fused16_kernel fit
-// badly or k is short (s = 7: 2304 x 2000 x 2560 264 -> 228 us, 3000 x 3000 x 500 107 -> 94; s = 9: 6001 x 5200 x 256 299 -> 251).
+// badly or k is short (s = 7: 2304 x 2000 x 2560 264 -> 228 us, 3000 x 3000 x 500 107 -> 94; s = 9: 6001 x 5200 x 256 299 -> 251).  The
+// 128 x 64 tile is then worked on in runs: a work-group takes the tiles b, b + grid, ..., the copies of the next tile's first
+// steps follow those of the last stage, and the epilogue stands between them (4096 x 4096 x 1024, s = 8 / 9 387 / 469 us as 64 x 64 tiles, 373 /
+// 447 in runs; 64 x 64 tiles gain nothing by runs).
 // What bounds it: the board's power cap, as the other large products (register-only loop of the same instruction: 4200 TOP/s).
 #pragma once
 #include "gemm_dev.h"
@@ -174,13 +177,15 @@ struct PassSched : PassBase<SN, W, V, N, D, DB, TARGET, PAIR> {
 
 // KG groups of WVM x WVN wavefronts of 32 x 32 outputs, a ring of at most SLOTS slots to each group; the groups take every
 // KG-th 64-deep k-step of the same tile
-template <int WVM_, int WVN_, int SLOTS_, int KG_ = 1>
+template <int WVM_, int WVN_, int SLOTS_, int KG_ = 1, bool PERSIST_ = false>
 struct PassTile {
+    static constexpr bool PERSIST = PERSIST_;
     static constexpr int WVM = WVM_, WVN = WVN_, NW = WVM * WVN, SLOTS = SLOTS_, KG = KG_, THREADS = 64 * NW * KG;
     static constexpr int SLOT = (WVM + WVN) * 2 * kFragBytes, GROUP = SLOTS * SLOT, LDS = KG * GROUP;
     static_assert(LDS <= kLdsBytes, "rings do not fit LDS");
 };
 using PassTileWide = PassTile<4, 2, 13>;       // 128 x 64, 156 KiB
+using PassTileRuns = PassTile<4, 2, 13, 1, true>;      // the same for one pass, several tiles to a work-group
 using PassTileSmall = PassTile<2, 2, 10>;      // 64 x 64, 80 KiB: two work-groups to a compute unit
 // operands are read from LDS this many matrix instructions ahead; products between synchronisations (16 ... 40 products and
 // 6 ... 16 instructions are within 1 % of each other at 13 and 18 slices,
@@ -210,9 +215,18 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
                                                  int tiles_m, int tiles_n, int Q)
 {
     constexpr int WVM = T::WVM, WVN = T::WVN, NW = T::NW, SLOT = T::SLOT, KG = T::KG;
+    constexpr bool PERSIST = T::PERSIST;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
+    // (several tiles to a work-group: those of the blocks b, b + gridDim.x, ...)
+    unsigned b = blockIdx.x;
+    const unsigned blocks = PERSIST ? (unsigned)tile_order_blocks(tiles_m, tiles_n, false) : 0;
     int tm, tn;
-    if (!tile_of_block_xcd(blockIdx.x, tiles_m, tiles_n, false, tm, tn)) return;
+    auto next_tile = [&]() {
+        for (; b < blocks; b += gridDim.x)
+            if (tile_of_block_xcd(b, tiles_m, tiles_n, false, tm, tn)) return true;
+        return false;
+    };
+    if (PERSIST ? !next_tile() : !tile_of_block_xcd(b, tiles_m, tiles_n, false, tm, tn)) return;
     const int lane = threadIdx.x & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kg = KG == 1 ? 0 : wave_all / NW, wave = wave_all - kg * NW;
@@ -228,12 +242,19 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
     constexpr bool PAIR = NW == 8;
     static_assert((NW == 8 && WVM == 4 && WVN == 2) || (NW == 4 && WVM == 2 && WVN == 2), "units per wavefront");
     const int cls = wave >> 2, ub = wave & 3;            // (four wavefronts: class 0)
-    const int8_t *srcA = pA + (size_t)(tm * WVM + (wave >> 1)) * row_bytes + (size_t)((wave & 1) * stride) * kFragBytes;
-    const int8_t *srcB = pB + (size_t)(tn * WVN + (ub >> 1)) * row_bytes + (size_t)((ub & 1) * stride + cls) * kFragBytes;
+    const int8_t *srcA = pA + (size_t)((PERSIST ? 0 : tm * WVM) + (wave >> 1)) * row_bytes + (size_t)((wave & 1) * stride) * kFragBytes;
+    const int8_t *srcB = pB + (size_t)((PERSIST ? 0 : tn * WVN) + (ub >> 1)) * row_bytes + (size_t)((ub & 1) * stride + cls) * kFragBytes;
     const unsigned dstA = lds0 + wave * kFragBytes, dstB = lds0 + (2 * WVM + ub) * kFragBytes;
     const unsigned dstB2 = dstB + cls * SLOT;            // (from the even step's slot to this class's)
     const unsigned lane16 = lane * 16;
-    auto stage_off = [&](int st) { return lane16 + (unsigned)((st < nst ? st : nst - 1) * KG + kg) * STG; };
+    // (PERSIST: the tile is in the lane offset, 32 bits; behind the last stage come the first ones of the next tile)
+    unsigned tileA = PERSIST ? (unsigned)(tm * WVM) * (unsigned)row_bytes : 0, tileB = PERSIST ? (unsigned)(tn * WVN) * (unsigned)row_bytes : 0;
+    unsigned nextA = 0, nextB = 0;
+    bool more = false;
+    auto stage_off = [&](int st, unsigned tile, unsigned next) {
+        if (PERSIST && more && st >= nst) return lane16 + next + (unsigned)(st - nst) * STG;
+        return lane16 + tile + (unsigned)((st < nst ? st : nst - 1) * KG + kg) * STG;
+    };
     // this lane's part of a 16 x 64 operand in a pair of 32 x 32 fragments, as in gemm_fused16_kernel
     const int lofs = ((lane >> 4) >> 1) * kFragBytes + ((lane & 15) + 32 * ((lane >> 4) & 1)) * 16;
     const unsigned char *ldsA = lds + wm * 2 * kFragBytes + lofs, *ldsB = lds + (WVM + wn) * 2 * kFragBytes + lofs;
@@ -243,6 +264,7 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
     v4i acc[widest<NP>(WS)][4];                          // [diagonal of the pass, the last one first][16 x 16 block (i2, j2)]
 
     static_assert(KG == 1 || (KG == 2 && NP == 1), "k in halves: one pass");
+    static_assert(!PERSIST || (KG == 1 && NP == 1), "several tiles: one pass");
     // k in halves: a group finishes the blocks of i2 = kg and hands the others over, through LDS nobody else uses any more
     auto exchange = [&]() {
         constexpr int W = WS[0];
@@ -258,12 +280,13 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
 #pragma unroll
             for (int j2 = 0; j2 < 2; ++j2) acc[a][j2] = (kg ? acc[a][2 + j2] : acc[a][j2]) + x[((a * 2 + kg) * 2 + j2) * 64];
     };
-    const int m0 = (tm * WVM + wm) * 32, n0 = (tn * WVN + wn) * 32;
+    int m0 = (tm * WVM + wm) * 32, n0 = (tn * WVN + wn) * 32;
     // (one pass: the exponents of the 32 rows and columns are asked for here, a value per lane, and not where a lone tile
     // would wait for them)
     constexpr bool EARLY = NP == 1;
     int early = 0;
-    if constexpr (EARLY) early = lane < 32 ? eA[m0 + lane] : eB[n0 + lane - 32];          // (padded like the planes)
+    auto ask = [&]() { early = lane < 32 ? eA[m0 + lane] : eB[n0 + lane - 32]; };           // (padded like the planes)
+    if constexpr (EARLY) ask();
     // Adds the sums of pass p to the entries, in C as they are so far (not yet scaled) between passes.
     const bool stream = stream_c(C, ldc);
     auto finish = [&](auto PP) {
@@ -336,14 +359,17 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
         static_assert(S::issued(0) > 0 && S::issued(0) <= N, "first copies");
         static_for<0, S::issued(0)>([&](auto QQ) {
             constexpr int q = decltype(QQ)::value;
-            copyA(QQ, stage_off(q / V), q / V * (V * SLOT));
-            copyB(QQ, stage_off(q / V), q / V * (V * SLOT));
+            copyA(QQ, stage_off(q / V, tileA, 0), q / V * (V * SLOT));
+            copyB(QQ, stage_off(q / V, tileB, 0), q / V * (V * SLOT));
         });
         if constexpr (p > 0) finish(std::integral_constant<int, p - 1>{});         // (the copies land meanwhile)
+        auto clear = [&]() {
 #pragma unroll
-        for (int a = 0; a < W; ++a)
+            for (int a = 0; a < W; ++a)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) acc[a][b] = v4i{0, 0, 0, 0};
+                for (int q = 0; q < 4; ++q) acc[a][q] = v4i{0, 0, 0, 0};
+        };
+        clear();
 
         v4i A_[SN][2], B_[SN][2], An[SN][2], Bn[SN][2];  // (An, Bn: of the next stage)
         auto loadA = [&](v4i (&d)[2], int i, unsigned ring) {
@@ -362,13 +388,25 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
             if constexpr (S::readB(i) < 0) loadB(B_[i], i, 0);
         });
         unsigned ring = 0;                                   // LDS offset of the stage's first slot
+        int mn = 0, nn = 0;
+        auto look_ahead = [&]() {
+            b += gridDim.x;
+            if (!(more = next_tile())) return;
+            nextA = (unsigned)(tm * WVM) * (unsigned)row_bytes;
+            nextB = (unsigned)(tn * WVN) * (unsigned)row_bytes;
+            mn = (tm * WVM + wm) * 32;
+            nn = (tn * WVN + wn) * 32;
+        };
+        if constexpr (PERSIST) look_ahead();
         for (int st = 0; st < nst; ++st) {
-            // (towards the end the copies and the reads ahead go on, of the last stage again: nobody uses them)
+            // (towards the end the copies and the reads ahead go on, of the last stage again -- nobody uses them -- or of the
+            // first stages of the next tile)
             constexpr int DA = (V - 1 + N) / V + 1;
-            unsigned so[DA + 1], rg[DA + 1];
+            unsigned so[DA + 1], sb[DA + 1], rg[DA + 1];
 #pragma unroll
             for (int d = 0; d <= DA; ++d) {
-                so[d] = stage_off(st + d);
+                so[d] = stage_off(st + d, tileA, nextA);
+                sb[d] = PERSIST ? stage_off(st + d, tileB, nextB) : so[d];
                 rg[d] = R == 1 ? 0u : d == 0 ? ring : rg[d - 1] + V * SLOT == N * SLOT ? 0u : rg[d - 1] + V * SLOT;
             }
             static_for<0, NM>([&](auto E) {
@@ -394,7 +432,7 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
                 if constexpr (cp >= 0) {
                     constexpr int q = cp / 2;
                     if constexpr (cp % 2 == 0) copyA(std::integral_constant<int, q>{}, so[q / V], rg[q / V]);
-                    else copyB(std::integral_constant<int, q>{}, so[q / V], rg[q / V]);
+                    else copyB(std::integral_constant<int, q>{}, sb[q / V], rg[q / V]);
                 }
             });
             static_for<0, SN>([&](auto I) {
@@ -406,6 +444,19 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
                 }
             });
             ring = rg[1];
+            if constexpr (PERSIST)
+                if (st + 1 == nst && more) {
+                    // the tile is done: its epilogue while the first copies of the next one fly
+                    finish(PP);
+                    clear();
+                    tileA = nextA;
+                    tileB = nextB;
+                    m0 = mn;
+                    n0 = nn;
+                    ask();
+                    look_ahead();
+                    st = -1;
+                }
         }
         // no copy is in flight and nobody reads when the next pass begins to fill the ring
         wait_vmcnt<0>();
@@ -429,6 +480,10 @@ template <class T, int... Ws>
 hipError_t launch_passes(int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                          const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
 {
+    // (32-bit lane offsets to the tile where a work-group takes several: larger planes go to a launch of single tiles)
+    if constexpr (T::PERSIST)
+        if ((size_t)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * stride >= (1ULL << 32))
+            return launch_passes<PassTile<T::WVM, T::WVN, T::SLOTS>, Ws...>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
     constexpr int TM = 32 * T::WVM, TN = 32 * T::WVN, NP = sizeof...(Ws), WS[NP] = {Ws...};
     for (int p = 1; p < NP; ++p)
         if (diagonals_before<NP>(WS, p) % Q != 0) return hipErrorInvalidValue;      // (gemm_passes_shape() does not ask for it)
@@ -437,7 +492,12 @@ hipError_t launch_passes(int m, int n, int kp, int stride, const int8_t *pA, con
     if (hipError_t e = allow_dynamic_lds((const void *)kern, T::LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + TM - 1) / TM, tiles_n = (n + TN - 1) / TN;
     note_gemm_kernel("gemm_passes_kernel<%d> tile %dx%d, %d pass%s", (Ws + ...), TM, TN, NP, NP == 1 ? "" : "es");
-    kern<<<(unsigned)tile_order_blocks(tiles_m, tiles_n, false), T::THREADS, T::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride,
+    long long blocks = tile_order_blocks(tiles_m, tiles_n, false);
+    if (T::PERSIST) {
+        const long long slots = (long long)device_cus() * (8 / T::NW);
+        blocks = blocks < slots ? blocks : slots;
+    }
+    kern<<<(unsigned)blocks, T::THREADS, T::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride,
                                                                                     tiles_m, tiles_n, Q);
     return hipGetLastError();
 }
@@ -459,8 +519,8 @@ hipError_t launch_pass_plan(int m, int n, int kp, int stride, const int8_t *pA, 
                                        const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)     \
     {                                                                                                                       \
         if (small) return launch_pass_plan<PassTileSmall, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);             \
-        if constexpr (S_ >= 10) return launch_pass_plan<PassTileWide, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st); \
-        return hipErrorInvalidValue;                                                                                        \
+        using Wide = std::conditional_t<(S_ >= 10), PassTileWide, PassTileRuns>;                                            \
+        return launch_pass_plan<Wide, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);                                 \
     }
 
 }  // namespace oz

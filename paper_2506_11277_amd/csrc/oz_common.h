@@ -318,8 +318,6 @@ inline double pair_rounds(long long tiles, int cus)
     if (whole == 0) return rest <= cus ? 0.65 : 1.0;
     return whole + (rest == 0 ? 0.0 : rest <= cus ? 0.5 : part < 0.95 ? 0.95 : part);
 }
-// what launches with fewer, larger tiles lose at short k to copies and epilogues that nothing hides
-inline double short_k_cost(int kp) { return 1.0 + 40.0 / kp; }
 // (stride: slices per entry in the planes, at least s; shape from gemm_passes_shape)
 hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,
                               const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
