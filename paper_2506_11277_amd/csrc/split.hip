@@ -361,12 +361,32 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
 // 1024, s = 3 30.1 and 32.4 / 34.9 and 38.2 / 39.8 and 43.2 / 47.8 and 52.0, k = 2048, s = 3 54.5 and 48.2 / 65.6 and 58.0 / 78.2 and 75.3 /
 // 103 and 107, s = 7 63.2 and 57.9 / 80.1 and 92.1 / 98.2 and 112); the line is where the longest contractions change over
 // at few slices, and what it costs the shorter ones below it is at most 3 % of a call (12000 x 200 x 1000, s = 7: 113 and 117)
-static int scale_split_rows(int m, int n, int kp) { return kp <= 2048 && (long long)m + n >= 12288 ? 8 : 4; }
+//
+// More slices write more: where the planes (slices x rows x k bytes) no longer fit the caches, eight rows, whose pieces fill whole
+// lines, are ahead whatever k is (event times, us, four and eight rows: 3000 x 3000 x 2500 s = 13 98 and 74, 2500 x 2400 x 2500 81 and 73,
+// 2600 x 2600 x 3000 111 and 84, but s = 7 55 and 60, 57 and 65; 5120^2 x 2048 s = 7 92 and 80; 4096^2 x 2048, 109 MB, 42 and 45), and so
+// they are from 6000 rows on at k up to 256 (6001 x 5200 x 256 26.1 and 23.3, 3000 x 3000 x 256 19.7 and 19.1; k = 512 23.5 and 27.0); with
+// fewer than 4096 rows too few work-groups are left (1400 x 1400 x 3000 s = 18 47 and 57).
+static int scale_split_rows(int m, int n, int kp, int c)
+{
+    const long long rows = (long long)m + n;
+    return (kp <= 2048 && rows >= 12288) || (kp <= 256 && rows >= 6000) || (rows >= 4096 && c * rows * kp >= 118000000LL) ? 8 : 4;
+}
 
-static int scale_split_waves(int rows, int kp)
+// Wavefronts: 64 k (four rows) or 32 k (eight) to each, up to sixteen; with four rows up to eight where there are two work-groups
+// for every compute unit, so that one loads while the other stores (sixteen and eight, us, s = 7: 1600 x 1600 x 1536 31.7 and 28.1, 3000 x 3000 x 1536
+// 44.3 and 37.6, 2000 x 2100 x 4000 76 and 65, 1024^3 20.6 and 20.0; 500 x 500 x 2048, 250 work-groups, 20.9 and 21.4) -- and planes that
+// fit the caches (2500 x 2400 x 2500 s = 9 58 and 64)
+static int scale_split_waves(int m, int n, int rows, int kp, int c)
 {
     const int waves = kp / 16 * rows / 16;
-    return waves < 1 ? 1 : waves < 16 ? waves : 16;
+    const int most = rows == 4 && kp > 512 && ((long long)m + n) / rows >= 2LL * device_cus() &&
+                             c * ((long long)m + n) * kp < 100000000LL
+                         ? 8
+                         : 16;
+    if (waves <= most) return waves < 1 ? 1 : waves;
+    const int sweeps = (waves + most - 1) / most;
+    return most == 16 ? 16 : (waves + sweeps - 1) / sweeps;       // (of eight, no more than the sweeps over k keep busy)
 }
 
 static long long scale_split_groups(int m, int n, int rows)
@@ -385,8 +405,8 @@ long long scale_split_threads(int m, int n, int k)
     if (m <= 0 || n <= 0 || k <= 0) return 0;
     const int kp = round_up(k, kPad);
     if (kp > 2048 && (kp > 4096 || ((long long)m + n) * kp > 18LL << 20)) return 0;
-    const int rows = scale_split_rows(m, n, kp);
-    const long long threads = scale_split_groups(m, n, rows) * 64 * scale_split_waves(rows, kp);
+    const int rows = scale_split_rows(m, n, kp, 0);          // (more slices: other shapes of some thousand rows at most)
+    const long long threads = scale_split_groups(m, n, rows) * 64 * scale_split_waves(m, n, rows, kp, 0);
     return threads < 1LL << 32 ? threads : 0;
 }
 
@@ -395,26 +415,27 @@ hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, con
                               unsigned long long *header, size_t bad_offset, hipStream_t st)
 {
     if (!scale_split_threads(m, n, k) || cA < sA || cB < sB) return hipErrorInvalidValue;
-    const int kp = round_up(k, kPad);
+    const int kp = round_up(k, kPad), c = cA > cB ? cA : cB;
     auto *bad = (unsigned *)((char *)header + bad_offset);
     auto launch = [&](auto PRC, auto NVC) {
         constexpr int PR = decltype(PRC)::value, NV = decltype(NVC)::value;
         const int panelsA = (m + PR - 1) / PR, panels = panelsA + (n + PR - 1) / PR;
         auto kern = nearest ? scale_split_kernel<true, PR, NV> : scale_split_kernel<false, PR, NV>;
-        kern<<<(unsigned)scale_split_groups(m, n, PR), 64 * scale_split_waves(PR, kp), 0, st>>>(
+        kern<<<(unsigned)scale_split_groups(m, n, PR), 64 * scale_split_waves(m, n, PR, kp, c), 0, st>>>(
             (const unsigned long long *)A, lda, m, (const unsigned long long *)B, ldb, n, k, sA, sB, cA, cB, eA, eB, pA, pB, kp / kFrag,
             panelsA, header, panels, (long long)bad_offset, bad);
     };
-    auto by_k = [&](auto PRC) {
-        constexpr int PR = decltype(PRC)::value, SWEEP = 16 * 16 * (16 / PR);       // k of 16 wavefronts
-        if (kp <= SWEEP) launch(PRC, std::integral_constant<int, 1>{});
-        else if (kp <= 2 * SWEEP) launch(PRC, std::integral_constant<int, 2>{});
-        else if (kp <= 3 * SWEEP) launch(PRC, std::integral_constant<int, 3>{});
-        else launch(PRC, std::integral_constant<int, 4>{});
+    auto by_k = [&](auto PRC) -> hipError_t {
+        constexpr int PR = decltype(PRC)::value;
+        const int sweep = scale_split_waves(m, n, PR, kp, c) * 16 * (16 / PR);           // k of all wavefronts
+        switch ((kp + sweep - 1) / sweep) {
+#define OZ_CASE(NV_) case NV_: launch(PRC, std::integral_constant<int, NV_>{}); return hipGetLastError();
+            OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8)
+#undef OZ_CASE
+        }
+        return hipErrorInvalidValue;
     };
-    if (scale_split_rows(m, n, kp) == 8) by_k(std::integral_constant<int, 8>{});
-    else by_k(std::integral_constant<int, 4>{});
-    return hipGetLastError();
+    return scale_split_rows(m, n, kp, c) == 8 ? by_k(std::integral_constant<int, 8>{}) : by_k(std::integral_constant<int, 4>{});
 }
 
 hipError_t launch_collect_bad(unsigned long long *header, hipStream_t st)
