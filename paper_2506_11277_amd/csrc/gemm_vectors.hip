@@ -128,6 +128,15 @@ __global__ __launch_bounds__(512) void gemm_vectors_kernel(const unsigned long l
     for (int d = 0; d < AHEAD; ++d) fetch(first + 1 + d, x[d]);
 #pragma unroll
     for (int l = 0; l < S; ++l) put(l, abase);
+    // (from 3 slices on the short operand's first slices have landed before the loop. The compiler moves their loads down to it,
+    // behind the raw entries, and as it counts what may be in flight for both ways into the loop at once, it then waited for
+    // everything, entries of steps to come included, once per AHEAD steps. Product alone, us, before -> now: 6000 x 64 x 6001,
+    // 4 / 6 / 8 slices 75.6 / 93.9 / 114.9 -> 75.4 / 93.3 / 110.7; 8192 x 64 x 8192, 6 slices 141.0 -> 139.3. With 2 slices
+    // 64 x 8192 x 8192 lost by it, 124.7 -> 127.5)
+    if constexpr (S > 2) {
+#pragma unroll
+        for (int h = 0; h < S; ++h) asm volatile("" : "+v"(bf[h]));
+    }
     __syncthreads();
 
     // (the loop runs over whole groups of AHEAD steps: those beyond the last one multiply zeros)
