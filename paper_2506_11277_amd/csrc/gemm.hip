@@ -1132,27 +1132,14 @@ static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, b
                 const double tabulated = fused16_preferred(s, false) ? fused16_launch_cost(s, m, n, cus) : launch_cost(m, n, tm, tn, cus);
                 const double four_waves = launch_cost(m, n, 64, 64, cus) / kSmallSpeed[s];
                 small = small_tiles > tiles && four_waves < tabulated;
-                // The streaming kernel (gemm_passes_dev.h), by the time the launches take: rounds as above, at the fraction
-                // kPairSpeed (64 x 64 tiles, two work-groups to a compute unit) or kWideSpeed (128 x 64, a work-group after the
-                // other's tiles in one launch) of the tabulated tile's rate (4096^3, s = 4 ... 9: 502 / 677 / 939 / 1174 / 1473 / 1777 and, from 5
-                // on, 664 / 887 / 1176 / 1438 / 1761 us against 430 / 604 / 831 / 1134 / 1432 / 1768), and what copies and epilogues add: 1.1 ps per
-                // entry of C where the next work-group's or tile's products hide most of them, 2.1 in the other kernels
-                // (4096 x 4096 x 256, s = 5 / 7 / 9: 74 us for 128 x 128 tiles, 61 / 93 / 129 for these, of which the products take 38 / 71 /
-                // 114).  GEMM before and so: 2304 x 2000 x 2560 s = 5 / 7 / 9 156 / 264 / 388 -> 140 / 228 / 342, 1500^3 s = 7 / 8 97 / 130 -> 84 / 104,
-                // 6001 x 5200 x 256 s = 7 / 9 211 / 299 -> 183 / 251, 3500 x 3500 x 800 s = 5 / 8 159 / 296 -> 143 / 265, 3328 x 1562 x 817 s = 5 /
-                // 8 68 / 123 -> 60 / 116, 4096 x 4096 x 1024 s = 9 469 -> 447.  Where the measure calls it even the others stay (s = 4: 2688 x 2688 x 1000 84 us a call against 87, GEMM at 1500^3 45.4
-                // against 47.4).  Up to k = 128 the choice between the other tiles stands as tests/test_gpu_parity.py has it,
-                // though it is behind there (2500 x 2500 x 100, s = 7 40.5 against 32.9).
-                static constexpr double kPairSpeed[10] = {0, 0, 0, 0, 0.856, 0.89, 0.885, 0.966, 0.97, 0.995};
-                static constexpr double kWideSpeed[10] = {0, 0, 0, 0, 0.87, 0.905, 0.936, 0.965, 1.0, 1.005};
+                // The streaming kernel (gemm_passes_dev.h) where the launch takes less time (gemm_passes.hip).  Up to k = 128 the choice
+                // between the other tiles stands as tests/test_gpu_parity.py has it, though it is behind there (2500 x 2500 x 100, s = 7
+                // 40.5 against 32.9).
                 if (s >= 4 && s <= 9 && kp > 128) {
-                    const long long wide_tiles = (long long)((m + 127) / 128) * ((n + 63) / 64);
-                    const double per_entry = 1800.0 / ((double)kp * (s * (s + 1) / 2));       // 1.1 ps in units of the products' time
-                    const double pairs = pair_rounds(small_tiles, cus) * 8192.0 / kPairSpeed[s] * (1.0 + per_entry);
-                    const double wide = s <= 6 || wide_tiles > cus ? launch_cost(m, n, 128, 64, cus) / kWideSpeed[s] * (1.0 + per_entry) : 1e30;
-                    const double others = (small ? four_waves : tabulated) * (1.0 + 2.0 * per_entry);
-                    if ((pairs < wide ? pairs : wide) < (s == 4 ? 0.86 : s <= 6 ? 0.92 : 0.98) * others)
-                        return launch_gemm_passes(pairs < wide ? kPassSmall : kPassWide, s, m, n, kp, s, pA, pB, eA, eB, C, ldc, Q, st);
+                    int om = 64, on = 64;
+                    if (!small) fused16_launch_tile(s, m, n, om, on);
+                    const PassShape shape = gemm_one_pass_shape(s, m, n, kp, om, on);
+                    if (shape != kNoPasses) return launch_gemm_passes(shape, s, m, n, kp, s, pA, pB, eA, eB, C, ldc, Q, st);
                 }
             } else
                 small = tiles < limit && small_tiles > tiles;     // test knob: a plain threshold on the tile count

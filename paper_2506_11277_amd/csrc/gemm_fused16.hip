@@ -778,6 +778,16 @@ double fused16_launch_cost(int s, int m, int n, int cus)
     return launch_cost(m, n, tm, tn, cus);
 }
 
+void fused16_launch_tile(int s, int m, int n, int &tm, int &tn)
+{
+    fused16_tile(s, tm, tn);
+    switch (alt_tile(s, m, n)) {
+        case 1: tm = 192, tn = 128; break;
+        case 2: tm = 128, tn = 128; break;
+        case 3: tm = 128, tn = 64; break;
+    }
+}
+
 int fused16_split_k_slots(int s, int kp)
 {
     if (s < 2 || s > 9) return 0;

@@ -1,6 +1,6 @@
 // Slice products in passes over groups of diagonals: which shape runs, and the launch (kernels: gemm_passes_dev.h, instantiated
 // in gemm_passes_4.hip ... gemm_passes_19.hip; 32 x 32 tiles: gemm_small.hip).
-#include "oz_common.h"
+#include "gemm_dev.h"
 
 namespace oz {
 
@@ -12,6 +12,68 @@ OZ_DECLARE(10) OZ_DECLARE(11) OZ_DECLARE(12) OZ_DECLARE(13) OZ_DECLARE(14) OZ_DE
 OZ_DECLARE(18) OZ_DECLARE(19) OZ_DECLARE(20)
 #undef OZ_DECLARE
 
+// ---- Time of a launch, us: rounds * (product * x + round) + once ----
+// x: slice products per entry times kp, in thousands.  `round` is what a round adds whatever its length (first copies, epilogue, the
+// sums parked between passes), `once` what a launch adds.  Fitted to the GEMM phases of 1800 random calls of 4 ... 9 slices and 680 of
+// 10 ... 12, up to 4 ms, k > 128; the fits leave 3 ... 6 percent.  Where the epilogues of one work-group run beside the products of another
+// (64 x 64 tiles in pairs, runs of 128 x 64 tiles), a round adds 0.7 ... 2.7 us instead of 4 ... 5, but the last of them hides behind nothing:
+// `once` is 6 ... 7 us instead of 4.5.  So a launch of a single round gains nothing by them.
+struct LaunchTime {
+    double product, round, once;
+    double us(double rounds, double x) const { return rounds * (product * x + round) + once; }
+};
+
+// Rounds count the work-groups of the XCD that gets most: a grid in the two-dimensional order has up to 4 % more of them than tiles,
+// and an XCD with one tile too many needs a round more (3200 x 613 x 1152, s = 9: 500 tiles of 64 x 64, 65 of them on two XCDs
+// with room for 64: 85 us instead of 62 in 128 x 64 tiles).
+static long long order_blocks(int m, int n, int tm, int tn) { return tile_order_blocks((m + tm - 1) / tm, (n + tn - 1) / tn, false); }
+
+// One work-group to a compute unit: a partly filled last round counts 0.7 of a full one plus 0.3 of its share (0.8 and 0.2 from 10 slices on,
+// where passes and fuller registers leave less to the power cap).
+static double single_rounds(int s, long long blocks, int cus)
+{
+    const double share = s > 9 ? 0.2 : 0.3;
+    return (1.0 - share) * (double)((blocks + cus - 1) / cus) + share * (double)blocks / cus;
+}
+
+// 64 x 64 tiles, two work-groups to a compute unit, in units of the time two of them take together: one alone takes 0.65 of it;
+// behind whole rounds work-groups start as others end, and the last ones count about half a unit, or most of one where some
+// compute units get two of them (s = 7: 1500^3, 576 tiles, 1.53; 2304 x 2000 x 2560, 1152 tiles, 2.48; 3328 x 1562 x 817,
+// 1300 tiles, 2.95; s = 9: 4455 x 700 x 2660, 770 tiles, 1.99); more with few slices, whose compute units are furthest from the power cap
+// (s = 4: 1592^3, 640 work-groups: 48 us, 45 in 128 x 128 tiles).
+static double pair_rounds(int s, long long blocks, int cus)
+{
+    const long long whole = blocks / (2 * cus), rest = blocks % (2 * cus);
+    const double part = (double)rest / (2 * cus);
+    if (rest == 0) return (double)whole;
+    if (s > 9) return whole == 0 ? (rest <= cus ? 0.65 : 1.0) : whole + (rest <= cus ? 0.5 : part < 0.95 ? 0.95 : part);
+    if (rest > cus) return whole + 0.7 + 0.3 * part;
+    return whole == 0 ? 0.65 : whole + (s == 4 ? 0.6 : s <= 6 ? 0.45 : 0.35) + 0.2 * part;
+}
+
+// 4 ... 9 slices: the other kernels by their tile (128 x 64 outputs count one round, larger tiles as many more).  What is taken where the
+// figures are even is what stood there before up to 6 slices, whose fits are the looser ones.  Calls, operands that change from one to
+// the next, against the other kernels alone and against the best of the three: geometric means over 900 random sizes 1.085 and 0.997, slowest
+// 0.92 (5440 x 384 x 1216, s = 4; else 0.975).
+PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn)
+{
+    if (s < 4 || s > 9 || m <= 0 || n <= 0) return kNoPasses;
+    static constexpr LaunchTime kPairs[6] = {{1.454, 2.7, 5.1}, {1.389, 2.1, 5.8}, {1.368, 1.65, 6.0}, {1.284, 1.35, 5.95}, {1.242, 1.2, 6.3}, {1.203, 0.85, 6.85}};
+    static constexpr LaunchTime kRuns[6] = {{1.344, 2.0, 6.3}, {1.363, 1.7, 6.0}, {1.272, 1.7, 6.1}, {1.245, 1.8, 6.1}, {1.169, 2.3, 5.7}, {1.136, 2.25, 6.15}};
+    static constexpr LaunchTime k64[6] = {{1.844, 3.0, 5.4}, {1.62, 4.9, 4.0}, {1.64, 3.7, 6.0}, {1.484, 2.25, 7.3}, {1.57, 7.2, 4.6}, {1.417, 6.8, 4.5}};
+    static constexpr LaunchTime k128x64[6] = {{1.4, 4.5, 4.9}, {1.387, 4.5, 4.9}, {1.241, 4.8, 4.7}, {1.193, 4.75, 4.5}, {1.153, 5.75, 4.05}, {1.126, 5.4, 4.5}};
+    static constexpr LaunchTime k128x128[3] = {{1.226, 3.85, 5.85}, {1.147, 4.6, 4.35}, {1.109, 4.05, 5.95}}, k192x128{1.188, 3.95, 4.65};
+    static constexpr double kAhead[6] = {0.98, 0.985, 0.99, 1.0, 1.0, 1.0};
+    const int cus = device_cus();
+    const double x = 1e-3 * kp * (s * (s + 1) / 2);
+    const double pairs = kPairs[s - 4].us(pair_rounds(s, order_blocks(m, n, 64, 64), cus), x);
+    const double runs = kRuns[s - 4].us(single_rounds(s, order_blocks(m, n, 128, 64), cus), x);
+    const LaunchTime &t = tm == 64 ? k64[s - 4] : tm == 192 ? k192x128 : tn == 64 || s > 6 ? k128x64[s - 4] : k128x128[s - 4];
+    const double others = t.us(single_rounds(s, order_blocks(m, n, tm, tn), cus) * (tm * tn / 8192.0), x);
+    if ((pairs < runs ? pairs : runs) >= kAhead[s - 4] * others) return kNoPasses;
+    return pairs < runs ? kPassSmall : kPassWide;
+}
+
 // Which shape, if any (GEMM phases in us, s = 11 / 13 / 16 / 18).
 // Up to one tile of 32 x 32 per compute unit, and up to 1.75 where the products repay a second round: these, k in eighths
 // (402^3 before 25.7 / 33.9 / 44.7 / 62.8, now 16.1 / 18.8 / 23.0 / 26.0; 1.64 tiles: 600 x 700 x 384 21.8 / 28.0 / 36.1 / 49.1, 23.6 / 28.1 / 34.6 / 40.4,
@@ -21,7 +83,7 @@ OZ_DECLARE(18) OZ_DECLARE(19) OZ_DECLARE(20)
 // slices (800^3: against 49.8 / 65.2 / 83.2 in passes; 18: 95.0).
 // Up to 12 slices the fixed costs of two passes are only repaid by several rounds or a longer k (s = 11, one-pass kernel against
 // passes: 1000 x 1100 x 500 39.7 / 46.3, 1038 x 2512 x 66 33.5 / 36.3, but 1300^3 119 / 114, 3000 x 3000 x 500 234 / 219).
-// 128 x 64 or 64 x 64 by rounds of the chip: two 64 x 64 tiles at a time cost a compute unit 1.04 of a 128 x 64 one (pair_rounds);
+// 128 x 64 or 64 x 64 by rounds of the chip: two 64 x 64 tiles at a time cost a compute unit 1.04 of a 128 x 64 one ;
 // at short k the 128 x 64 tile also pays for copies and epilogues that nothing hides (2085 x 4740 x 1000, 4.98 against 4.83
 // rounds, s = 13 580 / 584, 18 953 / 940; 3000 x 3000 x 500, 4.41 against 4.31, s = 13 306 / 280; 2207^3, 2.46 against 2.39, 693 / 627).
 PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
@@ -39,7 +101,7 @@ PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
     if (small <= cus) return s <= 16 ? kNoPasses : kPassSmall;
     if (s <= 12 && !(kp >= 1024 || (kp >= 384 && wide > cus))) return kNoPasses;
     const double rounds = (double)wide / cus, whole = (double)((wide + cus - 1) / cus);
-    return 1.04 * pair_rounds(small, cus) < (0.8 * whole + 0.2 * rounds) * (1.0 + 40.0 / kp) ? kPassSmall : kPassWide;
+    return 1.04 * pair_rounds(s, small, cus) < (0.8 * whole + 0.2 * rounds) * (1.0 + 40.0 / kp) ? kPassSmall : kPassWide;
 }
 
 hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,

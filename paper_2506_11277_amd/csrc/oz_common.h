@@ -245,6 +245,7 @@ inline double launch_cost(int m, int n, int tm, int tn, int cus)
     return (0.8 * whole + 0.2 * exact) * tm * tn;
 }
 double fused16_launch_cost(int s, int m, int n, int cus);
+void fused16_launch_tile(int s, int m, int n, int &tm, int &tn);       // ... and that tile
 // compute units of the current device, asked for once per device ordinal
 inline int device_cus()
 {
@@ -307,17 +308,8 @@ constexpr PassPlan pass_plan(int s)
 }
 enum PassShape { kNoPasses, kPassEighths, kPassSmall, kPassWide };
 PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q);
-// Duration of 64 x 64 tiles, two work-groups to a compute unit, in units of the time two of them take together: one alone takes
-// 0.65 of it; behind whole rounds work-groups start as others end, and the last ones count half a unit, or nearly one where some
-// compute units get two of them (s = 7: 1500^3, 576 tiles, 1.53; 2304 x 2000 x 2560, 1152 tiles, 2.48; 3328 x 1562 x 817,
-// 1300 tiles, 2.95; s = 9: 4455 x 700 x 2660, 770 tiles, 1.99).
-inline double pair_rounds(long long tiles, int cus)
-{
-    const long long whole = tiles / (2 * cus), rest = tiles % (2 * cus);
-    const double part = (double)rest / (2 * cus);
-    if (whole == 0) return rest <= cus ? 0.65 : 1.0;
-    return whole + (rest == 0 ? 0.0 : rest <= cus ? 0.5 : part < 0.95 ? 0.95 : part);
-}
+// 4 ... 9 slices: kNoPasses where the kernel of one stage to a barrier that would run otherwise, with tiles of tm x tn, is the faster one
+PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn);
 // (stride: slices per entry in the planes, at least s; shape from gemm_passes_shape)
 hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,
                               const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
