@@ -1075,6 +1075,31 @@ hipError_t launch_gemm_fused(int m, int n, int kp, int sA, int sB, bool all_prod
     return hipSuccess;
 }
 
+// tile tabulated for equal counts up to kSmallMaxS
+static void fused_tabulated_tile(int s, int &tm, int &tn)
+{
+    tm = 128, tn = s <= 4 || s == 6 ? 128 : 64;
+    if (fused16_preferred(s, false)) fused16_tile(s, tm, tn);
+}
+
+// The 64 x 64 tile where it finishes sooner.  A launch takes (rounds of the compute units) x (time of a
+// tile), a partly filled round nearly as long as a full one; the small tile runs its products at the fraction
+// kSmallSpeed of the tabulated tile's rate (8192^3, both kernels measured per slice count).  So few tiles
+// of the tabulated shape lose to many small ones (2048^2, s = 2: 128 tiles of 256 x 128 against 4 rounds of
+// 64 x 64: the small tile is 18 % faster), but not always (2560^2: 200 large tiles are 57 % faster than 7
+// rounds of small ones, which a plain "fewer tiles than compute units" rule gets wrong).
+bool fused_small_tile(int s, int m, int n)
+{
+    if (s < 1 || s > kSmallMaxS) return false;
+    static constexpr double kSmallSpeed[kSmallMaxS + 1] = {0, 0.7, 0.63, 0.69, 0.74, 0.70, 0.76, 0.87, 0.72, 0.80, 0.93, 0.9, 0.9};
+    const int cus = device_cus();
+    int tm, tn;
+    fused_tabulated_tile(s, tm, tn);
+    const long long tiles = (long long)((m + tm - 1) / tm) * ((n + tn - 1) / tn), small = (long long)((m + 63) / 64) * ((n + 63) / 64);
+    const double tabulated = fused16_preferred(s, false) ? fused16_launch_cost(s, m, n, cus) : launch_cost(m, n, tm, tn, cus);
+    return small > tiles && launch_cost(m, n, 64, 64, cus) / kSmallSpeed[s] < tabulated;
+}
+
 static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, bool all_products, const int8_t *pA,
                                          const int8_t *pB, const int32_t *eA, const int32_t *eB, double *C, int ldc,
                                          int32_t *dump, long long *totals, int Q, bool kslots, hipStream_t st)
@@ -1088,17 +1113,6 @@ static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, b
     if (sA == sB) {
         const int s = sA;
         if (!dump && !totals && s <= kSmallMaxS) {
-            // The 64 x 64 tile where it finishes sooner.  A launch takes (rounds of the compute units) x (time of a
-            // tile), a partly filled round nearly as long as a full one; the small tile runs its products at the fraction
-            // kSmallSpeed of the tabulated tile's rate (8192^3, both kernels measured per slice count).  So few tiles
-            // of the tabulated shape lose to many small ones (2048^2, s = 2: 128 tiles of 256 x 128 against 4 rounds of
-            // 64 x 64: the small tile is 18 % faster), but not always (2560^2: 200 large tiles are 57 % faster than 7
-            // rounds of small ones, which a plain "fewer tiles than compute units" rule gets wrong).
-            int tm = 128, tn = 128;
-            if (fused16_preferred(s, false)) fused16_tile(s, tm, tn);
-            else if (s <= 4 || s == 6) { tm = 128; tn = 128; }
-            else { tm = 128; tn = 64; }
-            const long long tiles = (long long)((m + tm - 1) / tm) * ((n + tn - 1) / tn);
             const long long small_tiles = (long long)((m + 63) / 64) * ((n + 63) / 64);
             const long long limit = g_small_below_tiles.load();
             bool small;
@@ -1128,10 +1142,7 @@ static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, b
                     return s >= 7 || (s <= 3 && kp >= 1024 && small_tiles <= cus)
                                ? launch_gemm_halves16(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st)
                                : launch_gemm_halves(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
-                static constexpr double kSmallSpeed[kSmallMaxS + 1] = {0, 0.7, 0.63, 0.69, 0.74, 0.70, 0.76, 0.87, 0.72, 0.80, 0.93, 0.9, 0.9};
-                const double tabulated = fused16_preferred(s, false) ? fused16_launch_cost(s, m, n, cus) : launch_cost(m, n, tm, tn, cus);
-                const double four_waves = launch_cost(m, n, 64, 64, cus) / kSmallSpeed[s];
-                small = small_tiles > tiles && four_waves < tabulated;
+                small = fused_small_tile(s, m, n);
                 // The streaming kernel (gemm_passes_dev.h) where the launch takes less time (gemm_passes.hip).  Up to k = 128 the choice
                 // between the other tiles stands as tests/test_gpu_parity.py has it, though it is behind there (2500 x 2500 x 100, s = 7
                 // 40.5 against 32.9).
@@ -1141,8 +1152,12 @@ static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, b
                     const PassShape shape = gemm_one_pass_shape(s, m, n, kp, om, on);
                     if (shape != kNoPasses) return launch_gemm_passes(shape, s, m, n, kp, s, pA, pB, eA, eB, C, ldc, Q, st);
                 }
-            } else
+            } else {
+                int tm, tn;
+                fused_tabulated_tile(s, tm, tn);
+                const long long tiles = (long long)((m + tm - 1) / tm) * ((n + tn - 1) / tn);
                 small = tiles < limit && small_tiles > tiles;     // test knob: a plain threshold on the tile count
+            }
             if (small)
                 return dispatch_fused_small(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
         }

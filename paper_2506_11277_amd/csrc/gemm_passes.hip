@@ -74,16 +74,23 @@ PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn)
     return pairs < runs ? kPassSmall : kPassWide;
 }
 
-// Which shape, if any (GEMM phases in us, s = 11 / 13 / 16 / 18).
+// 10 ... 20 slices (phases in us, s = 11 / 13 / 16 / 18).
 // Up to one tile of 32 x 32 per compute unit, and up to 1.75 where the products repay a second round: these, k in eighths
 // (402^3 before 25.7 / 33.9 / 44.7 / 62.8, now 16.1 / 18.8 / 23.0 / 26.0; 1.64 tiles: 600 x 700 x 384 21.8 / 28.0 / 36.1 / 49.1, 23.6 / 28.1 / 34.6 / 40.4,
 // 600 x 700 x 188 17.6 / 21.8 / 27.1 / 36.5, 20.8 / 23.9 / 28.5 / 33.0; 800^3, 2.4 tiles, 40.6 / 54.8 / 75.1 / 102, 53.1 / 66.2 / 84.7 / 100;
 // 10 slices have a kernel of one pass there).
 // Then, up to one 64 x 64 tile per compute unit, the one-pass kernels on that tile with 512 registers to a wavefront up to 16
-// slices (800^3: against 49.8 / 65.2 / 83.2 in passes; 18: 95.0).
-// Up to 12 slices the fixed costs of two passes are only repaid by several rounds or a longer k (s = 11, one-pass kernel against
-// passes: 1000 x 1100 x 500 39.7 / 46.3, 1038 x 2512 x 66 33.5 / 36.3, but 1300^3 119 / 114, 3000 x 3000 x 500 234 / 219).
-// 128 x 64 or 64 x 64 by rounds of the chip: two 64 x 64 tiles at a time cost a compute unit 1.04 of a 128 x 64 one ;
+// slices (800^3: against 49.8 / 65.2 / 83.2 in passes; 18: 95.0), beyond at short k (calls, one-pass kernel against passes: s = 19 896 x 832 x 113
+// 31.2 / 34.2, 704 x 1240 x 167 45.8 / 49.8; s = 17 908 x 717 x 103 26.9 / 27.9, 640 x 1253 x 448 60.9 / 60.6; s = 18 978 x 768 x 86 30.1 / 29.4, 896 x 418 x 118
+// 28.3 / 28.7).
+// 10 ... 12 slices by the time of the launches; the one-pass kernel, 128 x 64 or 64 x 64 tiles, stays where the figures are even, and at the
+// shortest contractions (s = 11 768 x 3372 x 116 34.9 against 37.4).  What decides is rounds: it is 5 to 10 percent ahead in whole ones (s = 10, calls: 1280^3 91.2 against 100, 1872^3
+// 253 / 274, 384 x 3066 x 2801 207 / 239; s = 11 604 x 1811 x 5512 426 / 460), behind where its last one is nearly empty and pairs of
+// 64 x 64 tiles fit (s = 12 2688 x 2368 x 286 161 / 139, s = 11 1614 x 2688 x 423 128 / 117, s = 10 4537 x 599 x 576 93.4 / 87.9).
+// Launches long enough to sit at the power cap run 5 percent faster in passes of 128 x 64 tiles than the fit has them (4073^3, s = 11 2622 / 2465; 3746^3,
+// s = 12 2483 / 2326).  Operands badly scaled
+// along k, so that every slice has digits: products with zero slices draw less power, and their figures mislead.
+// Beyond, 128 x 64 or 64 x 64 by rounds of the chip: two 64 x 64 tiles at a time cost a compute unit 1.04 of a 128 x 64 one;
 // at short k the 128 x 64 tile also pays for copies and epilogues that nothing hides (2085 x 4740 x 1000, 4.98 against 4.83
 // rounds, s = 13 580 / 584, 18 953 / 940; 3000 x 3000 x 500, 4.41 against 4.31, s = 13 306 / 280; 2207^3, 2.46 against 2.39, 693 / 627).
 PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
@@ -97,11 +104,20 @@ PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
     const PassPlan P = pass_plan(s);
     for (int p = 0, d = 0; p + 1 < P.n; ++p)
         if ((d += P.w[p]) % Q != 0) return kNoPasses;                // a level of Q diagonals straddles two passes
-    const long long small = tiles(64, 64), wide = tiles(128, 64);
-    if (small <= cus) return s <= 16 ? kNoPasses : kPassSmall;
-    if (s <= 12 && !(kp >= 1024 || (kp >= 384 && wide > cus))) return kNoPasses;
-    const double rounds = (double)wide / cus, whole = (double)((wide + cus - 1) / cus);
-    return 1.04 * pair_rounds(s, small, cus) < (0.8 * whole + 0.2 * rounds) * (1.0 + 40.0 / kp) ? kPassSmall : kPassWide;
+    if (tiles(64, 64) <= cus) return s <= 16 || kp < (s == 18 ? 256 : 512) ? kNoPasses : kPassSmall;
+    const double small = pair_rounds(s, order_blocks(m, n, 64, 64), cus);
+    const long long blocks = order_blocks(m, n, 128, 64);
+    const double wide = single_rounds(s, blocks, cus);
+    if (s > 12) return 1.04 * small < wide * (1.0 + 40.0 / kp) ? kPassSmall : kPassWide;
+    static constexpr LaunchTime kPairs[3] = {{1.034, 7.3, 8.0}, {1.0, 7.3, 8.0}, {0.97, 7.3, 8.0}}, kLone{1.0, 10.3, 6.7};
+    static constexpr LaunchTime kOne{1.01, 5.2, 4.6}, kOne64[3] = {{1.178, 9.2, 5.5}, {1.12, 9.2, 5.5}, {1.168, 9.2, 5.5}};
+    const double x = 1e-3 * kp * (s * (s + 1) / 2);
+    const double pairs = kPairs[s - 10].us(small, x);
+    double lone = s == 10 ? 1e30 : kLone.us(wide, x);              // (no 128 x 64 tile in passes for 10 slices: nowhere ahead)
+    if (lone > 400.0) lone *= 0.95;
+    const double one = fused_small_tile(s, m, n) ? kOne64[s - 10].us(0.5 * single_rounds(s, tiles(64, 64), cus), x) : kOne.us(wide, x);
+    if (kp <= 128 || (pairs < lone ? pairs : lone) >= 0.985 * one) return kNoPasses;
+    return pairs < lone ? kPassSmall : kPassWide;
 }
 
 hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,

@@ -520,7 +520,8 @@ hipError_t launch_pass_plan(int m, int n, int kp, int stride, const int8_t *pA, 
     {                                                                                                                       \
         if (small) return launch_pass_plan<PassTileSmall, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);             \
         using Wide = std::conditional_t<(S_ >= 10), PassTileWide, PassTileRuns>;                                            \
-        return launch_pass_plan<Wide, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);                                 \
+        if constexpr (S_ == 10) return hipErrorInvalidValue;                   /* (nowhere ahead: gemm_passes_shape) */     \
+        else return launch_pass_plan<Wide, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);                            \
     }
 
 }  // namespace oz

@@ -283,6 +283,8 @@ hipError_t launch_gemm_vectors(int m, int n, int k, const double *A, int lda, co
                                int8_t *pA, int8_t *pB, double *C, int ldc, int Q, hipStream_t st);
 // false while a test knob steers the choice of kernel (the parity tests then look at the planes of both operands)
 bool fused_automatic();
+// equal counts up to 12 in the kernels of one pass: 64 x 64 tiles by four wavefronts rather than the tabulated ones
+bool fused_small_tile(int s, int m, int n);
 // product sets beyond the fused kernels (planes with the slices per entry of blocks_plan); totals: blocks_totals_bytes()
 hipError_t launch_gemm_blocks(int m, int n, int kp, int sA, int sB, bool all_products, const int8_t *pA,
                               const int8_t *pB, const int32_t *eA, const int32_t *eB, double *C, int ldc,

@@ -69,11 +69,14 @@ def test_planes_too_large_for_the_offsets_of_a_run():
 
 
 # Shapes where tiles in pairs or runs, or passes, are behind: one XCD with a tile more than it has places for, a round and a bit with few
-# slices
+# slices, whole rounds with 10 and 11, a single round of short contractions
 @pytest.mark.parametrize("m,n,k,s,name", [
     (3200, 613, 1152, 9, "tile 128x64"), (731, 3573, 3538, 5, "gemm_fused16_kernel<5> tile 128x128"),
     (5120, 512, 5208, 6, "gemm_fused16_kernel<6> tile 128x128"), (1664, 1664, 1664, 4, "gemm_fused16_kernel<4> tile 128x128"),
-    (384, 5760, 3648, 6, "gemm_fused16_kernel<6> tile 128x128")])
+    (384, 5760, 3648, 6, "gemm_fused16_kernel<6> tile 128x128"),
+    (1280, 1280, 1280, 10, "gemm_fused_kernel<10>"), (4005, 960, 257, 10, "gemm_fused_kernel<10>"), (384, 3066, 2801, 10, "gemm_fused_kernel<10>"),
+    (604, 1811, 5512, 11, "gemm_fused_kernel<11>"), (1090, 1090, 1090, 11, "gemm_fused_kernel<11>"),
+    (896, 832, 113, 19, "gemm_fused_kernel<19>"), (908, 717, 103, 17, "gemm_fused_kernel<17>")])
 def test_where_the_larger_tiles_stay(m, n, k, s, name):
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the expectations are worked out for 256 compute units")
@@ -84,16 +87,25 @@ def test_where_the_larger_tiles_stay(m, n, k, s, name):
 
 
 # 128 x 64 tiles: one partly filled round, ragged edges; 64 x 64 tiles: a second work-group on some compute units, edges; two
-# k-steps, an odd number of k-steps of 64, many
+# 64-deep k-steps (k = 40 and 65) and many
 @pytest.mark.parametrize("s", range(10, 21))
-@pytest.mark.parametrize("m,n,k,tile", [(1025, 1153, 1030, "128x64"), (2050, 2020, 1100, "64x64"), (1030, 1400, 65, "64x64"),
-                                        (2300, 4600, 40, "64x64"), (80, 20000, 400, "64x64")])
-def test_passes_through_lds(m, n, k, tile, s):
+@pytest.mark.parametrize("m,n,k,tile,least", [(1025, 1153, 1030, "128x64", 13), (2050, 2020, 1100, "64x64", 10), (1030, 1400, 65, "64x64", 13),
+                                              (2300, 4600, 40, "64x64", 13), (80, 20000, 400, "64x64", 10)])
+def test_passes_through_lds(m, n, k, tile, least, s):
     A, B = workloads.lognormal(m, n, k, 1.0, 70 + s)
     special(A, B)
-    name = f"gemm_passes_kernel<{s}> tile {tile}" if s > 12 or k > 384 else ""
+    name = f"gemm_passes_kernel<{s}> tile {tile}" if s >= least else ""
     both_ways(A, B, s, s, name)
     both_ways(A, B, s, s, name, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=3)
+
+
+# 11 and 12 slices take 128 x 64 tiles where the launch is long
+@pytest.mark.parametrize("s", [11, 12])
+def test_long_launches_of_few_passes(s):
+    m, n, k = 1030, 1000, 11000
+    A, B = workloads.lognormal(m, n, k, 1.0, 60 + s)
+    special(A, B)
+    both_ways(A, B, s, s, f"gemm_passes_kernel<{s}> tile 128x64")
 
 
 # 32 x 32 tiles, k in eighths: fewer k-blocks than wavefronts, one more than a round of them, edges of tiles, the ends of the rule; any
