@@ -162,22 +162,40 @@ __global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restri
 // takes the k-blocks w, w + 8, ...; row l of the products frees slice l of A and slice S - 1 - l of B, which are
 // loaded again for its next k-block at once.  The eight sums per output meet in LDS, kRound diagonals at a time;
 // wavefront w finishes accumulator registers 2 w and 2 w + 1.
-// Tile of a work-group: equal runs of tiles to the XCDs, in strips of four tile rows.  (Four tiles of a 64 x 64 one after the
+// Tile of a work-group: equal runs of tiles to the XCDs, in strips of four tile rows -- of all tile rows where there are twice as many tile
+// columns or more.  (Four tiles of a 64 x 64 one after the
 // other, with nothing to do for those beyond the edge, gave some XCDs half as many tiles again where a side has an odd number of
-// them: 130 x 1500 x 3000, s = 3 / 7 20.2 / 44.1 us, now 12.9 / 25.1; 32 x 6000 x 200, s = 7 14.2, now 9.0.)  The tile's place is on the way to the
-// first load: one multiplication with magic = ceil(2^32 / (4 tiles_n)) in place of the three divisions of tile_of_block(), which
-// take 0.2 us of 12 (exact while the number of tiles times 4 tiles_n is below 2^32: some thousand tiles at most come here).
-__device__ __forceinline__ void tile_in_strips(unsigned b, int tiles_m, int tiles_n, unsigned magic, int &tm, int &tn)
+// them: 130 x 1500 x 3000, s = 3 / 7 20.2 / 44.1 us, now 12.9 / 25.1; 32 x 6000 x 200, s = 7 14.2, now 9.0.  What the order costs beyond the product
+// shows in the NEXT call's set-up, which writes planes that L2s of other XCDs hold: whole columns leave most slices of B with
+// the XCD that wrote them, rows and columns of strips do not.  Calls, 160 random sizes, against the groups of four, strips / whole columns: twice as many
+// columns or more 0.970 / 0.960, slowest 1.05 / 1.01, and 256 x 1100 x 410, s = 7 20.7, 22.0 / 20.4; about square 0.995 / 1.001; more rows 0.963 / 1.004.  One
+// in thirty stays 2 to 4 percent behind the groups of four, 384^3 s = 7 11.9 against 12.2 among them.)
+// The tile's place is on the way to the first load: one multiplication with magic = ceil(2^32 / d), d = 4 tiles_n or tiles_m, in place of the three
+// divisions of tile_of_block(), which take 0.2 us of 12 (exact while the number of tiles times d is below 2^32: some thousand tiles at most come
+// here).
+__device__ __forceinline__ void tile_in_strips(unsigned b, int tiles_m, int tiles_n, unsigned magic, int whole, int &tm, int &tn)
 {
     const unsigned nb = (unsigned)(tiles_m * tiles_n), xcd = b & 7, rem = nb & 7;
     const unsigned lin = xcd * (nb >> 3) + (xcd < rem ? xcd : rem) + (b >> 3);
-    const unsigned strip = __umulhi(lin, magic), in = lin - strip * (4u * tiles_n);
-    const unsigned left = tiles_m - 4 * strip;                // rows of this strip, if fewer than four
+    const unsigned q = __umulhi(lin, magic);
+    if (whole) {
+        tn = (int)q;
+        tm = (int)(lin - q * (unsigned)tiles_m);
+        return;
+    }
+    const unsigned in = lin - q * (4u * tiles_n);
+    const unsigned left = tiles_m - 4 * q;                    // rows of this strip, if fewer than four
     const unsigned c = left >= 4 ? in >> 2 : left == 3 ? in / 3u : left == 2 ? in >> 1 : in;
     tn = (int)c;
-    tm = (int)(4 * strip + in - c * (left >= 4 ? 4u : left));
+    tm = (int)(4 * q + in - c * (left >= 4 ? 4u : left));
 }
-inline unsigned strip_magic(int tiles_n) { return (unsigned)(((1ULL << 32) + 4ULL * tiles_n - 1) / (4ULL * tiles_n)); }
+// (up to four tile rows the two are the same)
+inline int strip_whole(int tiles_m, int tiles_n) { return tiles_m > 4 && tiles_n >= 2 * tiles_m; }
+inline unsigned strip_magic(int tiles_m, int tiles_n)
+{
+    const unsigned long long d = strip_whole(tiles_m, tiles_n) ? tiles_m : 4ULL * tiles_n;
+    return (unsigned)(((1ULL << 32) + d - 1) / d);
+}
 
 template <int S>
 struct CfgEighths {
@@ -189,11 +207,11 @@ template <int S>
 __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restrict__ pA, const int8_t *__restrict__ pB,
                                                            const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
                                                            double *__restrict__ C, int ldc, int m, int n, int KB,
-                                                           int tiles_m, int tiles_n, unsigned magic, int Q)
+                                                           int tiles_m, int tiles_n, unsigned magic, int whole, int Q)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     int tm, tn;
-    tile_in_strips(blockIdx.x, tiles_m, tiles_n, magic, tm, tn);
+    tile_in_strips(blockIdx.x, tiles_m, tiles_n, magic, whole, tm, tn);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t row_bytes = (size_t)KB * (S * kFragBytes);
@@ -273,11 +291,11 @@ template <int... Ws>
 __global__ __launch_bounds__(512) void gemm_eighths_passes_kernel(
     const int8_t *__restrict__ pA, const int8_t *__restrict__ pB, const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
     double *__restrict__ C, int ldc, int m, int n, int KB, int stride, int tiles_m, int tiles_n, unsigned magic,
-    int Q)
+    int whole, int Q)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     int tm, tn;
-    tile_in_strips(blockIdx.x, tiles_m, tiles_n, magic, tm, tn);
+    tile_in_strips(blockIdx.x, tiles_m, tiles_n, magic, whole, tm, tn);
     const unsigned lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const size_t kb_bytes = (size_t)stride * kFragBytes, row_bytes = (size_t)KB * kb_bytes;
@@ -390,7 +408,7 @@ hipError_t launch_eighths(int m, int n, int kp, const int8_t *pA, const int8_t *
     if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgEighths<S>::LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
     note_gemm_kernel("gemm_eighths_kernel<%d> tile 32x32, 8 wavefronts, k in eighths", S);
-    kern<<<(unsigned)(tiles_m * tiles_n), 512, CfgEighths<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, strip_magic(tiles_n), Q);
+    kern<<<(unsigned)(tiles_m * tiles_n), 512, CfgEighths<S>::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, strip_magic(tiles_m, tiles_n), strip_whole(tiles_m, tiles_n), Q);
     return hipGetLastError();
 }
 
@@ -405,7 +423,7 @@ hipError_t launch_eighths_passes(int m, int n, int kp, int stride, const int8_t 
     const int tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
     note_gemm_kernel("gemm_eighths_passes_kernel<%d> tile 32x32, 8 wavefronts, k in eighths", (Ws + ...));
     kern<<<(unsigned)(tiles_m * tiles_n), 512, LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride, tiles_m, tiles_n,
-                                                    strip_magic(tiles_n), Q);
+                                                    strip_magic(tiles_m, tiles_n), strip_whole(tiles_m, tiles_n), Q);
     return hipGetLastError();
 }
 

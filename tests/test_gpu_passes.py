@@ -111,7 +111,7 @@ def test_long_launches_of_few_passes(s):
 # 32 x 32 tiles, k in eighths: fewer k-blocks than wavefronts, one more than a round of them, edges of tiles, the ends of the rule; any
 # level size
 @pytest.mark.parametrize("s", range(11, 21))
-@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (33, 31, 130), (97, 70, 289), (512, 512, 64), (512, 896, 560), (40, 1000, 1100), (31, 65, 6657)])
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (33, 31, 130), (161, 1300, 70), (97, 70, 289), (512, 512, 64), (512, 896, 560), (40, 1000, 1100), (31, 65, 6657)])
 def test_passes_of_a_divided_contraction(m, n, k, s):
     A, B = workloads.lognormal(m, n, k, 1.0, 90 + s)
     if m > 4:

@@ -44,7 +44,7 @@ def special(A, B):
 
 @pytest.mark.parametrize("s", range(1, 11))
 @pytest.mark.parametrize("m,n,k,kernel", [
-    (1, 1, 1, "eighths"), (33, 31, 130, "eighths"), (512, 512, 64, "eighths"), (97, 70, 1000, "eighths"), (40, 300, 2100, "eighths"),
+    (1, 1, 1, "eighths"), (33, 31, 130, "eighths"), (161, 1300, 70, "eighths"), (300, 610, 140, "eighths"), (512, 512, 64, "eighths"), (97, 70, 1000, "eighths"), (40, 300, 2100, "eighths"),
     (705, 961, 65, "halves"), (1024, 1000, 129, "halves"), (65, 8000, 700, "halves"),
 ])
 def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
