@@ -357,33 +357,41 @@ hipError_t launch_split(char side, int rows, int cols, const double *X, int ldx,
 // Rows to a work-group.  Four put the most compute units to work (a compute unit takes in some 10-25 GB/s whatever
 // it asks for: 1024^3 s = 7 27.1 / 21.3 / 21.5 us for 16 / 8 / 4 rows, 256 x 256 x 1024 25.4 / 18.3 / 15.4, 1024 x 1024 x 2048 41.0 /
 // 25.9 / 24.4, 2048^3 40.9 / 42.7 / 37.5; two rows: 29.7 in the last but one); eight where there are plenty of rows and the
-// pieces of cache lines begin to count.  Where that is depends on k (eight against four rows, m = n = 4096 / 5120 / 6144 / 8192: k =
+// pieces of cache lines begin to count.  With few slices, where that is depends on k (one call repeated, eight against four rows, m = n = 4096 / 5120 / 6144 / 8192: k =
 // 1024, s = 3 30.1 and 32.4 / 34.9 and 38.2 / 39.8 and 43.2 / 47.8 and 52.0, k = 2048, s = 3 54.5 and 48.2 / 65.6 and 58.0 / 78.2 and 75.3 /
 // 103 and 107, s = 7 63.2 and 57.9 / 80.1 and 92.1 / 98.2 and 112); the line is where the longest contractions change over
 // at few slices, and what it costs the shorter ones below it is at most 3 % of a call (12000 x 200 x 1000, s = 7: 113 and 117)
 //
-// More slices write more: where the planes (slices x rows x k bytes) no longer fit the caches, eight rows, whose pieces fill whole
-// lines, are ahead whatever k is (event times, us, four and eight rows: 3000 x 3000 x 2500 s = 13 98 and 74, 2500 x 2400 x 2500 81 and 73,
-// 2600 x 2600 x 3000 111 and 84, but s = 7 55 and 60, 57 and 65; 5120^2 x 2048 s = 7 92 and 80; 4096^2 x 2048, 109 MB, 42 and 45), and so
-// they are from 6000 rows on at k up to 256 (6001 x 5200 x 256 26.1 and 23.3, 3000 x 3000 x 256 19.7 and 19.1; k = 512 23.5 and 27.0); with
-// fewer than 4096 rows too few work-groups are left (1400 x 1400 x 3000 s = 18 47 and 57).
+// More slices write more, and eight rows, whose pieces fill whole lines, are ahead once the planes outgrow the caches: by bytes, a
+// row of A counting more than a column of B, which is read in whole lines whichever way (calls, us, four and eight rows, operands that change from one to
+// the next: 2600 x 2600 x 3000 s = 7, 140 MB, A alone 55, 459 and 444; 3736 x 129 x 3968 s = 7, 107, 141 and 128; 7040 x 75 x 1152 s = 9, 74, 77 and
+// 71; but 35 x 4096 x 1792 s = 9, 67, 57.5 and 65.5; 2112^3 s = 5, 46, 149 and 163; even at 2500 x 2400 x 2500 s = 7, 88; from twelve
+// slices on ahead whichever operand they are of, 48 x 5568 x 1367 s = 13, 103, 102 and 98).  k up to 256: from 6000 rows on (6001 x 5200 x 256 26.1 and 23.3, 3000 x 3000 x 256 19.7
+// and 19.1; k = 512 23.5 and 27.0).  With fewer than 3000 rows too few work-groups are left.
 static int scale_split_rows(int m, int n, int kp, int c)
 {
     const long long rows = (long long)m + n;
-    return (kp <= 2048 && rows >= 12288) || (kp <= 256 && rows >= 6000) || (rows >= 4096 && c * rows * kp >= 118000000LL) ? 8 : 4;
+    const double bytes = (double)c * kp;                  // of a row
+    const bool large = rows >= 3000 && (bytes * (m + 0.4 * n) >= 70e6 || (c >= 12 && bytes * rows >= 80e6));
+    return (kp <= 2048 && rows >= 12288) || (kp <= 256 && rows >= 6000) || large ? 8 : 4;
 }
 
-// Wavefronts: 64 k (four rows) or 32 k (eight) to each, up to sixteen; with four rows up to eight where there are two work-groups
-// for every compute unit, so that one loads while the other stores (sixteen and eight, us, s = 7: 1600 x 1600 x 1536 31.7 and 28.1, 3000 x 3000 x 1536
-// 44.3 and 37.6, 2000 x 2100 x 4000 76 and 65, 1024^3 20.6 and 20.0; 500 x 500 x 2048, 250 work-groups, 20.9 and 21.4) -- and planes that
-// fit the caches (2500 x 2400 x 2500 s = 9 58 and 64)
+// Wavefronts: 64 k (four rows) or 32 k (eight) to each, up to sixteen.  With four rows, two work-groups for every compute unit and planes up to
+// 100 MB, eight, so that one work-group loads while another stores, where sixteen leave much of a compute unit or of their last sweep over k empty: at 14 ...
+// 24 times 64 k (one full work-group to a compute unit, or a second sweep at most half full), at 34 ... 36 and from 50 on; at 26 ... 32 and 38 ... 48 their
+// sweeps are full and they are even or ahead, but where columns of B, up to nine slices, are what there is most of, eight keep ahead up to 40.  Calls, sixteen
+// and eight, geometric means over 1200 random sizes: kp = 768 0.986, 896 and 1024 1.026, 1152 1.047, 1536 1.021, 1664 ... 2048 1.000, 2176 1.014, 2432 ...
+// 3072 0.985, 3328 1.07, 3712 1.03 (1024^3 s = 7 35.2 and 34.5, 1600 x 1600 x 1536 108 and 103, 20 x 5869 x 2368 s = 5 70.2 and 67.6, 2091 x 75 x 1792 s = 5 27.1
+// and 27.5, 2432 x 105 x 2812 s = 2 29.6 and 33.9).  Few slices store little: from 640 on where there are 4096 rows.  Against sixteen throughout, with
+// the rows above: 1.022 over 1440 sizes, slowest 0.91; operands that the caches still hold, as after the estimator, lose up to 4 percent (1280^3 s = 6 95.8
+// and 99).
 static int scale_split_waves(int m, int n, int rows, int kp, int c)
 {
     const int waves = kp / 16 * rows / 16;
-    const int most = rows == 4 && kp > 512 && ((long long)m + n) / rows >= 2LL * device_cus() &&
-                             c * ((long long)m + n) * kp < 100000000LL
-                         ? 8
-                         : 16;
+    const long long R = (long long)m + n;
+    const bool apart = (kp >= 896 && kp <= 1536) || (kp >= 2176 && kp <= 2304) || kp >= 3200 || (n >= m && c <= 9 && kp >= 1664 && kp <= 2560) ||
+                       (R >= 4096 && ((c <= 3 && kp >= 640 && kp <= 2304) || (c <= 7 && kp == 640)));
+    const int most = rows == 4 && apart && R / rows >= 2LL * device_cus() && c * R * kp < 100000000LL ? 8 : 16;
     if (waves <= most) return waves < 1 ? 1 : waves;
     const int sweeps = (waves + most - 1) / most;
     return most == 16 ? 16 : (waves + sweeps - 1) / sweeps;       // (of eight, no more than the sweeps over k keep busy)
@@ -405,7 +413,7 @@ long long scale_split_threads(int m, int n, int k)
     if (m <= 0 || n <= 0 || k <= 0) return 0;
     const int kp = round_up(k, kPad);
     if (kp > 2048 && (kp > 4096 || ((long long)m + n) * kp > 18LL << 20)) return 0;
-    const int rows = scale_split_rows(m, n, kp, 0);          // (more slices: other shapes of some thousand rows at most)
+    const int rows = scale_split_rows(m, n, kp, 0);          // (more slices: other shapes, below 12288 rows)
     const long long threads = scale_split_groups(m, n, rows) * 64 * scale_split_waves(m, n, rows, kp, 0);
     return threads < 1LL << 32 ? threads : 0;
 }
@@ -430,7 +438,12 @@ hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, con
         const int sweep = scale_split_waves(m, n, PR, kp, c) * 16 * (16 / PR);           // k of all wavefronts
         switch ((kp + sweep - 1) / sweep) {
 #define OZ_CASE(NV_) case NV_: launch(PRC, std::integral_constant<int, NV_>{}); return hipGetLastError();
-            OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8)
+            OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(7) OZ_CASE(8)
+            case 6:                                             // (of eight rows only: scale_split_waves)
+                if constexpr (PR == 8) {
+                    launch(PRC, std::integral_constant<int, 6>{});
+                    return hipGetLastError();
+                }
 #undef OZ_CASE
         }
         return hipErrorInvalidValue;

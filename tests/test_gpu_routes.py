@@ -67,7 +67,7 @@ def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
                                    (12000, 300, 1100)])
 @pytest.mark.parametrize("sA,sB,nearest", [(1, 1, False), (7, 7, True), (9, 9, False), (9, 10, True), (19, 18, False), (24, 32, True)])
 def test_scales_and_slices_in_one_launch(m, n, k, sA, sB, nearest):
-    # every number of sweeps over k, both panel heights, the limits of the rule, windows of slices that end on and off
+    # up to four sweeps over k (more: the test below), both panel heights, the limits of the rule, windows of slices that end on and off
     # a whole window, zero slices appended to the short operand, leading dimensions that are odd
     if m > 4000 and sA + sB > 19:
         pytest.skip("large shapes with one pair of windows only")
@@ -79,6 +79,31 @@ def test_scales_and_slices_in_one_launch(m, n, k, sA, sB, nearest):
     dB.copy_(torch.as_tensor(B))
     splitting = ozimmu.SPLIT_NEAREST if nearest else ozimmu.SPLIT_TRUNCATE
     check(ozimmu.dgemm3(dA, dB, sA, sB, splitting=splitting), A, B, sA, sB, nearest=nearest)
+
+
+# five to eight sweeps over k: four rows to a work-group (1100 x 1050: five, seven, eight; 4100 x 90: three of eight wavefronts), eight
+# rows (2500 x 1700: five to eight; 3003 x 37: six, with a last work-group of three rows), the ends of the rule by bytes (2000 x 2100 x 4000 with 6 and 7
+# slices)
+@pytest.mark.parametrize("nearest", [False, True])
+@pytest.mark.parametrize("m,n,k,s", [(1100, 1050, 2200, 7), (1100, 1050, 3401, 7), (1100, 1050, 4090, 7), (4100, 90, 1099, 3), (2500, 1700, 2490, 13),
+                                     (2500, 1700, 2689, 13), (2500, 1700, 3200, 13), (2500, 1700, 4090, 13), (3003, 37, 2565, 13),
+                                     (2000, 2100, 4000, 6), (2000, 2100, 4000, 7)])
+def test_sweeps_of_the_one_launch_set_up(m, n, k, s, nearest):
+    print(f"{m}x{n}x{k} s={s}", flush=True)
+    assert ozimmu.lib().ozimmu_debug_setup_threads(m, n, k) > 0
+    A, B = workloads.lognormal(m, n, k, 1.0, 17 + s)
+    special(A, B)
+    dA, dB = ozimmu.colmajor_empty(m + 1, k)[1:, :], ozimmu.colmajor_empty(k + 3, n)[:k, :]
+    dA.copy_(torch.as_tensor(A))
+    dB.copy_(torch.as_tensor(B))
+    splitting = ozimmu.SPLIT_NEAREST if nearest else ozimmu.SPLIT_TRUNCATE
+    ws = torch.empty(ozimmu.lib().ozimmu_workspace_bytes2(m, n, k, s, s, 0), dtype=torch.uint8, device="cuda")
+    check(ozimmu.dgemm3(dA, dB, s, s, splitting=splitting, workspace=ws, check_finite=True), A, B, s, s, nearest=nearest)
+    for X in (dA, dB):                       # the last entry of either operand is looked at
+        X[-1, -1] = float("inf")
+        with pytest.raises(ozimmu.OzimmuError):
+            ozimmu.dgemm3(dA, dB, s, s, splitting=splitting, workspace=ws, check_finite=True)
+        X[-1, -1] = 0.0
 
 
 def test_more_rows_than_the_one_launch_set_up_has_threads_for():
