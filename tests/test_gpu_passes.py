@@ -86,6 +86,19 @@ def test_where_the_larger_tiles_stay(m, n, k, s, name):
     assert torch.equal(C, steered(lambda: ozimmu.dgemm(dA, dB, s)))
 
 
+@pytest.mark.parametrize("choice,name", [(1, "gemm_fused16_kernel<5> tile 128x128"), (2, "gemm_fused16_kernel<5> tile 128x64"),
+                                         (0, "gemm_passes_kernel<5>")])
+def test_a_forced_tile_is_the_one_that_runs(choice, name):
+    dA, dB = workloads.lognormal_device(3500, 3500, 300, 1.0, 19)
+    try:
+        ozimmu.debug_tile_choice(choice)
+        ozimmu.dgemm(dA, dB, 5)
+    finally:
+        ozimmu.debug_tile_choice(0)
+    if choice or torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert ozimmu.last_gemm_kernel().startswith(name), ozimmu.last_gemm_kernel()
+
+
 # 128 x 64 tiles: one partly filled round, ragged edges; 64 x 64 tiles: a second work-group on some compute units, edges; two
 # 64-deep k-steps (k = 40 and 65) and many
 @pytest.mark.parametrize("s", range(10, 21))
