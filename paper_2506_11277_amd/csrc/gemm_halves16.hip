@@ -17,7 +17,7 @@ namespace {
 using PassTileHalves = PassTile<2, 2, 10, 2>;       // 160 KiB
 
 template <int S>
-__global__ __launch_bounds__(PassTileHalves::THREADS, 2) void gemm_halves_kernel(
+__global__ __launch_bounds__(PassTileHalves::THREADS, 2) void gemm_halves16_kernel(
     const int8_t *__restrict__ pA, const int8_t *__restrict__ pB, const int32_t *__restrict__ eA,
     const int32_t *__restrict__ eB, double *__restrict__ C, int ldc, int m, int n, int KB, int tiles_m, int tiles_n, int Q)
 {
@@ -28,11 +28,11 @@ template <int S>
 hipError_t launch_halves16(int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA, const int32_t *eB,
                            double *C, int ldc, int Q, hipStream_t st)
 {
-    auto kern = gemm_halves_kernel<S>;
+    auto kern = gemm_halves16_kernel<S>;
     static std::atomic<unsigned long long> configured{0};
     if (hipError_t e = allow_dynamic_lds((const void *)kern, PassTileHalves::LDS, configured); e != hipSuccess) return e;
     const int tiles_m = (m + 63) / 64, tiles_n = (n + 63) / 64;
-    note_gemm_kernel("gemm_halves_kernel<%d> tile 64x64, 8 wavefronts, k in halves, 16x16x64", S);
+    note_gemm_kernel("gemm_halves16_kernel<%d> tile 64x64, 8 wavefronts, k in halves", S);
     kern<<<(unsigned)tile_order_blocks(tiles_m, tiles_n, false), PassTileHalves::THREADS, PassTileHalves::LDS, st>>>(
         pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, tiles_m, tiles_n, Q);
     return hipGetLastError();

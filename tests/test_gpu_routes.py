@@ -46,6 +46,7 @@ def special(A, B):
 @pytest.mark.parametrize("m,n,k,kernel", [
     (1, 1, 1, "eighths"), (33, 31, 130, "eighths"), (161, 1300, 70, "eighths"), (300, 610, 140, "eighths"), (512, 512, 64, "eighths"), (97, 70, 1000, "eighths"), (40, 300, 2100, "eighths"),
     (705, 961, 65, "halves"), (1024, 1000, 129, "halves"), (65, 8000, 700, "halves"),
+    (705, 961, 2049, "halves"), (1000, 1000, 1100, "halves"),
 ])
 def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
     # tiles of 32 x 32 (k in eighths) and of 64 x 64 (k in halves): every slice count, k-blocks that do not divide
@@ -57,6 +58,8 @@ def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
     dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
     C = ozimmu.dgemm(dA, dB, s)
     if torch.cuda.get_device_properties(0).multi_processor_count == 256 and 2 <= s <= 9:
+        if kernel == "halves" and (s >= 7 or (s <= 3 and k >= 1024)):
+            kernel = "halves16"
         assert ozimmu.last_gemm_kernel().startswith(f"gemm_{kernel}_kernel<{s}>"), ozimmu.last_gemm_kernel()
     check(C, A, B, s, s)
     check(ozimmu.dgemm3(dA, dB, s, s, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2), A, B, s, s, nearest=True, Q=2)
@@ -252,7 +255,7 @@ def test_six_slices_follow_the_same_rule_as_seven(n, k, kernel):
     A, B = workloads.lognormal(n, n, k, 1.0, 23)
     for s in (6, 7):
         C = ozimmu.dgemm(ozimmu.to_colmajor(A), ozimmu.to_colmajor(B), s)
-        assert ozimmu.last_gemm_kernel().startswith(f"gemm_{kernel}_kernel<{s}>"), ozimmu.last_gemm_kernel()
+        assert ozimmu.last_gemm_kernel().startswith(f"gemm_{kernel + '16' * (kernel == 'halves' and s == 7)}_kernel<{s}>"), ozimmu.last_gemm_kernel()
         check(C, A, B, s, s)
 
 
