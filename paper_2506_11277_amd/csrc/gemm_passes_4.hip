@@ -1,4 +1,4 @@
-// Slices streamed through a ring, one pass, 64 x 64 tiles: 4 ... 9 slices.
+// Slices streamed through a ring, one pass, 64 x 64 tiles and runs of 128 x 64: 4 ... 9 slices.
 #include "gemm_passes_dev.h"
 
 namespace oz {

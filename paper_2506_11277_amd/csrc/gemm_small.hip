@@ -14,15 +14,14 @@ namespace oz {
 namespace {
 
 // ---- tile 64 x 64, 2 x 2 x 2 wavefronts (m, n, k), operands staged through LDS (2 ... 6 slices) -----------------------------------
-// A stage is two 32-deep k-blocks of the four fragment rows; ring of three stages where they fit the LDS, else two.
+// A stage is two 32-deep k-blocks of the four fragment rows; ring of three stages.
 // The loop is the hand-pipelined one of gemm_fused_kernel: slices of A from the last to the first, operands of slice
 // l - 1 read while the products of slice l run, the end-of-stage barrier before the products of slice 0, copies of a
 // later stage issued one at a time behind single matrix instructions.
 template <int S>
 struct CfgHalves {
     static constexpr int STAGE = 4 * 2 * S * kFragBytes;
-    static constexpr int NSTG = 3 * STAGE <= kLdsBytes ? 3 : 2;
-    static constexpr int LDS = NSTG * STAGE;                // also holds the exchange of the sums: 16 S KiB
+    static constexpr int LDS = 3 * STAGE;                   // also holds the exchange of the sums: 16 S KiB
     static_assert(LDS <= kLdsBytes, "stages do not fit LDS");
 };
 
@@ -33,7 +32,7 @@ __global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restri
                                                           int tiles_m, int tiles_n, int Q)
 {
     using G = CfgHalves<S>;
-    constexpr int NSTG = G::NSTG, STAGE = G::STAGE, CHUNK = 2 * S * kFragBytes, NW = 8, NU = S;
+    constexpr int STAGE = G::STAGE, CHUNK = 2 * S * kFragBytes, NW = 8, NU = S;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
     int tm, tn;
@@ -55,12 +54,12 @@ __global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restri
         lds_dma16_at<i * NW * kFragBytes>(src[i], voff, ldsbuf);
     };
     const int nst = KB / 2;
-    static_for<0, NSTG - 1>([&](auto P) {
+    static_for<0, 2>([&](auto P) {
         constexpr int p = decltype(P)::value;
         const unsigned v = lane * 16 + (unsigned)(p < nst ? p : nst - 1) * (unsigned)CHUNK;
         static_for<0, NU>([&](auto I) { issue(I, v, ldsw + p * STAGE); });
     });
-    wait_vmcnt<(NSTG - 2) * NU>();
+    wait_vmcnt<NU>();
     __syncthreads();
 
     v16i acc[S];
@@ -80,10 +79,9 @@ __global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restri
     int buf = 0;
     for (int st = 0; st < nst; ++st) {
         // (towards the end the copies and the reads ahead go on, of the last stage again: nobody uses them)
-        const int ahead = st + NSTG - 1 < nst ? st + NSTG - 1 : nst - 1;
+        const int ahead = st + 2 < nst ? st + 2 : nst - 1;
         const unsigned vnext = lane * 16 + (unsigned)ahead * (unsigned)CHUNK;
-        const int buf1 = buf + 1 == NSTG ? 0 : buf + 1;
-        const int bufc = NSTG == 2 ? buf1 : (buf1 + 1 == NSTG ? 0 : buf1 + 1);
+        const int buf1 = buf + 1 == 3 ? 0 : buf + 1, bufc = buf1 + 1 == 3 ? 0 : buf1 + 1;
         const unsigned ldsnext = ldsw + bufc * STAGE;
         const unsigned char *cur = lds + buf * STAGE, *nxt = lds + buf1 * STAGE;
         if constexpr (NU > NSLOT) static_for<0, NU>([&](auto I) { issue(I, vnext, ldsnext); });
@@ -99,7 +97,7 @@ __global__ __launch_bounds__(512) void gemm_halves_kernel(const int8_t *__restri
                 constexpr int hh = decltype(HH)::value, h = l == 0 ? S - 1 - hh : hh;
                 if constexpr (l == 0 && hh == 0) {
                     // nothing of this stage is left to read, and the next one must have landed
-                    wait_vmcnt<(NSTG - 2) * NU>();
+                    wait_vmcnt<NU>();
                     __syncthreads();
                     afn = readA(S - 1, nxt);
                     bfn = readB(0, nxt);
