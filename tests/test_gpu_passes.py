@@ -135,11 +135,13 @@ def test_passes_of_a_divided_contraction(m, n, k, s):
         both_ways(A, B, s, s, name, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=Q)
 
 
-# levels that would straddle two passes take the one-pass kernels; counts that differ little run as equal ones
-@pytest.mark.parametrize("sA,sB,Q", [(13, 13, 2), (13, 13, 4), (16, 16, 2), (12, 13, 1), (18, 17, 3), (20, 19, 1), (10, 14, 1)])
-def test_levels_and_different_counts(sA, sB, Q):
+# levels that would straddle two passes take the one-pass kernels, levels that end with a pass do not; counts that differ little run
+# as equal ones
+@pytest.mark.parametrize("sA,sB,Q,passes", [(13, 13, 4, False), (16, 16, 2, False), (13, 13, 2, True), (12, 13, 1, True), (18, 17, 3, True), (20, 19, 1, True),
+                                            (10, 14, 1, True)])
+def test_levels_and_different_counts(sA, sB, Q, passes):
     A, B = workloads.lognormal(1100, 1090, 300, 1.0, 5)
-    both_ways(A, B, sA, sB, "", level_diagonals=Q)
+    both_ways(A, B, sA, sB, f"gemm_passes_kernel<{max(sA, sB)}>" if passes else "gemm_fused_kernel", level_diagonals=Q)
 
 
 def test_leading_dimensions_and_odd_alignment():
