@@ -74,7 +74,7 @@ PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn)
     return pairs < runs ? kPassSmall : kPassWide;
 }
 
-// 10 ... 20 slices (phases in us, s = 11 / 13 / 16 / 18).
+// 10 ... 20 slices (phases in us, s = 11 / 13 / 16 / 18; lognormal operands up to here and in the last paragraph).
 // Up to one tile of 32 x 32 per compute unit, and up to 1.75 where the products repay a second round: these, k in eighths
 // (402^3 before 25.7 / 33.9 / 44.7 / 62.8, now 16.1 / 18.8 / 23.0 / 26.0; 1.64 tiles: 600 x 700 x 384 21.8 / 28.0 / 36.1 / 49.1, 23.6 / 28.1 / 34.6 / 40.4,
 // 600 x 700 x 188 17.6 / 21.8 / 27.1 / 36.5, 20.8 / 23.9 / 28.5 / 33.0; 800^3, 2.4 tiles, 40.6 / 54.8 / 75.1 / 102, 53.1 / 66.2 / 84.7 / 100;
@@ -89,7 +89,8 @@ PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn)
 // 64 x 64 tiles fit (s = 12 2688 x 2368 x 286 161 / 139, s = 11 1614 x 2688 x 423 128 / 117, s = 10 4537 x 599 x 576 93.4 / 87.9).
 // Launches long enough to sit at the power cap run 5 percent faster in passes of 128 x 64 tiles than the fit has them (4073^3, s = 11 2622 / 2465; 3746^3,
 // s = 12 2483 / 2326).  Operands badly scaled
-// along k, so that every slice has digits: products with zero slices draw less power, and their figures mislead.
+// along k, which is what asks for so many slices, digits in all of them; under the power cap the figures depend on the digits (lognormal entries
+// have none from the 9th slice on: with them passes of 10 slices measured ahead at 4096^3, 3070 -> 3210 TOP/s).
 // Beyond, 128 x 64 or 64 x 64 by rounds of the chip: two 64 x 64 tiles at a time cost a compute unit 1.04 of a 128 x 64 one;
 // at short k the 128 x 64 tile also pays for copies and epilogues that nothing hides (2085 x 4740 x 1000, 4.98 against 4.83
 // rounds, s = 13 580 / 584, 18 953 / 940; 3000 x 3000 x 500, 4.41 against 4.31, s = 13 306 / 280; 2207^3, 2.46 against 2.39, 693 / 627).

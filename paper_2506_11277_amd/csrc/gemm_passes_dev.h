@@ -14,17 +14,18 @@
 // for W steps, each read from LDS once, and each slice of the tile is copied to LDS once per pass.  The slices go through a
 // ring of LDS slots, one step (slice of A, slice of B) to a slot, filled by LDS-DMA several steps ahead; a barrier stands about
 // every 24 products, when the slots of the steps before it become free.  Small first passes cost least, as the last
-// pass moves all s slices whatever its width: (3, 9) rather than (6, 6) for 12 slices (3526 against 3460 TOP/s at 4096^3), but no wider than nine
-// diagonals, 144 accumulator registers and 72 of B.  The first pass is a multiple of three where that costs less than two
+// pass moves all s slices whatever its width: (3, 9) rather than (6, 6) for 12 slices (4150 against 4020 TOP/s at 4096^3), but no wider than nine
+// diagonals, 144 accumulator registers and 72 of B (two or three registers spill in 128 x 64 tiles with 12, 15, 19 and 20 slices, two in 64 x 64 with 20).  The first pass is a multiple of three where that costs less than two
 // percent, so that levels of three diagonals end with it.
 //
 // 16x16x64 instruction, 32 x 32 outputs per wavefront.  Two shapes: 128 x 64 tile, eight wavefronts, 156 KiB ring, one work-group to a compute
 // unit; 64 x 64 tile, four wavefronts, 80 KiB ring, two work-groups to a compute unit, whose first copies and epilogues
-// hide behind each other's products: 0-5 % slower in whole rounds of the chip, ahead where the tiles of 128 x 64 leave a round partly filled.
-// Int8 TOP/s of the products, before -> 128 x 64 / 64 x 64 (what ran before: gemm_fused_kernel, 18: blocks):
-//   4096^3                s = 10 3158 -> 3137 / 3072, 13 2932 -> 3479 / 3423, 16 3183 -> 3637 / 3598, 18 3320 -> 4013 / 3648, 20 2979 -> 4114
-//   2500 x 2400 x 2500    s = 10 2988 -> 3147 / 3001, 13 2996 -> 3508 / 3332, 16 3229 -> 3681 / 3653, 18 2943 -> 3842 / 3776
-//   2207^3                s = 10 2565 -> 2562 / 2787, 13 2745 -> 2823 / 3119, 16 2938 -> 3025 / 3390, 18 2527 -> 3174 / 3577
+// hide behind each other's products: within 4 % of each other in whole rounds of the chip, ahead where the tiles of 128 x 64 leave a round partly filled.
+// Int8 TOP/s of the products, before -> 128 x 64 / 64 x 64 (what ran before: gemm_fused_kernel, 18 at 4096^3: blocks; operands badly scaled along k,
+// digits in all slices; lognormal ones, none from the 9th slice on, had measured 10 to 15 % lower throughout):
+//   4096^3                s = 10 3750 -> - / 3580, 13 3560 -> 4150 / 4070, 16 3810 -> 4240 / 4340, 18 3550 -> 4460 / 4480, 20 3150 -> 4420 / 4360
+//   2500 x 2400 x 2500    s = 10 3520 -> - / 3480, 13 3330 -> 3850 / 3840, 16 3590 -> 3970 / 4060, 18 3080 -> 4110 / 4170
+//   2207^3                s = 10 3040 -> - / 3290, 13 3210 -> 3090 / 3670, 16 3450 -> 3170 / 3880, 18 2670 -> 3290 / 3990
 // 4 ... 9 slices fit one pass; the 64 x 64 tile serves them too where whole rounds of the larger tiles of gemm_fused16_kernel fit
 // badly or k is short (s = 7: 2304 x 2000 x 2560 264 -> 228 us, 3000 x 3000 x 500 107 -> 94; s = 9: 6001 x 5200 x 256 299 -> 251).  The
 // 128 x 64 tile is then worked on in runs: a work-group takes the tiles b, b + grid, ..., the copies of the next tile's first

@@ -292,10 +292,10 @@ hipError_t launch_gemm_blocks(int m, int n, int kp, int sA, int sB, bool all_pro
 // Equal counts, whole contraction in int32, slices streamed through a ring of LDS slots (gemm_passes_dev.h): 4 ... 9 slices in one pass,
 // 10 ... 20 with the diagonals in passes (32 x 32 tiles: gemm_small.hip).
 // Widths of the passes: at most nine diagonals (accumulator registers), the first one small (what is moved goes with the
-// sum of the pass ends) and a multiple of three (levels of three diagonals).  128 x 64 tile at 2500 x 2400 x 2500, us: 10 as (3, 7) / (2, 8) /
-// (5, 5) 531 / 528 / 548, 12 as (3, 9) / (4, 8) / (6, 6) 695 / 708 / 723, 13 as (6, 7) / (4, 9) 806 / 800, 14 as (6, 8) / (5, 9)
-// 904 / 899, 16 as (9, 7) / (7, 9) 1108 / 1097, 17 as (9, 8) / (8, 9) 1227 / 1225; 4096^3 19 as (3, 9, 7) / (6, 6, 7) 6488 / 6641,
-// 20 as (3, 9, 8) / (6, 6, 8) 7016 / 7189.
+// sum of the pass ends) and a multiple of three (levels of three diagonals).  128 x 64 tile at 2500 x 2400 x 2500, us, every slice with digits: 12 as (3, 9) /
+// (4, 8) / (6, 6) 602 / 607 / 622, 13 as (6, 7) / (4, 9) 710 / 707, 14 as (6, 8) / (5, 9) / (7, 7) 808 / 814 / 820, 15 as (6, 9) / (7, 8) 903 / 928, 16 as (9, 7) /
+// (7, 9) 1029 / 1008, 17 as (9, 8) / (8, 9) 1136 / 1164; 4096^3 18 as (9, 9) / (6, 6, 6) 5274 / 5579, 19 as (3, 9, 7) / (6, 6, 7) 6054 / 6135, 20 as (3, 9, 8) /
+// (6, 6, 8) 6534 / 6626; 64 x 64 tile at 2207^3 10 as (3, 7) / (2, 8) / (5, 5) 360 / 348 / 370.
 struct PassPlan {
     int n, w[3];
 };
