@@ -139,6 +139,15 @@ __device__ __forceinline__ void lds_dma16_at(const void *sbase, unsigned voff, u
                  : "memory", "m0", "scc");
 }
 
+// The same with all lanes (lanes = ~0) or none (0); all are active before and behind it.
+template <int IMM>
+__device__ __forceinline__ void lds_dma16_masked_at(const void *sbase, unsigned voff, unsigned ldsbase, unsigned lanes)
+{
+    asm volatile("s_mov_b32 exec_lo, %4\n\ts_mov_b32 exec_hi, %4\n\ts_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, -1" ::"s"(ldsbase),
+                 "n"(IMM), "v"(voff), "s"(sbase), "s"(lanes)
+                 : "memory", "m0", "scc");
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {

@@ -5,7 +5,7 @@
 namespace oz {
 
 #define OZ_DECLARE(S_)                                                                                                      \
-    hipError_t launch_gemm_passes_##S_(bool small, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,    \
+    hipError_t launch_gemm_passes_##S_(PassShape shape, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, \
                                        const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
 OZ_DECLARE(4) OZ_DECLARE(5) OZ_DECLARE(6) OZ_DECLARE(7) OZ_DECLARE(8) OZ_DECLARE(9)
 OZ_DECLARE(10) OZ_DECLARE(11) OZ_DECLARE(12) OZ_DECLARE(13) OZ_DECLARE(14) OZ_DECLARE(15) OZ_DECLARE(16) OZ_DECLARE(17)
@@ -70,6 +70,16 @@ PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn)
     const double runs = kRuns[s - 4].us(single_rounds(s, order_blocks(m, n, 128, 64), cus), x);
     const LaunchTime &t = tm == 64 ? k64[s - 4] : tm == 192 ? k192x128 : tn == 64 || s > 6 ? k128x64[s - 4] : k128x128[s - 4];
     const double others = t.us(single_rounds(s, order_blocks(m, n, tm, tn), cus) * (tm * tn / 8192.0), x);
+    // 96 x 64 tiles, 7 ... 9 slices (its round is not scaled by the area).  Per product 0.92 ... 0.97 of a work-group's rate in 128 x 64 tiles away from the power cap,
+    // so it pays where its rounds fit better: 1531 x 777 x 1001, s = 8, 208 tiles and one round as 156 of 128 x 64: calls 53.1 -> 46.4;
+    // 1412 x 721 x 811, s = 9 55.4 -> 47.0; 640 x 1756 x 2461, s = 9 138 -> 122; 2304 x 2000 x 2560, s = 7, three whole rounds, 281 -> 268.  260 random
+    // sizes of more than 256 tiles of 64 x 64: taken by 67 of them, 11.7 percent faster there, none slower; with 1.0 for 0.98 by 78, the slowest 2 percent behind.
+    // (kp > 256: shorter ones gain little, 1600 x 1536 x 230, s = 9 31.5 / 32.4; 32-bit offsets into the planes)
+    if (s >= 7 && kp > 256 && (long long)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * s < (1LL << 32)) {
+        static constexpr LaunchTime kMiddle[3] = {{0.935, 1.64, 6.15}, {0.896, 1.85, 6.3}, {0.898, 1.75, 6.5}};
+        const double middle = kMiddle[s - 7].us(single_rounds(s, order_blocks(m, n, 96, 64), cus), x), rest = pairs < runs ? pairs : runs;
+        if (middle < 0.98 * (rest < others ? rest : others)) return kPassMiddle;
+    }
     if ((pairs < runs ? pairs : runs) >= kAhead[s - 4] * others) return kNoPasses;
     return pairs < runs ? kPassSmall : kPassWide;
 }
@@ -127,9 +137,8 @@ hipError_t launch_gemm_passes(PassShape shape, int s, int m, int n, int kp, int 
     if (m <= 0 || n <= 0) return hipSuccess;
     if (shape == kNoPasses || stride < s) return hipErrorInvalidValue;
     if (shape == kPassEighths) return launch_gemm_eighths_passes(s, m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
-    const bool small = shape == kPassSmall;
     switch (s) {
-#define OZ_CASE(S_) case S_: return launch_gemm_passes_##S_(small, m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
+#define OZ_CASE(S_) case S_: return launch_gemm_passes_##S_(shape, m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
         OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9)
         OZ_CASE(10) OZ_CASE(11) OZ_CASE(12) OZ_CASE(13) OZ_CASE(14) OZ_CASE(15) OZ_CASE(16) OZ_CASE(17) OZ_CASE(18) OZ_CASE(19)
         OZ_CASE(20)

@@ -31,6 +31,11 @@
 // 128 x 64 tile is then worked on in runs: a work-group takes the tiles b, b + grid, ..., the copies of the next tile's first
 // steps follow those of the last stage, and the epilogue stands between them (4096 x 4096 x 1024, s = 8 / 9 387 / 469 us as 64 x 64 tiles, 373 /
 // 447 in runs; 64 x 64 tiles gain nothing by runs).
+// 96 x 64 tiles in runs, twelve wavefronts of 32 x 16 outputs, three to a SIMD: for 7 ... 9 slices where 128 x 64 tiles leave a round partly filled and
+// pairs of 64 x 64 ones do too.  A wavefront reads three 16-row operands for two blocks where 32 x 32 reads four for four, so LDS is read
+// half as often again (about 0.85 of its cycles with the copies), which costs nothing under the power cap (1536 x 1024 x 8000, s = 7, one whole
+// round: 3.13 POP/s) and 10 to 15 percent away from it.  Eight wavefronts of 48 x 16, which read less, were behind: two to a SIMD (1531 x 777 x 1001,
+// s = 8: calls 50.6 against 46.4).
 // What bounds it: the board's power cap, as the other large products (register-only loop of the same instruction: 4200 TOP/s).
 #pragma once
 #include "gemm_dev.h"
@@ -42,14 +47,16 @@ namespace {
 // Compile-time schedule of one 64-deep k-step ("stage") of a pass: SN slices, the last W diagonals of their reduced set.
 // A stage is V >= SN positions of the stream (those from SN on are empty), the ring has N slots, N a divisor or a multiple of V
 // so that every slot is a compile-time constant within a stage.
-template <int SN, int W, int V, int N, int D, int DB, int TARGET, bool PAIR>
+// MF: matrix instructions of a product (16 x 16 blocks of a wavefront).
+enum Copies { kCopyBoth, kCopyPair, kCopyOne };
+template <int SN, int W, int V, int N, int D, int DB, int TARGET, int COPIES, int MF>
 struct PassBase {
     static_assert(V >= SN && (V % N == 0 || N % V == 0));
     static constexpr int used(int i) { return i >= SN ? 0 : i + 1 < W ? i + 1 : W; }      // products of step i
     static constexpr int start(int i)                                       // first matrix instruction of step i
     {
         int e = 0;
-        for (int q = 0; q < i; ++q) e += 4 * used(q);
+        for (int q = 0; q < i; ++q) e += MF * used(q);
         return e;
     }
     static constexpr int NM = start(SN);
@@ -60,11 +67,11 @@ struct PassBase {
         return i;
     }
     // product number p of step i meets B slice of step i - j, j = used - 1 - p
-    static constexpr int j_of(int e) { return used(step_of(e)) - 1 - (e - start(step_of(e))) / 4; }
+    static constexpr int j_of(int e) { return used(step_of(e)) - 1 - (e - start(step_of(e))) / MF; }
     static constexpr int readA(int i) { return start(i) - D; }
     static constexpr int readB(int i)
     {
-        const int need = start(i) + 4 * (used(i) - 1);
+        const int need = start(i) + MF * (used(i) - 1);
         return need - DB < start(i) - D ? start(i) - D : need - DB;
     }
     // synchronisations: boundary k = first step that may be read only after it; about TARGET products apart
@@ -75,22 +82,23 @@ struct PassBase {
     {
         return k < 0 ? r.b[k + r.n] - V : k >= r.n ? r.b[k - r.n] + V : r.b[k];
     }
-    // copies a wavefront of class c has issued for the steps below q: one of A per step; of B one per step, or (PAIR: 4 units
-    // of B, 8 wavefronts) the even steps by class 0 and the odd ones by class 1, both behind the odd step's copy of A
+    // copies a wavefront of class c has issued for the steps below q: one of A per step; of B one per step (kCopyBoth), or (kCopyPair: 4 units
+    // of B, 8 wavefronts) the even steps by class 0 and the odd ones by class 1, both behind the odd step's copy of A; or one per
+    // step, of either operand (kCopyOne)
     static constexpr int count(int q)
     {
         const int st = q >= 0 ? q / V : -((-q + V - 1) / V);
         int i = q - st * V;
         if (i > SN) i = SN;
-        const int per = PAIR ? SN + (SN + 1) / 2 : 2 * SN;
+        const int per = COPIES == kCopyPair ? SN + (SN + 1) / 2 : COPIES == kCopyOne ? SN : 2 * SN;
         if (i == SN) return (st + 1) * per;
-        return st * per + (PAIR ? i + i / 2 : 2 * i);
+        return st * per + (COPIES == kCopyPair ? i + i / 2 : COPIES == kCopyOne ? i : 2 * i);
     }
     static constexpr int flying(const Bounds &r, int k)       // copies that may still be in flight at synchronisation k
     {
         int b = at(r, k + 1);
         const int i = (b + 4 * V) % V, iss = at(r, k - 1) + N;
-        if (PAIR && i % 2 == 1 && i < SN) ++b;         // the even step's B comes with the odd step after it
+        if (COPIES == kCopyPair && i % 2 == 1 && i < SN) ++b;         // the even step's B comes with the odd step after it
         return b > iss ? -1 : count(iss) - count(b);
     }
     static constexpr Bounds make()
@@ -111,9 +119,10 @@ struct PassBase {
     }
 };
 
-template <int SN, int W, int V, int N, int D, int DB, int TARGET, bool PAIR>
-struct PassSched : PassBase<SN, W, V, N, D, DB, TARGET, PAIR> {
-    using P = PassBase<SN, W, V, N, D, DB, TARGET, PAIR>;
+template <int SN, int W, int V, int N, int D, int DB, int TARGET, int COPIES, int MF>
+struct PassSched : PassBase<SN, W, V, N, D, DB, TARGET, COPIES, MF> {
+    using P = PassBase<SN, W, V, N, D, DB, TARGET, COPIES, MF>;
+    static constexpr int PARTS = COPIES == kCopyOne ? 1 : 2;
     using P::start, P::used, P::readA, P::readB, P::NM, P::at;
     static constexpr typename P::Bounds BS = P::make();
     static constexpr int NSYNC = BS.n;
@@ -139,21 +148,21 @@ struct PassSched : PassBase<SN, W, V, N, D, DB, TARGET, PAIR> {
             if (readA(i) == e || readB(i) == e || readA(i) + NM == e || readB(i) + NM == e) return true;
         return false;
     }
-    // copy issued behind matrix instruction e: 2 * step + part, or -1.  The copies of interval k
+    // copy issued behind matrix instruction e: PARTS * step + part, or -1.  The copies of interval k
     // (steps issued(k) ... issued(k + 1) - 1) go one behind each matrix instruction from the start of the interval on.
     static constexpr int from(int k) { return k == 0 ? 0 : sync_at(k); }
     static constexpr int copy_at(int e)
     {
         for (int k = 0; k < NSYNC; ++k) {
-            const int n = 2 * (issued(k + 1) - issued(k)), f = from(k);
-            if (e >= f && e < f + n) return 2 * issued(k) + (e - f);
+            const int n = PARTS * (issued(k + 1) - issued(k)), f = from(k);
+            if (e >= f && e < f + n) return PARTS * issued(k) + (e - f);
         }
         return -1;
     }
     static constexpr bool fits()
     {
         for (int k = 0; k < NSYNC; ++k) {
-            const int n = 2 * (issued(k + 1) - issued(k));
+            const int n = PARTS * (issued(k + 1) - issued(k));
             const int end = k + 1 < NSYNC ? sync_at(k + 1) : sync_at(0) + NM;
             if (from(k) + n > end) return false;
         }
@@ -176,22 +185,26 @@ struct PassSched : PassBase<SN, W, V, N, D, DB, TARGET, PAIR> {
     static_assert(ordered(), "a read on the wrong side of a synchronisation");
 };
 
-// KG groups of WVM x WVN wavefronts of 32 x 32 outputs, a ring of at most SLOTS slots to each group; the groups take every
+// KG groups of WVM x WVN wavefronts of 32 x 32 outputs (NI = 1: 32 x 16), a ring of at most SLOTS slots to each group; the groups take every
 // KG-th 64-deep k-step of the same tile
-template <int WVM_, int WVN_, int SLOTS_, int KG_ = 1, bool PERSIST_ = false>
+template <int WVM_, int WVN_, int SLOTS_, int KG_ = 1, bool PERSIST_ = false, int NI_ = 2>
 struct PassTile {
     static constexpr bool PERSIST = PERSIST_;
-    static constexpr int WVM = WVM_, WVN = WVN_, NW = WVM * WVN, SLOTS = SLOTS_, KG = KG_, THREADS = 64 * NW * KG;
-    static constexpr int SLOT = (WVM + WVN) * 2 * kFragBytes, GROUP = SLOTS * SLOT, LDS = KG * GROUP;
+    static constexpr int WVM = WVM_, WVN = WVN_, NI = NI_, NW = WVM * WVN, SLOTS = SLOTS_, KG = KG_, THREADS = 64 * NW * KG;
+    static constexpr int FM = WVM, FN = WVN * NI / 2, TM = 32 * FM, TN = 32 * FN;        // fragment rows of A and B, outputs
+    static constexpr int COPIES = NW == 4 ? kCopyBoth : NW == 8 ? kCopyPair : kCopyOne;
+    static constexpr int UNITS = 2 * (FM + FN), SLOT = UNITS * kFragBytes, GROUP = SLOTS * SLOT, LDS = KG * GROUP;
     static_assert(LDS <= kLdsBytes, "rings do not fit LDS");
 };
 using PassTileWide = PassTile<4, 2, 13>;       // 128 x 64, 156 KiB
 using PassTileRuns = PassTile<4, 2, 13, 1, true>;      // the same for one pass, several tiles to a work-group
 using PassTileSmall = PassTile<2, 2, 10>;      // 64 x 64, 80 KiB: two work-groups to a compute unit
+using PassTileMiddle = PassTile<3, 4, 16, 1, true, 1>;     // 96 x 64 in runs, twelve wavefronts of 32 x 16, 160 KiB
 // operands are read from LDS this many matrix instructions ahead; products between synchronisations (16 ... 40 products and
 // 6 ... 16 instructions are within 1 % of each other at 13 and 18 slices,
 // one pass of 8 slices, 64 x 64 tile, 1024 x 1024 x 4096: 104 us with 16, 111 with 24)
-constexpr int kPassAhead = 8, kPassProducts = 24, kPassProductsOne = 16;
+// 96 x 64, three wavefronts to a SIMD, 1536 x 1024 x 8000 s = 7: GEMM 240 us with 16 products and 8 instructions, 229 with 24 and 8, 227 with 32 and 10)
+constexpr int kPassAhead = 8, kPassProducts = 24, kPassProductsOne = 16, kPassAheadMiddle = 10, kPassProductsMiddle = 32;
 
 // positions of a stage and slots of the ring: whole stages in the ring or two rings in a stage
 template <int SN, int SLOTS>
@@ -215,7 +228,7 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
                                                  double *__restrict__ C, int ldc, int m, int n, int KB, int stride,
                                                  int tiles_m, int tiles_n, int Q)
 {
-    constexpr int WVM = T::WVM, WVN = T::WVN, NW = T::NW, SLOT = T::SLOT, KG = T::KG;
+    constexpr int WVM = T::WVM, NW = T::NW, NI = T::NI, MF = 2 * NI, FM = T::FM, FN = T::FN, SLOT = T::SLOT, KG = T::KG;
     constexpr bool PERSIST = T::PERSIST;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
     // (several tiles to a work-group: those of the blocks b, b + gridDim.x, ...)
@@ -240,16 +253,28 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
     // Copies of a step: its slice of the WVM fragment rows of A, two k-halves each, one 1 KiB unit to a wavefront; of the
     // two fragment rows of B likewise, four units, so eight wavefronts (PAIR) copy two steps at a time, wavefronts of
     // class 0 the even step's and of class 1 the odd one's (the last step of an odd number: both the same).
-    constexpr bool PAIR = NW == 8;
-    static_assert((NW == 8 && WVM == 4 && WVN == 2) || (NW == 4 && WVM == 2 && WVN == 2), "units per wavefront");
+    // 96 x 64: six units of A and four of B for twelve wavefronts, one each (ONE); two have none and copy with no lane active.
+    constexpr bool PAIR = T::COPIES == kCopyPair, ONE = T::COPIES == kCopyOne;
+    static_assert((NW == 8 && FM == 4 && FN == 2) || (NW == 4 && FM == 2 && FN == 2) || (ONE && T::UNITS <= NW), "units per wavefront");
     const int cls = wave >> 2, ub = wave & 3;            // (four wavefronts: class 0)
-    const int8_t *srcA = pA + (size_t)((PERSIST ? 0 : tm * WVM) + (wave >> 1)) * row_bytes + (size_t)((wave & 1) * stride) * kFragBytes;
-    const int8_t *srcB = pB + (size_t)((PERSIST ? 0 : tn * WVN) + (ub >> 1)) * row_bytes + (size_t)((ub & 1) * stride + cls) * kFragBytes;
-    const unsigned dstA = lds0 + wave * kFragBytes, dstB = lds0 + (2 * WVM + ub) * kFragBytes;
+    const bool unitA = !ONE || wave < 2 * FM;            // (ONE: this wavefront's unit is one of A)
+    const unsigned lanes = (unsigned)((wave - T::UNITS) >> 31);     // (ONE: all ones where there is one)
+    // (the last tile of 96 rows may reach beyond the planes, which end at a multiple of 128: its rows there repeat the last ones)
+    const int rowsA = (m + kPad - 1) / kPad * (kPad / kFrag);
+    auto unit_row = [&](int tm_, int tn_) -> unsigned {   // ONE: fragment row of this wavefront's unit
+        const int a = tm_ * FM + (wave >> 1), b = tn_ * FN + ((wave - 2 * FM) >> 1 & (FN - 1));
+        return unitA ? (a < rowsA ? a : rowsA - 1) : b;
+    };
+    const int8_t *srcA = pA + (size_t)((PERSIST ? 0 : tm * FM) + (wave >> 1)) * row_bytes + (size_t)((wave & 1) * stride) * kFragBytes;
+    const int8_t *srcB = pB + (size_t)((PERSIST ? 0 : tn * FN) + (ub >> 1)) * row_bytes + (size_t)((ub & 1) * stride + cls) * kFragBytes;
+    const unsigned dstA = lds0 + wave * kFragBytes, dstB = lds0 + (2 * FM + ub) * kFragBytes;
     const unsigned dstB2 = dstB + cls * SLOT;            // (from the even step's slot to this class's)
+    if constexpr (ONE) srcA = (unitA ? pA : pB) + (size_t)((wave & 1) * stride) * kFragBytes;
     const unsigned lane16 = lane * 16;
     // (PERSIST: the tile is in the lane offset, 32 bits; behind the last stage come the first ones of the next tile)
-    unsigned tileA = PERSIST ? (unsigned)(tm * WVM) * (unsigned)row_bytes : 0, tileB = PERSIST ? (unsigned)(tn * WVN) * (unsigned)row_bytes : 0;
+    static_assert(!ONE || PERSIST, "one unit a wavefront: the tile in the lane offset");
+    unsigned tileA = ONE ? unit_row(tm, tn) * (unsigned)row_bytes : PERSIST ? (unsigned)(tm * FM) * (unsigned)row_bytes : 0;
+    unsigned tileB = PERSIST ? (unsigned)(tn * FN) * (unsigned)row_bytes : 0;
     unsigned nextA = 0, nextB = 0;
     bool more = false;
     auto stage_off = [&](int st, unsigned tile, unsigned next) {
@@ -258,11 +283,11 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
     };
     // this lane's part of a 16 x 64 operand in a pair of 32 x 32 fragments, as in gemm_fused16_kernel
     const int lofs = ((lane >> 4) >> 1) * kFragBytes + ((lane & 15) + 32 * ((lane >> 4) & 1)) * 16;
-    const unsigned char *ldsA = lds + wm * 2 * kFragBytes + lofs, *ldsB = lds + (WVM + wn) * 2 * kFragBytes + lofs;
+    const unsigned char *ldsA = lds + wm * 2 * kFragBytes + lofs, *ldsB = lds + (FM + wn * NI / 2) * 2 * kFragBytes + (NI == 1 ? (wn & 1) * 256 : 0) + lofs;
 
     constexpr int NP = sizeof...(Ws);
     constexpr int WS[NP] = {Ws...};
-    v4i acc[widest<NP>(WS)][4];                          // [diagonal of the pass, the last one first][16 x 16 block (i2, j2)]
+    v4i acc[widest<NP>(WS)][MF];                         // [diagonal of the pass, the last one first][16 x 16 block (i2, j2)]
 
     static_assert(KG == 1 || (KG == 2 && NP == 1), "k in halves: one pass");
     static_assert(!PERSIST || (KG == 1 && NP == 1), "several tiles: one pass");
@@ -281,12 +306,15 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
 #pragma unroll
             for (int j2 = 0; j2 < 2; ++j2) acc[a][j2] = (kg ? acc[a][2 + j2] : acc[a][j2]) + x[((a * 2 + kg) * 2 + j2) * 64];
     };
-    int m0 = (tm * WVM + wm) * 32, n0 = (tn * WVN + wn) * 32;
+    int m0 = (tm * FM + wm) * 32, n0 = tn * T::TN + wn * 16 * NI;
     // (one pass: the exponents of the 32 rows and columns are asked for here, a value per lane, and not where a lone tile
     // would wait for them)
     constexpr bool EARLY = NP == 1;
     int early = 0;
-    auto ask = [&]() { early = lane < 32 ? eA[m0 + lane] : eB[n0 + lane - 32]; };           // (padded like the planes)
+    auto ask = [&]() {                                   // (padded like the planes)
+        const int ma = FM % 4 == 0 || FM == 2 || m0 + lane < rowsA * kFrag ? m0 + lane : 0;
+        early = lane < 32 ? eA[ma] : eB[n0 + ((lane - 32) & (16 * NI - 1))];
+    };
     if constexpr (EARLY) ask();
     // Adds the sums of pass p to the entries, in C as they are so far (not yet scaled) between passes.
     const bool stream = stream_c(C, ldc);
@@ -300,12 +328,12 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
                 if constexpr (EARLY) {                   // (before lanes beyond the edge leave)
                     ea = __shfl(early, (KG == 1 ? i2 : kg) * 16 + (lane & 15));
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) eb[q >> 2][q & 3] = __shfl(early, 32 + (q >> 2) * 16 + 4 * (lane >> 4) + (q & 3));
+                    for (int q = 0; q < 4 * NI; ++q) eb[q >> 2][q & 3] = __shfl(early, 32 + (q >> 2) * 16 + 4 * (lane >> 4) + (q & 3));
                 }
                 if (mi >= m) continue;
                 if constexpr (!EARLY && p + 1 == NP) ea = eA[mi];
 #pragma unroll
-                for (int j2 = 0; j2 < 2; ++j2)
+                for (int j2 = 0; j2 < NI; ++j2)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int nj = n0 + j2 * 16 + 4 * (lane >> 4) + r;
@@ -316,7 +344,7 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
 #pragma unroll
                         for (int a = 0; a < W; ++a) {
                             const double unit = __builtin_ldexp(1.0, -kSliceBits * (BEFORE + a + 2));
-                            const int d = acc[W - 1 - a][i2 * 2 + j2][r];
+                            const int d = acc[W - 1 - a][i2 * NI + j2][r];
                             if constexpr (ORDER.value == kPlainOrder) sum.S = __builtin_fma((double)d, unit, sum.S);
                             else sum.add((double)d * unit, Q, a == W - 1);
                         }
@@ -334,22 +362,26 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
         constexpr int p = decltype(PP)::value, W = WS[p], SN = diagonals_before<NP>(WS, p) + W;
         using G = PassRing<SN, T::SLOTS>;
         constexpr int V = G::V, N = G::N, R = N > V ? N / V : 1;         // (R: stages in the ring)
-        using S = PassSched<SN, W, V, N, kPassAhead, kPassAhead, NP == 1 ? kPassProductsOne : kPassProducts, PAIR>;
+        constexpr int AHEAD = ONE ? kPassAheadMiddle : kPassAhead;
+        using S = PassSched<SN, W, V, N, AHEAD, AHEAD, ONE ? kPassProductsMiddle : NP == 1 ? kPassProductsOne : kPassProducts, T::COPIES, MF>;
         constexpr int NM = S::NM;
         const int8_t *sA[SN], *sB[SN], *sBlast = srcB + (SN - 1 - cls) * kFragBytes;
 #pragma unroll
         for (int i = 0; i < SN; ++i) {
             sA[i] = srcA + (SN - 1 - i) * kFragBytes;
             sB[i] = srcB + (PAIR && i % 2 ? i - 1 : i) * kFragBytes;
+            if constexpr (ONE) sA[i] = srcA + (unitA ? SN - 1 - i : i) * kFragBytes;
         }
         // Copies of position q of the stream, counted from the start of a stage whose slots begin at `ring`; voff: lane and stage.
         auto copyA = [&](auto QQ, unsigned voff, unsigned ring) {
             constexpr int q = decltype(QQ)::value, i = q % V;
-            if constexpr (i < SN) lds_dma16_at<(q % (R > 1 ? V : N)) * SLOT>(sA[i], voff, dstA + ring);
+            constexpr int to = (q % (R > 1 ? V : N)) * SLOT;
+            if constexpr (i < SN && ONE) lds_dma16_masked_at<to>(sA[i], voff, dstA + ring, lanes);
+            else if constexpr (i < SN) lds_dma16_at<to>(sA[i], voff, dstA + ring);
         };
         auto copyB = [&](auto QQ, unsigned voff, unsigned ring) {
             constexpr int q = decltype(QQ)::value, i = q % V, slot = q % (R > 1 ? V : N);
-            if constexpr (i >= SN) return;
+            if constexpr (i >= SN || ONE) return;
             else if constexpr (!PAIR) lds_dma16_at<slot * SLOT>(sB[i], voff, dstB + ring);
             else if constexpr (i % 2 == 1) {
                 static_assert(slot > 0 || R == 1, "pair across the end of the ring");
@@ -368,18 +400,18 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
 #pragma unroll
             for (int a = 0; a < W; ++a)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) acc[a][q] = v4i{0, 0, 0, 0};
+                for (int q = 0; q < MF; ++q) acc[a][q] = v4i{0, 0, 0, 0};
         };
         clear();
 
-        v4i A_[SN][2], B_[SN][2], An[SN][2], Bn[SN][2];  // (An, Bn: of the next stage)
+        v4i A_[SN][2], B_[SN][NI], An[SN][2], Bn[SN][NI];       // (An, Bn: of the next stage)
         auto loadA = [&](v4i (&d)[2], int i, unsigned ring) {
 #pragma unroll
             for (int i2 = 0; i2 < 2; ++i2) d[i2] = *(const v4i *)(ldsA + ring + (i % (R > 1 ? V : N)) * SLOT + i2 * 256);
         };
-        auto loadB = [&](v4i (&d)[2], int i, unsigned ring) {
+        auto loadB = [&](v4i (&d)[NI], int i, unsigned ring) {
 #pragma unroll
-            for (int j2 = 0; j2 < 2; ++j2) d[j2] = *(const v4i *)(ldsB + ring + (i % (R > 1 ? V : N)) * SLOT + j2 * 256);
+            for (int j2 = 0; j2 < NI; ++j2) d[j2] = *(const v4i *)(ldsB + ring + (i % (R > 1 ? V : N)) * SLOT + j2 * 256);
         };
         wait_vmcnt<S::flying(0)>();
         __syncthreads();
@@ -393,10 +425,10 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
         auto look_ahead = [&]() {
             b += gridDim.x;
             if (!(more = next_tile())) return;
-            nextA = (unsigned)(tm * WVM) * (unsigned)row_bytes;
-            nextB = (unsigned)(tn * WVN) * (unsigned)row_bytes;
-            mn = (tm * WVM + wm) * 32;
-            nn = (tn * WVN + wn) * 32;
+            nextA = (ONE ? unit_row(tm, tn) : (unsigned)(tm * FM)) * (unsigned)row_bytes;
+            nextB = (unsigned)(tn * FN) * (unsigned)row_bytes;
+            mn = (tm * FM + wm) * 32;
+            nn = tn * T::TN + wn * 16 * NI;
         };
         if constexpr (PERSIST) look_ahead();
         for (int st = 0; st < nst; ++st) {
@@ -412,7 +444,7 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
             }
             static_for<0, NM>([&](auto E) {
                 constexpr int e = decltype(E)::value;
-                constexpr int i = S::step_of(e), j = S::j_of(e), b = e % 4, i2 = b >> 1, j2 = b & 1;
+                constexpr int i = S::step_of(e), j = S::j_of(e), b = e % MF, i2 = b / NI, j2 = b % NI;
                 if constexpr (S::any_event(e)) {
                     __builtin_amdgcn_sched_barrier(0);       // (the compiler moves no read or product across)
                     if constexpr (S::is_sync(e)) {
@@ -431,8 +463,8 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
                 acc[j][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(B_[i - j][j2], A_[i][i2], acc[j][b], 0, 0, 0);
                 constexpr int cp = S::copy_at(e);
                 if constexpr (cp >= 0) {
-                    constexpr int q = cp / 2;
-                    if constexpr (cp % 2 == 0) copyA(std::integral_constant<int, q>{}, so[q / V], rg[q / V]);
+                    constexpr int q = cp / S::PARTS;
+                    if constexpr (cp % S::PARTS == 0) copyA(std::integral_constant<int, q>{}, so[q / V], rg[q / V]);
                     else copyB(std::integral_constant<int, q>{}, sb[q / V], rg[q / V]);
                 }
             });
@@ -441,7 +473,7 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     if constexpr (S::readA(i) < 0) A_[i][h] = An[i][h];
-                    if constexpr (S::readB(i) < 0) B_[i][h] = Bn[i][h];
+                    if constexpr (S::readB(i) < 0) if (h < NI) B_[i][h] = Bn[i][h];
                 }
             });
             ring = rg[1];
@@ -468,7 +500,7 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
 }
 
 template <class T, int... Ws>
-__global__ __launch_bounds__(T::THREADS, 2) void gemm_passes_kernel(
+__global__ __launch_bounds__(T::THREADS, T::NW == 12 ? 3 : 2) void gemm_passes_kernel(
     const int8_t *__restrict__ pA, const int8_t *__restrict__ pB, const int32_t *__restrict__ eA,
     const int32_t *__restrict__ eB, double *__restrict__ C, int ldc, int m, int n, int KB, int stride, int tiles_m,
     int tiles_n, int Q)
@@ -482,10 +514,10 @@ hipError_t launch_passes(int m, int n, int kp, int stride, const int8_t *pA, con
                          const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
 {
     // (32-bit lane offsets to the tile where a work-group takes several: larger planes go to a launch of single tiles)
-    if constexpr (T::PERSIST)
+    if constexpr (T::PERSIST && T::COPIES == kCopyPair)
         if ((size_t)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * stride >= (1ULL << 32))
             return launch_passes<PassTile<T::WVM, T::WVN, T::SLOTS>, Ws...>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
-    constexpr int TM = 32 * T::WVM, TN = 32 * T::WVN, NP = sizeof...(Ws), WS[NP] = {Ws...};
+    constexpr int TM = T::TM, TN = T::TN, NP = sizeof...(Ws), WS[NP] = {Ws...};
     for (int p = 1; p < NP; ++p)
         if (diagonals_before<NP>(WS, p) % Q != 0) return hipErrorInvalidValue;      // (gemm_passes_shape() does not ask for it)
     auto kern = gemm_passes_kernel<T, Ws...>;
@@ -495,7 +527,7 @@ hipError_t launch_passes(int m, int n, int kp, int stride, const int8_t *pA, con
     note_gemm_kernel("gemm_passes_kernel<%d> tile %dx%d, %d pass%s", (Ws + ...), TM, TN, NP, NP == 1 ? "" : "es");
     long long blocks = tile_order_blocks(tiles_m, tiles_n, false);
     if (T::PERSIST) {
-        const long long slots = (long long)device_cus() * (8 / T::NW);
+        const long long slots = (long long)device_cus() * (T::NW == 4 ? 2 : 1);
         blocks = blocks < slots ? blocks : slots;
     }
     kern<<<(unsigned)blocks, T::THREADS, T::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride,
@@ -516,10 +548,12 @@ hipError_t launch_pass_plan(int m, int n, int kp, int stride, const int8_t *pA, 
     else return launch_passes<T, P.w[0], P.w[1], P.w[2]>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
 }
 #define OZ_DEFINE_GEMM_PASSES(S_)                                                                                           \
-    hipError_t launch_gemm_passes_##S_(bool small, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,    \
+    hipError_t launch_gemm_passes_##S_(PassShape shape, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB,    \
                                        const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)     \
     {                                                                                                                       \
-        if (small) return launch_pass_plan<PassTileSmall, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);             \
+        if (shape == kPassSmall) return launch_pass_plan<PassTileSmall, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st); \
+        if constexpr (S_ >= 7 && S_ <= 9)                                                                                   \
+            if (shape == kPassMiddle) return launch_pass_plan<PassTileMiddle, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st); \
         using Wide = std::conditional_t<(S_ >= 10), PassTileWide, PassTileRuns>;                                            \
         if constexpr (S_ == 10) return hipErrorInvalidValue;                   /* (nowhere ahead: gemm_passes_shape) */     \
         else return launch_pass_plan<Wide, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);                            \

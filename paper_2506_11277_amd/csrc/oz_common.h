@@ -308,7 +308,7 @@ constexpr PassPlan pass_plan(int s)
            : s <= 18 ? PassPlan{2, {9, s - 9, 0}}
                      : PassPlan{3, {3, 9, s - 12}};
 }
-enum PassShape { kNoPasses, kPassEighths, kPassSmall, kPassWide };
+enum PassShape { kNoPasses, kPassEighths, kPassSmall, kPassMiddle, kPassWide };
 PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q);
 // 4 ... 9 slices: kNoPasses where the kernel of one stage to a barrier that would run otherwise, with tiles of tm x tn, is the faster one
 PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn);

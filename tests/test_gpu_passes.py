@@ -54,6 +54,16 @@ def test_one_pass_in_runs(m, n, k, s):
     both_ways(A, B, s, s, f"gemm_passes_kernel<{s}> tile 128x64")
 
 
+# 96 x 64 tiles: one round and several, a last tile that reaches beyond the planes (1650 rows, padded to 1664), the shortest contraction
+@pytest.mark.parametrize("s", [7, 8, 9])
+@pytest.mark.parametrize("m,n,k", [(1531, 777, 1001), (1650, 700, 300), (1650, 2670, 700), (2304, 2000, 600), (1000, 1190, 257)])
+def test_tiles_of_96_rows(m, n, k, s):
+    A, B = workloads.lognormal(m, n, k, 1.0, 40 + s)
+    special(A, B)
+    both_ways(A, B, s, s, f"gemm_passes_kernel<{s}> tile 96x64")
+    both_ways(A, B, s - 1, s, "", splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2)
+
+
 def test_planes_too_large_for_the_offsets_of_a_run():
     # the planes of A take 4.3 GB: beyond 32-bit offsets, so a work-group takes one tile
     m, n, k, s = 340000, 130, 1400, 9
