@@ -269,6 +269,15 @@ static int dgemm_impl(int m, int n, int k, const double *A, int lda, const doubl
         prof_mark(prof, 3, st);
         return OZIMMU_OK;
     }
+    // the smallest products: one launch for everything (operands are read while C is written)
+    if (!all_products && sA == sB && w.path == kPathFused && w.cA == sA && fused_automatic() && gemm_eighths_whole_handles(m, n, k, sA, nearest) &&
+        !overlap(C, m, n, ldc, A, m, k, lda) && !overlap(C, m, n, ldc, B, k, n, ldb)) {
+        prof_mark(prof, 1, st);
+        prof_mark(prof, 2, st);
+        OZ_TRY(launch_gemm_eighths_whole(m, n, k, A, lda, B, ldb, sA, nearest, eA, eB, pA, pB, hdr, w.off_minA, C, ldc, Q, st));
+        prof_mark(prof, 3, st);
+        return OZIMMU_OK;
+    }
     if (scale_split_handles(m, n, k)) {
         prof_mark(prof, 1, st);
         OZ_TRY(launch_scale_split(m, n, k, A, lda, B, ldb, sA, sB, w.cA, w.cB, eA, eB, pA, pB, nearest, hdr, w.off_minA, st));

@@ -8,6 +8,7 @@
 // k-blocks, four the odd ones, and the two int32 halves of every diagonal sum are added in LDS at the end (exact, so
 // the result is the same bit for bit).  Smaller problems still use 32 x 32 tiles, each wavefront a k-block in eight.
 #include "gemm_dev.h"
+#include "slice_dev.h"
 
 namespace oz {
 
@@ -201,6 +202,40 @@ struct CfgEighths {
     static constexpr int LDS = ROUND * 8 * 8 * 64 * 8;
 };
 
+// The sums of the eight wavefronts meet in LDS, ROUND diagonals at a time; f gets those of accumulator registers 2 wave and 2 wave + 1.
+template <int S, class F>
+__device__ __forceinline__ void eighths_sums(const v16i (&acc)[S], unsigned char *lds, int lane, int wave, F &&f)
+{
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    v2i *x = (v2i *)lds;
+    int D[2][S];
+    constexpr int ROUND = CfgEighths<S>::ROUND;
+    static_for<0, (S + ROUND - 1) / ROUND>([&](auto P) {
+        constexpr int a0 = decltype(P)::value * ROUND, a1 = a0 + ROUND < S ? a0 + ROUND : S;
+        if constexpr (a0 > 0) __syncthreads();
+#pragma unroll
+        for (int a = a0; a < a1; ++a)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) x[(((a - a0) * 8 + r) * 8 + wave) * 64 + lane] = v2i{acc[a][2 * r], acc[a][2 * r + 1]};
+        __syncthreads();
+#pragma unroll
+        for (int a = a0; a < a1; ++a) {
+            v2i s{0, 0};
+#pragma unroll
+            for (int w = 0; w < 8; ++w) s += x[(((a - a0) * 8 + wave) * 8 + w) * 64 + lane];
+            D[0][a] = s[0];
+            D[1][a] = s[1];
+        }
+    });
+    f(D);
+}
+// column of the tile that register 2 wave + r of a lane belongs to
+__device__ __forceinline__ int eighths_column(int wave, int lane, int r)
+{
+    const int rr = 2 * wave + r;
+    return 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
+}
+
 template <int S>
 __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restrict__ pA, const int8_t *__restrict__ pB,
                                                            const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
@@ -244,37 +279,161 @@ __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restr
             });
         }
     }
-    typedef int v2i __attribute__((ext_vector_type(2)));
-    v2i *x = (v2i *)lds;
-    int D[2][S];
-    constexpr int ROUND = CfgEighths<S>::ROUND;
-    static_for<0, (S + ROUND - 1) / ROUND>([&](auto P) {
-        constexpr int a0 = decltype(P)::value * ROUND, a1 = a0 + ROUND < S ? a0 + ROUND : S;
-        if constexpr (a0 > 0) __syncthreads();
+    eighths_sums<S>(acc, lds, lane, wave, [&](const int (&D)[2][S]) {
+        const int mi = tm * 32 + (lane & 31);
+        if (mi >= m) return;
+        const bool stream = stream_c(C, ldc);
+        const int ea = eA[mi];
 #pragma unroll
-        for (int a = a0; a < a1; ++a)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) x[(((a - a0) * 8 + r) * 8 + wave) * 64 + lane] = v2i{acc[a][2 * r], acc[a][2 * r + 1]};
-        __syncthreads();
-#pragma unroll
-        for (int a = a0; a < a1; ++a) {
-            v2i s{0, 0};
-#pragma unroll
-            for (int w = 0; w < 8; ++w) s += x[(((a - a0) * 8 + wave) * 8 + w) * 64 + lane];
-            D[0][a] = s[0];
-            D[1][a] = s[1];
+        for (int r = 0; r < 2; ++r) {
+            const int nj = tn * 32 + eighths_column(wave, lane, r);
+            if (nj < n) store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[r], Q), ea + eB[nj]), stream);
         }
     });
-    const int mi = tm * 32 + (lane & 31);
-    if (mi >= m) return;
-    const bool stream = stream_c(C, ldc);
-    const int ea = eA[mi];
+}
+
+// ---- the same tile, scales and slices in the same launch: contractions of up to 256, few tiles ----------------------------------
+// A wavefront has one k-block of the tile, 32 deep (EPL = 16 entries of either operand to a lane), or half of one up to k = 128 (EPL = 8): it reads the
+// entries, the maxima of the rows and columns meet in LDS, and the slices go from the registers that they are formed in to the matrix
+// instruction.  Every row is read and sliced once for each tile of its row, which few tiles make up for by the launch and the
+// gap between the two (128^3, s = 3: 3.4 + 4.1 us on the device and as much again of launches).  The planes, exponents and non-finite words that a call
+// leaves in the workspace are written by the tiles of the first column (A) and row (B).
+// What bounds it: the host up to five slices, then slicing, eight entries of either operand to a lane and one wavefront to a SIMD's issue slot.
+constexpr int kWholeMost = 9, kWholeNearest = 4, kWholeLong = 3;      // slices: k up to 128, nearest ones, k up to 256
+template <int S, bool NEAREST, int EPL>
+__global__ __launch_bounds__(512) void gemm_eighths_whole_kernel(
+    const unsigned long long *__restrict__ A, int lda, const unsigned long long *__restrict__ B, int ldb, int32_t *__restrict__ eA,
+    int32_t *__restrict__ eB, int8_t *__restrict__ pA, int8_t *__restrict__ pB, double *__restrict__ C, int ldc, int m, int n, int K, int KB, int tiles_m,
+    unsigned long long *__restrict__ header, long long bad_offset, int Q)
+{
+    constexpr int NQ = EPL / 4;                              // quads of a lane
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int tm = blockIdx.x % (unsigned)tiles_m, tn = blockIdx.x / (unsigned)tiles_m, tiles_n = gridDim.x / (unsigned)tiles_m;
+    const int lane = threadIdx.x & 63, r = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int k0 = wave * 2 * EPL, kl = k0 + hh * EPL;       // of the wavefront and of the lane
+    const int ra = tm * 32 + r, rb = tn * 32 + r;
+    // (rows beyond the operand repeat its last one, at a scale that makes every slice zero)
+    const unsigned long long *a = A + (ra < m ? ra : m - 1), *b = B + (size_t)(rb < n ? rb : n - 1) * ldb;
+    unsigned long long xa[NQ][4], xb[NQ][4];
+    if (k0 + 2 * EPL <= K) {
+        typedef unsigned long long pair __attribute__((ext_vector_type(2), aligned(8)));
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int rr = 2 * wave + r;
-        const int nj = tn * 32 + 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
-        if (nj < n) store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[r], Q), ea + eB[nj]), stream);
+        for (int t = 0; t < EPL; ++t) xa[t >> 2][t & 3] = a[(size_t)(kl + t) * lda];
+#pragma unroll
+        for (int t = 0; t < EPL; t += 2) {
+            const pair v = *(const pair *)(b + kl + t);
+            xb[t >> 2][t & 3] = v[0];
+            xb[t >> 2][(t & 3) + 1] = v[1];
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < EPL; ++t) {
+            const int k = kl + t < K ? kl + t : K - 1;
+            xa[t >> 2][t & 3] = a[(size_t)k * lda];
+            xb[t >> 2][t & 3] = b[k];
+        }
+#pragma unroll
+        for (int t = 0; t < EPL; ++t) {
+            xa[t >> 2][t & 3] = kl + t < K ? xa[t >> 2][t & 3] : 0ULL;
+            xb[t >> 2][t & 3] = kl + t < K ? xb[t >> 2][t & 3] : 0ULL;
+        }
     }
+    auto *const smx = (unsigned long long *)lds;             // [operand][wavefront][row]
+    unsigned long long mx[2] = {0, 0};
+#pragma unroll
+    for (int t = 0; t < EPL; ++t) {
+        const unsigned long long u = xa[t >> 2][t & 3] & 0x7fffffffffffffffULL, v = xb[t >> 2][t & 3] & 0x7fffffffffffffffULL;
+        mx[0] = u > mx[0] ? u : mx[0];
+        mx[1] = v > mx[1] ? v : mx[1];
+    }
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        const unsigned long long u = __shfl_xor(mx[o], 32);
+        mx[o] = u > mx[o] ? u : mx[o];
+        if (hh == 0) smx[(o * 8 + wave) * 32 + r] = mx[o];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const unsigned long long u = smx[(o * 8 + w) * 32 + r];
+            mx[o] = u > mx[o] ? u : mx[o];
+        }
+    const int ea = exponent_above(mx[0]) + (NEAREST ? 1 : 0), eb = exponent_above(mx[1]) + (NEAREST ? 1 : 0);
+    if (wave == 0) {
+        unsigned *const bad = (unsigned *)((char *)header + bad_offset);
+        const unsigned long long anyA = __ballot(mx[0] >= 0x7ff0000000000000ULL), anyB = __ballot(mx[1] >= 0x7ff0000000000000ULL);
+        if (tn == 0) {
+            if (hh == 0) eA[ra] = ra < m ? ea : 0;
+            if (lane == 0) bad[tm] = anyA ? 1u : 0u;
+        }
+        if (tm == 0) {
+            if (hh == 0) eB[rb] = rb < n ? eb : 0;
+            if (lane == 0) bad[tiles_m + tn] = anyB ? 1u : 0u;
+        }
+        if (blockIdx.x == 0 && lane < 6) {                   // the header, as scale_split_kernel writes it
+            const unsigned long long v[6] = {0ULL, (unsigned long long)(tiles_m + tiles_n), (unsigned long long)bad_offset, kBadWordsMagic,
+                                             (unsigned long long)(uintptr_t)header, 0ULL};
+            header[lane == 0 ? 0 : kHeaderBadWords + lane - 1] = v[lane];
+        }
+    }
+    typedef int vec __attribute__((ext_vector_type(NQ)));
+    vec af[S], bf[S];
+    auto slice = [&](const unsigned long long (&x)[NQ][4], int e, vec (&to)[S]) __attribute__((always_inline)) {
+        Quad<NEAREST> q[NQ];
+#pragma unroll
+        for (int t = 0; t < NQ; ++t) q[t].load(x[t], e);
+        static_for<0, S>([&](auto LC) __attribute__((always_inline)) {
+            constexpr int l = decltype(LC)::value, WIN = Quad<NEAREST>::WIN;
+#pragma unroll
+            for (int t = 0; t < NQ; ++t) {
+                if constexpr (l % WIN == 0) q[t].window();
+                to[l][t] = (int)q[t].template word<l % WIN + 1>();
+            }
+        });
+    };
+    constexpr int kZeroScale = 4096;                         // exponent at which every finite number has zero slices only
+    slice(xa, ra < m ? ea : kZeroScale, af);
+    slice(xb, rb < n ? eb : kZeroScale, bf);
+    v16i acc[S];
+#pragma unroll
+    for (int d = 0; d < S; ++d)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[d][q] = 0;
+    static_for<0, S>([&](auto L) {
+        constexpr int l = decltype(L)::value;
+        static_for<0, S - l>([&](auto H) {
+            constexpr int h = decltype(H)::value;
+            if constexpr (EPL == 16) acc[l + h] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[h], af[l], acc[l + h], 0, 0, 0);
+            else acc[l + h] = __builtin_amdgcn_mfma_i32_32x32x16_i8(__builtin_bit_cast(long, bf[h]), __builtin_bit_cast(long, af[l]), acc[l + h], 0, 0, 0);
+        });
+    });
+    auto *const sexp = (int *)(smx + 2 * 8 * 32);            // exponents of the columns, for the lanes of other columns
+    if (wave == 0 && hh == 0) sexp[r] = eb;
+    // planes: entry (r, k) of a k-block at 16 (r + 32 (k / 16)) + k % 16
+    auto store = [&](int8_t *planes, int tile, const vec (&from)[S]) {
+        int8_t *to = planes + ((size_t)tile * KB + k0 / 32) * (S * kFragBytes) + (EPL == 16 ? lane * 16 : (r + 32 * (wave & 1)) * 16 + 8 * hh);
+#pragma unroll
+        for (int l = 0; l < S; ++l) *(vec *)(to + l * kFragBytes) = from[l];
+    };
+    if (tn == 0) store(pA, tm, af);
+    if (tm == 0) store(pB, tn, bf);
+    __syncthreads();
+    int ec[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) ec[q] = sexp[eighths_column(wave, lane, q)];
+    __syncthreads();
+    eighths_sums<S>(acc, lds, lane, wave, [&](const int (&D)[2][S]) {
+        if (ra >= m) return;
+        const bool stream = stream_c(C, ldc);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int nj = tn * 32 + eighths_column(wave, lane, q);
+            if (nj < n) store_c(&C[ra + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[q], Q), ea + ec[q]), stream);
+        }
+    });
 }
 
 // ---- the same tile for 11 ... 20 slices, whose diagonal sums do not fit the registers together: passes over groups of Ws
@@ -434,7 +593,57 @@ hipError_t launch_eighths_plan(int m, int n, int kp, int stride, const int8_t *p
     else return launch_eighths_passes<P.w[0], P.w[1], P.w[2]>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
 }
 
+template <int S, bool NEAREST>
+hipError_t launch_eighths_whole(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int32_t *eA, int32_t *eB, int8_t *pA, int8_t *pB,
+                                unsigned long long *header, size_t bad_offset, double *C, int ldc, int Q, hipStream_t st)
+{
+    const int kp = round_up(k, kPad), tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
+    note_gemm_kernel("gemm_eighths_kernel<%d> tile 32x32, 8 wavefronts, k in eighths, scales and slices in the same launch", S);
+    auto launch = [&](auto EC) -> hipError_t {
+        auto kern = gemm_eighths_whole_kernel<S, NEAREST, decltype(EC)::value>;
+        static std::atomic<unsigned long long> configured{0};
+        if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgEighths<S>::LDS, configured); e != hipSuccess) return e;
+        kern<<<(unsigned)(tiles_m * tiles_n), 512, CfgEighths<S>::LDS, st>>>((const unsigned long long *)A, lda, (const unsigned long long *)B, ldb, eA, eB, pA, pB,
+                                                                             C, ldc, m, n, k, kp / kFrag, tiles_m, header, (long long)bad_offset, Q);
+        return hipGetLastError();
+    };
+    if (kp <= 128) return launch(std::integral_constant<int, 8>{});
+    if constexpr (S <= kWholeLong && !NEAREST) return launch(std::integral_constant<int, 16>{});
+    return hipErrorInvalidValue;
+}
+
 }  // namespace
+
+// Where it pays (calls, us, two launches and this; 9 us is what the host takes for two of them, 6 for one): up to one tile to a compute unit and k = 128
+// throughout (128^3 s = 1 / 3 / 5 / 7 / 8 / 9 8.7 / 9.6 / 8.8 / 9.6 / 8.9 / 9.4 and 6.2 / 6.8 / 7.6 / 8.0 / 8.5 / 9.3, 512 x 512 x 128 s = 3 / 7 9.7 / 9.9 and
+// 6.8 / 8.8; 10 slices even; 700 x 700 x 128, 484 tiles, s = 3 / 7 9.6 / 12.6 and 8.9 / 15.6); up to 256, where a wavefront slices twice as
+// much, with three slices (128 x 128 x 256 s = 2 / 3 / 4 / 5 8.7 / 9.5 / 8.7 / 8.7 and 6.9 / 7.7 / 8.4 / 9.8, 500 x 500 x 256 s = 4 8.8 and 9.2);
+// nearest slices, which cost half as much again, up to four (128^3 s = 3 / 7 8.9 / 9.0 and 7.3 / 10.1).
+bool gemm_eighths_whole_handles(int m, int n, int k, int s, bool nearest)
+{
+    if (m < 1 || n < 1 || k < 1 || (long long)((m + 31) / 32) * ((n + 31) / 32) > device_cus()) return false;
+    return k <= 128 ? s <= (nearest ? kWholeNearest : kWholeMost) : k <= 256 && s <= kWholeLong && !nearest;
+}
+
+hipError_t launch_gemm_eighths_whole(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int s, bool nearest, int32_t *eA,
+                                     int32_t *eB, int8_t *pA, int8_t *pB, unsigned long long *header, size_t bad_offset, double *C, int ldc, int Q,
+                                     hipStream_t st)
+{
+    if (!gemm_eighths_whole_handles(m, n, k, s, nearest)) return hipErrorInvalidValue;
+    auto launch = [&](auto SC) -> hipError_t {
+        constexpr int S = decltype(SC)::value;
+        if constexpr (S <= kWholeNearest)
+            if (nearest) return launch_eighths_whole<S, true>(m, n, k, A, lda, B, ldb, eA, eB, pA, pB, header, bad_offset, C, ldc, Q, st);
+        return launch_eighths_whole<S, false>(m, n, k, A, lda, B, ldb, eA, eB, pA, pB, header, bad_offset, C, ldc, Q, st);
+    };
+    static_assert(kWholeMost == 9, "cases");
+    switch (s) {
+#define OZ_CASE(S_) case S_: return launch(std::integral_constant<int, S_>{});
+        OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9)
+#undef OZ_CASE
+    }
+    return hipErrorInvalidValue;
+}
 
 hipError_t launch_gemm_eighths_passes(int s, int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                                       const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)

@@ -273,6 +273,12 @@ hipError_t launch_gemm_halves16(int s, int m, int n, int kp, const int8_t *pA, c
                                 const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
 hipError_t launch_gemm_eighths(int s, int m, int n, int kp, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                                const int32_t *eB, double *C, int ldc, int Q, hipStream_t st);
+// the same with scales and slices formed in the launch (equal counts, contractions up to 256, few tiles); C may not share memory with A or B.
+// It leaves planes, exponents, header and non-finite words as launch_scale_split does.
+bool gemm_eighths_whole_handles(int m, int n, int k, int s, bool nearest);
+hipError_t launch_gemm_eighths_whole(int m, int n, int k, const double *A, int lda, const double *B, int ldb, int s, bool nearest, int32_t *eA,
+                                     int32_t *eB, int8_t *pA, int8_t *pB, unsigned long long *header, size_t bad_offset, double *C, int ldc, int Q,
+                                     hipStream_t st);
 // equal counts 2 ... 9, one operand of at most 64 rows / columns, the other large (gemm_vectors.hip): the planes of the
 // short operand must hold its slices, the long one is sliced by the kernel (exponents from its maxima, stored as
 // launch_split_both stores them); its planes are only room

@@ -65,6 +65,58 @@ def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
     check(ozimmu.dgemm3(dA, dB, s, s, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2), A, B, s, s, nearest=True, Q=2)
 
 
+WHOLE = "scales and slices in the same launch"
+
+
+# Scales, slices and product in one launch: edges of tiles, half k-blocks that are whole, ragged and empty, both depths, the ends of the rule; the
+# planes, exponents and the non-finite report that it leaves
+@pytest.mark.parametrize("s", range(1, 10))
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (33, 31, 15), (64, 32, 128), (100, 130, 113), (512, 500, 97), (31, 65, 129), (200, 190, 255), (480, 512, 256)])
+def test_everything_in_one_launch(m, n, k, s):
+    A, B = workloads.pow2_scaled(m, n, k, 30, 3 + k)
+    if m > 4:
+        special(A, B)
+    dA, dB = ozimmu.colmajor_empty(m + 1, k)[1:, :], ozimmu.colmajor_empty(k + 3, n)[3:, :]
+    dA.copy_(torch.as_tensor(A))
+    dB.copy_(torch.as_tensor(B))
+    ws = ozimmu.alloc_workspace(m, n, k, s)
+    ws.fill_(0x5a)
+    big = ozimmu.colmajor_empty(m + 3, n).fill_(7.0)
+    C = ozimmu.dgemm(dA, dB, s, C=big[2:m + 2, :], workspace=ws, check_finite=True)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert (WHOLE in ozimmu.last_gemm_kernel()) == (k <= 128 or s <= 3), ozimmu.last_gemm_kernel()
+    check(C, A, B, s, s)
+    assert (big[:2] == 7).all() and (big[m + 2:] == 7).all()
+    other = ozimmu.alloc_workspace(m, n, k, s)
+    try:
+        ozimmu.debug_small_tile_limit(256)
+        want = ozimmu.dgemm(dA, dB, s, workspace=other)
+    finally:
+        ozimmu.debug_small_tile_limit(-1)
+    assert WHOLE not in ozimmu.last_gemm_kernel() and torch.equal(C, want)
+    for x, y in zip(ozimmu.get_exponents(m, n, k, s, ws), ozimmu.get_exponents(m, n, k, s, other)):
+        assert torch.equal(x, y)
+    assert torch.equal(ozimmu.debug_diagonals(m, n, k, s, ws), ozimmu.debug_diagonals(m, n, k, s, other))
+    check(ozimmu.dgemm3(dA, dB, s, s, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2), A, B, s, s, nearest=True, Q=2)
+    for X in (dA, dB):                       # the last entry of either operand is looked at
+        X[-1, -1] = float("nan")
+        with pytest.raises(ozimmu.OzimmuError):
+            ozimmu.dgemm(dA, dB, s, workspace=ws, check_finite=True)
+        X[-1, -1] = 0.0
+
+
+def test_a_result_over_an_operand_takes_two_launches():
+    m, s = 96, 3
+    A, B = workloads.lognormal(m, m, m, 1.0, 8)
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    want = ozimmu.dgemm(dA, dB, s)
+    assert WHOLE in ozimmu.last_gemm_kernel()
+    for X, Y, C in ((dA.clone(memory_format=torch.preserve_format), dB, 0), (dA, dB.clone(memory_format=torch.preserve_format), 1)):
+        C = (X, Y)[C]
+        ozimmu.dgemm(X, Y, s, C=C)
+        assert WHOLE not in ozimmu.last_gemm_kernel() and torch.equal(C, want)
+
+
 @pytest.mark.parametrize("m,n,k", [(5, 3, 1), (4, 9, 127), (64, 6, 128), (17, 33, 129), (70, 50, 1023), (70, 50, 1024), (31, 8, 1025),
                                    (9, 130, 2048), (33, 20, 2049), (65, 40, 4096), (7, 5, 4097), (9000, 3288, 40), (8200, 4100, 513),
                                    (12000, 300, 1100)])
