@@ -19,7 +19,7 @@ constexpr unsigned kOnes = 0x01010101u, kTops = 0x80808080u, kLows = 0x7f7f7f7fu
 template <bool NEAREST>
 struct Quad {
     static constexpr int WIN = NEAREST ? 8 : 9;       // slices per window
-    double y[4];               // what the windows so far have left, scaled so that the next slice starts below 2^0
+    double y[4];               // what the windows so far have left, scaled so that the next slice starts below 2^31
     unsigned neg;              // byte mask of the negative entries
     unsigned sticky;           // NEAREST: byte i = last slice of the window below whose guard bit entry i has bits left
     unsigned carry;            // NEAREST: byte i = c_{l-1} of entry i
@@ -30,7 +30,7 @@ struct Quad {
         neg = carry = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            y[i] = ldexp(__builtin_fabs(__longlong_as_double((long long)bits[i])), -e);
+            y[i] = ldexp(__builtin_fabs(__longlong_as_double((long long)bits[i])), 31 - e);
             neg |= (unsigned)((int)(bits[i] >> 32) >> 31) & (0xffu << (8 * i));
         }
     }
@@ -40,18 +40,18 @@ struct Quad {
         sticky = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            double t = y[i] * 2147483648.0;
-            hi[i] = (unsigned)t;
-            t = (t - (double)hi[i]) * 4294967296.0;
+            hi[i] = (unsigned)y[i];
+            const double t = (y[i] - (double)hi[i]) * 4294967296.0;
             lo[i] = (unsigned)t;
             y[i] = t - (double)lo[i];
-            if (NEAREST) {
+            if (!NEAREST) y[i] *= 2147483648.0;
+            else {
                 // bits left below the guard bit 62 - 7 j of slice j: always if anything is left beyond the window, else
                 // while j <= (61 - (lowest bit of the window)) / 7
                 const unsigned long long F = (unsigned long long)hi[i] << 32 | lo[i];
                 const int x = y[i] != 0.0 ? 63 : F ? 61 - __builtin_ctzll(F) : 0;
                 sticky |= (((unsigned)(x < 0 ? 0 : x) * 9363u) >> 16) << (8 * i);      // x / 7
-                y[i] = (y[i] + (double)(lo[i] & 127u)) * 0.0078125;  // (the window's last seven bits belong to the next one)
+                y[i] = (y[i] + (double)(lo[i] & 127u)) * 16777216.0;  // (the window's last seven bits belong to the next one)
             }
         }
     }
@@ -72,8 +72,11 @@ struct Quad {
     __device__ __forceinline__ unsigned word()
     {
         unsigned v;
-        if constexpr (!NEAREST) v = fields<63 - kSliceBits * J, 7>();
-        else {
+        if constexpr (!NEAREST) {
+            // -v, byte by byte, where neg: ((v ^ 7f) + 1) ^ 80, which no byte carries out of (v < 128)
+            v = fields<63 - kSliceBits * J, 7>();
+            return ((v ^ (neg & kLows)) + (neg & kOnes)) ^ (neg & kTops);
+        } else {
             const unsigned g = fields<62 - kSliceBits * J, 8>();         // slice and the guard bit below it
             const unsigned f = (g >> 1) & kLows;
             const unsigned left = (((sticky | kTops) - (unsigned)J * kOnes) >> 7) & kOnes;   // J <= sticky
