@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void split_both_kernel(const unsigned long lon
 // line run on the same XCD, one after the other in launch order.  The four bytes a lane has of a slice make up PR * 16
 // contiguous bytes of the fragment with those of its neighbours.
 // bad[b] != 0: work-group b has met a NaN or an infinity (the maximum of the bit patterns shows it).
-template <bool NEAREST, int PR, int NV>
+template <bool NEAREST, int PR, int NV, bool THROUGH>
 __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long long *__restrict__ A, int lda, int m,
                                                            const unsigned long long *__restrict__ B, int ldb, int n, int K,
                                                            int sA, int sB, int cA, int cB, int32_t *__restrict__ eA,
@@ -290,7 +290,11 @@ __global__ __launch_bounds__(1024) void scale_split_kernel(const unsigned long l
         unsigned *dst = (unsigned *)(base + (size_t)(c >> 1) * ((size_t)cs * kFragBytes) + (c & 1) * (32 * 16));
         Quad<NEAREST> el[1];
         el[0].load(x[v], e);
-        for_each_slice<NEAREST, 1>(el, s, [&](int l, const unsigned (&wd)[1]) { dst[(size_t)(l - 1) * (kFragBytes / 4)] = wd[0]; });
+        for_each_slice<NEAREST, 1>(el, s, [&](int l, const unsigned (&wd)[1]) {
+            unsigned *to = dst + (size_t)(l - 1) * (kFragBytes / 4);
+            if constexpr (THROUGH) asm volatile("global_store_dword %0, %1, off sc1" ::"v"(to), "v"(wd[0]) : "memory");
+            else *to = wd[0];
+        });
         // (the planes hold cs >= s slices per entry; those beyond s are zeros)
         for (int l = s + 1; l <= cs; ++l) dst[(size_t)(l - 1) * (kFragBytes / 4)] = 0;
     }
@@ -397,6 +401,12 @@ static int scale_split_waves(int m, int n, int rows, int kp, int c)
     return most == 16 ? 16 : (waves + sweeps - 1) / sweeps;       // (of eight, no more than the sweeps over k keep busy)
 }
 
+// Whether the slices are written through the L2s as they are formed (device-scope stores) rather than at the end of the launch, when the next one
+// waits for it: where the planes are small enough that the memory-side cache takes them at once. Calls, us, plain and through, by bytes of the planes: 10 MB
+// 1024 x 1024 x 512 s = 9 28.6 and 28.0; 15 MB 1024^3 s = 7 35.2 and 34.3; 20 MB 1200^3 s = 7 55.8 and 54.3; 31 MB 1500^3 s = 7 102.7 and 101.8; 42 MB 1700^3 s = 7
+// 129.9 and 130.1; 52 MB 1900^3 s = 7 174.7 and 183.4; 72 MB 2000^3 s = 9 263 and 274.
+static bool scale_split_through(int m, int n, int kp, int c) { return (long long)c * kp * ((long long)m + n) <= 32000000LL; }
+
 static long long scale_split_groups(int m, int n, int rows)
 {
     return (((long long)m + rows - 1) / rows + ((long long)n + rows - 1) / rows + 7) / 8 * 8;
@@ -428,7 +438,8 @@ hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, con
     auto launch = [&](auto PRC, auto NVC) {
         constexpr int PR = decltype(PRC)::value, NV = decltype(NVC)::value;
         const int panelsA = (m + PR - 1) / PR, panels = panelsA + (n + PR - 1) / PR;
-        auto kern = nearest ? scale_split_kernel<true, PR, NV> : scale_split_kernel<false, PR, NV>;
+        auto kern = scale_split_through(m, n, kp, c) ? (nearest ? scale_split_kernel<true, PR, NV, true> : scale_split_kernel<false, PR, NV, true>)
+                                                     : (nearest ? scale_split_kernel<true, PR, NV, false> : scale_split_kernel<false, PR, NV, false>);
         kern<<<(unsigned)scale_split_groups(m, n, PR), 64 * scale_split_waves(m, n, PR, kp, c), 0, st>>>(
             (const unsigned long long *)A, lda, m, (const unsigned long long *)B, ldb, n, k, sA, sB, cA, cB, eA, eB, pA, pB, kp / kFrag,
             panelsA, header, panels, (long long)bad_offset, bad);

@@ -136,6 +136,16 @@ def test_scales_and_slices_in_one_launch(m, n, k, sA, sB, nearest):
     check(ozimmu.dgemm3(dA, dB, sA, sB, splitting=splitting), A, B, sA, sB, nearest=nearest)
 
 
+# planes of 32000000 bytes, the most that are written through the caches, and of a little more; four and eight rows to a work-group
+@pytest.mark.parametrize("nearest", [False, True])
+@pytest.mark.parametrize("m,n,k,s", [(1300, 1200, 1280, 10), (1300, 1201, 1280, 10), (1203, 47, 3100, 8), (7000, 1000, 250, 15), (7000, 1000, 250, 16)])
+def test_planes_written_through(m, n, k, s, nearest):
+    A, B = workloads.lognormal(m, n, k, 1.0, 23 + s)
+    special(A, B)
+    splitting = ozimmu.SPLIT_NEAREST if nearest else ozimmu.SPLIT_TRUNCATE
+    check(ozimmu.dgemm3(ozimmu.to_colmajor(A), ozimmu.to_colmajor(B), s, s, splitting=splitting), A, B, s, s, nearest=nearest)
+
+
 # five to eight sweeps over k: four rows to a work-group (1100 x 1050: five, seven, eight; 4100 x 90: three of eight wavefronts), eight
 # rows (2500 x 1700: five to eight; 3003 x 37: six, with a last work-group of three rows), the ends of the rule by bytes (2000 x 2100 x 4000 with 6 and 7
 # slices)
