@@ -202,13 +202,12 @@ struct CfgEighths {
     static constexpr int LDS = ROUND * 8 * 8 * 64 * 8;
 };
 
-// The sums of the eight wavefronts meet in LDS, ROUND diagonals at a time; f gets those of accumulator registers 2 wave and 2 wave + 1.
-template <int S, class F>
-__device__ __forceinline__ void eighths_sums(const v16i (&acc)[S], unsigned char *lds, int lane, int wave, F &&f)
+// The sums of the eight wavefronts meet in LDS, ROUND diagonals at a time; D: those of accumulator registers 2 wave and 2 wave + 1.
+template <int S>
+__device__ __forceinline__ void eighths_sums(const v16i (&acc)[S], unsigned char *lds, int lane, int wave, int (&D)[2][S])
 {
     typedef int v2i __attribute__((ext_vector_type(2)));
     v2i *x = (v2i *)lds;
-    int D[2][S];
     constexpr int ROUND = CfgEighths<S>::ROUND;
     static_for<0, (S + ROUND - 1) / ROUND>([&](auto P) {
         constexpr int a0 = decltype(P)::value * ROUND, a1 = a0 + ROUND < S ? a0 + ROUND : S;
@@ -227,7 +226,6 @@ __device__ __forceinline__ void eighths_sums(const v16i (&acc)[S], unsigned char
             D[1][a] = s[1];
         }
     });
-    f(D);
 }
 // column of the tile that register 2 wave + r of a lane belongs to
 __device__ __forceinline__ int eighths_column(int wave, int lane, int r)
@@ -279,17 +277,17 @@ __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restr
             });
         }
     }
-    eighths_sums<S>(acc, lds, lane, wave, [&](const int (&D)[2][S]) {
-        const int mi = tm * 32 + (lane & 31);
-        if (mi >= m) return;
-        const bool stream = stream_c(C, ldc);
-        const int ea = eA[mi];
+    int D[2][S];
+    eighths_sums<S>(acc, lds, lane, wave, D);
+    const int mi = tm * 32 + (lane & 31);
+    if (mi >= m) return;
+    const bool stream = stream_c(C, ldc);
+    const int ea = eA[mi];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            const int nj = tn * 32 + eighths_column(wave, lane, r);
-            if (nj < n) store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[r], Q), ea + eB[nj]), stream);
-        }
-    });
+    for (int r = 0; r < 2; ++r) {
+        const int nj = tn * 32 + eighths_column(wave, lane, r);
+        if (nj < n) store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[r], Q), ea + eB[nj]), stream);
+    }
 }
 
 // ---- the same tile, scales and slices in the same launch: contractions of up to 256, few tiles ----------------------------------
@@ -425,15 +423,15 @@ __global__ __launch_bounds__(512) void gemm_eighths_whole_kernel(
 #pragma unroll
     for (int q = 0; q < 2; ++q) ec[q] = sexp[eighths_column(wave, lane, q)];
     __syncthreads();
-    eighths_sums<S>(acc, lds, lane, wave, [&](const int (&D)[2][S]) {
-        if (ra >= m) return;
-        const bool stream = stream_c(C, ldc);
+    int D[2][S];
+    eighths_sums<S>(acc, lds, lane, wave, D);
+    if (ra >= m) return;
+    const bool stream = stream_c(C, ldc);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int nj = tn * 32 + eighths_column(wave, lane, q);
-            if (nj < n) store_c(&C[ra + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[q], Q), ea + ec[q]), stream);
-        }
-    });
+    for (int q = 0; q < 2; ++q) {
+        const int nj = tn * 32 + eighths_column(wave, lane, q);
+        if (nj < n) store_c(&C[ra + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[q], Q), ea + ec[q]), stream);
+    }
 }
 
 // ---- the same tile for 11 ... 20 slices, whose diagonal sums do not fit the registers together: passes over groups of Ws
