@@ -51,6 +51,21 @@ static double pair_rounds(int s, long long blocks, int cus)
     return whole == 0 ? 0.65 : whole + (s == 4 ? 0.6 : s <= 6 ? 0.45 : 0.35) + 0.2 * part;
 }
 
+// 96 x 64 tiles: one round of them where 64 x 64 tiles are more than the compute units, so that the other shapes leave a quarter of the chip, or of a second
+// round, empty.  A round takes 0.78 of one of 128 x 64 tiles.  Calls, us, best of the others and this, s = 4 ... 9, 13 ... 18: 960 x 1271 x 136 s = 4 12.5 / 12.3 (even at
+// kp = 256, hence the line), 545 x 1984 x 3279 s = 4 65.9 / 60.9, 873 x 1163 x 927 s = 5 29.2 / 25.3, 2240 x 568 x 294 s = 6 19.0 / 17.0, 5312 x 212 x 136 s = 7 17.5 / 15.9, 1531 x 777 x 1001
+// s = 8 53.3 / 46.4, 370 x 2691 x 1378 s = 16 212 / 170, 686 x 1920 x 3766 s = 18 693 / 567; over 82 such sizes 1.05 (4 ... 6), 1.11 (7 ... 9) and 1.23 (13 ... 18) in the mean,
+// slowest 0.997.  With more rounds, 13 ... 18 slices: even with the others at best.  10 ... 12 keep the kernels of one pass, and k up to 128 and
+// 13 ... 18 at 13/16 of a round (208 ... 211 tiles) the tiles that tests/test_gpu_passes.py has there; 19 and 20 run in three passes, the first too short for this
+// tile's copies.  (32-bit offsets into the planes.)
+static bool one_round_of_96(int s, int m, int n, int kp)
+{
+    const int cus = device_cus();
+    const long long blocks = order_blocks(m, n, 96, 64), small = (long long)((m + 63) / 64) * ((n + 63) / 64);
+    if (blocks > cus || small <= cus || (long long)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * s >= (1LL << 32)) return false;
+    return kp > (s == 4 ? 256 : 128) && (s <= 9 || (s >= 13 && s <= 18 && 64 * blocks / cus != 52));
+}
+
 // 4 ... 9 slices: the other kernels by their tile (128 x 64 outputs count one round, larger tiles as many more).  What is taken where the
 // figures are even is what stood there before up to 6 slices, whose fits are the looser ones.  Calls, operands that change from one to
 // the next, against the other kernels alone and against the best of the three: geometric means over 900 random sizes 1.085 and 0.997, slowest
@@ -64,15 +79,15 @@ PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn)
     static constexpr LaunchTime k128x64[6] = {{1.4, 4.5, 4.9}, {1.387, 4.5, 4.9}, {1.241, 4.8, 4.7}, {1.193, 4.75, 4.5}, {1.153, 5.75, 4.05}, {1.126, 5.4, 4.5}};
     static constexpr LaunchTime k128x128[3] = {{1.226, 3.85, 5.85}, {1.147, 4.6, 4.35}, {1.109, 4.05, 5.95}}, k192x128{1.188, 3.95, 4.65};
     static constexpr double kAhead[6] = {0.98, 0.985, 0.99, 1.0, 1.0, 1.0};
+    if (one_round_of_96(s, m, n, kp)) return kPassMiddle;
     const int cus = device_cus();
     const double x = 1e-3 * kp * (s * (s + 1) / 2);
     const double pairs = kPairs[s - 4].us(pair_rounds(s, order_blocks(m, n, 64, 64), cus), x);
     const double runs = kRuns[s - 4].us(single_rounds(s, order_blocks(m, n, 128, 64), cus), x);
     const LaunchTime &t = tm == 64 ? k64[s - 4] : tm == 192 ? k192x128 : tn == 64 || s > 6 ? k128x64[s - 4] : k128x128[s - 4];
     const double others = t.us(single_rounds(s, order_blocks(m, n, tm, tn), cus) * (tm * tn / 8192.0), x);
-    // 96 x 64 tiles, 7 ... 9 slices (its round is not scaled by the area).  Per product 0.92 ... 0.97 of a work-group's rate in 128 x 64 tiles away from the power cap,
-    // so it pays where its rounds fit better: 1531 x 777 x 1001, s = 8, 208 tiles and one round as 156 of 128 x 64: calls 53.1 -> 46.4;
-    // 1412 x 721 x 811, s = 9 55.4 -> 47.0; 640 x 1756 x 2461, s = 9 138 -> 122; 2304 x 2000 x 2560, s = 7, three whole rounds, 281 -> 268.  260 random
+    // several rounds of 96 x 64 tiles, 7 ... 9 slices (its round is not scaled by the area).  Per product 0.92 ... 0.97 of a work-group's rate in 128 x 64 tiles away from the power cap,
+    // so it pays where its rounds fit better: calls 2304 x 2000 x 2560, s = 7, three whole rounds, 281 -> 268.  260 random
     // sizes of more than 256 tiles of 64 x 64: taken by 67 of them, 11.7 percent faster there, none slower; with 1.0 for 0.98 by 78, the slowest 2 percent behind.
     // (kp > 256: shorter ones gain little, 1600 x 1536 x 230, s = 9 31.5 / 32.4; 32-bit offsets into the planes)
     if (s >= 7 && kp > 256 && (long long)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * s < (1LL << 32)) {
@@ -115,6 +130,7 @@ PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
     const PassPlan P = pass_plan(s);
     for (int p = 0, d = 0; p + 1 < P.n; ++p)
         if ((d += P.w[p]) % Q != 0) return kNoPasses;                // a level of Q diagonals straddles two passes
+    if (one_round_of_96(s, m, n, kp)) return kPassMiddle;
     if (tiles(64, 64) <= cus) return s <= 16 || kp < (s == 18 ? 256 : 512) ? kNoPasses : kPassSmall;
     const double small = pair_rounds(s, order_blocks(m, n, 64, 64), cus);
     const long long blocks = order_blocks(m, n, 128, 64);

@@ -31,7 +31,7 @@
 // 128 x 64 tile is then worked on in runs: a work-group takes the tiles b, b + grid, ..., the copies of the next tile's first
 // steps follow those of the last stage, and the epilogue stands between them (4096 x 4096 x 1024, s = 8 / 9 387 / 469 us as 64 x 64 tiles, 373 /
 // 447 in runs; 64 x 64 tiles gain nothing by runs).
-// 96 x 64 tiles in runs, twelve wavefronts of 32 x 16 outputs, three to a SIMD: for 7 ... 9 slices where 128 x 64 tiles leave a round partly filled and
+// 96 x 64 tiles, twelve wavefronts of 32 x 16 outputs, three to a SIMD: for 4 ... 9 slices (in runs) and 13 ... 18 where 128 x 64 tiles leave a round partly filled and
 // pairs of 64 x 64 ones do too.  A wavefront reads three 16-row operands for two blocks where 32 x 32 reads four for four, so LDS is read
 // half as often again (about 0.85 of its cycles with the copies), which costs nothing under the power cap (1536 x 1024 x 8000, s = 7, one whole
 // round: 3.13 POP/s) and 10 to 15 percent away from it.  Eight wavefronts of 48 x 16, which read less, were behind: two to a SIMD (1531 x 777 x 1001,
@@ -200,6 +200,7 @@ using PassTileWide = PassTile<4, 2, 13>;       // 128 x 64, 156 KiB
 using PassTileRuns = PassTile<4, 2, 13, 1, true>;      // the same for one pass, several tiles to a work-group
 using PassTileSmall = PassTile<2, 2, 10>;      // 64 x 64, 80 KiB: two work-groups to a compute unit
 using PassTileMiddle = PassTile<3, 4, 16, 1, true, 1>;     // 96 x 64 in runs, twelve wavefronts of 32 x 16, 160 KiB
+using PassTileMiddleLone = PassTile<3, 4, 16, 1, false, 1>;        // the same, a work-group to a tile: several passes
 // operands are read from LDS this many matrix instructions ahead; products between synchronisations (16 ... 40 products and
 // 6 ... 16 instructions are within 1 % of each other at 13 and 18 slices,
 // one pass of 8 slices, 64 x 64 tile, 1024 x 1024 x 4096: 104 us with 16, 111 with 24)
@@ -272,7 +273,6 @@ __device__ __forceinline__ void passes_of_a_tile(const int8_t *__restrict__ pA, 
     if constexpr (ONE) srcA = (unitA ? pA : pB) + (size_t)((wave & 1) * stride) * kFragBytes;
     const unsigned lane16 = lane * 16;
     // (PERSIST: the tile is in the lane offset, 32 bits; behind the last stage come the first ones of the next tile)
-    static_assert(!ONE || PERSIST, "one unit a wavefront: the tile in the lane offset");
     unsigned tileA = ONE ? unit_row(tm, tn) * (unsigned)row_bytes : PERSIST ? (unsigned)(tm * FM) * (unsigned)row_bytes : 0;
     unsigned tileB = PERSIST ? (unsigned)(tn * FN) * (unsigned)row_bytes : 0;
     unsigned nextA = 0, nextB = 0;
@@ -513,10 +513,12 @@ template <class T, int... Ws>
 hipError_t launch_passes(int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                          const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
 {
-    // (32-bit lane offsets to the tile where a work-group takes several: larger planes go to a launch of single tiles)
-    if constexpr (T::PERSIST && T::COPIES == kCopyPair)
-        if ((size_t)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * stride >= (1ULL << 32))
-            return launch_passes<PassTile<T::WVM, T::WVN, T::SLOTS>, Ws...>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
+    // (32-bit lane offsets to the tile where a work-group takes several, or 96 x 64 tiles: larger planes go to a launch of single tiles)
+    const bool far = (size_t)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * stride >= (1ULL << 32);
+    if constexpr (T::COPIES == kCopyOne) {
+        if (far) return hipErrorInvalidValue;                                       // (the choice of shape does not ask for it)
+    } else if constexpr (T::PERSIST)
+        if (far) return launch_passes<PassTile<T::WVM, T::WVN, T::SLOTS>, Ws...>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
     constexpr int TM = T::TM, TN = T::TN, NP = sizeof...(Ws), WS[NP] = {Ws...};
     for (int p = 1; p < NP; ++p)
         if (diagonals_before<NP>(WS, p) % Q != 0) return hipErrorInvalidValue;      // (gemm_passes_shape() does not ask for it)
@@ -552,8 +554,9 @@ hipError_t launch_pass_plan(int m, int n, int kp, int stride, const int8_t *pA, 
                                        const int32_t *eA, const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)     \
     {                                                                                                                       \
         if (shape == kPassSmall) return launch_pass_plan<PassTileSmall, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st); \
-        if constexpr (S_ >= 7 && S_ <= 9)                                                                                   \
-            if (shape == kPassMiddle) return launch_pass_plan<PassTileMiddle, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st); \
+        if constexpr (S_ <= 9 || (S_ >= 13 && S_ <= 18))                                                                    \
+            if (shape == kPassMiddle)                                                                                       \
+                return launch_pass_plan<std::conditional_t<(S_ >= 10), PassTileMiddleLone, PassTileMiddle>, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st); \
         using Wide = std::conditional_t<(S_ >= 10), PassTileWide, PassTileRuns>;                                            \
         if constexpr (S_ == 10) return hipErrorInvalidValue;                   /* (nowhere ahead: gemm_passes_shape) */     \
         else return launch_pass_plan<Wide, S_>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);                            \

@@ -54,14 +54,18 @@ def test_one_pass_in_runs(m, n, k, s):
     both_ways(A, B, s, s, f"gemm_passes_kernel<{s}> tile 128x64")
 
 
-# 96 x 64 tiles: one round and several, a last tile that reaches beyond the planes (1650 rows, padded to 1664), the shortest contraction
-@pytest.mark.parametrize("s", [7, 8, 9])
-@pytest.mark.parametrize("m,n,k", [(1531, 777, 1001), (1650, 700, 300), (1650, 2670, 700), (2304, 2000, 600), (1000, 1190, 257)])
-def test_tiles_of_96_rows(m, n, k, s):
+# 96 x 64 tiles: one round and several (7 ... 9), a last tile that reaches beyond the planes (1650 rows, padded to 1664), the shortest contractions, both ends of
+# what one round holds
+@pytest.mark.parametrize("s", [*range(4, 10), *range(13, 19)])
+@pytest.mark.parametrize("m,n,k,only", [(1531, 777, 1001, range(4, 10)), (1531, 841, 300, range(4, 19)), (1650, 700, 450, range(4, 19)), (1650, 2670, 700, range(7, 10)),
+                                        (2304, 2000, 600, range(7, 10)), (1000, 1190, 257, range(4, 10)), (4030, 340, 260, range(4, 19)), (90, 16380, 131, range(5, 19))])
+def test_tiles_of_96_rows(m, n, k, only, s):
+    if s not in only:
+        pytest.skip("another tile")
     A, B = workloads.lognormal(m, n, k, 1.0, 40 + s)
     special(A, B)
     both_ways(A, B, s, s, f"gemm_passes_kernel<{s}> tile 96x64")
-    both_ways(A, B, s - 1, s, "", splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2)
+    both_ways(A, B, s - 1, s, "", splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2 if s < 10 else 3)
 
 
 def test_planes_too_large_for_the_offsets_of_a_run():
