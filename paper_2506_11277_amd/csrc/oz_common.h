@@ -158,6 +158,8 @@ hipError_t launch_finalize(const unsigned long long *maxbits, int32_t *exps, int
 hipError_t launch_kappas(int m, int n, int k, const double *A, int lda, const double *B, int ldb, unsigned long long *hdr,
                          unsigned long long *maxA, unsigned long long *minA, unsigned long long *maxB,
                          unsigned long long *minB, int32_t *expA, int mp, int32_t *expB, int np, hipStream_t st);
+// hdr[0 ... 2] to pinned host memory (its address on the device)
+hipError_t launch_deliver(const unsigned long long *hdr, unsigned long long *host, hipStream_t st);
 hipError_t launch_clear_header(void *header, hipStream_t st);
 // the whole scale extraction of ozimmu_dgemm in three launches: clear, reduce both operands, exponents of both
 // (both_planes: whether the call will leave the planes of both operands, for kHeaderPlanes)

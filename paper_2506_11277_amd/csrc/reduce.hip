@@ -205,6 +205,12 @@ __global__ __launch_bounds__(256) void finalize_kappas_kernel(const unsigned lon
     if ((threadIdx.x & 63) == 0 && ratio) atomicMax(&kappa[isB ? 1 : 0], ratio);
 }
 
+// three words of the header to host memory
+__global__ void deliver_kernel(const unsigned long long *__restrict__ hdr, unsigned long long *__restrict__ host)
+{
+    if (threadIdx.x < 3) __hip_atomic_store(&host[threadIdx.x], hdr[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // exponents of both operands in one launch (no kappa)
 __global__ void finalize_both_kernel(const unsigned long long *__restrict__ maxA, int32_t *__restrict__ expA, int m,
                                      int mp, const unsigned long long *__restrict__ maxB, int32_t *__restrict__ expB,
@@ -256,6 +262,12 @@ hipError_t launch_kappas(int m, int n, int k, const double *A, int lda, const do
     if (hipError_t e = launch_maxima(m, n, k, A, lda, B, ldb, hdr, maxA, maxB, minA, minB, 0ULL, true, st); e != hipSuccess) return e;
     const int gA = (mp + 255) / 256, gB = (np + 255) / 256;
     finalize_kappas_kernel<<<gA + gB, 256, 0, st>>>(maxA, minA, expA, m, mp, maxB, minB, expB, n, np, hdr + 1, gA);
+    return hipGetLastError();
+}
+
+hipError_t launch_deliver(const unsigned long long *hdr, unsigned long long *host, hipStream_t st)
+{
+    deliver_kernel<<<1, 64, 0, st>>>(hdr, host);
     return hipGetLastError();
 }
 

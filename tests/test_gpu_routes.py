@@ -377,3 +377,29 @@ def test_hooks_refuse_planes_that_a_call_has_not_left(m, n):
     small = ozimmu.to_colmajor(A[:, :100]), ozimmu.to_colmajor(B[:100])
     ozimmu.dgemm(*small, s, workspace=ws)
     ozimmu.debug_diagonals(m, n, 100, s, ws)
+
+
+def test_estimates_from_several_threads():
+    # every call has words of its own in host memory while it waits
+    import threading
+    cases = [workloads.lognormal(40 + 3 * i, 30 + 5 * i, 50 + 7 * i, 0.5 + i, 60 + i) for i in range(8)]
+    dev = [(ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)) for A, B in cases]
+    want = [oracle.estimate_slices(A, B, 1e-9, s_max=ozimmu.MAX_SLICES) for A, B in cases]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            ws = ozimmu.alloc_workspace(*dev[i][0].shape[:1], dev[i][1].shape[1], dev[i][0].shape[1], 1)
+            for _ in range(20):
+                got = ozimmu.estimate_slices(*dev[i], 1e-9, workspace=ws)
+                if got != want[i]:
+                    wrong.append((i, got, want[i]))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(cases))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(timeout=60)
+    assert not wrong and not any(t.is_alive() for t in threads)
