@@ -291,20 +291,26 @@ __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restr
 }
 
 // ---- the same tile, scales and slices in the same launch: contractions of up to 256, few tiles ----------------------------------
-// A wavefront has one k-block of the tile, 32 deep (EPL = 16 entries of either operand to a lane), or half of one up to k = 128 (EPL = 8): it reads the
-// entries, the maxima of the rows and columns meet in LDS, and the slices go from the registers that they are formed in to the matrix
-// instruction.  Every row is read and sliced once for each tile of its row, which few tiles make up for by the launch and the
+// A wavefront reads and slices one k-block of the tile, 32 deep (EPL = 16 entries of either operand to a lane), or half of one up to k = 128 (EPL = 8); the
+// maxima of the rows and columns meet in LDS, then the slices do, and four wavefronts multiply them, 16 x 16 outputs each. (Every wavefront multiplying what it has
+// sliced, the eight sums meeting in LDS, moves 2.7 times the bytes through LDS: launch and kernel 8.1 / 10.5 us at
+// 128^3 s = 3 / 7, now 7.6 / 9.2.)  Every row is read and sliced once for each tile of its row, which few tiles make up for by the launch and the
 // gap between the two (128^3, s = 3: 3.4 + 4.1 us on the device and as much again of launches).  The planes, exponents and non-finite words that a call
 // leaves in the workspace are written by the tiles of the first column (A) and row (B).
-// What bounds it: the host up to five slices, then slicing, eight entries of either operand to a lane and one wavefront to a SIMD's issue slot.
-constexpr int kWholeMost = 9, kWholeNearest = 4, kWholeLong = 3;      // slices: k up to 128, nearest ones, k up to 256
+// What bounds it: the host up to seven slices, then slicing, eight entries of either operand to a lane and two wavefronts to a SIMD.
+constexpr int kWholeMost = 10, kWholeNearest = 8, kWholeLong = 4;      // slices: k up to 128, nearest ones, k up to 256
+template <int S, int EPL>
+struct CfgWhole {
+    static constexpr int HEAD = 2 * 8 * 32 * 8 + 64 * 4;     // maxima and exponents
+    static constexpr int LDS = HEAD + 2 * (EPL / 2) * S * kFragBytes;
+};
 template <int S, bool NEAREST, int EPL>
 __global__ __launch_bounds__(512) void gemm_eighths_whole_kernel(
     const unsigned long long *__restrict__ A, int lda, const unsigned long long *__restrict__ B, int ldb, int32_t *__restrict__ eA,
     int32_t *__restrict__ eB, int8_t *__restrict__ pA, int8_t *__restrict__ pB, double *__restrict__ C, int ldc, int m, int n, int K, int KB, int tiles_m,
     unsigned long long *__restrict__ header, long long bad_offset, int Q)
 {
-    constexpr int NQ = EPL / 4;                              // quads of a lane
+    constexpr int NQ = EPL / 4, KBL = EPL / 2;               // quads of a lane, k-blocks of the tile
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tm = blockIdx.x % (unsigned)tiles_m, tn = blockIdx.x / (unsigned)tiles_m, tiles_n = gridDim.x / (unsigned)tiles_m;
     const int lane = threadIdx.x & 63, r = lane & 31, hh = lane >> 5;
@@ -395,42 +401,56 @@ __global__ __launch_bounds__(512) void gemm_eighths_whole_kernel(
     constexpr int kZeroScale = 4096;                         // exponent at which every finite number has zero slices only
     slice(xa, ra < m ? ea : kZeroScale, af);
     slice(xb, rb < n ? eb : kZeroScale, bf);
-    v16i acc[S];
+    // entry (r, k) of a k-block at 16 (r + 32 (k / 16)) + k % 16, in LDS as in the planes
+    const int place = EPL == 16 ? lane * 16 : (r + 32 * (wave & 1)) * 16 + 8 * hh;
+    unsigned char *const sliced = lds + CfgWhole<S, EPL>::HEAD;
 #pragma unroll
-    for (int d = 0; d < S; ++d)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[d][q] = 0;
-    static_for<0, S>([&](auto L) {
-        constexpr int l = decltype(L)::value;
-        static_for<0, S - l>([&](auto H) {
-            constexpr int h = decltype(H)::value;
-            if constexpr (EPL == 16) acc[l + h] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[h], af[l], acc[l + h], 0, 0, 0);
-            else acc[l + h] = __builtin_amdgcn_mfma_i32_32x32x16_i8(__builtin_bit_cast(long, bf[h]), __builtin_bit_cast(long, af[l]), acc[l + h], 0, 0, 0);
-        });
-    });
-    auto *const sexp = (int *)(smx + 2 * 8 * 32);            // exponents of the columns, for the lanes of other columns
-    if (wave == 0 && hh == 0) sexp[r] = eb;
-    // planes: entry (r, k) of a k-block at 16 (r + 32 (k / 16)) + k % 16
-    auto store = [&](int8_t *planes, int tile, const vec (&from)[S]) {
-        int8_t *to = planes + ((size_t)tile * KB + k0 / 32) * (S * kFragBytes) + (EPL == 16 ? lane * 16 : (r + 32 * (wave & 1)) * 16 + 8 * hh);
+    for (int l = 0; l < S; ++l) {
+        *(vec *)(sliced + ((k0 / 32) * S + l) * kFragBytes + place) = af[l];
+        *(vec *)(sliced + ((KBL + k0 / 32) * S + l) * kFragBytes + place) = bf[l];
+    }
+    auto *const sexp = (int *)(smx + 2 * 8 * 32);            // exponents of rows and columns
+    if (wave == 0) sexp[lane] = hh ? eb : ea;
+    auto store = [&](int8_t *planes, int tile, const vec (&from)[S]) __attribute__((always_inline)) {
+        int8_t *to = planes + ((size_t)tile * KB + k0 / 32) * (S * kFragBytes) + place;
 #pragma unroll
         for (int l = 0; l < S; ++l) *(vec *)(to + l * kFragBytes) = from[l];
     };
     if (tn == 0) store(pA, tm, af);
     if (tm == 0) store(pB, tn, bf);
     __syncthreads();
-    int ec[2];
+    if (wave >= 4) return;
+    // 16 rows x 16 columns to each of four wavefronts; this lane's part of an operand as in gemm_fused16_kernel
+    const int i2 = wave & 1, j2 = wave >> 1;
+    const unsigned char *const mine = sliced + ((lane >> 4) >> 1) * (S * kFragBytes) + ((lane & 15) + 32 * ((lane >> 4) & 1)) * 16;
+    v4i acc[S];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) ec[q] = sexp[eighths_column(wave, lane, q)];
-    __syncthreads();
-    int D[2][S];
-    eighths_sums<S>(acc, lds, lane, wave, D);
-    if (ra >= m) return;
+    for (int d = 0; d < S; ++d) acc[d] = v4i{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KBL / 2; ++ks) {
+        v4i a16[S], b16[S];
+#pragma unroll
+        for (int l = 0; l < S; ++l) {
+            a16[l] = *(const v4i *)(mine + (2 * ks * S + l) * kFragBytes + i2 * 256);
+            b16[l] = *(const v4i *)(mine + ((KBL + 2 * ks) * S + l) * kFragBytes + j2 * 256);
+        }
+#pragma unroll
+        for (int l = 0; l < S; ++l)
+#pragma unroll
+            for (int h = 0; h < S - l; ++h) acc[l + h] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b16[h], a16[l], acc[l + h], 0, 0, 0);
+    }
+    const int mi = tm * 32 + i2 * 16 + (lane & 15);
+    if (mi >= m) return;
     const bool stream = stream_c(C, ldc);
+    const int er = sexp[i2 * 16 + (lane & 15)];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int nj = tn * 32 + eighths_column(wave, lane, q);
-        if (nj < n) store_c(&C[ra + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[q], Q), ea + ec[q]), stream);
+    for (int q = 0; q < 4; ++q) {
+        const int c = j2 * 16 + 4 * (lane >> 4) + q, nj = tn * 32 + c;
+        if (nj >= n) continue;
+        int d[S];
+#pragma unroll
+        for (int a = 0; a < S; ++a) d[a] = acc[a][q];
+        store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(d, Q), er + sexp[32 + c]), stream);
     }
 }
 
@@ -600,8 +620,9 @@ hipError_t launch_eighths_whole(int m, int n, int k, const double *A, int lda, c
     auto launch = [&](auto EC) -> hipError_t {
         auto kern = gemm_eighths_whole_kernel<S, NEAREST, decltype(EC)::value>;
         static std::atomic<unsigned long long> configured{0};
-        if (hipError_t e = allow_dynamic_lds((const void *)kern, CfgEighths<S>::LDS, configured); e != hipSuccess) return e;
-        kern<<<(unsigned)(tiles_m * tiles_n), 512, CfgEighths<S>::LDS, st>>>((const unsigned long long *)A, lda, (const unsigned long long *)B, ldb, eA, eB, pA, pB,
+        constexpr int LDS = CfgWhole<S, decltype(EC)::value>::LDS;
+        if (hipError_t e = allow_dynamic_lds((const void *)kern, LDS, configured); e != hipSuccess) return e;
+        kern<<<(unsigned)(tiles_m * tiles_n), 512, LDS, st>>>((const unsigned long long *)A, lda, (const unsigned long long *)B, ldb, eA, eB, pA, pB,
                                                                              C, ldc, m, n, k, kp / kFrag, tiles_m, header, (long long)bad_offset, Q);
         return hipGetLastError();
     };
@@ -612,11 +633,11 @@ hipError_t launch_eighths_whole(int m, int n, int k, const double *A, int lda, c
 
 }  // namespace
 
-// Where it pays (calls, us, two launches and this; 9 us is what the host takes for two of them, 6 for one): up to one tile to a compute unit and k = 128
-// throughout (128^3 s = 1 / 3 / 5 / 7 / 8 / 9 8.7 / 9.6 / 8.8 / 9.6 / 8.9 / 9.4 and 6.2 / 6.8 / 7.6 / 8.0 / 8.5 / 9.3, 512 x 512 x 128 s = 3 / 7 9.7 / 9.9 and
-// 6.8 / 8.8; 10 slices even; 700 x 700 x 128, 484 tiles, s = 3 / 7 9.6 / 12.6 and 8.9 / 15.6); up to 256, where a wavefront slices twice as
-// much, with three slices (128 x 128 x 256 s = 2 / 3 / 4 / 5 8.7 / 9.5 / 8.7 / 8.7 and 6.9 / 7.7 / 8.4 / 9.8, 500 x 500 x 256 s = 4 8.8 and 9.2);
-// nearest slices, which cost half as much again, up to four (128^3 s = 3 / 7 8.9 / 9.0 and 7.3 / 10.1).
+// Where it pays (calls, us, two launches and this; 9 us is what the host takes for two of them, 6.8 for one): up to one tile to a compute unit and k = 128
+// throughout (128^3 s = 1 / 3 / 5 / 7 / 9 / 10 8.7 / 9.6 / 8.8 / 9.6 / 9.4 / 10.4 and 6.8 / 6.8 / 7.0 / 6.8 / 7.4 / 8.1, 500 x 500 x 128 s = 3 / 7 / 10 9.7 / 9.9 / 11.3 and
+// 6.9 / 7.3 / 8.8; 700 x 700 x 128, 484 tiles, s = 7 12.6 against 15.6 then); up to 256, where a wavefront slices twice as much, with four slices (128 x 128 x 256 s = 2 / 3 /
+// 4 / 5 / 7 8.7 / 9.5 / 9.1 / 9.1 / 9.7 and 7.5 / 7.4 / 8.0 / 9.0 / 10.3, 500 x 500 x 256 s = 4 / 5 9.4 / 9.6 and 9.0 / 9.9); nearest slices, which cost half as much again, up to
+// eight (128^3 s = 3 / 6 / 8 8.9 / 9.4 / 9.6 and 7.1 / 8.4 / 9.4). Eleven and more: passes.
 bool gemm_eighths_whole_handles(int m, int n, int k, int s, bool nearest)
 {
     if (m < 1 || n < 1 || k < 1 || (long long)((m + 31) / 32) * ((n + 31) / 32) > device_cus()) return false;
@@ -634,10 +655,10 @@ hipError_t launch_gemm_eighths_whole(int m, int n, int k, const double *A, int l
             if (nearest) return launch_eighths_whole<S, true>(m, n, k, A, lda, B, ldb, eA, eB, pA, pB, header, bad_offset, C, ldc, Q, st);
         return launch_eighths_whole<S, false>(m, n, k, A, lda, B, ldb, eA, eB, pA, pB, header, bad_offset, C, ldc, Q, st);
     };
-    static_assert(kWholeMost == 9, "cases");
+    static_assert(kWholeMost == 10, "cases");
     switch (s) {
 #define OZ_CASE(S_) case S_: return launch(std::integral_constant<int, S_>{});
-        OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9)
+        OZ_CASE(1) OZ_CASE(2) OZ_CASE(3) OZ_CASE(4) OZ_CASE(5) OZ_CASE(6) OZ_CASE(7) OZ_CASE(8) OZ_CASE(9) OZ_CASE(10)
 #undef OZ_CASE
     }
     return hipErrorInvalidValue;

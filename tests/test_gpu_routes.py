@@ -70,7 +70,7 @@ WHOLE = "scales and slices in the same launch"
 
 # Scales, slices and product in one launch: edges of tiles, half k-blocks that are whole, ragged and empty, both depths, the ends of the rule; the
 # planes, exponents and the non-finite report that it leaves
-@pytest.mark.parametrize("s", range(1, 10))
+@pytest.mark.parametrize("s", range(1, 11))
 @pytest.mark.parametrize("m,n,k", [(1, 1, 1), (33, 31, 15), (64, 32, 128), (100, 130, 113), (512, 500, 97), (31, 65, 129), (200, 190, 255), (480, 512, 256)])
 def test_everything_in_one_launch(m, n, k, s):
     A, B = workloads.pow2_scaled(m, n, k, 30, 3 + k)
@@ -84,7 +84,7 @@ def test_everything_in_one_launch(m, n, k, s):
     big = ozimmu.colmajor_empty(m + 3, n).fill_(7.0)
     C = ozimmu.dgemm(dA, dB, s, C=big[2:m + 2, :], workspace=ws, check_finite=True)
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
-        assert (WHOLE in ozimmu.last_gemm_kernel()) == (k <= 128 or s <= 3), ozimmu.last_gemm_kernel()
+        assert (WHOLE in ozimmu.last_gemm_kernel()) == (k <= 128 or s <= 4), ozimmu.last_gemm_kernel()
     check(C, A, B, s, s)
     assert (big[:2] == 7).all() and (big[m + 2:] == 7).all()
     other = ozimmu.alloc_workspace(m, n, k, s)
