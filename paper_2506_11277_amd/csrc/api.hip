@@ -112,7 +112,7 @@ size_t ozimmu_split_scratch_bytes(char side, int rows, int cols)
     return 256 + 8 * (size_t)(nblk > 0 ? nblk : 1);
 }
 
-// Pinned host memory that a kernel writes three words into, for the estimators: a copy of 24 bytes to pageable memory takes
+// Pinned host memory that the last kernel of the estimators writes its three words into: a copy of 24 bytes to pageable memory takes
 // 7 us longer (estimate and product, us, copy and kernel: 200 x 300 x 200 s = 6 49.4 and 41.9, 2944 x 704 x 491 s = 8 82.1 and 75.9). One allocation of 64 slots, made by the first call and kept;
 // a call has a slot of its own until it returns, and copies if none is free or the allocation failed.
 namespace {
@@ -176,12 +176,11 @@ static int kappas(int m, int n, int k, const double *A, int lda, const double *B
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
     auto at = [&](size_t off) { return (unsigned long long *)(ws + off); };
-    OZ_TRY(launch_kappas(m, n, k, A, lda, B, ldb, at(w.off_header), at(w.off_maxA), at(w.off_minA), at(w.off_maxB), at(w.off_minB),
-                         (int32_t *)(ws + w.off_expA), w.mp, (int32_t *)(ws + w.off_expB), w.np, st));
-    unsigned long long host[3];
     HostWords words;
-    if (words.device) OZ_TRY(launch_deliver(at(w.off_header), words.device, st));
-    else OZ_TRY(hipMemcpyAsync(host, ws + w.off_header, sizeof(host), hipMemcpyDeviceToHost, st));
+    OZ_TRY(launch_kappas(m, n, k, A, lda, B, ldb, at(w.off_header), at(w.off_maxA), at(w.off_minA), at(w.off_maxB), at(w.off_minB),
+                         (int32_t *)(ws + w.off_expA), w.mp, (int32_t *)(ws + w.off_expB), w.np, words.device, st));
+    unsigned long long host[3];
+    if (!words.device) OZ_TRY(hipMemcpyAsync(host, ws + w.off_header, sizeof(host), hipMemcpyDeviceToHost, st));
     OZ_TRY(hipStreamSynchronize(st));
     if (words.device)
         for (int i = 0; i < 3; ++i) host[i] = words.host[i];

@@ -112,7 +112,7 @@ struct Workspace {
     int mp, np, kp;                 // padded extents
     int cA, cB;                     // slices per entry in the planes (gemm_path)
     int path;                       // GemmPath
-    size_t off_header;              // 256 B: [0] u32 non-finite flag, [8] u64 kappa_A bits, [16] u64 kappa_B bits, [64] see kHeaderBadWords, [96] see kHeaderPlanes
+    size_t off_header;              // 256 B: [0] u32 non-finite flag, [8] u64 kappa_A bits, [16] u64 kappa_B bits, [24] work-groups that have ended (finalize_kappas_kernel), [64] see kHeaderBadWords, [96] see kHeaderPlanes
     size_t off_maxA, off_minA;      // u64[mp]: integer view of max |a_ij| / min nonzero |a_ij| per row (minA onwards: the non-finite words of launch_scale_split)
     size_t off_maxB, off_minB;      // u64[np]
     size_t off_expA, off_expB;      // i32[mp], i32[np]
@@ -154,12 +154,11 @@ hipError_t launch_reduce(char side, int rows, int cols, const double *X, int ldx
 // exps[b] from maxbits[b], plus `bias` (1 for round-to-nearest slices, whose scale is twice as large)
 hipError_t launch_finalize(const unsigned long long *maxbits, int32_t *exps, int nblk, int bias, hipStream_t st);
 // maxima, smallest nonzero magnitudes and exponents of both operands, the largest ratio of the two per operand into
-// hdr[1] and hdr[2] (bit patterns of max / min); the header is cleared first.  Three launches.
+// hdr[1] and hdr[2] (bit patterns of max / min); the header is cleared first.  Three launches.  host: hdr[0 ... 2] go there too (pinned memory, its address
+// on the device, or null).
 hipError_t launch_kappas(int m, int n, int k, const double *A, int lda, const double *B, int ldb, unsigned long long *hdr,
                          unsigned long long *maxA, unsigned long long *minA, unsigned long long *maxB,
-                         unsigned long long *minB, int32_t *expA, int mp, int32_t *expB, int np, hipStream_t st);
-// hdr[0 ... 2] to pinned host memory (its address on the device)
-hipError_t launch_deliver(const unsigned long long *hdr, unsigned long long *host, hipStream_t st);
+                         unsigned long long *minB, int32_t *expA, int mp, int32_t *expB, int np, unsigned long long *host, hipStream_t st);
 hipError_t launch_clear_header(void *header, hipStream_t st);
 // the whole scale extraction of ozimmu_dgemm in three launches: clear, reduce both operands, exponents of both
 // (both_planes: whether the call will leave the planes of both operands, for kHeaderPlanes)
