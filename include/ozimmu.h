@@ -77,7 +77,9 @@ size_t ozimmu_planes_bytes(char side, int rows, int cols, int s, int layout);
  *   kappa_A = 2 max_i ( max_j |a_ij| / min_j |a_ij| ),  kappa_B likewise over columns of B,
  *   minima over the nonzero entries; all-zero rows/columns skipped;
  *   *s_out = smallest s >= 1 with  kappa_A 2^{-7s} + kappa_B 2^{-7s} <= tol.
- * One pass over A and B on the device; SYNCHRONISES the stream to return the result.
+ * One pass over A and B on the device; SYNCHRONISES the stream to return the result.  The result comes through 4 KiB of
+ * pinned host memory, which the first estimate of the process allocates (also while a stream is captured) and the process
+ * keeps, or is copied where that memory is not to be had.
  *   s_out  [host] receives s (OZIMMU_MAX_SLICES when unreachable)
  *   kappa  [host] optional (may be NULL): kappa[0] = kappa_A, kappa[1] = kappa_B
  * Returns OZIMMU_OK, OZIMMU_UNREACHABLE, OZIMMU_NONFINITE, OZIMMU_BAD_ARG (tol <= 0 or NaN,

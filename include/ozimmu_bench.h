@@ -102,12 +102,16 @@ int ozimmu_calibration_copy(void *dst, const void *src, size_t bytes, void *stre
  *   and (k1-k0) * 127^2 < 2^31, produced by the generic (pair-by-pair) GEMM kernel.
  * ozimmu_debug_setup_threads: threads of the launch that forms the scales and slices of both operands of an m x n x k
  *   product together, 0 where they are formed in separate launches.  Host only: no HIP call is made.
+ * ozimmu_debug_host_words: refuse = 1: the pinned words of the estimators are given up (not freed) and cannot be had again, so that
+ *   estimates copy their result; 0 (default): the next estimate allocates them.  Returns the slots that are free (64, less the calls that wait; 0 where there are
+ *   none).  Process-wide host state; not while another thread is inside an estimate.
  * ozimmu_debug_vectors_parts: parts of k in which an m x n x k product with s slices of both operands (leading
  *   dimensions m, k and m) runs in the few-vectors kernel, 0 where it runs in another.  Host only.
  */
 int ozimmu_debug_diagonals(int m, int n, int k, int s, const void *workspace, int32_t *D, void *stream);
 long long ozimmu_debug_setup_threads(int m, int n, int k);
 int ozimmu_debug_vectors_parts(int m, int n, int k, int s);
+int ozimmu_debug_host_words(int refuse);
 int ozimmu_debug_small_tile_limit(long long tiles);
 int ozimmu_debug_tile_choice(int choice);
 int ozimmu_debug_panel_bytes(long long bytes);

@@ -113,54 +113,66 @@ size_t ozimmu_split_scratch_bytes(char side, int rows, int cols)
 }
 
 // Pinned host memory that the last kernel of the estimators writes its three words into: a copy of 24 bytes to pageable memory takes
-// 7 us longer (estimate and product, us, copy and kernel: 200 x 300 x 200 s = 6 49.4 and 41.9, 2944 x 704 x 491 s = 8 82.1 and 75.9). One allocation of 64 slots, made by the first call and kept;
-// a call has a slot of its own until it returns, and copies if none is free or the allocation failed.
+// 7 us longer (estimate and product, us, copy and kernel: 200 x 300 x 200 s = 6 49.4 and 41.9, 2944 x 704 x 491 s = 8 82.1 and 75.9). One allocation of 64 slots, made by the first call that
+// gets it and kept; a call has a slot of its own until it returns, and copies if none is free or the allocation fails (the next call tries again).
 namespace {
+constexpr int kWordSlots = 64, kWordStride = 8;               // 64 bytes each
+struct {
+    std::mutex mutex;
+    std::atomic<unsigned long long *> base{nullptr};
+    std::atomic<unsigned long long> free{0};
+    std::atomic<bool> refuse{false};                          // test hook: allocations fail
+} g_words;
+
 class HostWords {
-    static constexpr int kSlots = 64, kStride = 8;            // 64 bytes each
-    struct Pool {
-        unsigned long long *base = nullptr;
-        std::atomic<unsigned long long> free{0};
-        Pool()
-        {
-            void *p = nullptr;
-            if (hipHostMalloc(&p, kSlots * kStride * 8, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-                (void)hipGetLastError();
-                return;
-            }
-            base = (unsigned long long *)p;
-            free = ~0ULL;
-        }
-    };
-    static Pool &pool()
-    {
-        static Pool *const p = new Pool;                      // (never destroyed: the runtime may be gone by then)
-        return *p;
-    }
     int slot = -1;
+
+    static unsigned long long *memory()
+    {
+        if (unsigned long long *p = g_words.base.load(std::memory_order_acquire)) return p;
+        std::lock_guard<std::mutex> lock(g_words.mutex);
+        if (unsigned long long *p = g_words.base.load(std::memory_order_acquire)) return p;
+        void *p = nullptr;
+        if (g_words.refuse) return nullptr;
+        // (an allocation spoils a capture that is under way on another stream, unless the thread's mode is the relaxed one)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        const hipError_t e = hipHostMalloc(&p, kWordSlots * kWordStride * 8, hipHostMallocPortable | hipHostMallocMapped);
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        g_words.free = ~0ULL;
+        g_words.base.store((unsigned long long *)p, std::memory_order_release);
+        return (unsigned long long *)p;
+    }
 
 public:
     volatile unsigned long long *host = nullptr;
     unsigned long long *device = nullptr;                     // null: none to be had
     HostWords()
     {
-        Pool &p = pool();
-        unsigned long long mask = p.free.load(std::memory_order_relaxed);
-        while (mask && !p.free.compare_exchange_weak(mask, mask & (mask - 1), std::memory_order_acquire)) {}
+        unsigned long long *base = memory();
+        if (!base) return;
+        unsigned long long mask = g_words.free.load(std::memory_order_relaxed);
+        while (mask && !g_words.free.compare_exchange_weak(mask, mask & (mask - 1), std::memory_order_acquire)) {}
         if (!mask) return;
         slot = __builtin_ctzll(mask);
-        unsigned long long *words = p.base + slot * kStride;
         void *d = nullptr;
-        if (hipHostGetDevicePointer(&d, words, 0) != hipSuccess || !d) {
+        if (hipHostGetDevicePointer(&d, base + slot * kWordStride, 0) != hipSuccess || !d) {
             (void)hipGetLastError();
+            give_back();
             return;
         }
-        host = words;
+        host = base + slot * kWordStride;
         device = (unsigned long long *)d;
     }
-    ~HostWords()
+    ~HostWords() { give_back(); }
+    void give_back()
     {
-        if (slot >= 0) pool().free.fetch_or(1ULL << slot, std::memory_order_release);
+        if (slot >= 0) g_words.free.fetch_or(1ULL << slot, std::memory_order_release);
+        slot = -1;
     }
     HostWords(const HostWords &) = delete;
     HostWords &operator=(const HostWords &) = delete;
@@ -521,6 +533,17 @@ int ozimmu_debug_small_tile_limit(long long tiles)
     if (tiles < -1) return OZIMMU_BAD_ARG;
     fused_set_small_tile_limit(tiles);
     return OZIMMU_OK;
+}
+
+int ozimmu_debug_host_words(int refuse)
+{
+    std::lock_guard<std::mutex> lock(g_words.mutex);
+    g_words.refuse = refuse != 0;
+    if (refuse) {
+        g_words.base = nullptr;
+        g_words.free = 0;
+    }
+    return __builtin_popcountll(g_words.free.load());
 }
 
 int ozimmu_debug_tile_choice(int choice)

@@ -59,6 +59,7 @@ _SIGNATURES = {
     "ozimmu_measure_int8_ceiling": (_c.c_int, [_c.c_int, _c.c_void_p, _c.POINTER(_c.c_float), _c.c_void_p]),
     "ozimmu_debug_small_tile_limit": (_c.c_int, [_c.c_longlong]),
     "ozimmu_debug_tile_choice": (_c.c_int, [_c.c_int]),
+    "ozimmu_debug_host_words": (_c.c_int, [_c.c_int]),
     "ozimmu_debug_panel_bytes": (_c.c_int, [_c.c_longlong]),
     "ozimmu_debug_setup_threads": (_c.c_longlong, [_c.c_int] * 3),
     "ozimmu_debug_vectors_parts": (_c.c_int, [_c.c_int] * 4),
@@ -403,6 +404,11 @@ def debug_tile_choice(choice):
     rc = lib().ozimmu_debug_tile_choice(int(choice))
     if rc != OK:
         raise OzimmuError(rc, "debug_tile_choice")
+
+
+def debug_host_words(refuse):
+    """Test hook: have estimates copy their result (True) or write it to pinned memory (False, the default); the free slots."""
+    return lib().ozimmu_debug_host_words(int(refuse))
 
 
 def debug_panel_bytes(nbytes):

@@ -403,3 +403,59 @@ def test_estimates_from_several_threads():
     for t in threads:
         t.join(timeout=60)
     assert not wrong and not any(t.is_alive() for t in threads)
+
+
+@pytest.fixture
+def host_words():
+    yield
+    ozimmu.debug_host_words(False)
+
+
+def test_estimates_without_pinned_memory(host_words):
+    # no pinned words to be had: the result is copied; then they are, though the first attempt has failed
+    A, B = workloads.lognormal(123, 77, 95, 1.0, 61)
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    want = oracle.estimate_slices(A, B, 1e-9, s_max=ozimmu.MAX_SLICES)
+    bad = dB.clone(memory_format=torch.preserve_format)
+    bad[-1, -1] = float("inf")
+
+    def both():
+        assert ozimmu.estimate_slices(dA, dB, 1e-9) == want
+        with pytest.raises(ozimmu.OzimmuError) as e:
+            ozimmu.estimate_slices(dA, bad, 1e-9)
+        assert e.value.code == ozimmu.NONFINITE
+
+    assert ozimmu.debug_host_words(True) == 0
+    both()
+    assert ozimmu.debug_host_words(False) == 0
+    both()
+    assert ozimmu.debug_host_words(False) == 64
+
+
+def forget_host_words():
+    ozimmu.debug_host_words(True)
+    assert ozimmu.debug_host_words(False) == 0
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local", "relaxed"])
+def test_first_estimate_while_a_stream_is_captured(host_words, mode):
+    # on the default stream, which the runtime may wait for meanwhile: the words are allocated then, and the capture is good
+    m, n, k, s = 123, 77, 95, 5
+    A, B = workloads.lognormal(m, n, k, 1.0, 63)
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    want = oracle.estimate_slices(A, B, 1e-9, s_max=ozimmu.MAX_SLICES)
+    C, ws, other = ozimmu.colmajor_empty(m, n), ozimmu.alloc_workspace(m, n, k, s), ozimmu.alloc_workspace(m, n, k, 1)
+    eager = ozimmu.dgemm(dA, dB, s, C=C, workspace=ws).clone()
+    forget_host_words()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode=mode):
+        ozimmu.dgemm(dA, dB, s, C=C, workspace=ws)
+        with torch.cuda.stream(torch.cuda.default_stream()):
+            got = [ozimmu.estimate_slices(dA, dB, 1e-9, workspace=other) for _ in range(2)]
+    assert got == [want, want] and ozimmu.debug_host_words(False) == 64
+    for _ in range(3):
+        C.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, eager)
+        assert ozimmu.estimate_slices(dA, dB, 1e-9, workspace=other) == want
