@@ -114,7 +114,7 @@ size_t ozimmu_split_scratch_bytes(char side, int rows, int cols)
 
 // Pinned host memory that the last kernel of the estimators writes its three words into: a copy of 24 bytes to pageable memory takes
 // 7 us longer (estimate and product, us, copy and kernel: 200 x 300 x 200 s = 6 49.4 and 41.9, 2944 x 704 x 491 s = 8 82.1 and 75.9). One allocation of 64 slots, made by the first call that
-// gets it and kept; a call has a slot of its own until it returns, and copies if none is free or the allocation fails (the next call tries again).
+// gets it and kept; a call has a slot of its own until it has waited for its stream, and copies if none is free or the allocation fails (the next call tries again).
 namespace {
 constexpr int kWordSlots = 64, kWordStride = 8;               // 64 bytes each
 struct {
@@ -168,7 +168,7 @@ public:
         host = base + slot * kWordStride;
         device = (unsigned long long *)d;
     }
-    ~HostWords() { give_back(); }
+    // Called once the stream has been waited for: where a launch or the wait failed, a kernel may still write to the slot, so nobody gets it again.
     void give_back()
     {
         if (slot >= 0) g_words.free.fetch_or(1ULL << slot, std::memory_order_release);
@@ -196,6 +196,7 @@ static int kappas(int m, int n, int k, const double *A, int lda, const double *B
     OZ_TRY(hipStreamSynchronize(st));
     if (words.device)
         for (int i = 0; i < 3; ++i) host[i] = words.host[i];
+    words.give_back();
     if (host[0] & 1ULL) return OZIMMU_NONFINITE;
     double ratioA, ratioB;
     std::memcpy(&ratioA, &host[1], 8);

@@ -459,3 +459,29 @@ def test_first_estimate_while_a_stream_is_captured(host_words, mode):
         torch.cuda.synchronize()
         assert torch.equal(C, eager)
         assert ozimmu.estimate_slices(dA, dB, 1e-9, workspace=other) == want
+
+
+def test_words_of_an_estimate_that_could_not_wait_are_not_given_to_another(host_words):
+    # while a stream is captured in the global mode the runtime refuses to wait for another: the estimate's kernels run on
+    import ctypes
+    import re
+    A, B = workloads.lognormal(64, 60, 70, 1.0, 62)
+    dA, dB = ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)
+    want = oracle.estimate_slices(A, B, 1e-9, s_max=ozimmu.MAX_SLICES)
+    forget_host_words()
+    assert ozimmu.estimate_slices(dA, dB, 1e-9) == want and ozimmu.debug_host_words(False) == 64
+    hip = ctypes.CDLL(re.search(r"\S*libamdhip64\.so\S*", open("/proc/self/maps").read())[0])
+    captured, other, ws = torch.cuda.Stream(), torch.cuda.Stream(), ozimmu.alloc_workspace(64, 60, 70, 1)
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(ctypes.c_void_p(captured.cuda_stream), 0) == 0
+    try:
+        with torch.cuda.stream(other), pytest.raises(ozimmu.OzimmuError) as e:
+            ozimmu.estimate_slices(dA, dB, 1e-9, workspace=ws)
+    finally:
+        graph = ctypes.c_void_p()
+        hip.hipStreamEndCapture(ctypes.c_void_p(captured.cuda_stream), ctypes.byref(graph))      # (spoilt by the refused wait)
+        hip.hipGetLastError()
+    assert e.value.code == ozimmu.HIP_ERROR
+    torch.cuda.synchronize()
+    assert ozimmu.debug_host_words(False) == 63
+    assert ozimmu.estimate_slices(dA, dB, 1e-9) == want and ozimmu.debug_host_words(False) == 63
