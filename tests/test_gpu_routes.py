@@ -386,7 +386,7 @@ def test_estimates_from_several_threads():
     dev = [(ozimmu.to_colmajor(A), ozimmu.to_colmajor(B)) for A, B in cases]
     want = [oracle.estimate_slices(A, B, 1e-9, s_max=ozimmu.MAX_SLICES) for A, B in cases]
     torch.cuda.synchronize()
-    wrong = []
+    wrong, done = [], []
 
     def work(i):
         stream = torch.cuda.Stream()
@@ -396,13 +396,14 @@ def test_estimates_from_several_threads():
                 got = ozimmu.estimate_slices(*dev[i], 1e-9, workspace=ws)
                 if got != want[i]:
                     wrong.append((i, got, want[i]))
+        done.append(i)
 
     threads = [threading.Thread(target=work, args=(i,)) for i in range(len(cases))]
     for t in threads:
         t.start()
     for t in threads:
         t.join(timeout=60)
-    assert not wrong and not any(t.is_alive() for t in threads)
+    assert not wrong and sorted(done) == list(range(len(cases)))      # (a thread that raised or hangs is not done)
 
 
 @pytest.fixture
