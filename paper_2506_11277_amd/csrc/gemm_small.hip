@@ -616,7 +616,7 @@ hipError_t launch_eighths_whole(int m, int n, int k, const double *A, int lda, c
                                 unsigned long long *header, size_t bad_offset, double *C, int ldc, int Q, hipStream_t st)
 {
     const int kp = round_up(k, kPad), tiles_m = (m + 31) / 32, tiles_n = (n + 31) / 32;
-    note_gemm_kernel("gemm_eighths_kernel<%d> tile 32x32, 8 wavefronts, k in eighths, scales and slices in the same launch", S);
+    note_gemm_kernel("gemm_eighths_whole_kernel<%d> tile 32x32, 8 wavefronts slice, 4 multiply", S);
     auto launch = [&](auto EC) -> hipError_t {
         auto kern = gemm_eighths_whole_kernel<S, NEAREST, decltype(EC)::value>;
         static std::atomic<unsigned long long> configured{0};

@@ -724,7 +724,7 @@ def test_small_tile_is_taken_where_it_finishes_sooner():
                        (2560, 2, "gemm_fused16_kernel<2> tile 256x128"), (3000, 3, "gemm_fused16_kernel<3> tile 128x128 ring of 3"),
                        (2304, 4, "gemm_fused16_kernel<4> tile 192x128"), (2560, 4, "gemm_fused16_kernel<4> tile 128x128"),
                        (2304, 6, "gemm_fused16_kernel<6> tile 128x64"), (2560, 6, "gemm_fused16_kernel<6> tile 128x128"),
-                       (3000, 7, "gemm_fused16_kernel<7> tile 128x64"), (100, 7, "gemm_eighths_kernel<7> tile 32x32"),
+                       (3000, 7, "gemm_fused16_kernel<7> tile 128x64"), (100, 7, "gemm_eighths_whole_kernel<7> tile 32x32"),
                        (1536, 7, "gemm_fused_kernel<7> equal counts tile 64x64, 4 wavefronts"),
                        (2240, 7, "gemm_fused_kernel<7> equal counts tile 64x64, 4 wavefronts"),
                        (1536, 10, "gemm_fused_kernel<10> equal counts tile 64x64, 4 wavefronts")]:

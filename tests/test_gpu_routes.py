@@ -44,7 +44,8 @@ def special(A, B):
 
 @pytest.mark.parametrize("s", range(1, 11))
 @pytest.mark.parametrize("m,n,k,kernel", [
-    (1, 1, 1, "eighths"), (33, 31, 130, "eighths"), (161, 1300, 70, "eighths"), (300, 610, 140, "eighths"), (512, 512, 64, "eighths"), (97, 70, 1000, "eighths"), (40, 300, 2100, "eighths"),
+    (1, 1, 1, "whole"), (33, 31, 130, "eighths"), (161, 1300, 70, "whole"), (300, 610, 140, "eighths"), (512, 512, 64, "whole"), (97, 70, 1000, "eighths"), (40, 300, 2100, "eighths"),
+    (545, 700, 1, "eighths"), (700, 545, 97, "eighths"), (640, 700, 128, "eighths"),      # (fewer k-blocks than wavefronts)
     (705, 961, 65, "halves"), (1024, 1000, 129, "halves"), (65, 8000, 700, "halves"),
     (705, 961, 2049, "halves"), (1000, 1000, 1100, "halves"),
 ])
@@ -60,12 +61,14 @@ def test_contraction_divided_within_a_work_group(m, n, k, kernel, s):
     if torch.cuda.get_device_properties(0).multi_processor_count == 256 and 2 <= s <= 9:
         if kernel == "halves" and (s >= 7 or (s <= 3 and k >= 1024)):
             kernel = "halves16"
+        if kernel == "whole" or (kernel == "eighths" and s <= 4 and k <= 256 and m < 512):
+            kernel = "eighths_whole"
         assert ozimmu.last_gemm_kernel().startswith(f"gemm_{kernel}_kernel<{s}>"), ozimmu.last_gemm_kernel()
     check(C, A, B, s, s)
     check(ozimmu.dgemm3(dA, dB, s, s, splitting=ozimmu.SPLIT_NEAREST, level_diagonals=2), A, B, s, s, nearest=True, Q=2)
 
 
-WHOLE = "scales and slices in the same launch"
+WHOLE = "gemm_eighths_whole_kernel<"
 
 
 # Scales, slices and product in one launch: edges of tiles, half k-blocks that are whole, ragged and empty, both depths, the ends of the rule; the
