@@ -33,7 +33,7 @@ def kernels(tmp_path_factory):
 
 
 @pytest.mark.parametrize("kernel", ["gemm_fused16_kernelILi%dELi0E" % s for s in range(2, 10)] + ["gemm_fused_kernelILi%dE" % s for s in (1, 10, 16, 20)] +
-                         ["gemm_halves_kernelILi4E", "gemm_halves16_kernelILi7E", "gemm_eighths_kernelILi7E"] +
+                         ["gemm_halves_kernelILi4E", "gemm_halves16_kernelILi7E", "gemm_eighths_kernelILi7E", "gemm_eighths_whole_kernelI"] +
                          ["gemm_eighths_passes_kernelI", "gemm_passes_kernelI"])
 def test_c_has_streaming_and_plain_stores(kernels, kernel):
     # columns of C on 64-byte boundaries are stored past the caches, others through them: both kinds of store have to be in
