@@ -313,7 +313,7 @@ def test_result_inside_the_long_operand(short_a):
     check(C, A, B, s, s)
 
 
-@pytest.mark.parametrize("n,k,kernel", [(512, 90, "eighths"), (576, 700, "eighths"), (672, 33, "eighths"), (704, 90, "halves")])
+@pytest.mark.parametrize("n,k,kernel", [(512, 90, "eighths_whole"), (576, 700, "eighths"), (672, 33, "eighths"), (704, 90, "halves")])
 def test_six_slices_follow_the_same_rule_as_seven(n, k, kernel):
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the expectations are worked out for 256 compute units")
