@@ -2,6 +2,7 @@
 
 (The other parity tests steer the choice of kernel; nothing is steered here.)  Every row of A and column of B has a
 scale of its own, so a sample of rows and columns of C is the oracle's product of these rows and columns."""
+import gc
 import time
 
 import numpy as np
@@ -413,6 +414,7 @@ def test_estimates_from_several_threads():
 def host_words():
     yield
     ozimmu.debug_host_words(False)
+    gc.collect()                             # (nothing of these tests is freed while another measures the allocator)
 
 
 def test_estimates_without_pinned_memory(host_words):
@@ -425,9 +427,8 @@ def test_estimates_without_pinned_memory(host_words):
 
     def both():
         assert ozimmu.estimate_slices(dA, dB, 1e-9) == want
-        with pytest.raises(ozimmu.OzimmuError) as e:
+        with pytest.raises(ozimmu.OzimmuError, match=f"status {ozimmu.NONFINITE} "):
             ozimmu.estimate_slices(dA, bad, 1e-9)
-        assert e.value.code == ozimmu.NONFINITE
 
     assert ozimmu.debug_host_words(True) == 0
     both()
@@ -479,13 +480,12 @@ def test_words_of_an_estimate_that_could_not_wait_are_not_given_to_another(host_
     torch.cuda.synchronize()
     assert hip.hipStreamBeginCapture(ctypes.c_void_p(captured.cuda_stream), 0) == 0
     try:
-        with torch.cuda.stream(other), pytest.raises(ozimmu.OzimmuError) as e:
+        with torch.cuda.stream(other), pytest.raises(ozimmu.OzimmuError, match=f"status {ozimmu.HIP_ERROR} "):
             ozimmu.estimate_slices(dA, dB, 1e-9, workspace=ws)
     finally:
         graph = ctypes.c_void_p()
         hip.hipStreamEndCapture(ctypes.c_void_p(captured.cuda_stream), ctypes.byref(graph))      # (spoilt by the refused wait)
         hip.hipGetLastError()
-    assert e.value.code == ozimmu.HIP_ERROR
     torch.cuda.synchronize()
     assert ozimmu.debug_host_words(False) == 63
     assert ozimmu.estimate_slices(dA, dB, 1e-9) == want and ozimmu.debug_host_words(False) == 63
