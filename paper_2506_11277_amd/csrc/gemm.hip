@@ -1144,9 +1144,9 @@ static hipError_t launch_gemm_fused_once(int m, int n, int kp, int sA, int sB, b
                                : launch_gemm_halves(s, m, n, kp, pA, pB, eA, eB, C, ldc, Q, st);
                 small = fused_small_tile(s, m, n);
                 // The streaming kernel (gemm_passes_dev.h) where the launch takes less time (gemm_passes.hip).  Up to k = 128 the choice
-                // between the other tiles stands as tests/test_gpu_parity.py has it, though it is behind there (2500 x 2500 x 100, s = 7
-                // 40.5 against 32.9).
-                if (s >= 4 && s <= 9 && kp > 128 && fused16_tile_choice() == 0) {
+                // between the other tiles stands as tests/test_gpu_parity.py has it, though it is behind there but for one round of 96 x 64 tiles
+                // (2500 x 2500 x 100, s = 7 40.5 against 32.9).
+                if (s >= 4 && s <= 9 && fused16_tile_choice() == 0) {
                     int om = 64, on = 64;
                     if (!small) fused16_launch_tile(s, m, n, om, on);
                     const PassShape shape = gemm_one_pass_shape(s, m, n, kp, om, on);

@@ -52,18 +52,17 @@ static double pair_rounds(int s, long long blocks, int cus)
 }
 
 // 96 x 64 tiles: one round of them where 64 x 64 tiles are more than the compute units, so that the other shapes leave a quarter of the chip, or of a second
-// round, empty.  A round takes 0.78 of one of 128 x 64 tiles.  Calls, us, best of the others and this, s = 4 ... 9, 13 ... 18: 960 x 1271 x 136 s = 4 12.5 / 12.3 (even at
-// kp = 256, hence the line), 545 x 1984 x 3279 s = 4 65.9 / 60.9, 873 x 1163 x 927 s = 5 29.2 / 25.3, 2240 x 568 x 294 s = 6 19.0 / 17.0, 5312 x 212 x 136 s = 7 17.5 / 15.9, 1531 x 777 x 1001
+// round, empty.  A round takes 0.78 of one of 128 x 64 tiles.  Calls, us, best of the others and this, s = 4 ... 9, 13 ... 18: 940 x 1398 x 156 s = 4 13.7 / 13.4 (even with
+// the others at kp = 256), 545 x 1984 x 3279 s = 4 65.9 / 60.9, 873 x 1163 x 927 s = 5 29.2 / 25.3, 2240 x 568 x 294 s = 6 19.0 / 17.0, 5312 x 212 x 136 s = 7 17.5 / 15.9, 1531 x 777 x 1001
 // s = 8 53.3 / 46.4, 370 x 2691 x 1378 s = 16 212 / 170, 686 x 1920 x 3766 s = 18 693 / 567; over 82 such sizes 1.05 (4 ... 6), 1.11 (7 ... 9) and 1.23 (13 ... 18) in the mean,
-// slowest 0.997.  With more rounds, 13 ... 18 slices: even with the others at best.  10 ... 12 keep the kernels of one pass, and k up to 128 and
-// 13 ... 18 at 13/16 of a round (208 ... 211 tiles) the tiles that tests/test_gpu_passes.py has there; 19 and 20 run in three passes, the first too short for this
-// tile's copies.  (32-bit offsets into the planes.)
-static bool one_round_of_96(int s, int m, int n, int kp)
+// slowest 0.997 (0.985 at kp = 256, s = 4).  k up to 128: 40 sizes of 13 ... 18 slices 1.17 in the mean, slowest 1.06 (1168 x 994 x 30 s = 17 34.1 / 28.6), 40 of 4 ... 9 1.17, slowest 1.05 (364 x 3520 x 27 s = 8 16.8 / 16.0).
+// With more rounds, 13 ... 18 slices: even with the others at best.  10 ... 12, 19 and 20 run in passes of which the first, three diagonals, is too short for this tile's
+// copies.  (256 tiles, and s kp of what one int32 block holds, keep the planes below 2^32 bytes, the offsets that this tile takes.)
+static bool one_round_of_96(int s, int m, int n)
 {
     const int cus = device_cus();
     const long long blocks = order_blocks(m, n, 96, 64), small = (long long)((m + 63) / 64) * ((n + 63) / 64);
-    if (blocks > cus || small <= cus || (long long)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * s >= (1LL << 32)) return false;
-    return kp > (s == 4 ? 256 : 128) && (s <= 9 || (s >= 13 && s <= 18 && 64 * blocks / cus != 52));
+    return (s <= 9 || (s >= 13 && s <= 18)) && blocks <= cus && small > cus;
 }
 
 // 4 ... 9 slices: the other kernels by their tile (128 x 64 outputs count one round, larger tiles as many more).  What is taken where the
@@ -79,7 +78,8 @@ PassShape gemm_one_pass_shape(int s, int m, int n, int kp, int tm, int tn)
     static constexpr LaunchTime k128x64[6] = {{1.4, 4.5, 4.9}, {1.387, 4.5, 4.9}, {1.241, 4.8, 4.7}, {1.193, 4.75, 4.5}, {1.153, 5.75, 4.05}, {1.126, 5.4, 4.5}};
     static constexpr LaunchTime k128x128[3] = {{1.226, 3.85, 5.85}, {1.147, 4.6, 4.35}, {1.109, 4.05, 5.95}}, k192x128{1.188, 3.95, 4.65};
     static constexpr double kAhead[6] = {0.98, 0.985, 0.99, 1.0, 1.0, 1.0};
-    if (one_round_of_96(s, m, n, kp)) return kPassMiddle;
+    if (one_round_of_96(s, m, n)) return kPassMiddle;
+    if (kp <= 128) return kNoPasses;                                 // (the fits are of longer contractions)
     const int cus = device_cus();
     const double x = 1e-3 * kp * (s * (s + 1) / 2);
     const double pairs = kPairs[s - 4].us(pair_rounds(s, order_blocks(m, n, 64, 64), cus), x);
@@ -130,7 +130,7 @@ PassShape gemm_passes_shape(int s, int m, int n, int kp, int Q)
     const PassPlan P = pass_plan(s);
     for (int p = 0, d = 0; p + 1 < P.n; ++p)
         if ((d += P.w[p]) % Q != 0) return kNoPasses;                // a level of Q diagonals straddles two passes
-    if (one_round_of_96(s, m, n, kp)) return kPassMiddle;
+    if (one_round_of_96(s, m, n)) return kPassMiddle;
     if (tiles(64, 64) <= cus) return s <= 16 || kp < (s == 18 ? 256 : 512) ? kNoPasses : kPassSmall;
     const double small = pair_rounds(s, order_blocks(m, n, 64, 64), cus);
     const long long blocks = order_blocks(m, n, 128, 64);

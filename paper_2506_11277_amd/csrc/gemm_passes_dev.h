@@ -513,10 +513,11 @@ template <class T, int... Ws>
 hipError_t launch_passes(int m, int n, int kp, int stride, const int8_t *pA, const int8_t *pB, const int32_t *eA,
                          const int32_t *eB, double *C, int ldc, int Q, hipStream_t st)
 {
-    // (32-bit lane offsets to the tile where a work-group takes several, or 96 x 64 tiles: larger planes go to a launch of single tiles)
+    // (32-bit lane offsets to the tile where a work-group takes several: larger planes go to a launch of single tiles; 96 x 64 tiles have no
+    // other way and the choice of shape does not ask for them)
     const bool far = (size_t)(m > n ? round_up(m, kPad) : round_up(n, kPad)) * kp * stride >= (1ULL << 32);
     if constexpr (T::COPIES == kCopyOne) {
-        if (far) return hipErrorInvalidValue;                                       // (the choice of shape does not ask for it)
+        if (far) return hipErrorInvalidValue;
     } else if constexpr (T::PERSIST)
         if (far) return launch_passes<PassTile<T::WVM, T::WVN, T::SLOTS>, Ws...>(m, n, kp, stride, pA, pB, eA, eB, C, ldc, Q, st);
     constexpr int TM = T::TM, TN = T::TN, NP = sizeof...(Ws), WS[NP] = {Ws...};
@@ -530,6 +531,8 @@ hipError_t launch_passes(int m, int n, int kp, int stride, const int8_t *pA, con
     long long blocks = tile_order_blocks(tiles_m, tiles_n, false);
     if (T::PERSIST) {
         const long long slots = (long long)device_cus() * (T::NW == 4 ? 2 : 1);
+        // (behind the last stage of a tile the ring is filled with the first ones of the next: a contraction is as long as the ring)
+        if (blocks > slots && kp / 64 < PassRing<WS[0], T::SLOTS>::N / PassRing<WS[0], T::SLOTS>::V) return hipErrorInvalidValue;
         blocks = blocks < slots ? blocks : slots;
     }
     kern<<<(unsigned)blocks, T::THREADS, T::LDS, st>>>(pA, pB, eA, eB, C, ldc, m, n, kp / kFrag, stride,

@@ -54,14 +54,16 @@ def test_one_pass_in_runs(m, n, k, s):
     both_ways(A, B, s, s, f"gemm_passes_kernel<{s}> tile 128x64")
 
 
-# 96 x 64 tiles: one round and several (7 ... 9), a last tile that reaches beyond the planes (1650 rows, padded to 1664), the shortest contractions, both ends of
-# what one round holds
-@pytest.mark.parametrize("s", [*range(4, 10), *range(13, 19)])
-@pytest.mark.parametrize("m,n,k,only", [(1531, 777, 1001, range(4, 10)), (1531, 841, 300, range(4, 19)), (1650, 700, 450, range(4, 19)), (1650, 2670, 700, range(7, 10)),
-                                        (2304, 2000, 600, range(7, 10)), (1000, 1190, 257, range(4, 10)), (4030, 340, 260, range(4, 19)), (90, 16380, 131, range(5, 19))])
-def test_tiles_of_96_rows(m, n, k, only, s):
-    if s not in only:
-        pytest.skip("another tile")
+# 96 x 64 tiles: one round and several (7 ... 9), a last tile that reaches beyond the planes (1650 rows, padded to 1664), contractions of a single k-block and more, both ends of
+# what one round holds and 13/16 of it
+ALL_96 = [*range(4, 10), *range(13, 19)]
+TILES_OF_96 = [((1531, 777, 1001), ALL_96), ((1531, 841, 300), ALL_96), ((1650, 700, 450), ALL_96), ((1650, 2670, 700), range(7, 10)), ((2304, 2000, 600), range(7, 10)),
+               ((1000, 1190, 257), ALL_96), ((4030, 340, 260), ALL_96), ((90, 16380, 131), ALL_96), ((1025, 1153, 1030), ALL_96), ((1030, 1400, 65), ALL_96),
+               ((1001, 1250, 1), ALL_96), ((1040, 1450, 128), ALL_96)]
+
+
+@pytest.mark.parametrize("m,n,k,s", [(*size, s) for size, counts in TILES_OF_96 for s in counts])
+def test_tiles_of_96_rows(m, n, k, s):
     A, B = workloads.lognormal(m, n, k, 1.0, 40 + s)
     special(A, B)
     both_ways(A, B, s, s, f"gemm_passes_kernel<{s}> tile 96x64")
@@ -116,7 +118,7 @@ def test_a_forced_tile_is_the_one_that_runs(choice, name):
 # 128 x 64 tiles: one partly filled round, ragged edges; 64 x 64 tiles: a second work-group on some compute units, edges; two
 # 64-deep k-steps (k = 40 and 65) and many
 @pytest.mark.parametrize("s", range(10, 21))
-@pytest.mark.parametrize("m,n,k,tile,least", [(1025, 1153, 1030, "128x64", 13), (2050, 2020, 1100, "64x64", 10), (1030, 1400, 65, "64x64", 13),
+@pytest.mark.parametrize("m,n,k,tile,least", [(1793, 1009, 1030, "128x64", 13), (2050, 2020, 1100, "64x64", 10), (1030, 1700, 65, "64x64", 13),
                                               (2300, 4600, 40, "64x64", 13), (80, 20000, 400, "64x64", 10)])
 def test_passes_through_lds(m, n, k, tile, least, s):
     A, B = workloads.lognormal(m, n, k, 1.0, 70 + s)
