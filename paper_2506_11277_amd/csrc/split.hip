@@ -402,10 +402,17 @@ static int scale_split_waves(int m, int n, int rows, int kp, int c)
 }
 
 // Whether the slices are written through the L2s as they are formed (device-scope stores) rather than at the end of the launch, when the next one
-// waits for it: where the planes are small enough that the memory-side cache takes them at once. Calls, us, plain and through, by bytes of the planes: 10 MB
-// 1024 x 1024 x 512 s = 9 28.6 and 28.0; 15 MB 1024^3 s = 7 35.2 and 34.3; 20 MB 1200^3 s = 7 55.8 and 54.3; 31 MB 1500^3 s = 7 102.7 and 101.8; 42 MB 1700^3 s = 7
-// 129.9 and 130.1; 52 MB 1900^3 s = 7 174.7 and 183.4; 72 MB 2000^3 s = 9 263 and 274.
-static bool scale_split_through(int m, int n, int kp, int c) { return (long long)c * kp * ((long long)m + n) <= 32000000LL; }
+// waits for it.  While operands and planes stay in the memory-side cache that gains 1 to 4 percent of a call; where the operands come from memory, the planes are
+// displaced meanwhile and the stores, halves of lines, go to memory beside the reads.  Calls, us, plain / through, one pair of operands over and over, and
+// pairs of 700 MB in turn in one workspace: 1472 x 152 x 1105 s = 7 (14 MB of operands) 24.6 / 23.4 and 26.4 / 27.2, 2432 x 140 x 768 s = 7 (16 MB) 27.8 / 27.8 and 29.6 / 32.2,
+// 1024 x 155 x 1797 s = 5 (17 MB) 24.3 / 23.6 and 25.9 / 27.3.  Means over 460 random sizes by the operands' bytes, the same two and pairs with workspaces of their own:
+// 2 to 4 MB 1.01, 1.01, 1.00; 4 to 5 MB 1.02, 1.02, 0.99; 5 to 8 MB 1.03, 1.02, 0.98; 8 to 16 MB 1.04, 1.01, 0.97; more 1.02, 0.96, 0.97.  So operands up to 4 MB, where
+// no way of having them is behind (planes up to 14 MB measured).
+static bool scale_split_through(int m, int n, int k, int kp, int c)
+{
+    const long long rows = (long long)m + n;
+    return 8 * rows * k <= 4000000LL && rows * kp * c <= 16000000LL;
+}
 
 static long long scale_split_groups(int m, int n, int rows)
 {
@@ -438,7 +445,7 @@ hipError_t launch_scale_split(int m, int n, int k, const double *A, int lda, con
     auto launch = [&](auto PRC, auto NVC) {
         constexpr int PR = decltype(PRC)::value, NV = decltype(NVC)::value;
         const int panelsA = (m + PR - 1) / PR, panels = panelsA + (n + PR - 1) / PR;
-        auto kern = scale_split_through(m, n, kp, c) ? (nearest ? scale_split_kernel<true, PR, NV, true> : scale_split_kernel<false, PR, NV, true>)
+        auto kern = scale_split_through(m, n, k, kp, c) ? (nearest ? scale_split_kernel<true, PR, NV, true> : scale_split_kernel<false, PR, NV, true>)
                                                      : (nearest ? scale_split_kernel<true, PR, NV, false> : scale_split_kernel<false, PR, NV, false>);
         kern<<<(unsigned)scale_split_groups(m, n, PR), 64 * scale_split_waves(m, n, PR, kp, c), 0, st>>>(
             (const unsigned long long *)A, lda, m, (const unsigned long long *)B, ldb, n, k, sA, sB, cA, cB, eA, eB, pA, pB, kp / kFrag,

@@ -140,9 +140,9 @@ def test_scales_and_slices_in_one_launch(m, n, k, sA, sB, nearest):
     check(ozimmu.dgemm3(dA, dB, sA, sB, splitting=splitting), A, B, sA, sB, nearest=nearest)
 
 
-# planes of 32000000 bytes, the most that are written through the caches, and of a little more; four and eight rows to a work-group
+# operands of 4000000 bytes and planes of 16000000, the most whose slices are written through the caches, and of a little more; four and eight rows to a work-group
 @pytest.mark.parametrize("nearest", [False, True])
-@pytest.mark.parametrize("m,n,k,s", [(1300, 1200, 1280, 10), (1300, 1201, 1280, 10), (1203, 47, 3100, 8), (7000, 1000, 250, 15), (7000, 1000, 250, 16)])
+@pytest.mark.parametrize("m,n,k,s", [(600, 400, 500, 8), (600, 401, 500, 8), (1203, 47, 400, 13), (6000, 250, 60, 20), (6000, 251, 60, 20), (7000, 1000, 60, 15), (7000, 1000, 250, 16), (1300, 1200, 1280, 10)])
 def test_planes_written_through(m, n, k, s, nearest):
     A, B = workloads.lognormal(m, n, k, 1.0, 23 + s)
     special(A, B)
