@@ -202,38 +202,6 @@ struct CfgEighths {
     static constexpr int LDS = ROUND * 8 * 8 * 64 * 8;
 };
 
-// The sums of the eight wavefronts meet in LDS, ROUND diagonals at a time; D: those of accumulator registers 2 wave and 2 wave + 1.
-template <int S>
-__device__ __forceinline__ void eighths_sums(const v16i (&acc)[S], unsigned char *lds, int lane, int wave, int (&D)[2][S])
-{
-    typedef int v2i __attribute__((ext_vector_type(2)));
-    v2i *x = (v2i *)lds;
-    constexpr int ROUND = CfgEighths<S>::ROUND;
-    static_for<0, (S + ROUND - 1) / ROUND>([&](auto P) {
-        constexpr int a0 = decltype(P)::value * ROUND, a1 = a0 + ROUND < S ? a0 + ROUND : S;
-        if constexpr (a0 > 0) __syncthreads();
-#pragma unroll
-        for (int a = a0; a < a1; ++a)
-#pragma unroll
-            for (int r = 0; r < 8; ++r) x[(((a - a0) * 8 + r) * 8 + wave) * 64 + lane] = v2i{acc[a][2 * r], acc[a][2 * r + 1]};
-        __syncthreads();
-#pragma unroll
-        for (int a = a0; a < a1; ++a) {
-            v2i s{0, 0};
-#pragma unroll
-            for (int w = 0; w < 8; ++w) s += x[(((a - a0) * 8 + wave) * 8 + w) * 64 + lane];
-            D[0][a] = s[0];
-            D[1][a] = s[1];
-        }
-    });
-}
-// column of the tile that register 2 wave + r of a lane belongs to
-__device__ __forceinline__ int eighths_column(int wave, int lane, int r)
-{
-    const int rr = 2 * wave + r;
-    return 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
-}
-
 template <int S>
 __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restrict__ pA, const int8_t *__restrict__ pB,
                                                            const int32_t *__restrict__ eA, const int32_t *__restrict__ eB,
@@ -277,15 +245,36 @@ __global__ __launch_bounds__(512) void gemm_eighths_kernel(const int8_t *__restr
             });
         }
     }
+    // the sums of the eight wavefronts meet in LDS, ROUND diagonals at a time; D: those of accumulator registers 2 wave and 2 wave + 1
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    v2i *x = (v2i *)lds;
     int D[2][S];
-    eighths_sums<S>(acc, lds, lane, wave, D);
+    constexpr int ROUND = CfgEighths<S>::ROUND;
+    static_for<0, (S + ROUND - 1) / ROUND>([&](auto P) {
+        constexpr int a0 = decltype(P)::value * ROUND, a1 = a0 + ROUND < S ? a0 + ROUND : S;
+        if constexpr (a0 > 0) __syncthreads();
+#pragma unroll
+        for (int a = a0; a < a1; ++a)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) x[(((a - a0) * 8 + r) * 8 + wave) * 64 + lane] = v2i{acc[a][2 * r], acc[a][2 * r + 1]};
+        __syncthreads();
+#pragma unroll
+        for (int a = a0; a < a1; ++a) {
+            v2i s{0, 0};
+#pragma unroll
+            for (int w = 0; w < 8; ++w) s += x[(((a - a0) * 8 + wave) * 8 + w) * 64 + lane];
+            D[0][a] = s[0];
+            D[1][a] = s[1];
+        }
+    });
     const int mi = tm * 32 + (lane & 31);
     if (mi >= m) return;
     const bool stream = stream_c(C, ldc);
     const int ea = eA[mi];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        const int nj = tn * 32 + eighths_column(wave, lane, r);
+        const int rr = 2 * wave + r;
+        const int nj = tn * 32 + 8 * (rr >> 2) + 4 * (lane >> 5) + (rr & 3);
         if (nj < n) store_c(&C[mi + (size_t)nj * ldc], ldexp(diagonal_sum<S>(D[r], Q), ea + eB[nj]), stream);
     }
 }
