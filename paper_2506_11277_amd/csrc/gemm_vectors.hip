@@ -10,11 +10,13 @@
 // the short side x four groups that take every fourth 32-deep k-block.  The two wavefronts of a group slice a 32 x 32
 // block of the long operand together (8 consecutive k per lane), multiply the block of the step before meanwhile, and
 // keep the raw entries of the one to three steps after in flight, as many as the registers hold: 32 KiB per compute unit each.
-// At 8192 x 64 x 8192, s = 7 the kernel takes 170 us and the maxima before it 80, where reading, slicing, writing and
-// multiplying took 567 us.  What bounds it: the slices of the short operand, read from the L2s once per 32 long rows, 56 KiB
-// per compute unit and step (multiplying alone, with nothing sliced and no long operand read, takes 104 us, 9.6 TB/s out
-// of the L2s, against 51 us of matrix instructions); slicing adds 35 us and the long operand's 3 TB/s the rest.  A barrier
-// every second step, and the window formed with integer shifts, changed nothing.
+// At 8192 x 64 x 8192, s = 7 the kernel takes 152 us and the maxima before it 77, where reading, slicing, writing and
+// multiplying took 567 us.  What bounds it: two chains of about 120 us each that two wavefronts to a SIMD overlap in part.  Kernel alone in a loop of calls, parts
+// of it left out: loading both operands, with the barriers and writes to LDS, 120 us (the long one alone 92, 5.8 TB/s; the short one's slices, out of the L2s once per 32 long
+// rows, alone 44); slicing and multiplying with the short one's slices loaded 125 (slicing alone 72, products with their LDS reads 85).  Nothing is
+// saturated: of the cycles matrix pipes 41 percent, vector ALUs 44, LDS 16; 3.5 TB/s from memory, 9.8 TB/s out of the L2s; the wavefronts wait for a
+// third.  The power cap is not it: with pauses of 4 ms between calls 153 us.  A barrier every second step, and the window formed with integer shifts, changed
+// nothing.
 // Few tiles are compensated by several parts of k; each part leaves its int32 sums in a slot of its own (in the room
 // the general path keeps the long operand's planes in) and a second kernel adds them.
 #include "gemm_dev.h"
